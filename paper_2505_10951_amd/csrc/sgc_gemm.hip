@@ -345,6 +345,345 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     }
 }
 
+// ---- the same products in smaller tiles -----------------------------------------------------------------
+// Few rows (a prompt, a handful of questions) make few 256 x 256 tiles: 300 rows x 6144 columns are 48 workgroups on 256
+// CUs, each walking the whole contraction alone, 85 us whatever the rows.  Here a workgroup of 4 wavefronts computes a
+// TM x TN tile with NST steps of 64 in LDS.  One barrier per step: behind it the step after is visible, and the step's own
+// buffer, whose operands every wavefront holds in registers by then, is free for the copies of step kt + NST.  The copies
+// are dealt between the products: issued in a row they hold up a wavefront's products for as long as the CU takes to
+// accept all of them (14.9 -> 13.8 us at 160 x 4096 x 4096, 41.9 -> 30.5 at 300 rows in 128 x 128 tiles).
+// What bounds such a launch is the CUs' intake (64 bytes a clock at best) and a step's chain of barrier, operand reads and
+// products.  Tiles of 64 rows therefore split the CONTRACTION between the wavefronts (KS: wavefront w multiplies the
+// 16-wide slice w of every step for the whole tile), which reads every operand from LDS once and not twice (22.3 ->
+// 14.9 us at 160 x 4096 x 4096); the four partial tiles are added through LDS at the end.
+// Tiles of 128 x 128 are split 2 x 2 (their partial tiles would take all registers).
+// The result lies in LDS as fp32 [TM][TN + 4], so that the stores to pages and rows can be arranged freely.
+// A tile of 64 columns takes channels 32 s .. 32 s + 31 of a head and their rotation partners 64 channels on.
+template <int TM_, int TN_, int NST_, int WGS_, bool KS_>
+struct SmallTile {
+    static constexpr int TM = TM_, TN = TN_;
+    static constexpr bool KS = KS_;
+    static constexpr int A_BYTES = TM * TK * 2, B_BYTES = TN * TK * 2;
+    static constexpr int STAGE = A_BYTES + B_BYTES;
+    static constexpr int NST = NST_;
+    static constexpr int WGS = WGS_;                             // workgroups per CU (LDS decides), one wavefront per SIMD each
+    static constexpr int LD = TN + 4;
+    static constexpr int PART = KS ? TM * TN * 4 : 0;            // one wavefront's partial tile
+    static constexpr int SUM_BYTES = PART + TM * LD * 4;
+    static constexpr int LDS = NST * STAGE > SUM_BYTES ? NST * STAGE : SUM_BYTES;
+    static constexpr int COPIES = STAGE / 4096;                  // 1 KiB copies per wavefront and step
+};
+using Tile64 = SmallTile<64, 64, 5, 2, true>;
+using Tile64x128 = SmallTile<64, 128, 6, 1, true>;
+using Tile128Deep = SmallTile<128, 128, 4, 1, false>;
+using Tile128Pair = SmallTile<128, 128, 2, 2, false>;
+
+// Barrier of a step: at most N of this wavefront's copies are still on their way and all its LDS reads have returned.
+// (__syncthreads() waits for every outstanding copy, which would leave one step in flight whatever the depth.)
+template <int N>
+__device__ __forceinline__ void step_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));      // vmcnt(N), lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <class T, bool QKV>
+__global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const GemmArgs g)
+{
+    constexpr int TM_ = T::TM, TN_ = T::TN, NST = T::NST, LD = T::LD;
+    constexpr int KK = T::KS ? 1 : 4;                            // 16-wide slices of a step this wavefront multiplies
+    constexpr int MB = TM_ / (T::KS ? 32 : 64), NB = TN_ / (T::KS ? 32 : 64);    // its 32 x 32 blocks
+    static_assert(NST >= 2 && T::COPIES * (NST - 1) < 64, "copies in flight are counted in 6 bits");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm = T::KS ? 0 : wave >> 1, wn = T::KS ? 0 : wave & 1;
+    const int h = lane >> 5, l31 = lane & 31;
+
+    // tile ids walk groups of up to 8 row tiles, column by column; every XCD takes a contiguous run of them, so a weight
+    // slab is fetched into one L2 and used there by all row tiles of the group
+    const int n_ct = g.n_col_tiles, n_rt = g.n_row_tiles;
+    const int total = n_ct * n_rt;
+    const int per = (total + 7) >> 3;
+    const int local = (int)blockIdx.x >> 3;
+    const int tid = ((int)blockIdx.x & 7) * per + local;
+    if (local >= per || tid >= total) return;
+    constexpr int GM = 8;
+    const int grp = tid / (GM * n_ct);
+    const int gsz = min(GM, n_rt - grp * GM);
+    const int in = tid - grp * GM * n_ct;
+    const int rt = __builtin_amdgcn_readfirstlane(grp * GM + in % gsz);
+    const int ct = __builtin_amdgcn_readfirstlane(in / gsz);
+
+    GemmRowTile t;
+    if (g.tiles) {
+        t = g.tiles[rt];
+    } else {
+        t.a = static_cast<const char *>(g.a) + (int64_t)rt * TM_ * g.K * 2;
+        t.c = g.c ? static_cast<char *>(g.c) + (int64_t)rt * TM_ * g.ldc * 2 : nullptr;
+        t.ck = t.cv = nullptr;
+        t.rows = (int32_t)min<int64_t>(TM_, g.M - (int64_t)rt * TM_);
+        t.pos0 = 0;
+        t.pt_off = 0;
+        t.dest0 = rt * TM_;
+    }
+    const int rows = __builtin_amdgcn_readfirstlane(t.rows);
+    const int K = g.K;
+    const int n_steps = K / TK;
+
+    // column j of the tile is column head0 + col_of(j) of the product
+    const int head0 = TN_ == 128 ? ct * 128 : (ct >> 1) * 128;
+    const int half32 = TN_ == 128 ? 0 : (ct & 1) * 32;
+    auto col_of = [&](int j) __attribute__((always_inline)) { return TN_ == 128 ? j : (j >> 5) * 64 + half32 + (j & 31); };
+
+    // ---- copies: instruction i of a wavefront moves 8 rows; lane (lr, slot) fetches chunk slot ^ perm(row), as above
+    const int lr = lane >> 3, slot = lane & 7;
+    uint32_t off[T::COPIES];
+    constexpr int A_COPIES = T::A_BYTES / 4096;
+    const char *a_base = static_cast<const char *>(t.a);
+    const char *b_base = static_cast<const char *>(g.w) + (int64_t)head0 * K * 2;
+#pragma unroll
+    for (int i = 0; i < T::COPIES; ++i) {
+        const bool is_a = i < A_COPIES;
+        const int row = is_a ? (TM_ / 4) * wave + 8 * i + lr : (TN_ / 4) * wave + 8 * (i - A_COPIES) + lr;
+        const uint32_t chunk = (uint32_t)(slot ^ lr ^ ((row >> 3) & 1));
+        off[i] = (uint32_t)(is_a ? min(row, rows - 1) : col_of(row)) * (uint32_t)(K * 2) + chunk * 16;
+    }
+    auto issue = [&](int kt, int stage) __attribute__((always_inline)) {
+        char *st = smem + stage * T::STAGE;
+        const uint32_t k_off = (uint32_t)kt * (TK * 2);
+#pragma unroll
+        for (int i = 0; i < T::COPIES; ++i) {
+            if (i < A_COPIES)
+                copy_1k_to_lds(a_base + (off[i] + k_off), st + wave * (T::A_BYTES / 4) + i * 1024);
+            else
+                copy_1k_to_lds(b_base + (off[i] + k_off), st + T::A_BYTES + wave * (T::B_BYTES / 4) + (i - A_COPIES) * 1024);
+        }
+    };
+
+    f32x16 acc[NB][MB];          // rows of the weight in the registers, rows of the left operand in the lanes
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // operand reads: lane (l31, h) of block b reads row 32 b + l31, chunk 2 kk + h of the step's eight (KS: kk = wave)
+    uint32_t r_off[KK];
+#pragma unroll
+    for (int k = 0; k < KK; ++k)
+        r_off[k] = (uint32_t)l31 * 128 + (((uint32_t)(T::KS ? wave : k) * 32) ^ ((uint32_t)(h ^ (lane & 7) ^ ((lane >> 3) & 1)) * 16));
+    const uint32_t x_region = (uint32_t)wm * (T::A_BYTES / 2), w_region = T::A_BYTES + (uint32_t)wn * (T::B_BYTES / 2);
+    auto load_ops = [&](int stage, bf16x8 (&x)[KK][MB], bf16x8 (&w)[KK][NB]) __attribute__((always_inline)) {
+        const char *st = smem + stage * T::STAGE;
+#pragma unroll
+        for (int k = 0; k < KK; ++k) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b) x[k][b] = *reinterpret_cast<const bf16x8 *>(st + x_region + b * 4096 + r_off[k]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) w[k][b] = *reinterpret_cast<const bf16x8 *>(st + w_region + b * 4096 + r_off[k]);
+        }
+    };
+    int stage = 0;               // buffer of step kt
+    auto after = [&](int s) __attribute__((always_inline)) { return s == NST - 1 ? 0 : s + 1; };
+    // One step: its operands are in x, w; those of the step behind it go to xn, wn.  STEADY: copies of step kt + NST are due,
+    // dealt between the products (all of a workgroup's copies in a row would hold up its products for as long as they take).
+    auto step = [&](int kt, const bf16x8 (&x)[KK][MB], const bf16x8 (&w)[KK][NB], bf16x8 (&xn)[KK][MB], bf16x8 (&wn_)[KK][NB], auto steady) __attribute__((always_inline)) {
+        constexpr bool STEADY = decltype(steady)::value;
+        if (STEADY || kt + NST <= n_steps)     // step kt + 1 has landed when only the copies of the NST - 2 behind it are outstanding
+            step_barrier<(NST - 2) * T::COPIES>();
+        else
+            step_barrier<0>();
+        const int mine = stage;
+        stage = after(stage);
+        if (!STEADY && kt + NST < n_steps) issue(kt + NST, mine);
+        load_ops(stage, xn, wn_);         // (behind the last step: some old step's operands, never used)
+        if (STEADY) issue(kt + NST, mine);
+#pragma unroll
+        for (int k = 0; k < KK; ++k)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < MB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[k][i], x[k][j], acc[i][j], 0, 0, 0);
+        if (STEADY) {                    // order: one-slice reads first; then products, reads and a copy in turn
+            if (T::KS) __builtin_amdgcn_sched_group_barrier(0x100, MB + NB, 0);
+#pragma unroll
+            for (int i = 0; i < T::COPIES; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, KK * MB * NB / T::COPIES, 0);
+                if (!T::KS) __builtin_amdgcn_sched_group_barrier(0x100, KK * (MB + NB) / T::COPIES, 0);
+                __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int i = 0; i < NST; ++i)
+        if (i < n_steps) issue(i, i);
+    bf16x8 x0[KK][MB], w0[KK][NB], x1[KK][MB], w1[KK][NB];
+    if (n_steps >= NST)
+        step_barrier<(NST - 1) * T::COPIES>();
+    else
+        step_barrier<0>();
+    load_ops(0, x0, w0);
+    int kt = 0;
+    for (; kt + 1 + NST < n_steps; kt += 2) {
+        step(kt, x0, w0, x1, w1, std::true_type{});
+        step(kt + 1, x1, w1, x0, w0, std::true_type{});
+    }
+    for (; kt + 2 <= n_steps; kt += 2) {
+        step(kt, x0, w0, x1, w1, std::false_type{});
+        step(kt + 1, x1, w1, x0, w0, std::false_type{});
+    }
+    if (kt < n_steps) step(kt, x0, w0, x1, w1, std::false_type{});
+    step_barrier<0>();           // every operand is read; the sums take the slabs' place
+
+    // ---- (KS) the four slices' sums: wavefronts 2 and 3 hand theirs to 0 and 1, which then hand each other half of theirs; the
+    // result is written as [TM][LD] behind the hand-over area.
+    auto slot_of = [&](char *area, int i, int j, int q4) __attribute__((always_inline)) { return reinterpret_cast<float4 *>(area + (((i * MB + j) * 4 + q4) * 64 + lane) * 16); };
+    auto give = [&](char *area, auto i0, auto i1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = i0; i < i1; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *slot_of(area, i, j, q4) = make_float4(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]);
+    };
+    auto take = [&](char *area, auto i0, auto i1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = i0; i < i1; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const float4 s = *slot_of(area, i, j, q4);
+                    acc[i][j][4 * q4] += s.x;
+                    acc[i][j][4 * q4 + 1] += s.y;
+                    acc[i][j][4 * q4 + 2] += s.z;
+                    acc[i][j][4 * q4 + 3] += s.w;
+                }
+    };
+    float *const cs = reinterpret_cast<float *>(smem + T::PART);
+    auto put = [&](auto i0, auto i1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = i0; i < i1; ++i)
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *reinterpret_cast<float4 *>(cs + ((wm * MB + j) * 32 + l31) * LD + (wn * NB + i) * 32 + 8 * q4 + 4 * h) =
+                        make_float4(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]);
+    };
+    const std::integral_constant<int, 0> first{};
+    const std::integral_constant<int, NB / 2> middle{};
+    const std::integral_constant<int, NB> last{};
+    if constexpr (T::KS) {
+        if (wave >= 2) give(smem + (wave - 2) * T::PART, first, last);
+        __syncthreads();
+        if (wave < 2) take(smem + wave * T::PART, first, last);
+        __syncthreads();
+        if (wave == 0)
+            give(smem, middle, last);
+        else if (wave == 1)
+            give(smem, first, middle);
+        __syncthreads();
+        if (wave == 0) {
+            take(smem, first, middle);
+            put(first, middle);
+        } else if (wave == 1) {
+            take(smem, middle, last);
+            put(middle, last);
+        }
+    } else {
+        put(first, last);
+    }
+    __syncthreads();
+
+    int kind = 0, hk = 0;        // 0 plain, 1 K head, 2 V head
+    if (QKV && head0 >= g.n_plain) {
+        const int kvh = (head0 - g.n_plain) / HD;
+        kind = kvh < g.n_kv_heads ? 1 : 2;
+        hk = kind == 1 ? kvh : kvh - g.n_kv_heads;
+    }
+    const int rows16 = (rows + 15) & ~15;
+    if (kind == 0 || g.kv_dest == 2) {
+        char *c = static_cast<char *>(kind == 0 ? t.c : kind == 1 ? t.ck : t.cv);
+        const int64_t ld = kind == 0 ? g.ldc : g.n_kv_heads * HD;
+        const int c0 = kind == 0 ? head0 : hk * HD;
+        if (!c) return;
+        for (int u = threadIdx.x; u < rows * (TN_ / 8); u += 256) {
+            const int i = u / (TN_ / 8), j = (u % (TN_ / 8)) * 8;
+            const float4 a = *reinterpret_cast<const float4 *>(cs + i * LD + j), b = *reinterpret_cast<const float4 *>(cs + i * LD + j + 4);
+            *reinterpret_cast<uint4 *>(c + (i * ld + c0 + col_of(j)) * 2) = make_uint4(pack2(a.x, a.y), pack2(a.z, a.w), pack2(b.x, b.y), pack2(b.z, b.w));
+        }
+    } else if (kind == 1) {
+        // 8 channels of a token and their partners; slots past a prompt's end in its last page are zeroed
+        const int n_rows = g.kv_dest == 0 ? min(rows16, TM_) : rows;
+        for (int u = threadIdx.x; u < n_rows * (TN_ / 16); u += 256) {
+            const int i = u / (TN_ / 16), p = (u % (TN_ / 16)) * 8;
+            const bool valid = i < rows;
+            int page, slot16, pos;
+            if (g.kv_dest == 0) {
+                pos = t.pos0 + i;
+                page = g.page_table[t.pt_off + (pos >> 4)];
+                slot16 = pos & 15;
+            } else {
+                const int2 d = g.row_dest[t.dest0 + i];
+                page = d.x >> 4;
+                slot16 = d.x & 15;
+                pos = d.y;
+            }
+            float x1[8], x2[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x1[e] = valid ? cs[i * LD + p + e] : 0.f;
+                x2[e] = valid ? cs[i * LD + TN_ / 2 + p + e] : 0.f;
+            }
+            const int c1 = half32 + p;
+            if (g.rope && valid) {
+                const float4 *tab = reinterpret_cast<const float4 *>(g.rope + (int64_t)pos * (HD / 2) + c1);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float4 t4 = tab[e];
+                    const float a0 = x1[2 * e], b0 = x2[2 * e], a1 = x1[2 * e + 1], b1 = x2[2 * e + 1];
+                    x1[2 * e] = a0 * t4.x - b0 * t4.y;
+                    x2[2 * e] = b0 * t4.x + a0 * t4.y;
+                    x1[2 * e + 1] = a1 * t4.z - b1 * t4.w;
+                    x2[2 * e + 1] = b1 * t4.z + a1 * t4.w;
+                }
+            }
+            char *dst = g.kv_base + (int64_t)page * g.page_bytes + (int64_t)hk * g.part_bytes;
+            *reinterpret_cast<uint4 *>(dst + k_page_index(slot16, c1) * 2) = make_uint4(pack2_f16(x1[0], x1[1]), pack2_f16(x1[2], x1[3]), pack2_f16(x1[4], x1[5]), pack2_f16(x1[6], x1[7]));
+            *reinterpret_cast<uint4 *>(dst + k_page_index(slot16, c1 + HD / 2) * 2) = make_uint4(pack2_f16(x2[0], x2[1]), pack2_f16(x2[2], x2[3]), pack2_f16(x2[4], x2[5]), pack2_f16(x2[6], x2[7]));
+        }
+    } else if (g.kv_dest == 0) {
+        // a page's 16 tokens of one channel: two runs of 8 tokens, 16 bytes each
+        for (int u = threadIdx.x; u < (rows16 / 16) * 2 * TN_; u += 256) {
+            const int j = u % TN_, hh = (u / TN_) & 1, r16 = (u / (2 * TN_)) * 16;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int tok = r16 + 4 * hh + (e & 3) + 8 * (e >> 2);
+                x[e] = tok < rows ? cs[tok * LD + j] : 0.f;
+            }
+            const int page = g.page_table[t.pt_off + ((t.pos0 + r16) >> 4)];
+            char *vp = g.kv_base + (int64_t)page * g.page_bytes + (int64_t)(g.n_kv_heads + hk) * g.part_bytes;
+            *reinterpret_cast<uint4 *>(vp + v_page_index(4 * hh, col_of(j)) * 2) = make_uint4(pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7]));
+        }
+    } else {
+        for (int u = threadIdx.x; u < rows * TN_; u += 256) {
+            const int i = u / TN_, j = u % TN_;
+            const int2 d = g.row_dest[t.dest0 + i];
+            __bf16 *vp = reinterpret_cast<__bf16 *>(g.kv_base + (int64_t)(d.x >> 4) * g.page_bytes + (int64_t)(g.n_kv_heads + hk) * g.part_bytes);
+            vp[v_page_index(d.x & 15, col_of(j))] = (__bf16)cs[i * LD + j];
+        }
+    }
+}
+
 // Any shape and both io types, one output element per thread, fp32 accumulation; columns are dealt to up to
 // three row-major outputs (Q, K, V or just one).
 __device__ inline float load_io(const void *p, int64_t i, int io_dtype)
@@ -403,10 +742,98 @@ __global__ void __launch_bounds__(256) zero_last_pages_kernel(char *spool, const
 }  // namespace
 
 
+namespace {
+
+template <class T>
+hipError_t launch_small(const GemmArgs &g, bool qkv, hipStream_t s)
+{
+    static bool configured = false;
+    constexpr int lds = T::LDS;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(proj_gemm_small_kernel<T, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(proj_gemm_small_kernel<T, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    const int per = (g.n_row_tiles * g.n_col_tiles + 7) / 8;
+    if (qkv)
+        hipLaunchKernelGGL((proj_gemm_small_kernel<T, true>), dim3(per * 8), dim3(256), lds, s, g);
+    else
+        hipLaunchKernelGGL((proj_gemm_small_kernel<T, false>), dim3(per * 8), dim3(256), lds, s, g);
+    return hipGetLastError();
+}
+
+// What a launch of n tiles takes, in microseconds, as measured on a chip of 256 CUs: a fixed part (launch, first copies,
+// sums, stores) and a part per 64-wide step that grows with the tiles a CU works on.  Per step, tiles on one CU:
+//   64 x 64        0.15 (1), 0.33 (2), 0.60 (3)      64 x 128      0.23-0.31
+//   128 x 128 deep 0.43-0.53                         128 x 128 in pairs 0.56 (1), 0.93 (2)
+//   256 x 256      1.2 (few tiles on the chip) .. 1.57 (256 of them)
+double proj_gemm_estimate(int kind, int64_t n, int K)
+{
+    const double steps = K / 64, rounds = (double)((n + 255) / 256);
+    switch (kind) {
+        case GEMM_64: return 3.5 + steps * (n <= 256 ? 0.15 : n <= 512 ? 0.33 : 0.20 * rounds);
+        case GEMM_64X128: return 6.0 + steps * 0.28 * rounds;
+        case GEMM_128_DEEP: return 6.0 + steps * 0.50 * rounds;
+        case GEMM_128_PAIR: return 6.0 + steps * (0.94 * (double)(n / 512) + (n % 512 == 0 ? 0.0 : n % 512 <= 256 ? 0.6 : 0.94));
+        default: return 7.0 + steps * (n < 256 ? 1.2 + 0.37 * (double)n / 256.0 : 1.55 * rounds);
+    }
+}
+
+}  // namespace
+
+int proj_gemm_tile_rows(int kind) { return kind == GEMM_256 ? 256 : kind == GEMM_128_DEEP || kind == GEMM_128_PAIR ? 128 : 64; }
+int proj_gemm_tile_cols(int kind) { return kind == GEMM_256 ? 256 : kind == GEMM_64 ? 64 : 128; }
+
+// The cheapest way by the estimate: all rows in tiles of one kind, or as many 256-row slabs as fill whole rounds of the chip
+// with 256 x 256 tiles and the rest in smaller ones (12977 x 4096 columns are 3.2 rounds: the fifth of a round that would
+// take a whole one goes out in 192 tiles of 128 x 128).
+GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K)
+{
+    // row tiles of the slabs behind the first `skip`, by tile height
+    auto cheapest = [&](int skip, bool big_too, int *kind) {
+        double best = 1e30;
+        for (int k = GEMM_256; k <= GEMM_64; ++k) {
+            if (k == GEMM_256 && !big_too) continue;
+            const int tm = proj_gemm_tile_rows(k), tn = proj_gemm_tile_cols(k);
+            int64_t rt = 0;
+            for (int i = skip; i < n_slabs; ++i) rt += (slab_rows[i] + tm - 1) / tm;
+            const double e = proj_gemm_estimate(k, rt * ((N + tn - 1) / tn), K);
+            if (e < best) {
+                best = e;
+                *kind = k;
+            }
+        }
+        return best;
+    };
+    GemmPlan p{0, GEMM_256};
+    double best = cheapest(0, true, &p.rest);
+    if (p.rest == GEMM_256) {
+        p.big_slabs = n_slabs;
+    }
+    const int ct = (N + 255) / 256;
+    const int64_t rounds = (int64_t)n_slabs * ct / 256;
+    const int big = (int)(rounds * 256 / ct);
+    if (big > 0 && big < n_slabs) {
+        int rest = GEMM_64;
+        const double both = proj_gemm_estimate(GEMM_256, (int64_t)big * ct, K) + cheapest(big, false, &rest);
+        if (both < best) p = GemmPlan{big, rest};
+    }
+    return p;
+}
+
 hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s)
 {
     const int total = g.n_row_tiles * g.n_col_tiles;
     if (total <= 0) return hipSuccess;
+    switch (g.kind) {
+        case GEMM_128_DEEP: return launch_small<Tile128Deep>(g, qkv, s);
+        case GEMM_128_PAIR: return launch_small<Tile128Pair>(g, qkv, s);
+        case GEMM_64X128: return launch_small<Tile64x128>(g, qkv, s);
+        case GEMM_64: return launch_small<Tile64>(g, qkv, s);
+        default: break;
+    }
     static bool configured[2] = {false, false};
     const void *kern = qkv ? reinterpret_cast<const void *>(proj_gemm_kernel<true>) : reinterpret_cast<const void *>(proj_gemm_kernel<false>);
     if (!configured[qkv]) {

@@ -1491,6 +1491,36 @@ static bool gemm_covers(const sgc_ctx *ctx, int64_t K, int64_t N)
     return ctx->p.io_dtype == SGC_BF16 && K >= 64 && K % 64 == 0 && K <= (1 << 20) && N >= 128 && N % 128 == 0;
 }
 
+// One launch of a projection: n_row_tiles row tiles of the given kind (tiles null: taken from g.a, g.c, g.M).
+static hipError_t launch_gemm_part(GemmArgs g, int kind, const GemmRowTile *tiles, int32_t n_row_tiles, bool qkv, hipStream_t s)
+{
+    if (n_row_tiles <= 0) return hipSuccess;
+    const int cols = proj_gemm_tile_cols(kind);
+    g.kind = kind;
+    g.tiles = tiles;
+    g.n_row_tiles = n_row_tiles;
+    g.n_col_tiles = (g.N + cols - 1) / cols;
+    return launch_proj_gemm(g, qkv, s);
+}
+
+// A projection whose left operand is one matrix of g.M rows.
+static hipError_t launch_gemm_matrix(const GemmArgs &g, bool qkv, hipStream_t s)
+{
+    std::vector<int32_t> slabs((size_t)((g.M + 255) / 256), 256);
+    slabs.back() = (int32_t)(g.M - (int64_t)(slabs.size() - 1) * 256);
+    const GemmPlan plan = proj_gemm_plan(slabs.data(), (int)slabs.size(), g.N, g.K);
+    hipError_t e = launch_gemm_part(g, GEMM_256, nullptr, plan.big_slabs, qkv, s);
+    if (e != hipSuccess || plan.big_slabs >= (int)slabs.size()) return e;
+    const int64_t r0 = (int64_t)plan.big_slabs * 256;
+    GemmArgs r = g;
+    r.a = static_cast<const char *>(g.a) + r0 * g.K * 2;
+    r.c = static_cast<char *>(g.c) + r0 * g.ldc * 2;
+    if (g.row_dest) r.row_dest = g.row_dest + r0;
+    r.M = g.M - r0;
+    const int rows = proj_gemm_tile_rows(plan.rest);
+    return launch_gemm_part(r, plan.rest, nullptr, (int32_t)((r.M + rows - 1) / rows), qkv, s);
+}
+
 int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int32_t *cluster_ids, int32_t layer,
                                    const void *const *dev_x, const void *dev_w_qkv, int32_t d_model, void *const *dev_q,
                                    void *hip_stream)
@@ -1543,8 +1573,17 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
     }
     hipError_t e = hipSuccess;
     if (fused) {
+        // slabs of up to 256 rows in the clusters' order; the plan says how many of them go out in 256 x 256 tiles
+        const int n_cols = any_q ? N : 2 * nkv;      // without any q output only the K and V rows of the weight are multiplied
+        std::vector<int32_t> slab_rows;
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t r = 0, P = c->cl[cluster_ids[i]].prefix_len; r < P; r += 256) slab_rows.push_back(std::min(256, P - r));
+        const GemmPlan plan = proj_gemm_plan(slab_rows.data(), (int)slab_rows.size(), n_cols, K);
+        const int rest_rows = proj_gemm_tile_rows(plan.rest);
         std::vector<GemmRowTile> tiles;
         int64_t row_base = 0;
+        int slab = 0;
+        size_t n_big = 0;
         for (int32_t i = 0; i < n; ++i) {
             const int32_t id = cluster_ids[i], P = c->cl[id].prefix_len;
             if (P == 0) continue;
@@ -1555,16 +1594,21 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
                 kptr.push_back(ks);
                 vptr.push_back(vs);
             }
-            for (int32_t r = 0; r < P; r += 256) {
-                GemmRowTile t{};
-                t.a = static_cast<const char *>(dev_x[i]) + (size_t)r * K * eb;
-                t.c = (dev_q && dev_q[i]) ? static_cast<char *>(dev_q[i]) + (size_t)r * nq * eb : nullptr;
-                t.ck = ks ? ks + (size_t)r * nkv * eb : nullptr;
-                t.cv = vs ? vs + (size_t)r * nkv * eb : nullptr;
-                t.rows = std::min(256, P - r);
-                t.pos0 = r;
-                t.pt_off = pt_off[id];
-                tiles.push_back(t);
+            for (int32_t r0 = 0; r0 < P; r0 += 256, ++slab) {
+                const bool big = slab < plan.big_slabs;
+                const int32_t step = big ? 256 : rest_rows, end = std::min(P, r0 + 256);
+                n_big += big;
+                for (int32_t r = r0; r < end; r += step) {
+                    GemmRowTile t{};
+                    t.a = static_cast<const char *>(dev_x[i]) + (size_t)r * K * eb;
+                    t.c = (dev_q && dev_q[i]) ? static_cast<char *>(dev_q[i]) + (size_t)r * nq * eb : nullptr;
+                    t.ck = ks ? ks + (size_t)r * nkv * eb : nullptr;
+                    t.cv = vs ? vs + (size_t)r * nkv * eb : nullptr;
+                    t.rows = std::min(step, end - r);
+                    t.pos0 = r;
+                    t.pt_off = pt_off[id];
+                    tiles.push_back(t);
+                }
             }
             row_base += P;
         }
@@ -1582,13 +1626,9 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
         }
         if (rc == SGC_OK) {
             GemmArgs g{};
-            // without any q output only the K and V rows of the weight are multiplied
             g.w = any_q ? dev_w_qkv : static_cast<const char *>(dev_w_qkv) + (size_t)nq * K * eb;
-            g.N = any_q ? N : 2 * nkv;
+            g.N = n_cols;
             g.K = K;
-            g.tiles = reinterpret_cast<const GemmRowTile *>(blk.p);
-            g.n_row_tiles = (int32_t)tiles.size();
-            g.n_col_tiles = (g.N + 255) / 256;
             g.ldc = nq;
             g.n_plain = any_q ? nq : 0;
             g.kv_dest = to_pages ? 0 : 2;
@@ -1598,7 +1638,9 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
             g.part_bytes = c->geom.head_part_bytes;
             g.page_table = c->d_page_table;
             g.rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
-            e = launch_proj_gemm(g, true, s);
+            const GemmRowTile *d_tiles = reinterpret_cast<const GemmRowTile *>(blk.p);
+            e = launch_gemm_part(g, GEMM_256, d_tiles, (int32_t)n_big, true, s);
+            if (e == hipSuccess) e = launch_gemm_part(g, plan.rest, d_tiles + n_big, (int32_t)(tiles.size() - n_big), true, s);
         }
         dev_release(ctx, blk, s);
     } else {
@@ -1691,8 +1733,6 @@ int sgc_project_qkv_suffix(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int3
         g.a = dev_x;
         g.c = dev_q;
         g.M = T;
-        g.n_row_tiles = (int32_t)((T + 255) / 256);
-        g.n_col_tiles = (N + 255) / 256;
         g.ldc = nq;
         g.n_plain = nq;
         g.kv_dest = 1;
@@ -1702,7 +1742,7 @@ int sgc_project_qkv_suffix(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int3
         g.part_bytes = (int64_t)kPageTokens * d * 2;
         g.row_dest = pl->d_row_dest;
         g.rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
-        SGC_HIP(ctx, launch_proj_gemm(g, true, s));
+        SGC_HIP(ctx, launch_gemm_matrix(g, true, s));
         pl->proj_state = 1;
     } else {
         const size_t need = (size_t)T * 2 * nkv * eb;
@@ -1740,11 +1780,9 @@ int sgc_project_out(sgc_ctx *ctx, const void *dev_o, const void *dev_w_o, int32_
         g.a = dev_o;
         g.c = dev_y;
         g.M = n_tokens;
-        g.n_row_tiles = (int32_t)((n_tokens + 255) / 256);
-        g.n_col_tiles = (N + 255) / 256;
         g.ldc = N;
         g.n_plain = N;
-        SGC_HIP(ctx, launch_proj_gemm(g, false, s));
+        SGC_HIP(ctx, launch_gemm_matrix(g, false, s));
     } else {
         SGC_HIP(ctx, launch_proj_generic(dev_o, dev_w_o, n_tokens, N, K, ctx->p.io_dtype, dev_y, N, nullptr, 0, nullptr, s));
     }

@@ -168,12 +168,24 @@ struct DecodeArgs {
 };
 
 // ---- projections around the attention (sgc_gemm.hip) -------------------------------------------
-// One slab of up to 256 rows of a projection's left operand and where its results go.
+// Tiles (rows x columns) a projection can be computed in: see proj_gemm_plan.
+enum { GEMM_256 = 0, GEMM_128_DEEP, GEMM_128_PAIR, GEMM_64X128, GEMM_64 };
+int proj_gemm_tile_rows(int kind);
+int proj_gemm_tile_cols(int kind);
+// The left operand's rows come in slabs of up to 256 rows: the first big_slabs of them are done in 256 x 256 tiles, the
+// others in tiles of kind `rest` (either part may be empty).
+struct GemmPlan {
+    int big_slabs;
+    int rest;
+};
+GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K);
+
+// One row tile of a projection's left operand and where its results go.
 struct GemmRowTile {
     const void *a;       // first row of the slab, [rows][K] bf16
     void *c;             // plain output (Q, or the whole product): first row of the slab, or null to store none
     void *ck, *cv;       // staged K / V outputs [rows][Hkv d] (first row of the slab), when keys are staged
-    int32_t rows;        // valid rows, 1..256
+    int32_t rows;        // valid rows, 1..the tile's height
     int32_t pos0;        // cache pages: position of the slab's first row inside its cluster (a multiple of 16)
     int32_t pt_off;      // cache pages: first page-table entry of the cluster
     int32_t dest0;       // suffix pages: index of the slab's first row in row_dest
@@ -185,11 +197,12 @@ static_assert(sizeof(GemmRowTile) == 48, "row tile record layout");
 struct GemmArgs {
     const void *w;                // [N][K] bf16
     int32_t N, K;
-    const GemmRowTile *tiles;     // [n_row_tiles], or null: slab r is rows 256 r .. of a / c below
+    const GemmRowTile *tiles;     // [n_row_tiles], or null: tile r is rows height * r .. of a / c below
     const void *a;
     void *c;
     int64_t M;
     int32_t n_row_tiles, n_col_tiles;
+    int32_t kind;                 // GEMM_256 ..
     int32_t ldc;
     int32_t n_plain;
     int32_t kv_dest;              // 0: the cache's pages (prompt), 1: the batch's suffix pages, 2: staging matrices
