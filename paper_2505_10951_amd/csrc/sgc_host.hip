@@ -740,6 +740,7 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         page_job.reserve(listed);
     }
     bool any_q = false;
+    std::vector<int32_t> chunk_page0;       // fp8 cache: first page of each piece the first ingest pass is done in
     for (int32_t i = 0; i < n; ++i) {
         const int32_t id = cluster_ids[i], P = c->cl[id].prefix_len;
         if (P == 0) continue;
@@ -754,6 +755,9 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         j.prefix_len = P;
         j.pt_off = pt_off[id];
         j.page0 = (int32_t)page_job.size();
+        j.chunk0 = (int32_t)chunk_page0.size();
+        if (c->d_scale)
+            for (int32_t p = 0; p < (int32_t)c->cl[id].pages.size(); p += kAmaxPages) chunk_page0.push_back(j.page0 + p);
         any_q = any_q || j.q != nullptr;
         page_job.insert(page_job.end(), c->cl[id].pages.size(), (int32_t)jobs.size());
         jobs.push_back(j);
@@ -787,14 +791,16 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             slots = std::max(slots, all);
         }
     }
-    // One block: [jobs][job of each page][tile seeds] from the host in one copy, then room for the tile records, which
-    // are written on the device from the seeds, the jobs and the cache's page table.
+    // One block: [jobs][job of each page][tile seeds][chunks] from the host in one copy, then room for the tile records, which
+    // are written on the device from the seeds, the jobs and the cache's page table, and for the fp8 ingest's partial maxima.
     const size_t n_tiles = slots * kXcd;
     const size_t jobs_bytes = (jobs.size() * sizeof(PrefixJob) + 255) / 256 * 256;
     const size_t pj_bytes = (page_job.size() * sizeof(int32_t) + 255) / 256 * 256;
     const size_t seeds_bytes = (n_tiles * sizeof(TileSeed) + 255) / 256 * 256;
-    const size_t copied = jobs_bytes + pj_bytes + seeds_bytes;
-    const size_t total = copied + n_tiles * sizeof(Tile);
+    const size_t chunks_bytes = (chunk_page0.size() * sizeof(int32_t) + 255) / 256 * 256;
+    const size_t copied = jobs_bytes + pj_bytes + seeds_bytes + chunks_bytes;
+    const size_t tiles_bytes = (n_tiles * sizeof(Tile) + 255) / 256 * 256;
+    const size_t total = copied + tiles_bytes + chunk_page0.size() * 2 * Hkv * sizeof(float);
     sgc_dev_block blk;
     if ((rc = dev_acquire(ctx, total, s, &blk)) != SGC_OK) return rc;
     char *host = nullptr;
@@ -807,6 +813,7 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     if (table_bytes) cache_tables_fill(c, reinterpret_cast<int32_t *>(host + copied));
     memcpy(host, jobs.data(), jobs.size() * sizeof(PrefixJob));
     memcpy(host + jobs_bytes, page_job.data(), page_job.size() * sizeof(int32_t));
+    if (!chunk_page0.empty()) memcpy(host + copied - chunks_bytes, chunk_page0.data(), chunk_page0.size() * sizeof(int32_t));
     const PrefixJob *d_jobs = reinterpret_cast<const PrefixJob *>(blk.p);
     const int32_t *d_page_job = reinterpret_cast<const int32_t *>(blk.p + jobs_bytes);
     const TileSeed *d_seeds = reinterpret_cast<const TileSeed *>(blk.p + jobs_bytes + pj_bytes);
@@ -843,7 +850,8 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     const bool expand = n_tiles > 0;
     if (rc == SGC_OK && !attend_only)
         e = launch_prefix_ingest(c->geom, layer, c->d_page_table, d_jobs, (int)jobs.size(), d_page_job, (int)page_job.size(),
-                                 ctx->p.io_dtype, ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr, expand ? &x : nullptr, s);
+                                 reinterpret_cast<const int32_t *>(blk.p + copied - chunks_bytes),
+                                 reinterpret_cast<float *>(blk.p + copied + tiles_bytes), (int)chunk_page0.size(), ctx->p.io_dtype, ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr, expand ? &x : nullptr, s);
     else if (rc == SGC_OK && expand)
         e = launch_expand_tiles(x, s);
     if (rc == SGC_OK && e == hipSuccess && any_q) {
