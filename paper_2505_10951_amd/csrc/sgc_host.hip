@@ -791,14 +791,20 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             slots = std::max(slots, all);
         }
     }
-    // One block: [jobs][job of each page][tile seeds][chunks] from the host in one copy, then room for the tile records, which
+    std::vector<GenericTile> gtiles;        // generic attention kernel
+    if (any_q && !ctx->use_mfma)
+        for (int ji = 0; ji < (int)jobs.size(); ++ji)
+            if (jobs[ji].q)
+                for (int64_t r = 0; r < (int64_t)jobs[ji].prefix_len * g; r += kGenericRows) gtiles.push_back({ji, (int32_t)r});
+    // One block: [jobs][job of each page][tile seeds][generic tiles][chunks] from the host in one copy, then room for the tile records, which
     // are written on the device from the seeds, the jobs and the cache's page table, and for the fp8 ingest's partial maxima.
     const size_t n_tiles = slots * kXcd;
     const size_t jobs_bytes = (jobs.size() * sizeof(PrefixJob) + 255) / 256 * 256;
     const size_t pj_bytes = (page_job.size() * sizeof(int32_t) + 255) / 256 * 256;
     const size_t seeds_bytes = (n_tiles * sizeof(TileSeed) + 255) / 256 * 256;
     const size_t chunks_bytes = (chunk_page0.size() * sizeof(int32_t) + 255) / 256 * 256;
-    const size_t copied = jobs_bytes + pj_bytes + seeds_bytes + chunks_bytes;
+    const size_t gtiles_bytes = (gtiles.size() * sizeof(GenericTile) + 255) / 256 * 256;
+    const size_t copied = jobs_bytes + pj_bytes + seeds_bytes + gtiles_bytes + chunks_bytes;
     const size_t tiles_bytes = (n_tiles * sizeof(Tile) + 255) / 256 * 256;
     const size_t total = copied + tiles_bytes + chunk_page0.size() * 2 * Hkv * sizeof(float);
     sgc_dev_block blk;
@@ -813,6 +819,7 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     if (table_bytes) cache_tables_fill(c, reinterpret_cast<int32_t *>(host + copied));
     memcpy(host, jobs.data(), jobs.size() * sizeof(PrefixJob));
     memcpy(host + jobs_bytes, page_job.data(), page_job.size() * sizeof(int32_t));
+    if (!gtiles.empty()) memcpy(host + jobs_bytes + pj_bytes + seeds_bytes, gtiles.data(), gtiles.size() * sizeof(GenericTile));
     if (!chunk_page0.empty()) memcpy(host + copied - chunks_bytes, chunk_page0.data(), chunk_page0.size() * sizeof(int32_t));
     const PrefixJob *d_jobs = reinterpret_cast<const PrefixJob *>(blk.p);
     const int32_t *d_page_job = reinterpret_cast<const int32_t *>(blk.p + jobs_bytes);
@@ -858,23 +865,14 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         AttnArgs a;
         fill_common_args(a, ctx, c, layer);
         a.mode = MODE_PREFIX;
+        a.jobs = d_jobs;
         if (ctx->use_mfma) {
-            a.jobs = d_jobs;
             a.tiles = d_tiles;
             a.n_tiles = (int32_t)n_tiles;
             e = launch_attn_mfma(a, s);
         } else {
-            for (const PrefixJob &j : jobs) {      // the generic kernel works on one cluster per launch
-                if (!j.q) continue;
-                a.q = j.q;
-                a.o = j.o;
-                a.lse = j.lse;
-                a.lse_stride = j.prefix_len;
-                a.prefix_cluster = j.cluster;
-                a.prefix_len = j.prefix_len;
-                e = launch_attn_generic(a, (int64_t)j.prefix_len * ctx->p.n_q_heads, s);
-                if (e != hipSuccess) break;
-            }
+            a.gtiles = reinterpret_cast<const GenericTile *>(blk.p + jobs_bytes + pj_bytes + seeds_bytes);
+            e = launch_attn_generic(a, (int)gtiles.size(), s);
         }
     }
     dev_release(ctx, blk, s);
@@ -1039,6 +1037,12 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
         if (pl->decode_cap > 0) build_decode_tiles(pl, want_rows);
         fill_tile_pt_off(pl, pl->cache);
     }
+    pl->gtiles.clear();
+    if (want_rows == 0) {
+        const int64_t g = ctx->p.n_q_heads / ctx->p.n_kv_heads;
+        for (int k = 0; k < pl->n_clusters; ++k)
+            for (int64_t r = 0; r < (pl->cl_tok_off[k + 1] - pl->cl_tok_off[k]) * g; r += kGenericRows) pl->gtiles.push_back({k, (int32_t)r});
+    }
     // The per-token records are only read by tiles that touch more queries than their own record describes.
     bool wide_tile = false;
     for (const Tile &t : pl->tiles) wide_tile = wide_tile || (t.n_rows > 0 && t.n_q > kTileQueries);
@@ -1061,6 +1065,7 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
         {pl->tok_src.data(), want_rows > 0 ? 0 : pl->tok_src.size() * 4, (const void **)&pl->d_tok_src},
         {pl->tok_qpos.data(), want_rows > 0 ? 0 : pl->tok_qpos.size() * 4, (const void **)&pl->d_tok_qpos},
         {pl->tok_sq.data(), want_rows > 0 ? 0 : pl->tok_sq.size() * 4, (const void **)&pl->d_tok_sq},
+        {pl->gtiles.data(), pl->gtiles.size() * sizeof(GenericTile), (const void **)&pl->d_gtiles},
         {pl->sq_src0.data(), pl->sq_src0.size() * 4, (const void **)&pl->d_sq_src0},
         {pl->sq_len.data(), pl->sq_len.size() * 4, (const void **)&pl->d_sq_len},
         {pl->sq_tok0.data(), pl->sq_tok0.size() * 4, (const void **)&pl->d_sq_tok0},
@@ -1204,6 +1209,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     a.tok_qpos = pl->d_tok_qpos;
     a.tok_sq = pl->d_tok_sq;
     a.tok_info = pl->d_tok_info;
+    a.gtiles = pl->d_gtiles;
     a.sq_src0 = pl->d_sq_src0;
     a.sq_len = pl->d_sq_len;
     a.sq_tok0 = pl->d_sq_tok0;
@@ -1226,7 +1232,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     if (ctx->use_mfma) {
         SGC_HIP(ctx, launch_attn_mfma(a, s));
     } else {
-        SGC_HIP(ctx, launch_attn_generic(a, pl->total_tokens * ctx->p.n_q_heads, s));
+        SGC_HIP(ctx, launch_attn_generic(a, (int)pl->gtiles.size(), s));
     }
     if (timed) {
         SGC_HIP(ctx, hipEventRecord(tev[2], s));

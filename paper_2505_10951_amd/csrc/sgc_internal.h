@@ -125,6 +125,13 @@ struct TileSeed {
 };
 static_assert(sizeof(TileSeed) == 32, "tile seed layout");
 
+// Generic attention kernel: 16 rows (token * g + head-in-group) of one unit, for every KV head.
+constexpr int kGenericRows = 16;
+struct GenericTile {
+    int32_t unit;    // cluster id, or (prefix mode) index of the job
+    int32_t row0;    // first row inside the unit
+};
+
 // Per sorted token: where it comes from and where it sits in its query.
 struct TokInfo {
     int32_t src;    // row of the token in the caller's packed arrays
@@ -249,11 +256,9 @@ struct AttnArgs {
     const int32_t *sq_page0;      // [n_queries] first page of the query in the suffix page pool
     const char *spool;            // suffix page pool (bf16 pages, same layout as cache pages) or null
     int64_t total_tokens;
-    // prefix mode: the MFMA kernel takes its clusters from jobs (a tile's tok_base field is the job index),
-    // the generic kernel works on one cluster per launch (prefix_cluster, prefix_len, q/k/v/o/lse above)
+    // prefix mode: the clusters are taken from jobs (MFMA kernel: a tile's tok_base field is the job index)
     const PrefixJob *jobs;
-    int32_t prefix_cluster;
-    int32_t prefix_len;
+    const GenericTile *gtiles;    // tiles of the generic kernel
     int32_t mode;
     int32_t n_q_heads, n_kv_heads, group, head_dim;
     int32_t io_dtype;
@@ -378,6 +383,8 @@ struct sgc_plan {
     const sgc::Tile *d_tiles = nullptr;
     std::vector<sgc::TileSeed> seeds;         // one per entry of tiles
     const sgc::TileSeed *d_seeds = nullptr;
+    std::vector<sgc::GenericTile> gtiles;     // generic attention kernel only
+    const sgc::GenericTile *d_gtiles = nullptr;
     const sgc::TokInfo *d_tok_info = nullptr;
     const int32_t *d_sq_query = nullptr;
     const sgc::Tile *d_dtiles = nullptr;
@@ -422,7 +429,7 @@ hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pa
 hipError_t launch_suffix_ingest(const AttnArgs &a, const int32_t *d_spage_sq, int n_spages, const ExpandArgs *expand,
                                 hipStream_t s);
 
-hipError_t launch_attn_generic(const AttnArgs &a, int64_t n_rows, hipStream_t s);
+hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s);
 // Decode, per (query, head): attention over the query's own keys (the step's new token was appended to the suffix
 // pages by the cached-part launch before) merged with the cached-prefix part.  head_dim 128, bf16.
 hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s);

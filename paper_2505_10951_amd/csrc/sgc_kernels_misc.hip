@@ -1,6 +1,6 @@
 // Support kernels of libsgc (gfx950): rotary table, prefix K/V ingest into cache pages,
 // canonical export/import of a cluster's cache, and the generic fp32-arithmetic attention kernel
-// (one wavefront per output row) that serves shapes the MFMA kernel does not cover.
+// that serves shapes the MFMA kernel does not cover.
 //
 // SubGCache (arXiv 2505.10951) Sec. 3.4: the representative prompt's K/V are computed once per
 // cluster and kept in GPU memory; each query's question tokens are appended to it.
@@ -964,59 +964,114 @@ __global__ void cache_import_kernel(PoolGeom g, int layer, const int32_t *pages,
     }
 }
 
-// ---- generic attention: one wavefront per (token, query head) row ----------------------------
-// Lane l walks keys l, l + 64, ... keeping its own running (max, sum, weighted V); the 64 partial
-// states are merged at the end.  All arithmetic is fp32; scores are kept in the log2 domain.
-template <int D>
-__global__ void __launch_bounds__(256) attn_generic_kernel(AttnArgs a)
-{
-    __shared__ float q_s[4][D];
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-    const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = a.group, half = D / 2;
-    const int64_t n_rows = (a.mode == MODE_SUFFIX ? a.total_tokens : (int64_t)a.prefix_len) * Hq;
-    const bool live = row < n_rows;     // dead waves still reach the barrier below
+// ---- generic attention: fp32 matrix cores, any type and head size ----------------------------------------
+// A workgroup takes 16 rows (token, head-in-group) of one (cluster or prompt, KV head); its NW wavefronts deal the blocks of
+// 16 keys among themselves and merge their partial softmax states at the end, so that a few hundred rows over a few hundred
+// keys fill the chip and a wavefront's chain is a handful of blocks.  v_mfma_f32_16x16x4, everything in fp32:
+//   scores: left operand = 16 keys (lane (j, q) = (lane % 16, lane / 16) holds channels q D/4 .. of key j), right operand =
+//           the 16 rows (row j, the same channels); lane (j, q) ends up with row j's scores of keys 4 q .. 4 q + 3;
+//   values: those four weights are, one register per instruction, the right operand of the second product, whose left
+//           operand takes channel 16 cb + j of keys 4 q .. 4 q + 3: one run of four tokens in a V page.
+// Bound on small shapes by the round trips of its look-ups and first loads: 44 -> 14 us for 380 tokens of 4 heads, d 64,
+// over 256 and 192 keys, the two prompts' own attention 2 x 37 -> 11 us in one launch (one wavefront per row, its lanes
+// walking the keys one by one, before).  8 wavefronts with heads of 64 channels (14.8 us with 4); 4 with 128, whose partial
+// outputs would not fit LDS otherwise.
+typedef __attribute__((ext_vector_type(4))) float gen_f32x4;
 
-    int h = 0, hk = 0, cluster = 0, P = 0, qpos = 0, n_cache = 0, n_self = 0;
-    int64_t src = 0, self_src0 = 0;
-    if (live) {
-        const int64_t tau = row / Hq;
-        h = (int)(row % Hq);
-        hk = h / g;
-        if (a.mode == MODE_SUFFIX) {
-            const int sq = a.tok_sq[tau];
-            cluster = a.sq_cluster[sq];
-            P = a.cl_prefix_len[cluster];
-            qpos = a.tok_qpos[tau];
-            src = a.tok_src[tau];
-            self_src0 = a.sq_src0[sq];
-            n_cache = P;
-            n_self = qpos + 1;
-        } else {
-            cluster = a.prefix_cluster;
-            P = 0;                 // position of row = its own index
-            qpos = (int)tau;
-            src = tau;
-            n_cache = qpos + 1;
-            n_self = 0;
-        }
-    }
-    const int pos = P + qpos;
-    // rotated query row into LDS (lanes 0 .. D/16-1 handle one chunk pair each)
-    if (live && lane < D / 16) {
-        float x1[8], x2[8];
-        const int64_t qrow = (src * Hq + h) * D;
-        load8(a.q, qrow + lane * 8, a.io_dtype, x1);
-        load8(a.q, qrow + half + lane * 8, a.io_dtype, x2);
-        if (a.rope) rope8(x1, x2, a.rope + (int64_t)pos * half + lane * 8);
+// 4 consecutive elements from element index idx (a multiple of 4)
+__device__ inline void load4(const void *base, int64_t idx, int dtype, float out[4])
+{
+    if (dtype == SGC_F32) {
+        const float4 a = *reinterpret_cast<const float4 *>(static_cast<const float *>(base) + idx);
+        out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
+    } else if (dtype == SGC_BF16) {
+        const uint2 a = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(base) + idx);
+        out[0] = __uint_as_float(a.x << 16);
+        out[1] = __uint_as_float(a.x & 0xFFFF0000u);
+        out[2] = __uint_as_float(a.y << 16);
+        out[3] = __uint_as_float(a.y & 0xFFFF0000u);
+    } else {
+        const uint32_t a = *reinterpret_cast<const uint32_t *>(static_cast<const uint8_t *>(base) + idx);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            q_s[wave][lane * 8 + i] = x1[i];
-            q_s[wave][half + lane * 8 + i] = x2[i];
-        }
+        for (int i = 0; i < 4; ++i) out[i] = e4m3_to_f32((uint8_t)(a >> (8 * i)));
     }
-    __syncthreads();
-    if (!live) return;
+}
+
+// Channels [q D/4, (q + 1) D/4) of a head vector at element index row, rotated at pos (rotate-half: a channel's partner is
+// D/2 away, in the vector's other half).
+template <int D>
+__device__ inline void load_rotated_quarter(const void *base, int64_t row, int dtype, const float2 *rope, int64_t pos, int q, float out[D / 4])
+{
+    constexpr int half = D / 2;
+    const int c0 = q * (D / 4), t0 = c0 & (half - 1);
+    const float sign = c0 < half ? -1.f : 1.f;
+#pragma unroll
+    for (int i = 0; i < D / 4; i += 8) {
+        float x[8];
+        load8(base, row + c0 + i, dtype, x);
+        if (rope) {
+            float y[8];
+            load8(base, row + (c0 ^ half) + i, dtype, y);
+            const float2 *tab = rope + pos * half + t0 + i;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = x[e] * tab[e].x + sign * (y[e] * tab[e].y);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[i + e] = x[e];
+    }
+}
+
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
+{
+    constexpr int NQ = D / 4, NB = D / 16, LD = D + 4;
+    __shared__ __attribute__((aligned(16))) float o_s[NW][16][LD];
+    __shared__ float m_s[NW][16], l_s[NW][16];
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int j = lane & 15, q = lane >> 4;
+    const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = a.group;
+    const GenericTile t = a.gtiles[blockIdx.x];
+    const int hk = blockIdx.y;
+
+    // ---- the lane's row (rows past the end repeat the last one)
+    const void *q_base = a.q;
+    void *o_base = a.o;
+    float *lse_base = a.lse;
+    int64_t lse_stride = a.lse_stride;
+    int cluster = t.unit, P, n_rows, tok_base = 0;
+    if (a.mode == MODE_SUFFIX) {
+        P = a.cl_prefix_len[cluster];
+        tok_base = a.cl_tok_off[cluster];
+        n_rows = (a.cl_tok_off[cluster + 1] - tok_base) * g;
+    } else {
+        const PrefixJob &job = a.jobs[t.unit];
+        cluster = job.cluster;
+        P = job.prefix_len;
+        n_rows = P * g;
+        q_base = job.q;
+        o_base = job.o;
+        lse_base = job.lse;
+        lse_stride = P;
+    }
+    auto row_of = [&](int i, int &head, int &src, int &qpos, int &sq) {
+        const int r = min(t.row0 + i, n_rows - 1), tk = r / g;
+        head = hk * g + (r - tk * g);
+        if (a.mode == MODE_SUFFIX) {
+            src = a.tok_src[tok_base + tk];
+            qpos = a.tok_qpos[tok_base + tk];
+            sq = a.tok_sq[tok_base + tk];
+        } else {
+            src = qpos = tk;
+            sq = 0;
+        }
+    };
+    int head, src, qpos, sq;
+    row_of(j, head, src, qpos, sq);
+    const int last_qpos = __shfl(qpos, 15), sq_lo = __shfl(sq, 0), sq_hi = __shfl(sq, 15);
+    const int n_cache = a.mode == MODE_SUFFIX ? P : qpos + 1;            // cached keys the row sees
+    const int n_blocks = ((a.mode == MODE_SUFFIX ? P : last_qpos + 1) + 15) / 16;
+    float qf[NQ];
+    load_rotated_quarter<D>(q_base, ((int64_t)src * Hq + head) * D, a.io_dtype, a.rope, (a.mode == MODE_SUFFIX ? P : 0) + qpos, q, qf);
 
     float k_scale = 1.f, v_scale = 1.f;
     if (a.kv_scale) {
@@ -1024,94 +1079,139 @@ __global__ void __launch_bounds__(256) attn_generic_kernel(AttnArgs a)
         k_scale = sc[hk];
         v_scale = sc[Hkv + hk];
     }
-    float m = -1e30f, l = 0.f, acc[D];
+    gen_f32x4 O[NB];
 #pragma unroll
-    for (int c = 0; c < D; ++c) acc[c] = 0.f;
+    for (int cb = 0; cb < NB; ++cb) O[cb] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -1e30f, l = 0.f;
+    // one block of 16 keys: kf = the lane's key's channels, vf = channel 16 cb + j of keys 4 q .. 4 q + 3, keep = first
+    // invisible of the lane's four keys
+    auto block = [&](const float (&kf)[NQ], const float (&vf)[NB][4], float scale, int keep) {
+        gen_f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = r < keep ? s[r] * scale : -INFINITY;
+            mx = fmaxf(mx, s[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx), alpha = exp2f(m - m_new);
+        m = m_new;
+        l *= alpha;
+        float p[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = exp2f(s[r] - m_new);
+            l += p[r];
+        }
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) O[cb][r] *= alpha;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[cb][r], p[r], O[cb], 0, 0, 0);
+        }
+    };
+
+    // ---- cached keys: a block is a page
     const int32_t *pt = a.page_table + a.cl_pt_off[cluster];
     const int kvd = a.pool.kv_dtype;
-
-    // cached keys
-    for (int j = lane; j < n_cache; j += kWave) {
-        const int page = pt[j / kPageTokens], tok = j % kPageTokens;
-        const char *kp = a.pool.k_part(a.layer, page, hk);
-        const char *vp = a.pool.v_part(a.layer, page, hk);
-        float s = 0.f;
+    auto fetch = [&](int b, float (&kf)[NQ], float (&vf)[NB][4]) {
+        const int page = pt[b];
+        const char *kp = a.pool.k_part(a.layer, page, hk), *vp = a.pool.v_part(a.layer, page, hk);
 #pragma unroll
-        for (int cc = 0; cc < D / 8; ++cc) {
-            float kk[8];
-            load8(kp, k_page_index(tok, cc * 8), k_elem_type(kvd), kk);
+        for (int i = 0; i < NQ; i += 8) load8(kp, k_page_index(j, q * NQ + i), k_elem_type(kvd), kf + i);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s += q_s[wave][cc * 8 + i] * kk[i];
-        }
-        s *= a.scale_log2e * k_scale;
-        float p, alpha = 1.f;
-        if (s > m) {
-            alpha = exp2f(m - s);
-            m = s;
-            p = 1.f;
-        } else {
-            p = exp2f(s - m);
-        }
-        l = l * alpha + p;
-        const float pv = p * v_scale;
+        for (int cb = 0; cb < NB; ++cb) load4(vp, v_page_index(4 * q, 16 * cb + j), kvd, vf[cb]);
+    };
+    {
+        float kf[NQ], vf[NB][4];
+        if (wave < n_blocks) fetch(wave, kf, vf);
+        for (int b = wave; b < n_blocks; b += NW) {
+            float kn[NQ], vn[NB][4];
+            fetch(min(b + NW, n_blocks - 1), kn, vn);              // the next block's loads travel meanwhile
+            if (a.kv_scale) {
 #pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] = acc[c] * alpha + pv * load1(vp, v_page_index(tok, c), kvd);
-    }
-    // the query's own suffix keys 0..qpos, rotated at P + j
-    for (int j = lane; j < n_self; j += kWave) {
-        const int64_t krow = ((self_src0 + j) * Hkv + hk) * D;
-        float s = 0.f;
+                for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
-        for (int cc = 0; cc < D / 16; ++cc) {
-            float x1[8], x2[8];
-            load8(a.k, krow + cc * 8, a.io_dtype, x1);
-            load8(a.k, krow + half + cc * 8, a.io_dtype, x2);
-            if (a.rope) rope8(x1, x2, a.rope + (int64_t)(P + j) * half + cc * 8);
+                    for (int r = 0; r < 4; ++r) vf[cb][r] *= v_scale;
+            }
+            block(kf, vf, a.scale_log2e * k_scale, n_cache - (16 * b + 4 * q));
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s += q_s[wave][cc * 8 + i] * x1[i] + q_s[wave][half + cc * 8 + i] * x2[i];
-        }
-        s *= a.scale_log2e;
-        float p, alpha = 1.f;
-        if (s > m) {
-            alpha = exp2f(m - s);
-            m = s;
-            p = 1.f;
-        } else {
-            p = exp2f(s - m);
-        }
-        l = l * alpha + p;
+            for (int i = 0; i < NQ; ++i) kf[i] = kn[i];
 #pragma unroll
-        for (int cc = 0; cc < D / 8; ++cc) {
-            float vv[8];
-            load8(a.v, krow + cc * 8, a.io_dtype, vv);
+            for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[cc * 8 + i] = acc[cc * 8 + i] * alpha + p * vv[i];
+                for (int r = 0; r < 4; ++r) vf[cb][r] = vn[cb][r];
         }
     }
-    // merge the 64 partial states
-    float M = m;
-    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    const float f = exp2f(m - M);
-    l *= f;
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-    const float inv_l = 1.0f / l;
-    const int64_t orow = (src * Hq + h) * D;
+    // ---- the suffix keys of every query the rows belong to, rotated at P + key on the way
+    if (a.mode == MODE_SUFFIX) {
+        int turn = n_blocks;
+        for (int si = sq_lo; si <= sq_hi; ++si) {
+            const int n_own = si == sq_hi ? last_qpos + 1 : a.sq_len[si];
+            const int64_t src0 = a.sq_src0[si];
+            for (int b = 0; b * 16 < n_own; ++b, ++turn) {
+                if (turn % NW != wave) continue;
+                float kf[NQ], vf[NB][4];
+                const int key = min(16 * b + j, n_own - 1);
+                load_rotated_quarter<D>(a.k, ((src0 + key) * Hkv + hk) * D, a.io_dtype, a.rope, P + key, q, kf);
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-        float x = acc[c] * f;
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        if (lane == (c & 63)) {
-            const float y = x * inv_l;
-            if (a.io_dtype == SGC_F32)
-                static_cast<float *>(a.o)[orow + c] = y;
-            else
-                static_cast<uint16_t *>(a.o)[orow + c] = f32_to_bf16(y);
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t vrow = ((src0 + min(16 * b + 4 * q + r, n_own - 1)) * Hkv + hk) * D;
+#pragma unroll
+                    for (int cb = 0; cb < NB; ++cb) vf[cb][r] = load1(a.v, vrow + 16 * cb + j, a.io_dtype);
+                }
+                block(kf, vf, a.scale_log2e, sq == si ? qpos + 1 - (16 * b + 4 * q) : 0);
+            }
         }
     }
-    if (a.lse && lane == 0) {
-        const int64_t col = a.mode == MODE_SUFFIX ? src : (int64_t)qpos;
-        a.lse[(int64_t)h * a.lse_stride + col] = (M + log2f(l)) * 0.6931471805599453f;
+    // ---- merge the wavefronts' states: lane (j, q) holds channels 16 cb + 4 q .. + 3 of row j
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (q == 0) {
+        m_s[wave][j] = m;
+        l_s[wave][j] = l;
     }
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) *reinterpret_cast<gen_f32x4 *>(&o_s[wave][j][16 * cb + 4 * q]) = O[cb];
+    __syncthreads();
+    const int i = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * NB;         // row i, channels c0 .. c0 + NB - 1
+    if (i >= 16) return;
+    if (t.row0 + i >= n_rows) return;
+    row_of(i, head, src, qpos, sq);
+    float M = m_s[0][i];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, m_s[w][i]);
+    float sum[NB], L = 0.f;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) sum[c] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float f = exp2f(m_s[w][i] - M);
+        L += f * l_s[w][i];
+#pragma unroll
+        for (int c = 0; c < NB; ++c) sum[c] += f * o_s[w][i][c0 + c];
+    }
+    const float inv = 1.0f / L;
+    const int64_t orow = ((int64_t)src * Hq + head) * D + c0;
+    if (a.io_dtype == SGC_F32) {
+#pragma unroll
+        for (int c = 0; c < NB; c += 4)
+            *reinterpret_cast<float4 *>(static_cast<float *>(o_base) + orow + c) = make_float4(sum[c] * inv, sum[c + 1] * inv, sum[c + 2] * inv, sum[c + 3] * inv);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NB; c += 4) {
+            uint2 y;
+            y.x = (uint32_t)f32_to_bf16(sum[c] * inv) | ((uint32_t)f32_to_bf16(sum[c + 1] * inv) << 16);
+            y.y = (uint32_t)f32_to_bf16(sum[c + 2] * inv) | ((uint32_t)f32_to_bf16(sum[c + 3] * inv) << 16);
+            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(o_base) + orow + c) = y;
+        }
+    }
+    if (lse_base && (threadIdx.x & 15) == 0)
+        lse_base[(int64_t)head * lse_stride + (a.mode == MODE_SUFFIX ? src : qpos)] = (M + log2f(L)) * 0.6931471805599453f;
 }
 
 }  // namespace
@@ -1269,14 +1369,14 @@ hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pa
     return hipGetLastError();
 }
 
-hipError_t launch_attn_generic(const AttnArgs &a, int64_t n_rows, hipStream_t s)
+hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s)
 {
-    if (n_rows <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((n_rows + 3) / 4);
+    if (n_gtiles <= 0) return hipSuccess;
+    const dim3 grid(n_gtiles, a.n_kv_heads);
     if (a.head_dim == 64)
-        hipLaunchKernelGGL(attn_generic_kernel<64>, dim3(blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((attn_generic_kernel<64, 8>), grid, dim3(512), 0, s, a);
     else
-        hipLaunchKernelGGL(attn_generic_kernel<128>, dim3(blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((attn_generic_kernel<128, 4>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
