@@ -9,7 +9,7 @@
 // bf16 kernel: a workgroup of 4 wavefronts computes a 256 x 256 tile of C; wavefront (wm, wn) owns the
 // 128 x 128 quadrant and keeps it in 16 accumulators of 32 x 32 (256 registers, one wavefront per SIMD).
 // The contraction runs in steps of 64: the 256 x 64 slabs of A and B (32 KiB each) are copied
-// global -> LDS without passing through registers, double buffered, one barrier per step.  In LDS a slab is
+// global -> LDS without passing through registers, into a ring of five, one barrier per step.  In LDS a slab is
 // row-major with 128-byte rows whose eight 16-byte chunks are permuted by (row & 7) ^ ((row >> 3) & 1); the
 // permutation is applied on the global side of the copy (the LDS side of such a copy is linear in the lane
 // index), and it spreads the 16-byte operand reads of 32 consecutive rows over all banks.
@@ -40,8 +40,8 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int TM = 256, TN = 256, TK = 64;
 constexpr int SLAB_BYTES = TM * TK * 2;          // 32 KiB: 256 rows of 128 bytes
-constexpr int STAGE_BYTES = 2 * SLAB_BYTES;      // A slab, then B slab
-constexpr int GEMM_LDS = 2 * STAGE_BYTES;        // 128 KiB
+constexpr int RING = 5;                          // slabs in LDS
+constexpr int GEMM_LDS = RING * SLAB_BYTES;      // 160 KiB
 constexpr int HD = 128;                          // head dim of the fused epilogue
 
 __device__ inline uint32_t pack2(float a, float b)
@@ -56,6 +56,17 @@ __device__ inline void copy_1k_to_lds(const char *src_lane, char *lds)
     const auto *g = (const __attribute__((address_space(1))) void *)src_lane;
     auto *l = (__attribute__((address_space(3))) void *)lds;
     __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
+}
+
+// Barrier of a step: at most N of this wavefront's copies are still on their way and all its LDS reads have returned.
+// (__syncthreads() waits for every outstanding copy, which would leave one step in flight whatever the depth.)
+template <int N>
+__device__ __forceinline__ void step_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));      // vmcnt(N), lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 template <bool QKV>
@@ -114,14 +125,18 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
         a_off[i] = (uint32_t)min(row, rows - 1) * (uint32_t)(K * 2) + chunk * 16;
         b_off[i] = (uint32_t)min(row, b_rows - 1) * (uint32_t)(K * 2) + chunk * 16;
     }
-    auto issue = [&](int kt, int stage) __attribute__((always_inline)) {
-        char *as = smem + stage * STAGE_BYTES + wave * 8192;
-        char *bs = as + SLAB_BYTES;
-        const uint32_t k_off = (uint32_t)kt * (TK * 2);
+    // copies [lo, hi) of this wavefront's eight of a slab: contraction step kt, ring slot `to`
+    auto copy_a = [&](int kt, int to, auto lo, auto hi) __attribute__((always_inline)) {
+        const char *src = a_base + (uint32_t)kt * (TK * 2);
+        char *as = smem + to * SLAB_BYTES + wave * 8192;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) copy_1k_to_lds(a_base + (a_off[i] + k_off), as + i * 1024);
+        for (int i = lo; i < hi; ++i) copy_1k_to_lds(src + a_off[i], as + i * 1024);
+    };
+    auto copy_b = [&](int kt, int to, auto lo, auto hi) __attribute__((always_inline)) {
+        const char *src = b_base + (uint32_t)kt * (TK * 2);
+        char *bs = smem + to * SLAB_BYTES + wave * 8192;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) copy_1k_to_lds(b_base + (b_off[i] + k_off), bs + i * 1024);
+        for (int i = lo; i < hi; ++i) copy_1k_to_lds(src + b_off[i], bs + i * 1024);
     };
 
     // ---- which output this wavefront makes
@@ -140,10 +155,8 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     uint32_t r_off[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) r_off[kk] = (uint32_t)l31 * 128 + (((uint32_t)kk * 32) ^ (perm * 16));
-    const uint32_t x_region = (uint32_t)wm * 16384, w_region = SLAB_BYTES + (uint32_t)wn * 16384;
-    // first operand: its rows land in the accumulator registers; second operand: its rows land in the lanes
-    const uint32_t p_region = v_orient ? x_region : w_region;
-    const uint32_t q_region = v_orient ? w_region : x_region;
+    // first operand (from slab A if v_orient, else B): its rows land in the accumulator registers; second: in the lanes
+    const uint32_t p_half = (uint32_t)(v_orient ? wm : wn) * 16384, q_half = (uint32_t)(v_orient ? wn : wm) * 16384;
 
     f32x16 acc[4][4];
 #pragma unroll
@@ -155,13 +168,22 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
 
     // Sub-step kk of a step multiplies the 16-wide slice kk of the slabs: 8 operand reads, 16 products.  The
     // reads run one sub-step ahead of the products, and the step's barrier sits in front of its LAST sub-step:
-    // by then every wavefront holds that sub-step's operands in registers, so the buffer can be refilled (copy of
-    // step kt + 2) and the first operands of step kt + 1 requested while the last 16 products still run.
-    auto load_ops = [&](const char *st, int kk, bf16x8 (&p)[4], bf16x8 (&q)[4]) __attribute__((always_inline)) {
+    // by then every wavefront holds that sub-step's operands in registers, so the step's two slots take B of step
+    // kt + 2 and A of step kt + 3, and the first operands of step kt + 1 are requested while the last 16 products run.
+    //
+    // The slabs lie in a ring of five (A of step kt in slot 2 kt mod 5, B in the next), so that a step's 16 copies can be
+    // dealt over all its products, one to four: half of B's in the last sub-step, half in the next step's first, A's in
+    // the second and third.  A CU takes in 64 bytes a clock, which for the 64 KiB of a step is half of its products'
+    // time, and copies issued faster than that hold up the products behind them.  With two pairs of slabs all of them had
+    // to go out in the last sub-step; the layer over ten prompts of 1024 and 320 questions (d_model 4096) took 2142 us
+    // that way, 2050 with B's eight in the last sub-step and A's over the next three, 2014 dealt evenly.
+    auto load_ops = [&](int sa, int kk, bf16x8 (&p)[4], bf16x8 (&q)[4]) __attribute__((always_inline)) {
+        const int sb = sa == RING - 1 ? 0 : sa + 1;
+        const char *ps = smem + (v_orient ? sa : sb) * SLAB_BYTES + p_half, *qs = smem + (v_orient ? sb : sa) * SLAB_BYTES + q_half;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            p[b] = *reinterpret_cast<const bf16x8 *>(st + p_region + b * 4096 + r_off[kk]);
-            q[b] = *reinterpret_cast<const bf16x8 *>(st + q_region + b * 4096 + r_off[kk]);
+            p[b] = *reinterpret_cast<const bf16x8 *>(ps + r_off[kk] + b * 4096);
+            q[b] = *reinterpret_cast<const bf16x8 *>(qs + r_off[kk] + b * 4096);
         }
     };
     auto products = [&](const bf16x8 (&p)[4], const bf16x8 (&q)[4]) __attribute__((always_inline)) {
@@ -172,59 +194,62 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                 acc[pi][qj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[pi], q[qj], acc[pi][qj], 0, 0, 0);
     };
     // Issue order of a sub-step: the 8 reads of the next sub-step go out in the shadow of the first 4 products,
-    // so that they have landed long before the next sub-step's first product asks for them.
-    auto order_reads_under_products = [&]() __attribute__((always_inline)) {
+    // so that they have landed long before the next sub-step's first product asks for them; the copies at even distances.
+    auto order = [&](auto reads, auto copies) __attribute__((always_inline)) {
+        constexpr int C = decltype(copies)::value;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 16; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one matrix-core instruction
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);     // two LDS reads
+            if (decltype(reads)::value && i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);     // two LDS reads
+            if ((i + 1) * C / 16 != i * C / 16) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);      // one copy
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 4> c4{};
+    const std::integral_constant<int, 8> c8{};
     bf16x8 p0[4], q0[4], p1[4], q1[4];
-    issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): this wavefront's copies have landed
-    __syncthreads();                             // everyone's have
-    if (n_steps > 1) issue(1, 1);
-    load_ops(smem, 0, p0, q0);
+    int sa = 0;                                  // ring slot of A of step kt
+    auto ring = [&](int s) __attribute__((always_inline)) { return s >= RING ? s - RING : s; };
+    copy_a(0, 0, c0, c8);
+    copy_b(0, 1, c0, c8);
+    __builtin_amdgcn_sched_barrier(0);           // the waits count copies: they leave in this order
+    if (n_steps > 1) {
+        copy_a(1, 2, c0, c8);
+        copy_b(1, 3, c0, c4);
+        step_barrier<12>();                      // the first two slabs have landed
+    } else {
+        step_barrier<0>();
+    }
+    load_ops(0, 0, p0, q0);
     __builtin_amdgcn_sched_barrier(0);
-    // one step; NEXT: a step follows (barrier, first operands of it), NEXT2: two follow (refill this step's buffer)
+    // one step; NEXT: a step follows (barrier, first operands of it), NEXT2: two follow (copies of that one are due)
     auto step = [&](int kt, auto next, auto next2) __attribute__((always_inline)) {
         constexpr bool NEXT = decltype(next)::value, NEXT2 = decltype(next2)::value;
-        const char *st = smem + (kt & 1) * STAGE_BYTES;
-        load_ops(st, 1, p1, q1);
+        const std::true_type reads{};
+        const int s4 = ring(sa + 4);
+        load_ops(sa, 1, p1, q1);
+        if (NEXT) copy_b(kt + 1, ring(sa + 3), c4, c8);
         products(p0, q0);
-        order_reads_under_products();
-        load_ops(st, 2, p0, q0);
+        order(reads, std::integral_constant<int, NEXT ? 4 : 0>{});
+        load_ops(sa, 2, p0, q0);
+        if (NEXT2) copy_a(kt + 2, s4, c0, c4);
         products(p1, q1);
-        order_reads_under_products();
-        load_ops(st, 3, p1, q1);
+        order(reads, std::integral_constant<int, NEXT2 ? 4 : 0>{});
+        load_ops(sa, 3, p1, q1);
+        if (NEXT2) copy_a(kt + 2, s4, c4, c8);
         products(p0, q0);
-        order_reads_under_products();
+        order(reads, std::integral_constant<int, NEXT2 ? 4 : 0>{});
         if (NEXT) {
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // the copies of step kt + 1, requested a step ago
-            __syncthreads();                  // every wavefront has read all of step kt out of LDS
+            // the slabs of step kt + 1 are there when only A of step kt + 2 is on its way; this step's are read out
+            step_barrier<NEXT2 ? 8 : 0>();
             __builtin_amdgcn_sched_barrier(0);
-            load_ops(smem + ((kt + 1) & 1) * STAGE_BYTES, 0, p0, q0);
-            if (NEXT2) issue(kt + 2, kt & 1);
+            load_ops(ring(sa + 2), 0, p0, q0);
+            if (NEXT2) copy_b(kt + 2, sa, c0, c4);
+            sa = ring(sa + 2);
         }
         products(p1, q1);
-        if (NEXT) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-            }
-        }
-        if (NEXT2) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-                __builtin_amdgcn_sched_group_barrier(0x010, 2, 1);     // two of the 16 copy instructions
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        order(std::integral_constant<bool, NEXT>{}, std::integral_constant<int, NEXT2 ? 4 : 0>{});
     };
     int kt = 0;
     for (; kt + 2 < n_steps; ++kt) step(kt, std::true_type{}, std::true_type{});
@@ -377,17 +402,6 @@ using Tile64 = SmallTile<64, 64, 5, 2, true>;
 using Tile64x128 = SmallTile<64, 128, 6, 1, true>;
 using Tile128Deep = SmallTile<128, 128, 4, 1, false>;
 using Tile128Pair = SmallTile<128, 128, 2, 2, false>;
-
-// Barrier of a step: at most N of this wavefront's copies are still on their way and all its LDS reads have returned.
-// (__syncthreads() waits for every outstanding copy, which would leave one step in flight whatever the depth.)
-template <int N>
-__device__ __forceinline__ void step_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));      // vmcnt(N), lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 template <class T, bool QKV>
 __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const GemmArgs g)
@@ -764,20 +778,23 @@ hipError_t launch_small(const GemmArgs &g, bool qkv, hipStream_t s)
     return hipGetLastError();
 }
 
-// What a launch of n tiles takes, in microseconds, as measured on a chip of 256 CUs: a fixed part (launch, first copies,
-// sums, stores) and a part per 64-wide step that grows with the tiles a CU works on.  Per step, tiles on one CU:
+// What a launch of n tiles takes, in microseconds, as measured on a chip of 256 CUs: a launch, and per round of tiles on a
+// CU the first copies, sums and stores and a part per 64-wide step that grows with the tiles a CU works on at a time.  Per
+// step, tiles on one CU:
 //   64 x 64        0.15 (1), 0.33 (2), 0.60 (3)      64 x 128      0.23-0.31
 //   128 x 128 deep 0.43-0.53                         128 x 128 in pairs 0.56 (1), 0.93 (2)
-//   256 x 256      1.2 (few tiles on the chip) .. 1.57 (256 of them)
+//   256 x 256      1.2 (few tiles on the chip) .. 1.42-1.55 (256 of them)
+// What the 256 x 256 tiles are taken for decides most: 10240 x 1024 x 1024 is 29 us in them and 48 in 1280 tiles of
+// 64 x 128, 2048 x 5120 x 4096 86 us and 112 in 128 x 128.
 double proj_gemm_estimate(int kind, int64_t n, int K)
 {
     const double steps = K / 64, rounds = (double)((n + 255) / 256);
     switch (kind) {
-        case GEMM_64: return 3.5 + steps * (n <= 256 ? 0.15 : n <= 512 ? 0.33 : 0.20 * rounds);
-        case GEMM_64X128: return 6.0 + steps * 0.28 * rounds;
-        case GEMM_128_DEEP: return 6.0 + steps * 0.50 * rounds;
+        case GEMM_64: return 3.5 + (n <= 256 ? 0.15 * steps : n <= 512 ? 0.33 * steps : rounds * (1.0 + 0.20 * steps));
+        case GEMM_64X128: return 3.0 + rounds * (3.0 + 0.28 * steps);
+        case GEMM_128_DEEP: return 3.0 + rounds * (3.0 + 0.50 * steps);
         case GEMM_128_PAIR: return 6.0 + steps * (0.94 * (double)(n / 512) + (n % 512 == 0 ? 0.0 : n % 512 <= 256 ? 0.6 : 0.94));
-        default: return 7.0 + steps * (n < 256 ? 1.2 + 0.37 * (double)n / 256.0 : 1.55 * rounds);
+        default: return 7.0 + steps * (n < 256 ? 1.2 + 0.22 * (double)n / 256.0 : 1.42 * rounds);
     }
 }
 
