@@ -451,11 +451,24 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     }
     // A step has few rows (one per query and head), so few row tiles: the cached keys of every row tile are split
     // into S ranges of whole 64-key steps, each range a tile of its own whose partial result the own-keys kernel
-    // merges.  A tile's fixed work (record, Q, store) costs about as much as eight steps, so S stays small: at
-    // most one tile per CU, at least eight steps per range (measured on 80 row tiles x 16 steps: S = 2, 3, 4, 6
-    // -> 42, 44, 45, 49 us per decode step).
-    int S = row_tiles > 0 ? (int)std::min<int64_t>(kDecodeMaxSplits, 256 / row_tiles) : 1;
-    S = std::max(1, std::min(S, max_steps / 8));
+    // merges, four ranges to a round trip.  A tile's fixed work (record, Q, store) costs about as much as eight steps, so
+    // on a full chip a range has at least eight and there is at most one tile per CU (80 row tiles x 16 steps: S = 2, 3
+    // -> 34, 36 us per decode step).  While half the CUs have no tile, three steps per range are the faster: 8 row
+    // tiles x 7 steps, S = 1, 2 -> 20.5, 18.5 us; x 47 steps, S = 5, 8, 9, 15 -> 25.2, 23.1, 23.7, 24.7 us (the merge's
+    // third and fourth round trip); 32 x 16 steps, S = 2, 4, 8 -> 22.1, 20.2, 20.9 us.  Past eight ranges only long
+    // prompts gain: 8 x 157 steps, S = 8, 16 -> 33.7, 30.3 us.
+    auto whole_trips = [](int n, int from) { return n > from ? n / 4 * 4 : n; };
+    int S = 1;
+    if (row_tiles > 0) {
+        const int full = std::min(max_steps / 8, (int)std::min<int64_t>(256 / row_tiles, 256));
+        const int half = std::min({max_steps / 3, (int)std::min<int64_t>(128 / row_tiles, 128), 8});
+        S = std::max({1, whole_trips(std::min(full, kDecodeMaxSplits), 8), whole_trips(half, 4)});
+        // Steps that may not allocate have a fixed array for the partial results: shorter ranges than eight steps, and more
+        // of them than eight, are only made where they fit.
+        // Nor are they for head groups past 16, whose own-keys kernel fetches range after range.
+        if (g > 16 || (size_t)S * (size_t)pl->n_queries * ctx->p.n_q_heads * (ctx->p.head_dim * 2 + sizeof(float)) > kNoAllocScratchBytes - 512 * (size_t)S)
+            S = std::max(1, std::min(full, 8));
+    }
     if (max_steps >= (1 << 24) / 64) S = 1;      // the position offset travels in 24 bits of the tile record
     pl->dec_splits = S;
     std::vector<std::vector<Light>> lists(kXcd);
@@ -1263,7 +1276,6 @@ int sgc_plan_enable_decode(sgc_plan *pl, int32_t max_new_tokens)
 // block from the context's pool.  Every GPU the library runs on holds its own copy of the array until the process
 // ends; host code never uses the array's name as an address, only what hipGetSymbolAddress returned for the
 // device that was current.
-constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 static char *g_noalloc_scratch_ptr[kMaxDevices] = {};

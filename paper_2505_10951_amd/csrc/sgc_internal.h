@@ -155,7 +155,8 @@ struct PrefixJob {
 constexpr int kAmaxPages = 8;    // pages whose largest magnitudes one workgroup of the fp8 ingest's first pass finds
 
 // One decode step of every (non-empty) query of a plan: arguments of the own-keys kernel.
-constexpr int kDecodeMaxSplits = 8;       // key ranges the cached part of a decode step may be split into
+constexpr int kDecodeMaxSplits = 16;      // key ranges the cached part of a decode step may be split into
+constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;    // partial results of a step that may not allocate
 constexpr int kDecodeMaxKeys = 1024;      // own keys (suffix + generated) a query may reach while decoding
 struct DecodeArgs {
     const void *q, *k, *v;        // the new token of every query: [n_queries][Hq][d], [n_queries][Hkv][d], bf16

@@ -754,7 +754,13 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
 // carry zeros), so lane (j, q) = (lane % 16, lane / 16) ends up with the scores of head j against tokens 4 q .. 4 q + 3 of
 // every page.  Those four values of two neighbouring pages are, as they stand, the lane's eight contraction slots of the
 // second product (keys x heads), whose left operand V^T takes, per lane, the 8-byte run of four tokens of channel
-// 16 cb + lane % 16 from each of the two pages.  Keys come in chunks of 4 pages with an online softmax over the chunks.
+// 16 cb + lane % 16 from each of the two pages.  Keys come in chunks of 2 pages with an online softmax over the chunks.
+// What bounds it is the chain of dependent loads (a few wavefronts per SIMD, 90 MB at 320 queries): the first chunk's keys and
+// the cached part's log-sum-exps are requested before the query rows, a chunk's values before its softmax, the cached
+// part's outputs of four ranges together.  Decode step of 320 queries over prompts of 1024 (8 KV heads, 57 own keys on average):
+// 34.7 -> 34.0 us; without head groups (32 KV heads, prompts of 500) 88.9 -> 82.3; 5 queries over 3001, five ranges:
+// 27.8 -> 25.2.  Chunks of 4 pages: 34.8, 87.3 and 25.5 (168 registers, two of them spilled); 2 pages with the next
+// chunk's keys requested before the softmax 34.9, 83.2 and 25.2.
 typedef __attribute__((ext_vector_type(8))) _Float16 dec_f16x8;
 typedef __attribute__((ext_vector_type(8))) __bf16 dec_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float dec_f32x4;
@@ -762,10 +768,10 @@ typedef __attribute__((ext_vector_type(4))) uint32_t dec_u32x4;
 
 __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs a)
 {
-    constexpr int d = 128, half = 64, CH = 4;        // CH: pages per chunk
+    constexpr int d = 128, half = 64, CH = 2;        // CH: pages per chunk
     const int lane = threadIdx.x & 63;
     const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = Hq / Hkv;
-    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= a.n_sq * Hkv) return;                 // (no barrier anywhere in this kernel)
     const int sq = unit / Hkv, hk = unit - sq * Hkv;
     const int j = lane & 15, q = lane >> 4;
@@ -779,6 +785,28 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
     const int64_t part = (int64_t)kPageTokens * d * 2;
     const int64_t page_stride = 2 * Hkv * part;
     const char *pages = a.spool + (int64_t)a.sq_page0[sq] * page_stride + (int64_t)hk * part;
+
+    const int64_t v_part = (int64_t)Hkv * part;
+    // the scores' left operands of a chunk: pages past the last are read as the last page again and masked
+    dec_u32x4 ka[CH][4];
+    auto load_keys = [&](int pg0) {
+#pragma unroll
+        for (int p = 0; p < CH; ++p) {
+            const char *kp = pages + (int64_t)min(pg0 + p, n_pages - 1) * page_stride + lane * 16;
+#pragma unroll
+            for (int cbk = 0; cbk < 4; ++cbk) ka[p][cbk] = *reinterpret_cast<const dec_u32x4 *>(kp + cbk * 1024);
+        }
+    };
+    load_keys(0);
+    // the cached part's log-sum-exps of the lane's head, range q + 4 i in lane group q
+    const int S_n = a.n_splits;
+    constexpr int LR = kDecodeMaxSplits / 4;
+    float lse_q[LR];
+#pragma unroll
+    for (int i = 0; i < LR; ++i) {
+        lse_q[i] = -INFINITY;
+        if (q + 4 * i < S_n && a.lse_cached) lse_q[i] = a.lse_cached[(q + 4 * i) * a.split_lse_elems + (int64_t)h * a.n_queries + n];
+    }
 
     // the query rows as right operands: chunk c8 = 4 cbk + q of 8 channels for cbk = 0..3; the rotation pairs chunk c8 with
     // chunk c8 + 8, both of which this lane holds (cbk and cbk + 2)
@@ -807,23 +835,29 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
     for (int cb = 0; cb < 8; ++cb) O[cb] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
     for (int pg0 = 0; pg0 < n_pages; pg0 += CH) {
-        // scores of the chunk (log2 units): pages past the last are read as the last page again and masked
+        // scores of the chunk (log2 units)
         dec_f32x4 S[CH];
-        {
-            dec_u32x4 ka[CH][4];
 #pragma unroll
-            for (int p = 0; p < CH; ++p) {
-                const char *kp = pages + (int64_t)min(pg0 + p, n_pages - 1) * page_stride + lane * 16;
+        for (int p = 0; p < CH; ++p) {
+            dec_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int cbk = 0; cbk < 4; ++cbk) ka[p][cbk] = *reinterpret_cast<const dec_u32x4 *>(kp + cbk * 1024);
-            }
+            for (int cbk = 0; cbk < 4; ++cbk)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(dec_f16x8, ka[p][cbk]), qb[cbk], acc, 0, 0, 0);
+            S[p] = acc;
+        }
+        // the values, on their way while the scores become weights
+        uint2 v0[CH / 2][8], v1[CH / 2][8];
 #pragma unroll
-            for (int p = 0; p < CH; ++p) {
-                dec_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int pp = 0; pp < CH / 2; ++pp) {
+            const char *va = pages + (int64_t)min(pg0 + 2 * pp, n_pages - 1) * page_stride + v_part;
+            const char *vb = pages + (int64_t)min(pg0 + 2 * pp + 1, n_pages - 1) * page_stride + v_part;
 #pragma unroll
-                for (int cbk = 0; cbk < 4; ++cbk)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(dec_f16x8, ka[p][cbk]), qb[cbk], acc, 0, 0, 0);
-                S[p] = acc;
+            for (int cb = 0; cb < 8; ++cb) {
+                // channel 16 cb + j: 32-channel group cb / 2, token block q & 1, channel (cb % 2) * 16 + j inside it, tokens
+                // 4 q .. 4 q + 3 = the half 8 (q >> 1) of the 16-byte run
+                const int off = ((((cb >> 1) * 2 + (q & 1)) * 32 + (cb & 1) * 16 + j) * 16) + 8 * (q >> 1);
+                v0[pp][cb] = *reinterpret_cast<const uint2 *>(va + off);
+                v1[pp][cb] = *reinterpret_cast<const uint2 *>(vb + off);
             }
         }
         float cmax = -INFINITY;
@@ -857,41 +891,29 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
             }
             const dec_u32x4 wb = {(uint32_t)w[0] | ((uint32_t)w[1] << 16), (uint32_t)w[2] | ((uint32_t)w[3] << 16),
                                   (uint32_t)w[4] | ((uint32_t)w[5] << 16), (uint32_t)w[6] | ((uint32_t)w[7] << 16)};
-            const char *va = pages + (int64_t)min(pg0 + 2 * pp, n_pages - 1) * page_stride + (int64_t)Hkv * part;
-            const char *vb = pages + (int64_t)min(pg0 + 2 * pp + 1, n_pages - 1) * page_stride + (int64_t)Hkv * part;
-            uint2 v0[8], v1[8];
 #pragma unroll
             for (int cb = 0; cb < 8; ++cb) {
-                // channel 16 cb + j: 32-channel group cb / 2, token block q & 1, channel (cb % 2) * 16 + j inside it, tokens
-                // 4 q .. 4 q + 3 = the half 8 (q >> 1) of the 16-byte run
-                const int off = ((((cb >> 1) * 2 + (q & 1)) * 32 + (cb & 1) * 16 + j) * 16) + 8 * (q >> 1);
-                v0[cb] = *reinterpret_cast<const uint2 *>(va + off);
-                v1[cb] = *reinterpret_cast<const uint2 *>(vb + off);
-            }
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                const dec_u32x4 av = {v0[cb].x, v0[cb].y, v1[cb].x, v1[cb].y};
+                const dec_u32x4 av = {v0[pp][cb].x, v0[pp][cb].y, v1[pp][cb].x, v1[pp][cb].y};
                 O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, av), __builtin_bit_cast(dec_bf16x8, wb), O[cb], 0, 0, 0);
             }
         }
+        if (pg0 + CH < n_pages) load_keys(pg0 + CH);
     }
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
-    if (!live) return;
     // merge with the cached-prefix part (natural-log LSE there, -inf for an empty range; log2 units here); the lane holds
     // channels 16 cb + 4 q .. + 3 of its head
     const uint16_t *oc = static_cast<const uint16_t *>(a.o_cached);
     uint16_t *og = static_cast<uint16_t *>(a.o);
-    const int S_n = a.n_splits;
     const float lse_own = m_run + log2f(l_run);
     float lse_c[kDecodeMaxSplits];
     float M = lse_own;
 #pragma unroll
     for (int sp = 0; sp < kDecodeMaxSplits; ++sp) {
-        lse_c[sp] = -INFINITY;
-        if (sp < S_n && a.lse_cached) lse_c[sp] = a.lse_cached[sp * a.split_lse_elems + (int64_t)h * a.n_queries + n] * 1.4426950408889634f;
+        lse_c[sp] = __shfl(lse_q[sp / 4], j + 16 * (sp % 4)) * 1.4426950408889634f;
         M = fmaxf(M, lse_c[sp]);
     }
+    if (!live) return;
     const float wo = exp2f(m_run - M);                        // weight of the unnormalised own sum
     float denom = exp2f(lse_own - M);
     float sum[8][4];
@@ -899,18 +921,30 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
     for (int cb = 0; cb < 8; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) sum[cb][r] = wo * O[cb][r];
+    // four ranges' outputs are requested together: asked for one range at a time, each costs a round trip of its own
 #pragma unroll
-    for (int sp = 0; sp < kDecodeMaxSplits; ++sp) {
-        if (!(lse_c[sp] > -INFINITY)) continue;
-        const float wc = exp2f(lse_c[sp] - M);
-        denom += wc;
+    for (int s0 = 0; s0 < kDecodeMaxSplits; s0 += 4) {
+        if (s0 >= S_n) break;
+        uint2 raw[4][8];
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) {
-            const uint2 raw = *reinterpret_cast<const uint2 *>(oc + sp * a.split_o_elems + io + cb * 16 + 4 * q);
-            sum[cb][0] += wc * bf16_to_f32((uint16_t)(raw.x & 0xFFFF));
-            sum[cb][1] += wc * bf16_to_f32((uint16_t)(raw.x >> 16));
-            sum[cb][2] += wc * bf16_to_f32((uint16_t)(raw.y & 0xFFFF));
-            sum[cb][3] += wc * bf16_to_f32((uint16_t)(raw.y >> 16));
+        for (int i = 0; i < 4; ++i) {
+            if (s0 + i >= S_n) break;
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) raw[i][cb] = *reinterpret_cast<const uint2 *>(oc + (s0 + i) * a.split_o_elems + io + cb * 16 + 4 * q);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s0 + i >= S_n) break;
+            if (!(lse_c[s0 + i] > -INFINITY)) continue;        // an empty range's output means nothing
+            const float wc = exp2f(lse_c[s0 + i] - M);
+            denom += wc;
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) {
+                sum[cb][0] += wc * bf16_to_f32((uint16_t)(raw[i][cb].x & 0xFFFF));
+                sum[cb][1] += wc * bf16_to_f32((uint16_t)(raw[i][cb].x >> 16));
+                sum[cb][2] += wc * bf16_to_f32((uint16_t)(raw[i][cb].y & 0xFFFF));
+                sum[cb][3] += wc * bf16_to_f32((uint16_t)(raw[i][cb].y >> 16));
+            }
         }
     }
     const float inv = 1.0f / denom;

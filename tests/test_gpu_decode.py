@@ -118,6 +118,26 @@ def test_decode_long_prompts_split_the_cached_keys_into_ranges(kv):
     assert np.isfinite(got[0]).all() and err <= TOL[kv] and lerr <= 5e-2
 
 
+@pytest.mark.parametrize("prefix_len, g", [
+    ([383], 4),                       # 6 steps of 64 keys: two ranges
+    ([193, 0, 64, 1], 4),             # four steps at the longest; the others leave ranges empty
+    ([769, 70], 1),                   # 13 steps: four ranges
+    ([1600, 1], 4),                   # 25 steps: eight, of three steps
+    ([6200, 129], 16),                # 97 steps: twelve
+    ([8193], 2),                      # 129 steps: sixteen
+    ([2000, 500], 32),                # a head group past 16: ranges of eight steps
+])
+def test_decode_ranges_of_few_row_tiles(prefix_len, g):
+    n = len(prefix_len)
+    w = workloads.custom("decode_few_tiles", n_q_heads=2 * g, n_kv_heads=2, head_dim=128, rope_base=500000.0, io_dtype="bf16",
+                         prefix_len=prefix_len, labels=[i % n for i in range(n + 1)],
+                         suffix_len=[(31, 16, 33, 0, 47)[i] for i in range(n + 1)], seed=61, k_outlier_scale=8.0)
+    got = _run_decode(w, 2)[0]
+    o_ref, lse_ref = _oracle_decode(w, 0, 2, oracle_caches(w, 0))
+    assert np.isfinite(got[0]).all()
+    assert np.abs(got[0] - o_ref).max() <= TOL["bf16"] and np.abs(got[1] - lse_ref).max() <= 5e-2
+
+
 @pytest.mark.parametrize("g", [16, 1])
 def test_decode_long_questions_and_the_widest_head_group(g):
     """Questions of up to 330 tokens (21 pages of own keys: six chunks of the own-keys kernel's online softmax, the last one
