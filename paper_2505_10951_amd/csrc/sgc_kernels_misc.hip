@@ -1117,9 +1117,32 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) O[cb] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -1e30f, l = 0.f;
+    // A key that a row does not see has weight 0 in the second product, and 0 x Inf and 0 x NaN are NaN.  Where some row does
+    // not see some key, values that are not finite are therefore taken out of the product (vf gets zeros) and added here, to the
+    // rows that see their key.
+    auto add_nonfinite = [&](const float (&p)[4], float (&vf)[NB][4], int keep) {
+        for (int qq = 0; qq < 4; ++qq) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float w = __shfl(p[r], j + 16 * qq);
+                const bool sees = r < __shfl(keep, j + 16 * qq);
+#pragma unroll
+                for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float v = __shfl(vf[cb][r], 4 * q + e + 16 * qq);
+                        if (sees && !(v * 0.f == 0.f)) O[cb][e] += w * v;
+                    }
+            }
+        }
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vf[cb][r] = vf[cb][r] * 0.f == 0.f ? vf[cb][r] : 0.f;
+    };
     // one block of 16 keys: kf = the lane's key's channels, vf = channel 16 cb + j of keys 4 q .. 4 q + 3, keep = first
     // invisible of the lane's four keys
-    auto block = [&](const float (&kf)[NQ], const float (&vf)[NB][4], float scale, int keep) {
+    auto block = [&](const float (&kf)[NQ], float (&vf)[NB][4], float scale, int keep) {
         gen_f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NQ; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
@@ -1141,9 +1164,19 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
             l += p[r];
         }
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) {
+        for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) O[cb][r] *= alpha;
+        if (__any(keep < 4)) {
+            float z = 0.f;                  // NaN if one of the lane's values is not finite
+#pragma unroll
+            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z = fmaf(vf[cb][r], 0.f, z);
+            if (__any(!(z == 0.f))) add_nonfinite(p, vf, keep);
+        }
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[cb][r], p[r], O[cb], 0, 0, 0);
         }

@@ -33,3 +33,64 @@ def test_generic_kernel_edges(io, d, Hq, Hkv, prefix, suffix):
             _, _, po, pl = orc.prefix_prefill(w.prefix_q(c), *w.prefix_kv(c), w.rope_base, want_lse=True)
             assert float(np.abs(o.float().cpu().numpy() - po).max()) <= bar
             assert float(np.abs(lse.cpu().numpy() - pl).max()) <= bar
+
+
+@pytest.mark.parametrize("io,kv,d", [("f32", "f32", 64), ("f32", "f32", 128), ("bf16", "bf16", 64), ("bf16", "fp8_e4m3", 64)])
+def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(io, kv, d):
+    """Inf and NaN in a late prompt token's and in one query's K, V: rows that do not see the token are bit for bit those of
+    the run with finite values, rows that see a value lose that one channel, rows that see a NaN key lose all."""
+    Hq, Hkv = 4, 2
+    w = workloads.custom("not_finite", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, rope_base=10000.0, io_dtype=io, kv_dtype=kv,
+                         prefix_len=[40, 5], labels=[0, 0, 1, 0, 0], suffix_len=[5, 3, 2, 37, 4], seed=d)
+    nan, inf = float("nan"), float("inf")
+
+    def check(out, ref, first, heads, channel):
+        """first[r]: row r sees the token; channel: the one that is lost, None for all"""
+        for h in range(Hq):
+            for r in range(ref.shape[0]):
+                hit = bool(first[r]) and h in heads
+                lost = np.zeros(d, bool)
+                if hit:
+                    lost[slice(None) if channel is None else channel] = True
+                assert np.array_equal(np.isfinite(out[r, h]), ~lost), (r, h)
+                assert np.array_equal(out[r, h][~lost], ref[r, h][~lost]), (r, h)
+
+    def prompt(poison):
+        with Session(w, kernel=sgc.SGC_KERNEL_GENERIC) as s:
+            s.alloc_cluster(0)
+            k, v = w.prefix_kv(0)
+            poison(k, v)
+            return s.prefix_prefill(0, k=k, v=v, with_q=True)[0].float().cpu().numpy()
+
+    def batch(poison):
+        with Session(w, kernel=sgc.SGC_KERNEL_GENERIC) as s:
+            for c in range(2):
+                s.alloc_cluster(c)
+                s.prefix_prefill(c)
+            s.assign()
+            q, k, v = w.suffix_qkv()
+            poison(k, v)
+            o = s.suffix_prefill(*(torch.from_numpy(x).to(device="cuda:0", dtype=torch.float32 if io == "f32" else torch.bfloat16) for x in (q, k, v)))
+            torch.cuda.synchronize()
+            return o.float().cpu().numpy()
+
+    group = {0: (0, 1), 1: (2, 3)}                      # KV head -> its query heads
+    cu = np.asarray(w.cu_seqlens)
+    query = np.searchsorted(cu, np.arange(cu[-1]), side="right") - 1
+    clean_p, clean_b = prompt(lambda k, v: None), batch(lambda k, v: None)
+    for hk, t, c, x in [(0, 35, 0, nan), (1, 39, d - 1, inf), (1, 16, 17, -inf), (0, 0, 3, nan)]:
+        if kv != "fp8_e4m3" or x != x:                  # (an infinity would move the head's scale)
+            def one(k, v):
+                v[t, hk, c] = x
+            check(prompt(one), clean_p, np.arange(40) >= t, group[hk], c)
+        def key(k, v):
+            k[t, hk, c] = nan
+        check(prompt(key), clean_p, np.arange(40) >= t, group[hk], None)
+    for hk, n, t, c, x in [(0, 0, 0, 0, inf), (1, 1, 2, d - 1, nan), (0, 3, 20, 5, -inf), (1, 3, 36, 33, nan), (0, 4, 1, 8, nan)]:
+        sees = (query == n) & (np.arange(cu[-1]) >= cu[n] + t)
+        def one(k, v):
+            v[cu[n] + t, hk, c] = x
+        check(batch(one), clean_b, sees, group[hk], c)
+        def key(k, v):
+            k[cu[n] + t, hk, c] = nan
+        check(batch(key), clean_b, sees, group[hk], None)
