@@ -33,7 +33,8 @@ __device__ inline uint16_t f32_to_bf16(float x)   // round to nearest even; NaN 
 // cache spent its time on; the scale's reciprocal is taken once (correctly rounded) and a quotient is corrected
 // twice by its residual, after which it is the correctly rounded one (Markstein: a quotient off by at most one unit,
 // corrected with a correctly rounded reciprocal; the first correction brings it there).  Residuals must not underflow,
-// so scales far from 1 divide.
+// so scales far from 1 divide.  A NaN (also of Inf / Inf, the scale of a head with an infinite element) is code 0x7F whatever
+// its sign; the hardware conversion gives 0xFF.
 struct E4m3Scale {
     float s, r;
     bool plain;          // wave-uniform: divide
@@ -46,6 +47,8 @@ __device__ inline float e4m3_quotient(float x, const E4m3Scale &q)
     y = fmaf(fmaf(-y, q.s, x), q.r, y);
     return copysignf(fmaf(fmaf(-y, q.s, x), q.r, y), x);        // (the residual of a negative zero is a positive one)
 }
+// 0xFF -> 0x7F in each byte: the addition carries into a byte's top bit only where its lower seven are all ones
+__device__ inline uint32_t e4m3_one_nan(uint32_t w) { return w & ~(((w & 0x7F7F7F7Fu) + 0x01010101u) & 0x80808080u); }
 __device__ inline uint2 e4m3_codes8(const float x[8], const E4m3Scale &q)
 {
     float y[8];
@@ -56,7 +59,7 @@ __device__ inline uint2 e4m3_codes8(const float x[8], const E4m3Scale &q)
     a = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], a, true);
     b = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], b, false);
     b = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], b, true);
-    return make_uint2((uint32_t)a, (uint32_t)b);
+    return make_uint2(e4m3_one_nan((uint32_t)a), e4m3_one_nan((uint32_t)b));
 }
 
 __device__ inline float e4m3_to_f32(uint8_t c)
