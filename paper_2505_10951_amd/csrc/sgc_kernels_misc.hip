@@ -1009,6 +1009,10 @@ __global__ void cache_import_kernel(PoolGeom g, int layer, const int32_t *pages,
 //           the 16 rows (row j, the same channels); lane (j, q) ends up with row j's scores of keys 4 q .. 4 q + 3;
 //   values: those four weights are, one register per instruction, the right operand of the second product, whose left
 //           operand takes channel 16 cb + j of keys 4 q .. 4 q + 3: one run of four tokens in a V page.
+// Sums: a block's 16 weighted values are added up by themselves and then to the running sum, and a score is two chains of
+// D/2 products.  One chain through all of a wavefront's keys was off by 5.9e-7 (2-norm) over 6001 keys (d 64) and 6.4e-7 over
+// 3000 (d 128), more than the 3.8e-7 and 4.3e-7 of the form with a row's keys dealt to 64 lanes; so it is 2.7e-7 and 3.0e-7,
+// for 0 (d 64) and 4 % (d 128) of the time.
 // Bound on small shapes by the round trips of its look-ups and first loads: 44 -> 14 us for 380 tokens of 4 heads, d 64,
 // over 256 and 192 keys, the two prompts' own attention 2 x 37 -> 11 us in one launch (one wavefront per row, its lanes
 // walking the keys one by one, before).  8 wavefronts with heads of 64 channels (14.8 us with 4); 4 with 128, whose partial
@@ -1123,7 +1127,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     // A key that a row does not see has weight 0 in the second product, and 0 x Inf and 0 x NaN are NaN.  Where some row does
     // not see some key, values that are not finite are therefore taken out of the product (vf gets zeros) and added here, to the
     // rows that see their key.
-    auto add_nonfinite = [&](const float (&p)[4], float (&vf)[NB][4], int keep) {
+    auto add_nonfinite = [&](const float (&p)[4], float (&vf)[NB][4], int keep, gen_f32x4 (&sum)[NB]) {
         for (int qq = 0; qq < 4; ++qq) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -1134,7 +1138,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float v = __shfl(vf[cb][r], 4 * q + e + 16 * qq);
-                        if (sees && !(v * 0.f == 0.f)) O[cb][e] += w * v;
+                        if (sees && !(v * 0.f == 0.f)) sum[cb][e] += w * v;
                     }
             }
         }
@@ -1146,9 +1150,12 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     // one block of 16 keys: kf = the lane's key's channels, vf = channel 16 cb + j of keys 4 q .. 4 q + 3, keep = first
     // invisible of the lane's four keys
     auto block = [&](const float (&kf)[NQ], float (&vf)[NB][4], float scale, int keep) {
-        gen_f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        gen_f32x4 part[2];
 #pragma unroll
-        for (int c = 0; c < NQ; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
+        for (int i = 0; i < 2; ++i) part[i] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) part[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], part[c & 1], 0, 0, 0);
+        gen_f32x4 s = part[0] + part[1];
         float mx = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1159,29 +1166,27 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m, mx), alpha = exp2f(m - m_new);
         m = m_new;
-        l *= alpha;
         float p[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            p[r] = exp2f(s[r] - m_new);
-            l += p[r];
-        }
+        for (int r = 0; r < 4; ++r) p[r] = exp2f(s[r] - m_new);
+        l = fmaf(l, alpha, (p[0] + p[1]) + (p[2] + p[3]));
+        gen_f32x4 seen[NB];
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) O[cb][r] *= alpha;
+        for (int cb = 0; cb < NB; ++cb) seen[cb] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
         if (__any(keep < 4)) {
             float z = 0.f;                  // NaN if one of the lane's values is not finite
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z = fmaf(vf[cb][r], 0.f, z);
-            if (__any(!(z == 0.f))) add_nonfinite(p, vf, keep);
+            if (__any(!(z == 0.f))) add_nonfinite(p, vf, keep, seen);
         }
 #pragma unroll
         for (int cb = 0; cb < NB; ++cb) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) O[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[cb][r], p[r], O[cb], 0, 0, 0);
+            for (int r = 0; r < 4; ++r) seen[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[cb][r], p[r], seen[cb], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) O[cb][r] = fmaf(O[cb][r], alpha, seen[cb][r]);
         }
     };
 

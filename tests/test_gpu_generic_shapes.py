@@ -94,3 +94,19 @@ def test_values_that_are_not_finite_stay_with_the_rows_that_see_them(io, kv, d):
         def key(k, v):
             k[cu[n] + t, hk, c] = nan
         check(batch(key), clean_b, sees, group[hk], None)
+
+
+@pytest.mark.parametrize("d,P,Hkv", [(64, 6001, 2), (128, 3000, 1)])
+def test_fp32_sums_over_a_long_prompt(d, P, Hkv):
+    """Error (2-norm) of rows over thousands of keys.  A chain of n additions of terms of random sign is off by about
+    2^-24 sqrt(n / 6) of its result: 6.6e-7 for one chain through the 750 keys a wavefront has here; 1e-7 for 16 keys and
+    1.7e-7 for the 47 blocks they come in.  Scores (two chains of d / 2 products) add 1.4e-7 to 2e-7, the exponentials and
+    the normaliser 1e-7: 2.7e-7 to 3e-7 in all, and the bar is between that and the one chain."""
+    w = workloads.custom("long_f32", n_q_heads=4, n_kv_heads=Hkv, head_dim=d, rope_base=500000.0, io_dtype="f32", prefix_len=[P],
+                         cluster_sizes=[4], suffix_range=(33, 33), seed=d)
+    out = run_workload(w, kernel=sgc.SGC_KERNEL_GENERIC)
+    ck, cv = orc.prefix_prefill(None, *w.prefix_kv(0), w.rope_base)[:2]
+    o_ref, _ = orc.suffix_prefill_batched(w.labels, w.cu_seqlens, [ck], [cv], *w.suffix_qkv(), w.rope_base)
+    err = float(np.linalg.norm(out["o"] - o_ref) / np.linalg.norm(o_ref))
+    print(f"d {d}, {P} keys: {err:.2e}", flush=True)
+    assert err <= 4.2e-7
