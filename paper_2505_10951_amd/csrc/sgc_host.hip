@@ -465,9 +465,9 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
         S = std::max({1, whole_trips(std::min(full, kDecodeMaxSplits), 8), whole_trips(half, 4)});
         // Steps that may not allocate have a fixed array for the partial results: shorter ranges than eight steps, and more
         // of them than eight, are only made where they fit.
-        // Nor are they for head groups past 16, whose own-keys kernel fetches range after range.
+        // Nor are they for head groups past 16.
         if (g > 16 || (size_t)S * (size_t)pl->n_queries * ctx->p.n_q_heads * (ctx->p.head_dim * 2 + sizeof(float)) > kNoAllocScratchBytes - 512 * (size_t)S)
-            S = std::max(1, std::min(full, 8));
+            S = std::max(1, std::min(full, kDecodeDotSplits));
     }
     if (max_steps >= (1 << 24) / 64) S = 1;      // the position offset travels in 24 bits of the tile record
     pl->dec_splits = S;

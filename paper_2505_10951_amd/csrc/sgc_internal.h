@@ -156,6 +156,7 @@ constexpr int kAmaxPages = 8;    // pages whose largest magnitudes one workgroup
 
 // One decode step of every (non-empty) query of a plan: arguments of the own-keys kernel.
 constexpr int kDecodeMaxSplits = 16;      // key ranges the cached part of a decode step may be split into
+constexpr int kDecodeDotSplits = 8;       // ... with head groups past 16, whose own-keys kernel fetches range after range
 constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;    // partial results of a step that may not allocate
 constexpr int kDecodeMaxKeys = 1024;      // own keys (suffix + generated) a query may reach while decoding
 struct DecodeArgs {

@@ -717,7 +717,9 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
         }
     }
     // merge with the cached-prefix part, which comes as n_splits partial results over key ranges (natural-log
-    // LSE there, -inf for an empty range; log2 units here)
+    // LSE there, -inf for an empty range; log2 units here).  The loops are unrolled over the ranges a plan gives this
+    // kernel at most: unrolled over sixteen a step of 64 heads over 2 took 29.1 us where it takes 27.0 (16 queries, one
+    // prompt of 200; 89.5 and 83.4 with 64 queries on each of 16 prompts).
     uint16_t *og = static_cast<uint16_t *>(a.o);
     const uint16_t *oc = static_cast<const uint16_t *>(a.o_cached);
     const int S = a.n_splits;
@@ -725,10 +727,10 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
     for (int gi = 0; gi < G; ++gi) {
         const int h = h0 + gi;
         const float lse_own = m[gi] + log2f(l[gi]);
-        float lse_c[kDecodeMaxSplits];
+        float lse_c[kDecodeDotSplits];
         float M = lse_own;
 #pragma unroll
-        for (int sp = 0; sp < kDecodeMaxSplits; ++sp) {
+        for (int sp = 0; sp < kDecodeDotSplits; ++sp) {
             lse_c[sp] = -INFINITY;
             if (sp < S && a.lse_cached) lse_c[sp] = a.lse_cached[sp * a.split_lse_elems + (int64_t)h * a.n_queries + n] * 1.4426950408889634f;
             M = fmaxf(M, lse_c[sp]);
@@ -737,7 +739,7 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
         float denom = exp2f(lse_own - M);
         float sum[2] = {wo * acc[gi][0], wo * acc[gi][1]};
 #pragma unroll
-        for (int sp = 0; sp < kDecodeMaxSplits; ++sp) {
+        for (int sp = 0; sp < kDecodeDotSplits; ++sp) {
             if (!(lse_c[sp] > -INFINITY)) continue;
             const float wc = exp2f(lse_c[sp] - M);
             denom += wc;
@@ -1353,6 +1355,7 @@ hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s)
         hipLaunchKernelGGL(decode_own_keys_mfma_kernel, dim3((units + 3) / 4), dim3(256), 0, s, d);
         return hipGetLastError();
     }
+    if (d.n_splits > kDecodeDotSplits) return hipErrorInvalidValue;          // (no plan does)
     const int G = g % 8 == 0 ? 8 : g % 4 == 0 ? 4 : g % 2 == 0 ? 2 : 1;      // heads per wavefront
     const dim3 grid((unsigned)((int64_t)d.n_sq * (d.n_q_heads / G)));
     const size_t lds = (size_t)G * (128 * 2 + (size_t)d.key_cap * (4 + 2));      // q rows (bf16), scores (fp32), weights (bf16)

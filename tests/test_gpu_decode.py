@@ -126,6 +126,7 @@ def test_decode_long_prompts_split_the_cached_keys_into_ranges(kv):
     ([6200, 129], 16),                # 97 steps: twelve
     ([8193], 2),                      # 129 steps: sixteen
     ([2000, 500], 32),                # a head group past 16: ranges of eight steps
+    ([8193], 32),                     # and never more than eight of them
 ])
 def test_decode_ranges_of_few_row_tiles(prefix_len, g):
     n = len(prefix_len)
