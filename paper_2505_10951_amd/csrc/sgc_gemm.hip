@@ -26,6 +26,7 @@
 // matrix and the ingest kernels take it from there.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "sgc_internal.h"
@@ -778,24 +779,50 @@ hipError_t launch_small(const GemmArgs &g, bool qkv, hipStream_t s)
     return hipGetLastError();
 }
 
-// What a launch of n tiles takes, in microseconds, as measured on a chip of 256 CUs: a launch, and per round of tiles on a
-// CU the first copies, sums and stores and a part per 64-wide step that grows with the tiles a CU works on at a time.  Per
-// step, tiles on one CU:
-//   64 x 64        0.15 (1), 0.33 (2), 0.60 (3)      64 x 128      0.23-0.31
-//   128 x 128 deep 0.43-0.53                         128 x 128 in pairs 0.56 (1), 0.93 (2)
-//   256 x 256      1.2 (few tiles on the chip) .. 1.42-1.55 (256 of them)
-// What the 256 x 256 tiles are taken for decides most: 10240 x 1024 x 1024 is 29 us in them and 48 in 1280 tiles of
-// 64 x 128, 2048 x 5120 x 4096 86 us and 112 in 128 x 128.
-double proj_gemm_estimate(int kind, int64_t n, int K)
+// What a launch of n tiles takes, in microseconds, on a chip of 256 CUs: a start, per round of tiles a fixed part (first
+// copies, sums, stores) and one per 64-wide step, less for a last round that leaves CUs idle or with one workgroup instead of
+// two; tiles that write keys and values into pages cost more, most where the slots are a batch's (two-byte stores of V).
+// Fitted to 408 shapes (16 to 16384 rows, 512 to 12288 columns, contractions of 640 to 8192; plain, prompt and batch
+// products), every tile kind measured on each: within 3 % in the median and 13 % for nine in ten.  Some of them, us,
+// 256 x 256 / 128 x 128 deep / pairs / 64 x 128 / 64 x 64:
+//   1000 x 4096 x 4096 (plain)                   73 / 40 / 46 / 45 / 49
+//   16384 x 4096 x 4096 (plain)                  421 / 620 / 509 / 699 / 760
+//   6400 x 6144 x 1024, batch                    123 / 152 / 118 / 205 / 154
+//   10 x 1024 x 10240 x 1024, prompts            242 / 296 / 236 / 474 / 387
+struct TileCost {
+    double start, round, step;              // per full round
+    double last, last_step;                 // of a last round with (nearly) idle CUs
+    double kv_pages, kv_slots;              // per round made of key and value tiles alone ...
+    double kv_pages_last, kv_slots_last;    // ... and what the last of their stores adds
+};
+constexpr TileCost kTileCost[5] = {
+    {0.5, 7.6, 1.54, 6.8, 1.025, 2.3, 14.5, 13.0, 14.5},        // GEMM_256
+    {2.0, 2.1, 0.552, 1.9, 0.434, 2.2, 9.5, 2.5, 8.0},          // GEMM_128_DEEP
+    {2.1, 3.2, 0.922, 0.0, 0.563, 1.4, 10.5, 3.5, 9.0},         // GEMM_128_PAIR: a round is 512 tiles
+    {1.0, 4.3, 0.284, 4.9, 0.201, 1.5, 5.2, 2.0, 2.5},          // GEMM_64X128
+    {2.1, 1.5, 0.353, 2.7, 0.132, 0.5, 2.4, 1.0, 0.0},          // GEMM_64: a round is 512 tiles
+};
+// kv: share of the columns that are keys and values, kv_dest where they go (GemmArgs)
+double proj_gemm_estimate(int kind, int64_t n, int K, double kv, int kv_dest)
 {
-    const double steps = K / 64, rounds = (double)((n + 255) / 256);
-    switch (kind) {
-        case GEMM_64: return 3.5 + (n <= 256 ? 0.15 * steps : n <= 512 ? 0.33 * steps : rounds * (1.0 + 0.20 * steps));
-        case GEMM_64X128: return 3.0 + rounds * (3.0 + 0.28 * steps);
-        case GEMM_128_DEEP: return 3.0 + rounds * (3.0 + 0.50 * steps);
-        case GEMM_128_PAIR: return 6.0 + steps * (0.94 * (double)(n / 512) + (n % 512 == 0 ? 0.0 : n % 512 <= 256 ? 0.6 : 0.94));
-        default: return 7.0 + steps * (n < 256 ? 1.2 + 0.22 * (double)n / 256.0 : 1.42 * rounds);
+    const TileCost &c = kTileCost[kind];
+    const bool pairs = kind == GEMM_128_PAIR || kind == GEMM_64;
+    const int64_t slots = pairs ? 512 : 256, full = n / slots;
+    const double steps = K / 64, x = (double)(n % slots) / (double)slots;      // x: how full the last round is
+    const double whole = c.round + c.step * steps, least = c.last + c.last_step * steps;
+    double last = 0.0, rounds = (double)full;
+    if (x > 0.0) {
+        if (kind == GEMM_128_PAIR)
+            last = least + std::max(0.0, (x - 0.25) / 0.75) * (whole - least);
+        else if (kind == GEMM_64)
+            last = x <= 0.5 ? least : whole;
+        else
+            last = least + x * x * x * (c.step - c.last_step) * steps;
+        rounds += kind == GEMM_128_PAIR ? x : kind == GEMM_64 && x <= 0.5 ? 0.5 : 1.0;
     }
+    double us = c.start + (double)full * whole + last;
+    if (kv > 0.0 && kv_dest < 2) us += rounds * kv * (kv_dest == 0 ? c.kv_pages : c.kv_slots) + (kv_dest == 0 ? c.kv_pages_last : c.kv_slots_last);
+    return us;
 }
 
 }  // namespace
@@ -805,9 +832,14 @@ int proj_gemm_tile_cols(int kind) { return kind == GEMM_256 ? 256 : kind == GEMM
 
 // The cheapest way by the estimate: all rows in tiles of one kind, or as many 256-row slabs as fill whole rounds of the chip
 // with 256 x 256 tiles and the rest in smaller ones (12977 x 4096 columns are 3.2 rounds: the fifth of a round that would
-// take a whole one goes out in 192 tiles of 128 x 128).
-GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K)
+// take a whole one goes out in 192 tiles of 128 x 128).  A second launch costs its start and the first one's drain: 4 us, 6
+// where slots of a batch are written, nothing beyond the stores counted above where whole pages are.  256 x 256 tiles alone are
+// kept unless something is 3 % cheaper: over the shapes above the choice then takes 0.8 % longer than the best one in the mean,
+// and never more than 3 % longer than 256 x 256 tiles alone.  (One time per step whatever the columns hold, and nothing per
+// round, sent 6400 rows x 6144 x 1024 of a batch out in two launches, 140 us for 123.)
+GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int n_plain, int kv_dest)
 {
+    const double kv = (double)(N - n_plain) / (double)N;
     // row tiles of the slabs behind the first `skip`, by tile height
     auto cheapest = [&](int skip, bool big_too, int *kind) {
         double best = 1e30;
@@ -816,7 +848,7 @@ GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K)
             const int tm = proj_gemm_tile_rows(k), tn = proj_gemm_tile_cols(k);
             int64_t rt = 0;
             for (int i = skip; i < n_slabs; ++i) rt += (slab_rows[i] + tm - 1) / tm;
-            const double e = proj_gemm_estimate(k, rt * ((N + tn - 1) / tn), K);
+            const double e = proj_gemm_estimate(k, rt * ((N + tn - 1) / tn), K, kv, kv_dest) * (k == GEMM_256 ? 0.97 : 1.0);
             if (e < best) {
                 best = e;
                 *kind = k;
@@ -825,19 +857,24 @@ GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K)
         return best;
     };
     GemmPlan p{0, GEMM_256};
-    double best = cheapest(0, true, &p.rest);
-    if (p.rest == GEMM_256) {
-        p.big_slabs = n_slabs;
-    }
+    const double best = cheapest(0, true, &p.rest);
+    if (p.rest == GEMM_256) p.big_slabs = n_slabs;
     const int ct = (N + 255) / 256;
     const int64_t rounds = (int64_t)n_slabs * ct / 256;
     const int big = (int)(rounds * 256 / ct);
     if (big > 0 && big < n_slabs) {
         int rest = GEMM_64;
-        const double both = proj_gemm_estimate(GEMM_256, (int64_t)big * ct, K) + cheapest(big, false, &rest);
+        const double both = proj_gemm_estimate(GEMM_256, (int64_t)big * ct, K, kv, kv_dest) + cheapest(big, false, &rest) + (kv > 0.0 && kv_dest == 0 ? 0.0 : kv > 0.0 && kv_dest == 1 ? 6.0 : 4.0);
         if (both < best) p = GemmPlan{big, rest};
     }
     return p;
+}
+
+extern "C" void sgc_debug_projection_plan(const int32_t *slab_rows, int32_t n_slabs, int32_t N, int32_t K, int32_t n_plain, int32_t kv_dest, int32_t *out)
+{
+    const GemmPlan p = proj_gemm_plan(slab_rows, n_slabs, N, K, n_plain, kv_dest);
+    out[0] = p.big_slabs;
+    out[1] = p.rest;
 }
 
 hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s)

@@ -1534,7 +1534,7 @@ static hipError_t launch_gemm_matrix(const GemmArgs &g, bool qkv, hipStream_t s)
 {
     std::vector<int32_t> slabs((size_t)((g.M + 255) / 256), 256);
     slabs.back() = (int32_t)(g.M - (int64_t)(slabs.size() - 1) * 256);
-    const GemmPlan plan = proj_gemm_plan(slabs.data(), (int)slabs.size(), g.N, g.K);
+    const GemmPlan plan = proj_gemm_plan(slabs.data(), (int)slabs.size(), g.N, g.K, g.n_plain, g.kv_dest);
     hipError_t e = launch_gemm_part(g, GEMM_256, nullptr, plan.big_slabs, qkv, s);
     if (e != hipSuccess || plan.big_slabs >= (int)slabs.size()) return e;
     const int64_t r0 = (int64_t)plan.big_slabs * 256;
@@ -1604,7 +1604,7 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
         std::vector<int32_t> slab_rows;
         for (int32_t i = 0; i < n; ++i)
             for (int32_t r = 0, P = c->cl[cluster_ids[i]].prefix_len; r < P; r += 256) slab_rows.push_back(std::min(256, P - r));
-        const GemmPlan plan = proj_gemm_plan(slab_rows.data(), (int)slab_rows.size(), n_cols, K);
+        const GemmPlan plan = proj_gemm_plan(slab_rows.data(), (int)slab_rows.size(), n_cols, K, any_q ? nq : 0, to_pages ? 0 : 2);
         const int rest_rows = proj_gemm_tile_rows(plan.rest);
         std::vector<GemmRowTile> tiles;
         int64_t row_base = 0;

@@ -189,7 +189,10 @@ struct GemmPlan {
     int big_slabs;
     int rest;
 };
-GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K);
+// (n_plain, kv_dest: as in GemmArgs)
+GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int n_plain, int kv_dest);
+// Not part of the interface: the plan as {big_slabs, rest}, so that tests can say which tiles a shape is computed in.
+extern "C" void sgc_debug_projection_plan(const int32_t *slab_rows, int32_t n_slabs, int32_t N, int32_t K, int32_t n_plain, int32_t kv_dest, int32_t *out);
 
 // One row tile of a projection's left operand and where its results go.
 struct GemmRowTile {
