@@ -769,8 +769,11 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         j.pt_off = pt_off[id];
         j.page0 = (int32_t)page_job.size();
         j.chunk0 = (int32_t)chunk_page0.size();
-        if (c->d_scale)
-            for (int32_t p = 0; p < (int32_t)c->cl[id].pages.size(); p += kAmaxPages) chunk_page0.push_back(j.page0 + p);
+        if (c->d_scale) {
+            const int64_t pages = (int64_t)c->cl[id].pages.size(), step = amax_chunk_pages(pages);
+            for (int64_t p = 0; p < pages; p += step) chunk_page0.push_back(j.page0 + (int32_t)p);
+        }
+        j.n_chunks = (int32_t)chunk_page0.size() - j.chunk0;
         any_q = any_q || j.q != nullptr;
         page_job.insert(page_job.end(), c->cl[id].pages.size(), (int32_t)jobs.size());
         jobs.push_back(j);

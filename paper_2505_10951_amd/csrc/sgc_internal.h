@@ -150,9 +150,12 @@ struct PrefixJob {
     int32_t prefix_len;
     int32_t pt_off;          // first entry of the cluster in the flat page table
     int32_t page0;           // first page of the job in the launch-wide page numbering
-    int32_t chunk0;          // fp8 cache: first of the job's kAmaxPages-page chunks in the launch-wide chunk numbering
+    int32_t chunk0;          // fp8 cache: first of the job's chunks in the launch-wide chunk numbering ...
+    int32_t n_chunks;        // ... and how many there are, of amax_chunk_pages(pages) pages each
 };
-constexpr int kAmaxPages = 8;    // pages whose largest magnitudes one workgroup of the fp8 ingest's first pass finds
+// Pages whose largest magnitudes one workgroup of the fp8 ingest's first pass finds: eight, so that a short prompt makes many
+// workgroups, but no more than 256 chunks to a prompt, because every workgroup of the second pass reads the maxima of all.
+constexpr int64_t amax_chunk_pages(int64_t pages) { return pages <= 8 * 256 ? 8 : (pages + 255) / 256; }
 
 // One decode step of every (non-empty) query of a plan: arguments of the own-keys kernel.
 constexpr int kDecodeMaxSplits = 16;      // key ranges the cached part of a decode step may be split into
@@ -419,8 +422,8 @@ hipError_t launch_expand_tiles(const ExpandArgs &e, hipStream_t s);
 // Prefix ingest of n_jobs clusters: rotate K, (quantise), write K and V into the clusters' pages.
 // d_page_job[p] is the job of launch-wide page p (n_pages of them).  expand (may be null): tile records to write in the
 // same launch, by workgroups appended to the grid.  fp8 cache: the first pass works in
-// n_chunks chunks of kAmaxPages pages (d_chunk_page0: their first launch-wide pages) and leaves [n_chunks][2][Hkv] maxima
-// in d_amax.
+// n_chunks chunks (d_chunk_page0: their first launch-wide pages) and leaves [2][Hkv][the job's chunks] maxima
+// per job in d_amax.
 hipError_t launch_prefix_ingest(const PoolGeom &g, int layer, const int32_t *d_page_table, const PrefixJob *d_jobs,
                                 int n_jobs, const int32_t *d_page_job, int n_pages, const int32_t *d_chunk_page0, float *d_amax,
                                 int n_chunks, int io_dtype, const float2 *rope, const ExpandArgs *expand, hipStream_t s);

@@ -202,8 +202,10 @@ __device__ inline void v_part_from_tile(char *vg, const uint16_t *vt)
     }
 }
 
-// fp8 cache, first pass: the largest |rotated K| and |V| of one head over kAmaxPages pages of a job, into
-// amax[chunk][2][Hkv].  The second pass takes the maximum over a job's chunks.  HBM-bound: it reads what the second pass
+// fp8 cache, first pass: the largest |rotated K| and |V| of one head over a chunk of a job's pages, into the job's part
+// [2][Hkv][chunk] of amax.  The second pass takes the maximum over a job's chunks: one or a few loads of neighbouring values per
+// lane.  (With [chunk][2][Hkv] and eight pages to a chunk whatever the prompt, those loads grew with its square: 131072 tokens
+// of 8 heads 840 us for both passes, 381 now; 16384 of 32 heads 200 and 160.)  HBM-bound: it reads what the second pass
 // reads.  (With one workgroup per page and an atomic maximum per wavefront into the job's 2 Hkv slots the launch waited
 // for the atomics: 243 us for 29 000 tokens of 8 heads, 33 us now.)
 __global__ void __launch_bounds__(256) ingest_amax_kernel(const PrefixJob *jobs, const int32_t *page_job, const int32_t *chunk_page0, float *amax,
@@ -212,7 +214,9 @@ __global__ void __launch_bounds__(256) ingest_amax_kernel(const PrefixJob *jobs,
     const int pg0 = chunk_page0[blockIdx.x];           // first launch-wide page of the chunk
     const PrefixJob job = jobs[page_job[pg0]];
     const int hk = blockIdx.y;
-    const int j0 = (pg0 - job.page0) * kPageTokens, j1 = min(j0 + kAmaxPages * kPageTokens, job.prefix_len);
+    const int chunk = blockIdx.x - job.chunk0;
+    const int j0 = (pg0 - job.page0) * kPageTokens;
+    const int j1 = chunk + 1 < job.n_chunks ? (chunk_page0[blockIdx.x + 1] - job.page0) * kPageTokens : job.prefix_len;
     const int half = d / 2, pairs = d / 16;
     float mk = 0.f, mv = 0.f;
     for (int it = threadIdx.x; it < (j1 - j0) * pairs; it += blockDim.x) {
@@ -245,16 +249,16 @@ __global__ void __launch_bounds__(256) ingest_amax_kernel(const PrefixJob *jobs,
         float m = part[0][threadIdx.x];
 #pragma unroll
         for (int w = 1; w < 4; ++w) m = fmaxf(m, part[w][threadIdx.x]);
-        amax[((int64_t)blockIdx.x * 2 + threadIdx.x) * Hkv + hk] = m;
+        amax[(int64_t)job.chunk0 * 2 * Hkv + ((int64_t)threadIdx.x * Hkv + hk) * job.n_chunks + chunk] = m;
     }
 }
 
 // The scale of one head of a job (which: 0 = K, 1 = V) from the chunks' maxima; every wavefront of the caller takes part.
 __device__ inline float scale_from_chunks(const float *amax, const PrefixJob &job, int which, int Hkv, int hk)
 {
-    const int n = ((job.prefix_len + kPageTokens - 1) / kPageTokens + kAmaxPages - 1) / kAmaxPages;
+    const float *p = amax + (int64_t)job.chunk0 * 2 * Hkv + ((int64_t)which * Hkv + hk) * job.n_chunks;
     float m = 0.f;
-    for (int i = threadIdx.x % kWave; i < n; i += kWave) m = fmaxf(m, amax[((int64_t)(job.chunk0 + i) * 2 + which) * Hkv + hk]);
+    for (int i = threadIdx.x % kWave; i < job.n_chunks; i += kWave) m = fmaxf(m, p[i]);
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     return m > 0.f ? m / 448.0f : 1.0f;
 }

@@ -1,5 +1,6 @@
 """The two passes of an fp8 cache's ingest at prompt lengths around its pieces (pages of 16 tokens, chunks of 8 pages, more
-chunks than a wavefront has lanes): scales and codes equal to the oracle's, wherever in the prompt the largest value sits."""
+chunks than a wavefront has lanes, and past 2048 pages longer chunks instead of more): scales and codes equal to the
+oracle's, wherever in the prompt the largest value sits."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,7 @@ from paper_2505_10951_amd.harness import Session  # noqa: E402
 
 
 @pytest.mark.parametrize("d,kernel", [(128, sgc.SGC_KERNEL_AUTO), (64, sgc.SGC_KERNEL_GENERIC)])
-@pytest.mark.parametrize("P", [1, 16, 127, 128, 129, 1000, 8209])
+@pytest.mark.parametrize("P", [1, 16, 127, 128, 129, 1000, 8209, 32768, 32769, 65600])
 def test_scales_and_codes_equal_the_oracle(P, d, kernel):
     Hkv = 2
     w = workloads.custom("fp8_ingest", n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=d, rope_base=0.0, io_dtype="bf16", kv_dtype="fp8_e4m3",
