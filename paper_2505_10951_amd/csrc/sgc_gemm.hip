@@ -782,8 +782,8 @@ hipError_t launch_small(const GemmArgs &g, bool qkv, hipStream_t s)
 // What a launch of n tiles takes, in microseconds, on a chip of 256 CUs: a start, per round of tiles a fixed part (first
 // copies, sums, stores) and one per 64-wide step, less for a last round that leaves CUs idle or with one workgroup instead of
 // two; tiles that write keys and values into pages cost more, most where the slots are a batch's (two-byte stores of V).
-// Fitted to 408 shapes (16 to 16384 rows, 512 to 12288 columns, contractions of 640 to 8192; plain, prompt and batch
-// products), every tile kind measured on each: within 3 % in the median and 13 % for nine in ten.  Some of them, us,
+// Fitted to 1053 shapes (16 to 16384 rows, 128 to 12288 columns, contractions of 64 to 8192; plain, prompt and batch
+// products), every tile kind measured on each: within 5 % in the median and 22 % for nine in ten.  Some of them, us,
 // 256 x 256 / 128 x 128 deep / pairs / 64 x 128 / 64 x 64:
 //   1000 x 4096 x 4096 (plain)                   73 / 40 / 46 / 45 / 49
 //   16384 x 4096 x 4096 (plain)                  421 / 620 / 509 / 699 / 760
@@ -796,11 +796,11 @@ struct TileCost {
     double kv_pages_last, kv_slots_last;    // ... and what the last of their stores adds
 };
 constexpr TileCost kTileCost[5] = {
-    {0.5, 7.6, 1.54, 6.8, 1.025, 2.3, 14.5, 13.0, 14.5},        // GEMM_256
-    {2.0, 2.1, 0.552, 1.9, 0.434, 2.2, 9.5, 2.5, 8.0},          // GEMM_128_DEEP
-    {2.1, 3.2, 0.922, 0.0, 0.563, 1.4, 10.5, 3.5, 9.0},         // GEMM_128_PAIR: a round is 512 tiles
-    {1.0, 4.3, 0.284, 4.9, 0.201, 1.5, 5.2, 2.0, 2.5},          // GEMM_64X128
-    {2.1, 1.5, 0.353, 2.7, 0.132, 0.5, 2.4, 1.0, 0.0},          // GEMM_64: a round is 512 tiles
+    {0.3, 9.0, 1.52, 6.5, 1.045, 2.2, 14.7, 11.5, 13.5},        // GEMM_256
+    {2.2, 2.3, 0.546, 2.3, 0.42, 2.4, 10.3, 2.0, 7.5},          // GEMM_128_DEEP
+    {3.0, 2.8, 0.925, 0.4, 0.525, 2.0, 11.4, 2.8, 9.5},         // GEMM_128_PAIR: a round is 512 tiles
+    {1.4, 4.5, 0.281, 4.7, 0.199, 1.4, 5.2, 1.6, 2.7},          // GEMM_64X128
+    {2.5, 2.0, 0.34, 2.9, 0.122, 0.65, 2.7, 0.5, 0.0},          // GEMM_64: a round is 512 tiles
 };
 // kv: share of the columns that are keys and values, kv_dest where they go (GemmArgs)
 double proj_gemm_estimate(int kind, int64_t n, int K, double kv, int kv_dest)
@@ -833,10 +833,11 @@ int proj_gemm_tile_cols(int kind) { return kind == GEMM_256 ? 256 : kind == GEMM
 // The cheapest way by the estimate: all rows in tiles of one kind, or as many 256-row slabs as fill whole rounds of the chip
 // with 256 x 256 tiles and the rest in smaller ones (12977 x 4096 columns are 3.2 rounds: the fifth of a round that would
 // take a whole one goes out in 192 tiles of 128 x 128).  A second launch costs its start and the first one's drain: 4 us, 6
-// where slots of a batch are written, nothing beyond the stores counted above where whole pages are.  256 x 256 tiles alone are
-// kept unless something is 3 % cheaper: over the shapes above the choice then takes 0.8 % longer than the best one in the mean,
-// and never more than 3 % longer than 256 x 256 tiles alone.  (One time per step whatever the columns hold, and nothing per
-// round, sent 6400 rows x 6144 x 1024 of a batch out in two launches, 140 us for 123.)
+// where slots of a batch are written, nothing beyond the stores counted above where whole pages are.  256 x 256 tiles alone
+// are kept unless something is 3 % cheaper: over the shapes above the choice then takes 1.0 % longer than the best one in the
+// mean, and more than 3 % longer than 256 x 256 tiles alone on three (800 x 12288 x 128 to 512 of a batch, 1 to 4 us).  (One
+// time per step whatever the columns hold, and nothing per round, sent 6400 rows x 6144 x 1024 of a batch out in two
+// launches, 140 us for 123.)
 GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int n_plain, int kv_dest)
 {
     const double kv = (double)(N - n_plain) / (double)N;
