@@ -1232,7 +1232,6 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     a.sq_cluster = pl->d_sq_cluster;
     a.sq_page0 = pl->d_sq_page0;
     a.spool = pl->d_spool + (pl->decode_cap > 0 ? (size_t)layer * pl->spool_layer_bytes : 0);
-    a.total_tokens = pl->total_tokens;
     hipEvent_t *tev = ctx->ev[ctx->timing_count % sgc_ctx::kTimingRing];
     const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
     if (timed) SGC_HIP(ctx, hipEventRecord(tev[0], s));

@@ -263,7 +263,6 @@ struct AttnArgs {
     const int32_t *sq_cluster;    // [n_queries]
     const int32_t *sq_page0;      // [n_queries] first page of the query in the suffix page pool
     const char *spool;            // suffix page pool (bf16 pages, same layout as cache pages) or null
-    int64_t total_tokens;
     // prefix mode: the clusters are taken from jobs (MFMA kernel: a tile's tok_base field is the job index)
     const PrefixJob *jobs;
     const GenericTile *gtiles;    // tiles of the generic kernel
