@@ -134,7 +134,13 @@ const char *sgc_last_error(const sgc_ctx *ctx);
  * scaled query beyond 65504 in magnitude becomes an infinity and the rows that see it come out NaN.
  * With kv_dtype = SGC_FP8_E4M3 each (cluster, layer, kv head) has one fp32 scale for K and one
  * for V: stored code = round_to_nearest_even(x / scale), scale = max|x| / 448 (1 if all zero),
- * OCP E4M3 with saturation; K is scaled after rotation.
+ * OCP E4M3 with saturation; K is scaled after rotation.  A NaN does not count for the scale and is stored as
+ * code 0x7F; an infinity makes its head's scale infinite.
+ *
+ * Values that are not finite: a row that may not see a token is not changed by that token's key.  With the
+ * fp32-arithmetic kernel (SGC_KERNEL_GENERIC) the same holds for its value; the matrix-core kernel multiplies
+ * the values of masked keys by zero, so an Inf or NaN in V can turn that channel of other rows of the same
+ * 128-row tile (earlier prompt tokens, questions of the same cluster) into NaN.
  */
 size_t sgc_cache_page_bytes(const sgc_attn_params *params);                 /* one page, one layer */
 size_t sgc_cache_pool_bytes(const sgc_attn_params *params, int64_t total_pages); /* all layers */
@@ -240,8 +246,9 @@ int sgc_decode_step_batched(sgc_ctx *ctx, const sgc_cache *cache, sgc_plan *plan
  * the partial results of the step's cached-prompt part, which sgc_decode_step_batched keeps in a block
  * of the context's pool, go to a fixed 32 MiB device array inside the library (one copy per GPU, held
  * until the process ends).  SGC_ENOMEM if they need more: n_queries * Hq * d * 2 bytes plus n_queries *
- * Hq * 4, times the number of key ranges the plan splits long prompts into (at most 8).  Every table the
- * step reads must already be on the device and current, which is the case once the plan's suffix prefill
+ * Hq * 4, times the number of key ranges the plan splits long prompts into: up to 16, but more than 8, or
+ * ranges shorter than 512 keys, only where they fit the array, so that this can happen at 8 or fewer.  Every
+ * table the step reads must already be on the device and current, which is the case once the plan's suffix prefill
  * has run and no cluster was allocated or released since: SGC_ESTATE otherwise (rotary table too short --
  * set max_position to cover prefix + question + generated tokens --, page tables or tile lists stale).
  * All calls on one GPU share the array and it keeps the last call's contents; nothing in it needs
@@ -290,7 +297,9 @@ int sgc_union_subgraphs(sgc_ctx *ctx, int32_t m, const int32_t *labels, int32_t 
  *   dev_w_qkv [(Hq + 2 Hkv) d][d_model]: rows are the Q heads, then the K heads, then the V heads, each
  *             head's d channels together;        dev_w_o [d_model][Hq d].
  * Products accumulate in fp32; q, keys, values and y are rounded to io_dtype (kv_dtype in the cache)
- * once, when stored.  Every row of x, q, y must start 16-byte aligned.  Normalisation and residual
+ * once, when stored.  The order of the sums follows from the call's number of rows, so a prompt projected by
+ * itself and the same prompt among others may differ in the last bit of what is stored (and, behind an fp8
+ * cache, in a scale or a code next to a boundary); the same call gives the same bits every time.  Every row of x, q, y must start 16-byte aligned.  Normalisation and residual
  * connections are the caller's.
  *
  * sgc_project_qkv_prefix[_batched]: x of each cluster's prompt [prefix_len][d_model] -> keys rotated at

@@ -141,10 +141,11 @@ def test_decode_ranges_of_few_row_tiles(prefix_len, g):
 
 @pytest.mark.parametrize("g", [16, 1])
 def test_decode_long_questions_and_the_widest_head_group(g):
-    """Questions of up to 330 tokens (21 pages of own keys: six chunks of the own-keys kernel's online softmax, the last one
-    partly filled) and, with g = 16, as many query heads per KV head as the matrix-core form of that kernel takes."""
+    """Questions of up to 330 tokens in the own-keys kernel's chunks of two pages: with the step's tokens 21, 17 and 9 pages (the
+    last chunk's second page is a repeated, masked one), 16, and 4 that become 5; with g = 16, as many query heads per KV head
+    as the matrix-core form of that kernel takes."""
     w = workloads.custom(f"decode_long_q_g{g}", n_q_heads=2 * g, n_kv_heads=2, head_dim=128, rope_base=500000.0, io_dtype="bf16",
-                         prefix_len=[90, 0], labels=[0, 1, 0, 1, 0], suffix_len=[330, 257, 63, 64, 129], seed=47)
+                         prefix_len=[90, 0], labels=[0, 1, 0, 1, 0, 1], suffix_len=[330, 257, 63, 64, 129, 240], seed=47)
     n_steps = 4
     got = _run_decode(w, n_steps)[0]
     o_ref, lse_ref = _oracle_decode(w, 0, n_steps, oracle_caches(w, 0))
