@@ -32,7 +32,8 @@ def _close(name, got, ref):
     (200, 4224, 7, 3), (300, 4096, 32, 3),                                       # 64 x 128
     (257, 8192, 4, 1), (600, 4096, 32, 1), (1000, 4096, 8, 1),                   # 128 x 128, deep
     (1, 128, 1, 2), (63, 128, 1, 2), (65, 384, 2, 2),                            # 128 x 128, two workgroups per CU: two and four
-    (2000, 4096, 32, 2), (2048, 4096, 7, 2), (16384, 4096, 1, 2),                # steps, many
+    (2000, 4096, 32, 2), (2048, 4096, 7, 2),                                     # steps, many, few in many tiles
+    (16384, 4096, 1, 2), (16300, 4096, 2, 2), (16384, 4096, 3, 2),
     (4097, 2048, 1, 0), (4097, 2048, 2, 0), (4097, 2048, 3, 0),                  # 256 x 256: fewer steps than the ring of slabs
     (4096, 4096, 32, 0),
     (4300, 4224, 8, 11), (5000, 4224, 16, 12), (4095, 4224, 7, 13), (4300, 4096, 32, 14),     # 256 x 256 and a remainder
@@ -50,6 +51,15 @@ def test_output_projection_rows_and_tiles(M, N, Hq, choice):
     sgc.sgc_ctx_destroy(ctx)
     _close(f"{M} x {N} x {K}", y[:M], x.float() @ w.float().T)
     assert bool((y[M] == 7.0).all()), "a row behind the last was written"
+
+
+@pytest.mark.parametrize("Hq,Hkv,d_model,rows", [(32, 8, 4096, 300), (16, 8, 1024, 1000), (16, 8, 1024, 2001), (2, 1, 64, 17)])
+def test_qkv_epilogues_per_tile(Hq, Hkv, d_model, rows):
+    """Queries, pages of the prompt and (through the attention over an empty prompt) pages of the batch."""
+    prompt = workloads.custom("tiles", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16",
+                              prefix_len=[rows, 0], cluster_sizes=[1, max(1, rows // 48)], suffix_range=(33, 64), seed=rows)
+    last = prompt.n_queries - 1
+    _run_layer(prompt, d_model, queries=sorted({0, last // 2, last}))
 
 
 @pytest.mark.parametrize("Hq,Hkv,d_model,prompts,choice", [
