@@ -5,8 +5,7 @@
 // the cluster's cached prompt.  One workgroup takes a tile of rows that all belong to one
 // (cluster, KV head): rows are (query, token, head-in-group) of ANY query of the cluster, so the
 // cached prefix K/V tiles staged in LDS are shared by several queries at once.  After the
-// prefix keys the same rows run causally over their own query's suffix keys, which a small
-// ingest kernel has put into pages of the same layout beforehand.
+// prefix keys the same rows run causally over their own query's suffix keys.
 //
 // Matrix-core mapping (v_mfma_f32_32x32x16_f16 / _bf16, 64-lane wavefronts):
 //   S^T = K Q^T : A = 32 keys x 16 channels (from LDS), B = 16 channels x 32 rows (Q, registers).
@@ -41,6 +40,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr int D = 128;                       // head dim
 constexpr int BN = 64;                       // keys per LDS tile (4 pages)
@@ -50,7 +50,7 @@ constexpr int LDS_TILE_BYTES = 4 * HALF_BYTES;   // two K buffers, then two V bu
 constexpr int K8_PART_BYTES = kPageTokens * D;    // one page's K of one head as e4m3 codes: 2 KiB
 constexpr int K8_PART_STRIDE = K8_PART_BYTES + 128;   // in LDS consecutive pages sit 2 KiB + 128 bytes apart: the two pages
                                                       // a 32-key operand read touches then fall into different banks
-constexpr int MAX_TILE_QUERIES = 256;        // queries a row tile can touch (one row each at least)
+constexpr int OWN_PAGES = BN / kPageTokens;   // pages of own-suffix keys in one of the K (V) buffers
 constexpr float kKeepBelow = 1073741824.0f;  // 2^30: a tile's weights may sum to this against a stale maximum
 
 // Combine a value with the one held by the lane 32 away (the other half of a score row), through
@@ -125,14 +125,6 @@ __device__ __forceinline__ void q_turn_half(char *qst, const uint4 &a0, const ui
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-struct TileDesc {
-    int kind;      // 0: cached prefix keys, 1: the suffix keys of sorted query q
-    int key0;      // first key of the tile (index inside the prefix / inside the query's suffix)
-    int q;         // sorted query (kind 1)
-    int page0;     // first suffix page of the tile (kind 1)
-    int page_last; // last suffix page of the query (kind 1)
-};
-
 // Decode (SubGCache App. A.2: up to 32 generated tokens per query): the blocks behind the tiles of a decode
 // step's launch append the step's new token of every query to its suffix pages, K rotated at position
 // P + len + step, V as given; 8 lanes per (sorted query, KV head), one 8-channel chunk of each half per lane.
@@ -185,16 +177,19 @@ __device__ inline void append_new_tokens(const AttnArgs &a, int blk)
 // twice the bf16 rate): the rotated, scaled query row is quantised to e4m3 with a power-of-two scale of its own, which
 // the instruction applies to the row's products in hardware, so scores come out in the same units as on the other
 // paths.  K codes then go to LDS as they are (2 KiB per page part); V is still widened to bf16 for the second product.
-template <int NW, int MI, bool KV_FP8, int MODE, bool QK8>
+//
+// OWN_RAW: the question tokens' keys and values are taken as the caller gives them (a.k, a.v), rotated and turned on their
+// way into LDS; otherwise they are read from the suffix page pool.
+template <int NW, int MI, bool KV_FP8, int MODE, bool QK8, bool OWN_RAW>
 __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mfma_kernel(const AttnArgs a)
 {
+    static_assert(NW == 4 && MI == 1, "the own-suffix part deals pages to four wavefronts of 32 rows");
     static_assert(!QK8 || (KV_FP8 && MI == 1 && NW == 4), "the fp8 first product needs an fp8 cache");
     if (MODE == MODE_SUFFIX && (int)blockIdx.x >= a.n_tiles) {
         append_new_tokens(a, (int)blockIdx.x - a.n_tiles);
         return;
     }
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    int2 *const qinfo = reinterpret_cast<int2 *>(smem + LDS_TILE_BYTES);   // (suffix length, first suffix page)
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -366,15 +361,21 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
 
     // ---- per-lane row bookkeeping ----
     const bool inline_queries = MODE == MODE_SUFFIX && __builtin_amdgcn_readfirstlane(t.n_q) <= kTileQueries;
-    int tq_tok0[kTileQueries], tq_src0[kTileQueries];
+    int tq_tok0[kTileQueries], tq_src0[kTileQueries], tq_page0[kTileQueries];
 #pragma unroll
     for (int k = 0; k < kTileQueries; ++k) {
         tq_tok0[k] = __builtin_amdgcn_readfirstlane(t.q[k].tok0);
         tq_src0[k] = __builtin_amdgcn_readfirstlane(t.q[k].src0);
+        tq_page0[k] = __builtin_amdgcn_readfirstlane(t.q[k].page0);
     }
+    // Own keys are numbered by slots, 16 to a page, over the suffix pages of all queries the tile touches: page 0 is the
+    // first page of query sq_lo, and the last one holds the tile's last row's own key.
+    const bool own = MODE == MODE_SUFFIX && !a.skip_self;
+    const int own_page0 = __builtin_amdgcn_readfirstlane(t.own_page0), n_own = own ? __builtin_amdgcn_readfirstlane(t.n_own_pages) : 0;
     bool valid[MI];
     int64_t io_row[MI];     // element offset of the row in q / o
-    int qpos[MI], sq[MI], lim[MI], src_tok[MI], head[MI];
+    int qpos[MI], lim[MI], src_tok[MI], head[MI];
+    int own_first = 0;      // slot of the first key of the row's query
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
         const int r = t.row0 + (wave * MI + mi) * 32 + n;
@@ -390,27 +391,25 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                 const int src0 = ge3 ? tq_src0[3] : ge2 ? tq_src0[2] : ge1 ? tq_src0[1] : tq_src0[0];
                 qpos[mi] = tau - first;
                 src_tok[mi] = src0 + qpos[mi];
-                sq[mi] = sq_lo + (int)ge1 + (int)ge2 + (int)ge3;
+                own_first = ((ge3 ? tq_page0[3] : ge2 ? tq_page0[2] : ge1 ? tq_page0[1] : tq_page0[0]) - own_page0) * kPageTokens;
             } else {
                 const TokInfo ti = a.tok_info[tau];
                 src_tok[mi] = ti.src;
                 qpos[mi] = ti.qpos;
-                sq[mi] = ti.sq;
+                own_first = (ti.page0 - own_page0) * kPageTokens;
             }
             lim[mi] = P;
         } else {
             src_tok[mi] = tk;
             qpos[mi] = tk;
-            sq[mi] = 0;
             lim[mi] = tk + 1;
         }
         io_row[mi] = ((int64_t)src_tok[mi] * Hq + head[mi]) * D;
     }
-    // wave-uniform bounds: visible cached keys, and the sorted queries of this wave's rows.  Rows are in
+    // wave-uniform bounds of the visible cached keys.  Rows are in
     // sorted order (and rows past the tile's end repeat its last row), so the first lane holds the minima
     // and lane 31 of the last row block the maxima.
     const int lim_min = __builtin_amdgcn_readlane(lim[0], 0), lim_max = __builtin_amdgcn_readlane(lim[MI - 1], 31);
-    const int wsq_min = __builtin_amdgcn_readlane(sq[0], 0), wsq_max = __builtin_amdgcn_readlane(sq[MI - 1], 31);
 
     if (!KV_FP8 && n_kt > 0) {
         fetch_cache(ids0, kbuf_of(0), ids0, vbuf_of(0));
@@ -526,22 +525,6 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                     q8[t][2 * pc] = w0;
                     q8[t][2 * pc + 1] = w1;
                 }
-        }
-    }
-
-    // ---- the queries this tile touches (suffix mode): lengths and first pages into LDS ----
-    // (read by the own-suffix tile iterator after the first barrier; placed after the Q loads so that the
-    // table look-ups of the rare many-queries case do not sit in front of them)
-    if (MODE == MODE_SUFFIX) {
-        if (inline_queries) {
-            if (tid < kTileQueries) {
-                const int len = tid == 0 ? t.q[0].len : tid == 1 ? t.q[1].len : tid == 2 ? t.q[2].len : t.q[3].len;
-                const int pg0 = tid == 0 ? t.q[0].page0 : tid == 1 ? t.q[1].page0 : tid == 2 ? t.q[2].page0 : t.q[3].page0;
-                qinfo[tid] = make_int2(len, pg0);
-            }
-        } else {
-            for (int i = tid; i <= sq_hi - sq_lo && i < MAX_TILE_QUERIES; i += NW * 64)
-                qinfo[i] = make_int2(a.sq_len[sq_lo + i], a.sq_page0[sq_lo + i]);
         }
     }
 
@@ -751,7 +734,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
             land_cache(nullptr, nullptr);
         }
     }
-    __syncthreads();       // also: qinfo is in LDS
+    __syncthreads();
     if (n_my > 0) {
         const char *k0 = kbuf_of(0);
 #pragma unroll
@@ -759,35 +742,94 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         qk_half_cache(s0, [&](int i) __attribute__((always_inline)) { frag[i] = kc_block(k0, 1, i); });
     }
     __syncthreads();       // every wavefront has read K of tile 0 before step 0 overwrites it
-    // ---- the stream of this row tile's own suffix key tiles ------------------------------------------------
-    // Scalar iterator over (query, 64-key tile); a query's LDS record is read when the stream reaches it.  The
-    // first tile is requested during the last cached step, into the buffers that step leaves free.
-    int it_q = sq_lo - 1, it_jt = 0, it_njt = 0, it_pg0 = 0, it_pglast = 0;
-#define SGC_NEXT_SELF(ok, d)                                                                        \
-    do {                                                                                            \
-        while (it_jt >= it_njt && it_q < sq_hi) {                                                   \
-            ++it_q;                                                                                 \
-            const int2 qi = qinfo[min(it_q - sq_lo, MAX_TILE_QUERIES - 1)];                         \
-            const int S__ = __builtin_amdgcn_readfirstlane(qi.x);                                   \
-            it_pg0 = __builtin_amdgcn_readfirstlane(qi.y);                                          \
-            it_pglast = it_pg0 + (S__ - 1) / kPageTokens;                                           \
-            it_njt = ((it_q == sq_hi ? last_qpos : S__ - 1) + BN) / BN;                             \
-            it_jt = 0;                                                                              \
-        }                                                                                           \
-        (ok) = it_jt < it_njt;                                                                      \
-        (d).key0 = it_jt * BN;                                                                      \
-        (d).q = it_q;                                                                               \
-        (d).page0 = it_pg0 + it_jt * 4;                                                             \
-        (d).page_last = it_pglast;                                                                  \
-        ++it_jt;                                                                                    \
-    } while (0)
-    auto fetch_self = [&](const TileDesc &d, char *kdst, char *vdst) __attribute__((always_inline)) {
-        const uint32_t po = (uint32_t)min(d.page0 + (lane & 3), d.page_last) * spool_page_256;
-        issue_copy_bf16(po, kdst, po, vdst, spool_base, spool_v_off);
+    // ---- own-suffix keys: bringing pages into LDS -----------------------------------------------------------
+    // The tile's own pages come in chunks of four, one page per wavefront, double buffered: chunk i in K buffer i & 1 and, counted
+    // from the one that the last cached step leaves free, V buffer i & 1.
+    auto own_kbuf = [&](int i) __attribute__((always_inline)) -> char * { return kbuf_of(i); };
+    auto own_vbuf = [&](int i) __attribute__((always_inline)) -> char * { return vbuf_of(n_kt + i); };
+    // (lane_again: per-lane offsets are worked out where they are used; kept from one use to the next they would push others out
+    // of the registers)
+    auto lane_again = [&]() __attribute__((always_inline)) -> int {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
     };
-    TileDesc cur = {1, 0, 0, 0, 0}, nxt = {1, 0, 0, 0, 0};
-    bool have = false, more = false;
-    if (MODE == MODE_SUFFIX && !a.skip_self) SGC_NEXT_SELF(have, cur);      // qinfo is visible since the barriers above
+    // Starts the copy of this wavefront's page of chunk i.  OWN_RAW: the rows as given, 256 bytes a token, tokens past the query's
+    // end repeating its last one; the 16-byte chunks of K's row r sit permuted by r, those of V's by 4 (r % 4), so that what
+    // reads them below covers all banks.
+    auto own_copy = [&](int i) __attribute__((always_inline)) {
+        const int p = i * OWN_PAGES + wave_u;
+        if (p >= n_own) return;
+        char *kd = own_kbuf(i) + wave_u * PART_BYTES, *vd = own_vbuf(i) + wave_u * PART_BYTES;
+        if constexpr (OWN_RAW) {
+            const SuffixPage pg = a.spages[own_page0 + p];
+            const int l = lane_again(), r0 = l >> 4, c = l & 15;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {           // rows 4 j .. 4 j + 3 of the page
+                const int r = 4 * j + r0;
+                const int64_t row = ((int64_t)(pg.row0 + min(r, pg.n - 1)) * Hkv + hk) * (D * 2);
+                const auto *gk = (const __attribute__((address_space(1))) void *)(static_cast<const char *>(a.k) + row + ((c ^ r) * 16));
+                const auto *gv = (const __attribute__((address_space(1))) void *)(static_cast<const char *>(a.v) + row + ((c ^ (4 * r0)) * 16));
+                __builtin_amdgcn_global_load_lds(gk, (__attribute__((address_space(3))) void *)(kd + j * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(gv, (__attribute__((address_space(3))) void *)(vd + j * 1024), 16, 0, 0);
+            }
+        } else {
+            const char *src = spool_base + ((uint64_t)((uint32_t)(own_page0 + p) * spool_page_256) << 8) + lane16;
+            copy_4k_to_lds(src, kd);
+            copy_4k_to_lds(src + spool_v_off, vd);
+        }
+    };
+    // OWN_RAW: this wavefront's page of chunk i is rotated in place and put into the pages' order: lane (r, c0) = (lane % 16,
+    // lane / 16) takes the 16-byte chunks c0, c0 + 4 of token r and their partners 8 further.  own_table requests the rotation's
+    // entries ahead of that.
+    float4 own_cs[2][4];
+    auto own_table = [&](int i) __attribute__((always_inline)) {
+        if constexpr (OWN_RAW) {
+            const int p = i * OWN_PAGES + wave_u;
+            if (p >= n_own) return;
+            const SuffixPage pg = a.spages[own_page0 + p];
+            const int l = lane_again(), pos = pg.pos0 + min(l & 15, pg.n - 1);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    own_cs[k][e] = a.rope ? reinterpret_cast<const float4 *>(a.rope + (int64_t)pos * (D / 2) + ((l >> 4) + 4 * k) * 8)[e]
+                                          : make_float4(1.f, 0.f, 1.f, 0.f);
+        }
+    };
+    auto own_rotate = [&](int i) __attribute__((always_inline)) {
+        if constexpr (OWN_RAW) {
+            if (i * OWN_PAGES + wave_u >= n_own) return;
+            const int l = lane_again(), r = l & 15, c0 = l >> 4;
+            char *kp = own_kbuf(i) + wave_u * PART_BYTES;
+            uint4 lo[2], hi[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int c = c0 + 4 * k;
+                lo[k] = *reinterpret_cast<const uint4 *>(kp + r * 256 + ((c ^ r) * 16));
+                hi[k] = *reinterpret_cast<const uint4 *>(kp + r * 256 + (((c + 8) ^ r) * 16));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int c = c0 + 4 * k;
+                const uint32_t wl[4] = {lo[k].x, lo[k].y, lo[k].z, lo[k].w}, wh[4] = {hi[k].x, hi[k].y, hi[k].z, hi[k].w};
+                uint32_t o1[4], o2[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float a0 = __uint_as_float(wl[e] << 16), a1 = __uint_as_float(wl[e] & 0xFFFF0000u);
+                    const float b0 = __uint_as_float(wh[e] << 16), b1 = __uint_as_float(wh[e] & 0xFFFF0000u);
+                    const float4 t4 = own_cs[k][e];
+                    o1[e] = pack2_f16(a0 * t4.x - b0 * t4.y, a1 * t4.z - b1 * t4.w);
+                    o2[e] = pack2_f16(b0 * t4.x + a0 * t4.y, b1 * t4.z + a1 * t4.w);
+                }
+                *reinterpret_cast<uint4 *>(kp + c * 256 + r * 16) = make_uint4(o1[0], o1[1], o1[2], o1[3]);
+                *reinterpret_cast<uint4 *>(kp + (c + 8) * 256 + r * 16) = make_uint4(o2[0], o2[1], o2[2], o2[3]);
+            }
+        }
+    };
 
     // One part's copy: per-lane source address and LDS destination.  Issued as four 1 KiB instructions that
     // the steady-state step spreads between its matrix instructions, so that a wavefront never sits on a
@@ -811,24 +853,25 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
             default: break;
         }
     };
-    // Step kt.  spread (a true_type / false_type tag): issue this step's copies between the matrix
-    // instructions (needs a bf16 cache, both copies due and this wavefront computing) or at the top.
-    auto cache_step = [&](const int kt, auto spread_tag) __attribute__((always_inline)) {
-        constexpr bool spread = decltype(spread_tag)::value;
-        char *kd = kt + 2 < n_kt ? kbuf_of(kt) : nullptr;
-        char *vd = kt + 1 < n_kt ? vbuf_of(kt + 1) : nullptr;
-        const uint32_t ids3 = cache_page_ids(kt + 3);    // issued before the copies, used a step later
+    // Step kt.  SPREAD issues its copies between the matrix instructions (needs a bf16 cache, both copies due and this
+    // wavefront computing), TOP at the step's top.  LAST (kt = n_kt - 1) has no next tile: no scores are started for one
+    // and the second half's V takes the window's places instead (8 of 32 products less).
+    enum { SPREAD, TOP, LAST };
+    auto cache_step = [&](const int kt, auto kind_tag) __attribute__((always_inline)) {
+        constexpr int kind = decltype(kind_tag)::value;
+        constexpr bool spread = kind == SPREAD, last = kind == LAST;
+        char *kd = !last && kt + 2 < n_kt ? kbuf_of(kt) : nullptr;
+        char *vd = !last && kt + 1 < n_kt ? vbuf_of(kt + 1) : nullptr;
+        uint32_t ids3 = 0;
+        if (!last) ids3 = cache_page_ids(kt + 3);    // issued before the copies, used a step later
         PartCopy first = {nullptr, nullptr}, second = {nullptr, nullptr};
         if (spread) {
-            if (NW == 4) {
-                first = cache_part(true, ids1, vd);      // V of tile kt + 1 is needed first
-                second = cache_part(false, ids2, kd);
-            } else {
-                first = moves_v ? cache_part(true, ids1, vd) : cache_part(false, ids2, kd);
-            }
+            first = cache_part(true, ids1, vd);      // V of tile kt + 1 is needed first
+            second = cache_part(false, ids2, kd);
+        } else if (last) {
+            if (own) own_copy(0);
         } else {
             if (kd || vd) fetch_cache(ids2, kd, ids1, vd);
-            if (MODE == MODE_SUFFIX && kt == n_kt - 1 && have) fetch_self(cur, kbuf_of(kt), vbuf_of(kt + 1));
         }
         ids1 = ids2;
         ids2 = ids3;
@@ -836,7 +879,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
             const int key0 = kt * BN;
             const bool masked = key0 + BN > lim_min;
             const bool careful = masked || fresh;
-            // Past this wave's last tile the "next" scores are formed from whatever the other K buffer holds
+            // Past this wave's last tile (but not the workgroup's) the "next" scores are formed from the other K buffer
             // and never used; this keeps the step free of branches around the matrix instructions.
             const char *kn = kbuf_of(kt + 1), *vc = vbuf_of(kt);
             auto keep = [&](int mi, int j) __attribute__((always_inline)) { return key0 + j < lim[mi]; };
@@ -862,30 +905,43 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
             weights(s0);
             if (weights_overflow()) redo(s0, s1, 0);
             pv_half([&](int i) __attribute__((always_inline)) {
-                frag[i] = kc_block(kn, 0, i);
-                if (spread && NW == 4) copy_quarter(second, i);
+                frag[i] = last ? v_block(vc, 1, i) : kc_block(kn, 0, i);
+                if (spread) copy_quarter(second, i);
             });
             // half 1
             if (careful) raise_reference(s1, 1, masked, keep);
-            qk_half_cache(s0, [&](int i) __attribute__((always_inline)) { frag[i] = v_block(vc, 1, i); });
+            if (!last) qk_half_cache(s0, [&](int i) __attribute__((always_inline)) { frag[i] = v_block(vc, 1, i); });
             weights(s1);
             if (weights_overflow()) redo(s1, s0, 1);
-            pv_half([&](int i) __attribute__((always_inline)) { frag[i] = kc_block(kn, 1, i); });
+            if (last) {
+                if (own) own_table(0);
+                pv_half(no_refill);
+            } else
+                pv_half([&](int i) __attribute__((always_inline)) { frag[i] = kc_block(kn, 1, i); });
             fresh = false;
         }
         land_cache(kd, vd);
-        __syncthreads();
+        if (!last || !own) __syncthreads();      // (the own-suffix part has barriers of its own)
     };
     {
         int kt = 0;
         if (!KV_FP8) {
             const int n_spread = min(n_kt - 2, MODE == MODE_SUFFIX ? n_kt : n_my);
-            for (; kt < n_spread; ++kt) cache_step(kt, std::true_type{});
+            for (; kt < n_spread; ++kt) cache_step(kt, std::integral_constant<int, SPREAD>{});
         }
-        for (; kt < n_kt; ++kt) cache_step(kt, std::false_type{});
+        for (; kt < n_kt - 1; ++kt) cache_step(kt, std::integral_constant<int, TOP>{});
+        if (n_kt > 0) cache_step(n_kt - 1, std::integral_constant<int, LAST>{});
     }
 
-    // ---- the suffix keys of every query this row tile touches, double buffered ------------------------
+    // ---- the own-suffix keys of the queries this row tile touches --------------------------------------------
+    // What this part costs is round trips and barriers, hardly any products: a tile touches two or three queries of some tens of
+    // tokens.  So the queries' pages are packed, four to a chunk whatever query they belong to, and the keys and values
+    // are taken as given where nothing else needs them as pages: an ingest launch in front of this one read and wrote as
+    // many bytes as the queries' rows themselves, and a 64-key step with a barrier per touched query cost more than the rotation
+    // of a page per wavefront and chunk does.  100 questions over ten prompts, four layers 588 -> 546 us with their prompts' prefill,
+    // 320 questions 432 -> 415 us, 1024 questions of 32 heads without groups 3370 -> 3005 us.
+    // Every wavefront walks the pages its own rows see, two at a time and with no barrier between them: a page belongs to one
+    // query, and a row sees the slots own_first .. own_first + qpos.
     bool v_scaled = !KV_FP8;
     if (MODE == MODE_SUFFIX) {
         if (!v_scaled) {        // fp8 cache: the accumulated cached part takes the V scale once
@@ -897,87 +953,69 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                     for (int r = 0; r < 16; ++r) oacc[mi][db][r] *= v_scale;
             v_scaled = true;
         }
-        // own tile i: K in K buffer (kpar + i) & 1, V in V buffer (vpar + i) & 1
-        int kpar = (n_kt + 1) & 1, vpar = n_kt & 1;
-        if (n_kt == 0) {
-            if (have) {
-                fetch_self(cur, kbuf_of(kpar), vbuf_of(vpar));
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-            }
-            __syncthreads();
+        if (own && n_kt == 0) {
+            own_copy(0);
+            own_table(0);
         }
-        while (have) {
-            SGC_NEXT_SELF(more, nxt);
-            if (more) fetch_self(nxt, kbuf_of(kpar ^ 1), vbuf_of(vpar ^ 1));
-            const int key0 = cur.key0, q = cur.q;
-            bool mine = false;                  // does a row of this wave belong to query q and reach key0?
+        const int wpg_lo = __builtin_amdgcn_readlane(own_first, 0) / kPageTokens;
+        const int wpg_hi = __builtin_amdgcn_readlane(own_first + qpos[0], 31) / kPageTokens;
+        // OWN_RAW: V rows are read transposed (ds_read_b64_tr_b16): of the 16 lanes of a group, lane 4 t + u asks for channels 4 u ..
+        // 4 u + 3 of token t and gets channel (lane % 16) of all four tokens.
+        const int tr = (lane & 15) >> 2;
+        const int lane_trow = (4 * h + tr) * 256 + (n >> 4) * 32 + (lane & 3) * 8;
+        for (int ci = 0, c0 = 0; c0 < n_own; ++ci, c0 += OWN_PAGES) {
+            const int c1 = min(c0 + OWN_PAGES, n_own);
+            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the chunk's pages have landed
+            own_rotate(ci);
+            __syncthreads();                             // (also: the chunk before this one has been read)
+            own_copy(ci + 1);
+            if (c1 < n_own) own_table(ci + 1);
+            const char *kc = own_kbuf(ci), *vc = own_vbuf(ci);
+            const int row_end = min(own_first + qpos[0], c1 * kPageTokens - 1);
+            for (int p = max(wpg_lo, c0); p <= min(wpg_hi, c1 - 1); p += 2) {
+                const int i0 = p - c0, i1 = min(p + 1, c1 - 1) - c0;       // (a second page past the end: the first again, masked)
+                const char *kp = kc + ((n >> 4) ? i1 : i0) * PART_BYTES + (h * kPageTokens + (n & 15)) * 16;
+                const char *v0 = vc + i0 * PART_BYTES, *v1 = vc + i1 * PART_BYTES;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) mine |= valid[mi] && sq[mi] == q && qpos[mi] >= key0;
-            if (q >= wsq_min && q <= wsq_max && __any(mine)) {
-                const char *kc = kbuf_of(kpar), *vc = vbuf_of(vpar);
-                // key j of the tile is visible to a row iff j <= reach (-1: another query's row); the 4 h of
-                // the lane's key index is taken off once
-                int reach[MI];
-                bool far = false;
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) {
-                    const int r0 = (valid[mi] && sq[mi] == q) ? qpos[mi] - key0 : -1;
-                    far |= r0 >= 32;
-                    reach[mi] = r0 - 4 * h;
-                }
-                const bool second_half = __any(far);        // does any row of this wave see keys 32..63 of the tile?
-                auto keep = [&](int mi, int j) __attribute__((always_inline)) { return j - 4 * h <= reach[mi]; };
-#pragma unroll
-                for (int i = 0; i < 8; ++i) frag[i] = k_block(kc, 0, i);
-                // all products of the tile start from the same -m_ref; a raise by half 0 is passed on to half 1
-                float before[MI];
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) before[mi] = m_ref[mi];
-                if (second_half) {
-                    qk_half(s0, [&](int i) __attribute__((always_inline)) { frag[i] = k_block(kc, 1, i); });
-                    qk_half(s1, [&](int i) __attribute__((always_inline)) { frag[i] = v_block(vc, 0, i); });
-                } else {
-                    qk_half(s0, [&](int i) __attribute__((always_inline)) { frag[i] = v_block(vc, 0, i); });
-                }
-                if (KV_FP8) rescale_self(s0, before);
-                raise_reference(s0, 0, true, keep);
+                for (int i = 0; i < 8; ++i) frag[i] = *reinterpret_cast<const bf16x8 *>(kp + i * 512);
+                qk_half(s0, [&](int i) __attribute__((always_inline)) {
+                    const char *vp = i < 4 ? v0 : v1;
+                    if constexpr (OWN_RAW) {
+                        const char *at = vp + lane_trow + (((i & 3) ^ tr) * 64);
+                        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+                        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+                        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + 8 * 256));
+                        frag[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+                    } else {
+                        frag[i] = *reinterpret_cast<const bf16x8 *>(vp + lane_voff + (i & 3) * 1024);
+                    }
+                });
+                if (KV_FP8) rescale_self(s0, m_ref);
+                // slot 16 p + j is visible iff own_first <= slot <= row_end; the 4 h of the lane's key index is taken off once
+                const int first = own_first - p * kPageTokens - 4 * h;
+                const uint32_t span = (uint32_t)(row_end - own_first);
+                const bool any = row_end >= own_first;
+                raise_reference(s0, 0, true, [&](int, int j) __attribute__((always_inline)) { return any && (uint32_t)(j - 4 * h - first) <= span; });
                 weights(s0);
-                if (second_half) {
-                    pv_half([&](int i) __attribute__((always_inline)) { frag[i] = v_block(vc, 1, i); });
-                    if (KV_FP8) rescale_self(s1, before);
-#pragma unroll
-                    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (FOLD) s1[mi][r] -= m_ref[mi] - before[mi];
-                    raise_reference(s1, 1, true, keep);
-                    weights(s1);
-                }
                 pv_half(no_refill);
             }
-            if (more) __builtin_amdgcn_s_waitcnt(0x0F70);
-            __syncthreads();
-            cur = nxt;
-            have = more;
-            kpar ^= 1;
-            vpar ^= 1;
         }
-#undef SGC_NEXT_SELF
     }
 
     // ---- normalise and store ----
     // A lane holds 4-channel pieces of its row; written out as they are they would make 8-byte stores scattered
-    // over 32 rows per instruction.  The wavefront instead stages its 32 x 128 outputs in its own 8 KiB slice of
-    // the tile buffers (idle now: every wavefront is past the last barrier behind its last read), the 16-byte
-    // chunks of row n permuted by n % 16 so that the writes and the reads below spread over all banks, and stores
+    // over 32 rows per instruction.  The wavefront instead stages its 32 x 128 outputs in
+    // 8 KiB of the K and V buffers that the chunk after the last own one would take (every wavefront is past the barrier behind
+    // their last read), the 16-byte chunks of row n permuted by n % 16 so that the writes and the reads below spread over all banks, and stores
     // four whole rows of 256 bytes per instruction.
     uint16_t *og = static_cast<uint16_t *>(o_base);
-    char *const ostage = smem + wave * MI * 8192;
+    const int own_chunks = (n_own + OWN_PAGES - 1) / OWN_PAGES;
+    char *const ostage[2] = {own_kbuf(own_chunks) + wave_u * PART_BYTES, own_vbuf(own_chunks) + wave_u * PART_BYTES};    // rows 0 .. 15, 16 .. 31
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
         const float l = half_sum(l_part[mi]);
         const float inv_l = (v_scaled ? 1.0f : v_scale) / l;
-        char *st = ostage + mi * 8192 + n * 256 + h * 8;
+        char *st = ((n >> 4) ? ostage[1] : ostage[0]) + (n & 15) * 256 + h * 8;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1000,7 +1038,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int r = 4 * k + (lane >> 4), c = lane & 15;     // row r of the block sits in lanes r and r + 32
-            const uint4 y = *reinterpret_cast<const uint4 *>(ostage + mi * 8192 + r * 256 + ((c ^ (r & 15)) * 16));
+            const uint4 y = *reinterpret_cast<const uint4 *>(ostage[k >> 2] + (r & 15) * 256 + ((c ^ (r & 15)) * 16));
             const int64_t row = __shfl(io_row[mi], r);
             const int ok = __shfl((int)valid[mi], r);
             if (ok) *reinterpret_cast<uint4 *>(og + row + c * 8) = y;
@@ -1008,14 +1046,12 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     }
 }
 
-constexpr size_t kDynLds = LDS_TILE_BYTES + MAX_TILE_QUERIES * sizeof(int2);
-
-template <int NW, int MI, bool FP8, int MODE, bool QK8>
+template <int NW, int MI, bool FP8, int MODE, bool QK8, bool OWN_RAW>
 hipError_t launch_one(const AttnArgs &a, int blocks, hipStream_t s)
 {
     static bool configured = false;     // raise the dynamic LDS limit once per instantiation
-    auto kern = attn_mfma_kernel<NW, MI, FP8, MODE, QK8>;
-    size_t lds = kDynLds;
+    auto kern = attn_mfma_kernel<NW, MI, FP8, MODE, QK8, OWN_RAW>;
+    size_t lds = LDS_TILE_BYTES;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -1041,11 +1077,15 @@ hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s)
         // a decode step's launch carries, behind its tiles, the blocks that append the step's new tokens
         const int per_block = NW * 64 / 8;
         const int blocks = a.n_tiles + (a.n_append * a.n_kv_heads + per_block - 1) / per_block;
-        if (fp8 && a.fp8_first_product) return launch_one<NW, MI, true, MODE_SUFFIX, true>(a, blocks, s);
-        return fp8 ? launch_one<NW, MI, true, MODE_SUFFIX, false>(a, blocks, s) : launch_one<NW, MI, false, MODE_SUFFIX, false>(a, blocks, s);
+        if (a.own_raw) {
+            if (fp8 && a.fp8_first_product) return launch_one<NW, MI, true, MODE_SUFFIX, true, true>(a, blocks, s);
+            return fp8 ? launch_one<NW, MI, true, MODE_SUFFIX, false, true>(a, blocks, s) : launch_one<NW, MI, false, MODE_SUFFIX, false, true>(a, blocks, s);
+        }
+        if (fp8 && a.fp8_first_product) return launch_one<NW, MI, true, MODE_SUFFIX, true, false>(a, blocks, s);
+        return fp8 ? launch_one<NW, MI, true, MODE_SUFFIX, false, false>(a, blocks, s) : launch_one<NW, MI, false, MODE_SUFFIX, false, false>(a, blocks, s);
     }
     // the prompt's own causal attention always takes the 16-bit first product
-    return fp8 ? launch_one<NW, MI, true, MODE_PREFIX, false>(a, a.n_tiles, s) : launch_one<NW, MI, false, MODE_PREFIX, false>(a, a.n_tiles, s);
+    return fp8 ? launch_one<NW, MI, true, MODE_PREFIX, false, false>(a, a.n_tiles, s) : launch_one<NW, MI, false, MODE_PREFIX, false, false>(a, a.n_tiles, s);
 }
 
 }  // namespace sgc

@@ -367,10 +367,12 @@ void build_tiles(sgc_plan *pl, int tile_rows)
             for (int q = 0; q < kTileQueries; ++q) {
                 const int32_t sq = t.sq_lo + q;
                 if (sq <= t.sq_hi)
-                    t.q[q] = {pl->sq_tok0[sq], pl->sq_src0[sq], pl->sq_len[sq], pl->sq_page0[sq]};
+                    t.q[q] = {pl->sq_tok0[sq], pl->sq_src0[sq], pl->sq_page0[sq]};
                 else
-                    t.q[q] = {INT32_MAX, 0, 0, 0};
+                    t.q[q] = {INT32_MAX, 0, 0};
             }
+            t.own_page0 = pl->sq_page0[t.sq_lo];
+            t.n_own_pages = pl->sq_page0[t.sq_hi] - t.own_page0 + t.last_qpos / kPageTokens + 1;
             pl->seeds[k * kXcd + x] = {t.cluster, t.hk, t.row0, t.n_rows, t.sq_lo, t.sq_hi, t.last_qpos, 0};
         }
     }
@@ -409,15 +411,18 @@ void fill_tile_pt_off(sgc_plan *pl, const sgc_cache *c)
     pl->tiles_generation = c->generation;
 }
 
-// Pages of the suffix page pool: every query gets room for its suffix plus decode_cap more tokens.
+// Suffix pages: every query gets room for its suffix plus decode_cap more tokens.
 void layout_suffix_pages(sgc_plan *pl)
 {
-    pl->spage_sq.clear();
+    pl->spages.clear();
     int32_t page = 0;
     for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) {
         pl->sq_page0[sq] = page;
         const int32_t np = (pl->sq_len[sq] + pl->decode_cap + kPageTokens - 1) / kPageTokens;
-        pl->spage_sq.insert(pl->spage_sq.end(), np, (int32_t)sq);
+        for (int32_t p = 0; p < np; ++p) {
+            const int32_t j = p * kPageTokens;
+            pl->spages.push_back({pl->sq_src0[sq] + j, std::min(pl->sq_len[sq] - j, kPageTokens), pl->cl_prefix_len[pl->sq_cluster[sq]] + j, 0});
+        }
         page += np;
     }
 }
@@ -969,7 +974,7 @@ int sgc_assign_clusters(sgc_ctx *ctx, const sgc_cache *c, int32_t n_queries, con
     pl->tok_src.resize(total);
     pl->tok_qpos.resize(total);
     pl->tok_sq.resize(total);
-    int32_t t = 0, maxpos = 0, spage = 0;
+    int32_t t = 0, maxpos = 0;
     pl->cl_sq_off.assign(n_clusters + 1, 0);
     for (int32_t k = 0; k < n_clusters; ++k) {
         pl->cl_tok_off[k] = t;
@@ -983,10 +988,7 @@ int sgc_assign_clusters(sgc_ctx *ctx, const sgc_cache *c, int32_t n_queries, con
             pl->sq_len.push_back(suffix_len[n]);
             pl->sq_tok0.push_back(t);
             pl->sq_cluster.push_back(k);
-            pl->sq_page0.push_back(spage);
-            const int32_t np = (suffix_len[n] + kPageTokens - 1) / kPageTokens;
-            for (int32_t pg = 0; pg < np; ++pg) pl->spage_sq.push_back(sq);
-            spage += np;
+            pl->sq_page0.push_back(0);           // (layout_suffix_pages)
             for (int32_t j = 0; j < suffix_len[n]; ++j, ++t) {
                 pl->tok_src[t] = cu_seqlens[n] + j;
                 pl->tok_qpos[t] = j;
@@ -1004,13 +1006,14 @@ int sgc_assign_clusters(sgc_ctx *ctx, const sgc_cache *c, int32_t n_queries, con
             pl->sq_len.push_back(0);
             pl->sq_tok0.push_back(t);
             pl->sq_cluster.push_back(k);
-            pl->sq_page0.push_back(spage);
+            pl->sq_page0.push_back(0);
             maxpos = std::max(maxpos, pl->cl_prefix_len[k]);
         }
     }
     pl->cl_tok_off[n_clusters] = t;
     pl->cl_sq_off[n_clusters] = (int32_t)pl->sq_len.size();
     pl->max_position = maxpos;
+    layout_suffix_pages(pl);
     *out_plan = pl;
     return SGC_OK;
 }
@@ -1065,7 +1068,7 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
     pl->tok_info.clear();
     if (wide_tile) {
         pl->tok_info.resize(pl->tok_src.size());
-        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->tok_sq[i], 0};
+        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->tok_sq[i], pl->sq_page0[pl->tok_sq[i]]};
     }
     pl->row_dest.clear();      // made when a projection first asks for it
 
@@ -1087,7 +1090,7 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
         {pl->sq_tok0.data(), pl->sq_tok0.size() * 4, (const void **)&pl->d_sq_tok0},
         {pl->sq_cluster.data(), pl->sq_cluster.size() * 4, (const void **)&pl->d_sq_cluster},
         {pl->sq_page0.data(), pl->sq_page0.size() * 4, (const void **)&pl->d_sq_page0},
-        {pl->spage_sq.data(), pl->spage_sq.size() * 4, (const void **)&pl->d_spage_sq},
+        {pl->spages.data(), pl->spages.size() * sizeof(SuffixPage), (const void **)&pl->d_spages},
         {pl->seeds.data(), pl->seeds.size() * sizeof(TileSeed), (const void **)&pl->d_seeds},
         {pl->tok_info.data(), pl->tok_info.size() * sizeof(TokInfo), (const void **)&pl->d_tok_info},
         {pl->sq_query.data(), pl->sq_query.size() * 4, (const void **)&pl->d_sq_query},
@@ -1116,11 +1119,12 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
     }
     if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s)) != SGC_OK) return rc;
     pl->expand_pending = !pl->tiles.empty();      // the records are written with the next suffix launch's ingest
-    if (want_rows > 0 && !pl->spage_sq.empty()) {
-        // suffix page pool: bf16 pages of every query's rotated suffix K and transposed V
+    if (want_rows > 0 && !pl->spages.empty()) {
+        // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps and projected keys
+        // (a plain suffix prefill reads its keys and values as they are given; held from here on so that no later call allocates it)
         // (decode: one pool per layer, since the pages have to outlive the layer's suffix launch; zeroed once,
         // so that pages no token has reached yet hold finite values)
-        pl->spool_layer_bytes = pl->spage_sq.size() * (size_t)2 * ctx->p.n_kv_heads * kPageTokens * ctx->p.head_dim * 2;
+        pl->spool_layer_bytes = pl->spages.size() * (size_t)2 * ctx->p.n_kv_heads * kPageTokens * ctx->p.head_dim * 2;
         pl->spool_bytes = pl->spool_layer_bytes * (pl->decode_cap > 0 ? (size_t)ctx->p.n_layers : 1);
         if ((rc = dev_acquire(ctx, pl->spool_bytes, s, &pl->spool_block)) != SGC_OK) return rc;
         pl->d_spool = pl->spool_block.p;
@@ -1231,6 +1235,19 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     a.sq_tok0 = pl->d_sq_tok0;
     a.sq_cluster = pl->d_sq_cluster;
     a.sq_page0 = pl->d_sq_page0;
+    a.spages = pl->d_spages;
+    // The attention kernel takes the question tokens' keys and values as they are given.  They are made into pages first where
+    // decode steps will read them, and where an output overlaps them (a tile's outputs are stored while others still read).
+    const size_t kv_bytes = (size_t)pl->total_tokens * ctx->p.n_kv_heads * ctx->p.head_dim * dtype_bytes(ctx->p.io_dtype);
+    const size_t o_bytes = kv_bytes / ctx->p.n_kv_heads * ctx->p.n_q_heads, lse_bytes = (size_t)pl->total_tokens * ctx->p.n_q_heads * sizeof(float);
+    auto overlap = [](const void *p, size_t pn, const void *q, size_t qn) {
+        const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(q);
+        return p && q && a0 < b0 + qn && b0 < a0 + pn;
+    };
+    const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && !overlap(dev_o, o_bytes, dev_k, kv_bytes) &&
+                         !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
+                         !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
+    a.own_raw = own_raw ? 1 : 0;
     a.spool = pl->d_spool + (pl->decode_cap > 0 ? (size_t)layer * pl->spool_layer_bytes : 0);
     hipEvent_t *tev = ctx->ev[ctx->timing_count % sgc_ctx::kTimingRing];
     const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
@@ -1238,8 +1255,8 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     // tile records that are due are written by workgroups appended to the ingest launch (they depend on nothing it writes)
     const ExpandArgs ex = plan_expand_args(pl, c);
     const bool expand = ctx->use_mfma && pl->expand_pending;
-    if (ctx->use_mfma && !skip_ingest)
-        SGC_HIP(ctx, launch_suffix_ingest(a, pl->d_spage_sq, (int)pl->spage_sq.size(), expand ? &ex : nullptr, s));
+    if (ctx->use_mfma && !skip_ingest && !own_raw)
+        SGC_HIP(ctx, launch_suffix_ingest(a, (int)pl->spages.size(), expand ? &ex : nullptr, s));
     else if (expand)
         SGC_HIP(ctx, launch_expand_tiles(ex, s));
     pl->expand_pending = false;

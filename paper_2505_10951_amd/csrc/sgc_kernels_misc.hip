@@ -285,7 +285,10 @@ __device__ inline void expand_one_tile(const ExpandArgs &e, int i)
 #pragma unroll
     for (int k = 0; k < 12; ++k) t.first_pages[k] = 0;
 #pragma unroll
-    for (int k = 0; k < kTileQueries; ++k) t.q[k] = {INT32_MAX, 0, 0, 0};
+    for (int k = 0; k < kTileQueries; ++k) t.q[k] = {INT32_MAX, 0, 0};
+    t.own_page0 = 0;
+    t.n_own_pages = 0;
+    t.unused[0] = t.unused[1] = 0;
     if (sd.n_rows > 0) {
         if (e.jobs) {
             const PrefixJob &j = e.jobs[sd.cluster];
@@ -304,8 +307,10 @@ __device__ inline void expand_one_tile(const ExpandArgs &e, int i)
 #pragma unroll
             for (int k = 0; k < kTileQueries; ++k) {
                 const int sq = sd.sq_lo + k;
-                if (sq <= sd.sq_hi) t.q[k] = {e.sq_tok0[sq], e.sq_src0[sq], e.sq_len[sq], e.sq_page0[sq]};
+                if (sq <= sd.sq_hi) t.q[k] = {e.sq_tok0[sq], e.sq_src0[sq], e.sq_page0[sq]};
             }
+            t.own_page0 = e.sq_page0[sd.sq_lo];
+            t.n_own_pages = e.sq_page0[sd.sq_hi] - t.own_page0 + sd.last_qpos / kPageTokens + 1;
         }
         const int n_pages = (t.prefix_len + kPageTokens - 1) / kPageTokens;
         if (n_pages > 0) {
@@ -491,7 +496,7 @@ __global__ void __launch_bounds__(128) ingest_write_fp8_kernel(PoolGeom g, int l
 // (SubGCache Sec. 3.4: the question tokens are appended to the cached prompt, so suffix token j of a
 // query whose cluster has P prefix tokens is rotated at position P + j).  One workgroup per
 // (suffix page, KV head); tokens past the query's end are written as zeros.
-__global__ void suffix_ingest_kernel(AttnArgs a, const int32_t *spage_sq, int n_spages, ExpandArgs ex)
+__global__ void suffix_ingest_kernel(AttnArgs a, int n_spages, ExpandArgs ex)
 {
     if ((int)blockIdx.x >= n_spages) {
         expand_in_ingest_grid(ex, n_spages);
@@ -499,12 +504,8 @@ __global__ void suffix_ingest_kernel(AttnArgs a, const int32_t *spage_sq, int n_
     }
     const int page = blockIdx.x, hk = blockIdx.y;
     const int Hkv = a.n_kv_heads, d = a.head_dim, half = d / 2, pairs = d / 16;
-    const int sq = spage_sq[page];
-    const int S = a.sq_len[sq];
-    const int64_t src0 = a.sq_src0[sq];
-    const int P = a.cl_prefix_len[a.sq_cluster[sq]];
-    const int tok0 = (page - a.sq_page0[sq]) * kPageTokens;
-    if (tok0 >= S) return;      // a page kept free for decoded tokens: not this kernel's to write
+    const SuffixPage pg = a.spages[page];
+    if (pg.n <= 0) return;      // a page kept free for decoded tokens: not this kernel's to write
     const int64_t part = (int64_t)kPageTokens * d * 2;
     char *kg = const_cast<char *>(a.spool) + (int64_t)page * 2 * Hkv * part + (int64_t)hk * part;
     char *vg = kg + (int64_t)Hkv * part;
@@ -514,14 +515,13 @@ __global__ void suffix_ingest_kernel(AttnArgs a, const int32_t *spage_sq, int n_
     const bool v_as_given = via_tile && a.io_dtype == SGC_BF16;      // bf16 values into bf16 pages: moved, not converted
     for (int it = threadIdx.x; it < kPageTokens * pairs; it += blockDim.x) {
         const int tok = it / pairs, cc = it % pairs;
-        const int j = tok0 + tok;
         float x1[8], x2[8], y1[8], y2[8];
         uint4 r1 = make_uint4(0, 0, 0, 0), r2 = r1;
-        if (j < S) {
-            const int64_t row = ((src0 + j) * Hkv + hk) * d;
+        if (tok < pg.n) {
+            const int64_t row = ((int64_t)(pg.row0 + tok) * Hkv + hk) * d;
             load8(a.k, row + cc * 8, a.io_dtype, x1);
             load8(a.k, row + half + cc * 8, a.io_dtype, x2);
-            if (a.rope) rope8(x1, x2, a.rope + (int64_t)(P + j) * half + cc * 8);
+            if (a.rope) rope8(x1, x2, a.rope + (int64_t)(pg.pos0 + tok) * half + cc * 8);
             if (v_as_given) {
                 r1 = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.v) + row + cc * 8);
                 r2 = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.v) + row + half + cc * 8);
@@ -1338,15 +1338,14 @@ hipError_t launch_expand_tiles(const ExpandArgs &e, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_suffix_ingest(const AttnArgs &a, const int32_t *d_spage_sq, int n_spages, const ExpandArgs *expand,
-                                hipStream_t s)
+hipError_t launch_suffix_ingest(const AttnArgs &a, int n_spages, const ExpandArgs *expand, hipStream_t s)
 {
     if (n_spages <= 0) return expand ? launch_expand_tiles(*expand, s) : hipSuccess;
     const size_t lds = 2 * (size_t)kPageTokens * a.head_dim * 2;
     ExpandArgs ex{};
     if (expand) ex = *expand;
     const dim3 grid(n_spages + expand_columns(ex.n, a.n_kv_heads), a.n_kv_heads);
-    hipLaunchKernelGGL(suffix_ingest_kernel, grid, dim3(128), lds, s, a, d_spage_sq, n_spages, ex);
+    hipLaunchKernelGGL(suffix_ingest_kernel, grid, dim3(128), lds, s, a, n_spages, ex);
     return hipGetLastError();
 }
 

@@ -1,0 +1,62 @@
+"""The question tokens' own keys in the matrix-core kernel, by each way they can reach it: as the caller gives them, out of suffix
+pages (a plan with decode steps; its spare pages lie between the queries), and out of pages because an output overlaps the values.
+Sizes around a page of 16 tokens, a chunk of four pages and a wavefront's 32 rows; tiles that touch one, four and more queries."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2505_10951_amd import sgc, workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2505_10951_amd.harness import Session, to_device, to_host_f32  # noqa: E402
+from ref_util import fp8_query_floor, oracle_caches, tight_bar  # noqa: E402
+
+SHAPES = [
+    # head groups of 4: rows of one query, of four, of five in a tile
+    (8, 2, [16], [33]), (8, 2, [70], [16, 15, 1, 17]), (8, 2, [64], [7, 6, 8, 5, 9, 1]),
+    # more than one chunk of pages behind a tile; no cached keys
+    (8, 1, [100], [63, 64, 65, 129]), (8, 2, [0, 1], [64, 1, 80, 16]),
+    # no head groups: 128 tokens to a tile, many pages each
+    (2, 2, [200, 40], [96, 24, 50, 31, 33, 128, 1, 1]), (1, 1, [65], [1] * 70),
+]
+
+
+def _run(w, route, kernel):
+    with Session(w, kernel=kernel) as s:
+        for c in range(w.n_clusters):
+            s.alloc_cluster(c)
+            s.prefix_prefill(c)
+        s.assign()
+        if route == "decode plan":
+            s.enable_decode(20)
+        dq, dk, dv = (to_device(x, "bf16") for x in w.suffix_qkv())
+        dlse = torch.zeros((w.n_q_heads, dq.shape[0]), device="cuda:0")
+        do = s.suffix_prefill(dq, dk, dv, do=dv if route == "output over the values" else None, dlse=dlse)
+        torch.cuda.synchronize()
+        return to_host_f32(do), dlse.cpu().numpy()
+
+
+@pytest.mark.parametrize("kv,rope", [("bf16", 10000.0), ("bf16", 0.0), ("fp8_e4m3", 10000.0)])
+@pytest.mark.parametrize("hq,hkv,prefix,suffix", SHAPES)
+def test_own_keys_by_every_route(hq, hkv, prefix, suffix, kv, rope):
+    if kv == "fp8_e4m3":
+        prefix = [max(p, 1) for p in prefix]
+    labels = np.arange(len(suffix)) % len(prefix)
+    w = workloads.custom("own", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=rope, io_dtype="bf16", kv_dtype=kv,
+                         prefix_len=prefix, labels=labels.astype(np.int32), suffix_len=np.array(suffix, np.int32), seed=len(suffix))
+    caches = oracle_caches(w)
+    ref, lse = orc.suffix_prefill_batched(w.labels, w.cu_seqlens, [caches[c][0] for c in range(w.n_clusters)],
+                                          [caches[c][1] for c in range(w.n_clusters)], *w.suffix_qkv(), w.rope_base)
+    # 16-bit caches: four times an ideal 16-bit kernel's error; fp8: the bar the other tests use (a key on a code's boundary)
+    bar, lse_bar = tight_bar(w, range(w.n_queries)) if kv == "bf16" else (6e-2, 2e-2)
+    routes = ["as given", "decode plan"] + (["output over the values"] if hq == hkv else [])
+    for route in routes:
+        o, got_lse = _run(w, route, sgc.SGC_KERNEL_MFMA)
+        assert float(np.abs(o - ref).max()) <= bar, route
+        assert float(np.abs(got_lse - lse).max()) <= max(lse_bar, 2e-2), route
+        if kv == "fp8_e4m3":        # query rows in e4m3 against the cache, in binary16 against own keys
+            floor = max(fp8_query_floor(*caches[int(w.labels[n])], *w.suffix_qkv_query(n), w.rope_base) for n in range(w.n_queries))
+            o, _ = _run(w, route, sgc.SGC_KERNEL_MFMA_FP8)
+            assert float(np.abs(o - ref).max()) <= 4 * floor + 6e-2, route
