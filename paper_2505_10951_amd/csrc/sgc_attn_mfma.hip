@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     const uint32_t ids0 = spread4(t.first_pages);
     uint32_t ids1 = spread4(t.first_pages + 4), ids2 = spread4(t.first_pages + 8);
     float k_scale = 1.f, v_scale = 1.f;
-    if (KV_FP8) {
+    if (KV_FP8 && P > 0) {      // (nothing has written the scales of a cluster without cached keys)
         const float *sc = a.kv_scale + ((int64_t)cluster * a.n_layers + a.layer) * 2 * Hkv;
         k_scale = sc[hk];
         v_scale = sc[Hkv + hk];
