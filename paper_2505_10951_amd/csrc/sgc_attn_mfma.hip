@@ -424,6 +424,25 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     {
         uint4 qlo[MI][4], qhi[MI][4];
         float4 cs[MI][4][4];            // (cos, sin) of two channels per entry
+        const bool rotate = a.rope != nullptr;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cs[mi][kb][i] = make_float4(1.f, 0.f, 1.f, 0.f);
+        if (rotate) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) {
+                const int pos = (MODE == MODE_SUFFIX ? P + pos_extra + a.pos_shift : 0) + qpos[mi];
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    const float4 *tab = reinterpret_cast<const float4 *>(a.rope + (int64_t)pos * 64 + kb * 16 + h * 8);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) cs[mi][kb][i] = tab[i];
+                }
+            }
+        }
         if (NW == 4 && !KV_FP8) {       // (with an fp8 cache the registers for it are not there, and prompts are long)
             // The operand layout wants 16-byte pieces of 32 different rows per instruction.  Loaded that way the
             // requests are 32 scattered 32-byte runs each; instead instruction j fetches rows 4 j .. 4 j + 3 whole
@@ -452,25 +471,6 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                     const int c0 = kb * 16 + h * 8;
                     qlo[mi][kb] = *reinterpret_cast<const uint4 *>(qrow + c0);
                     qhi[mi][kb] = *reinterpret_cast<const uint4 *>(qrow + 64 + c0);
-                }
-            }
-        }
-        const bool rotate = a.rope != nullptr;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) cs[mi][kb][i] = make_float4(1.f, 0.f, 1.f, 0.f);
-        if (rotate) {
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const int pos = (MODE == MODE_SUFFIX ? P + pos_extra + a.pos_shift : 0) + qpos[mi];
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb) {
-                    const float4 *tab = reinterpret_cast<const float4 *>(a.rope + (int64_t)pos * 64 + kb * 16 + h * 8);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) cs[mi][kb][i] = tab[i];
                 }
             }
         }
