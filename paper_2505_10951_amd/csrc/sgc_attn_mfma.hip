@@ -46,7 +46,7 @@ constexpr int D = 128;                       // head dim
 constexpr int BN = 64;                       // keys per LDS tile (4 pages)
 constexpr int PART_BYTES = kPageTokens * D * 2;   // one page's K (or V) of one head as bf16: 4 KiB
 constexpr int HALF_BYTES = 4 * PART_BYTES;   // the K (or V) of one 64-key tile: 16 KiB
-constexpr int LDS_TILE_BYTES = 4 * HALF_BYTES;   // two K buffers, then two V buffers
+constexpr int NW = 4, MI = 1;                // wavefronts of a workgroup, 32-row blocks of a wavefront
 constexpr int K8_PART_BYTES = kPageTokens * D;    // one page's K of one head as e4m3 codes: 2 KiB
 constexpr int K8_PART_STRIDE = K8_PART_BYTES + 128;   // in LDS consecutive pages sit 2 KiB + 128 bytes apart: the two pages
                                                       // a 32-key operand read touches then fall into different banks
@@ -78,6 +78,42 @@ __device__ inline uint32_t fp8x2_to_16x2(uint32_t w, bool high)
     }
     const auto r = high ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
     return __builtin_bit_cast(uint32_t, r);
+}
+
+// A record that no launch writes while it is read, at a wave-uniform address: through the scalar path, into scalar registers.
+// (The compiler must take a plain load for one that a store of the same kernel could change, and fetch it per lane.)
+template <typename T>
+__device__ inline T uniform_record(const T *p)
+{
+    const auto *words = (const __attribute__((address_space(4))) uint32_t *)p;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) w[i] = words[i];
+    return __builtin_bit_cast(T, w);
+}
+
+// V operands of two pages of token rows: eight blocks (page i / 4, 32-channel group i % 4) for the second product, read
+// transposed (ds_read_b64_tr_b16): of the 16 lanes of a group, lane 4 t + u asks for channels 4 u .. 4 u + 3 of token t and gets
+// channel (lane % 16) of all four tokens; the second read of a block is eight tokens further.  at: LDS address per block.  One asm block with
+// its wait: in front of the builtin the compiler waits for every copy to LDS in flight, the next chunk's among them.
+__device__ __forceinline__ void read_v_rows(const uint32_t (&at)[8], bf16x8 (&out)[8])
+{
+    s16x4 v[16];
+    asm volatile("ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %16 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %2, %17\n\tds_read_b64_tr_b16 %3, %17 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %4, %18\n\tds_read_b64_tr_b16 %5, %18 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %6, %19\n\tds_read_b64_tr_b16 %7, %19 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %8, %20\n\tds_read_b64_tr_b16 %9, %20 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %10, %21\n\tds_read_b64_tr_b16 %11, %21 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %12, %22\n\tds_read_b64_tr_b16 %13, %22 offset:2048\n\t"
+                 "ds_read_b64_tr_b16 %14, %23\n\tds_read_b64_tr_b16 %15, %23 offset:2048\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]),
+                   "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
+                 : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]), "v"(at[7])
+                 : "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v[2 * i], v[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // 4 KiB global -> LDS as four 1 KiB instructions, 16 bytes per lane: byte 1024 q + 16 lane of the source
@@ -180,11 +216,11 @@ __device__ inline void append_new_tokens(const AttnArgs &a, int blk)
 //
 // OWN_RAW: the question tokens' keys and values are taken as the caller gives them (a.k, a.v), rotated and turned on their
 // way into LDS; otherwise they are read from the suffix page pool.
-template <int NW, int MI, bool KV_FP8, int MODE, bool QK8, bool OWN_RAW>
-__global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mfma_kernel(const AttnArgs a)
+template <bool KV_FP8, int MODE, bool QK8, bool OWN_RAW>
+__global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
 {
     static_assert(NW == 4 && MI == 1, "the own-suffix part deals pages to four wavefronts of 32 rows");
-    static_assert(!QK8 || (KV_FP8 && MI == 1 && NW == 4), "the fp8 first product needs an fp8 cache");
+    static_assert(!QK8 || KV_FP8, "the fp8 first product needs an fp8 cache");
     if (MODE == MODE_SUFFIX && (int)blockIdx.x >= a.n_tiles) {
         append_new_tokens(a, (int)blockIdx.x - a.n_tiles);
         return;
@@ -198,7 +234,10 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = a.group;
 
     // ---- which tile ----
-    Tile t = a.tiles[blockIdx.x];
+    Tile t = uniform_record(a.tiles + blockIdx.x);
+    // (the whole record is asked for before its first use decides anything: one round trip)
+    asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad), "s"(t.first_pages[0]), "s"(t.first_pages[11]), "s"(t.q[0].tok0), "s"(t.q[3].page0),
+                 "s"(t.own_page0));
     if (t.n_rows == 0) return;
     // where the rows come from and go to: the batch's packed arrays, or (prefix mode) the job's
     const void *q_base = a.q;
@@ -206,7 +245,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     float *lse_base = a.lse;
     int64_t lse_stride = a.lse_stride;
     if (MODE == MODE_PREFIX) {
-        const PrefixJob &job = a.jobs[__builtin_amdgcn_readfirstlane(t.tok_base)];
+        const PrefixJob job = uniform_record(a.jobs + __builtin_amdgcn_readfirstlane(t.tok_base));
         q_base = job.q;
         o_base = job.o;
         lse_base = job.lse;
@@ -234,19 +273,15 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
 
     // ---- copy machinery ----------------------------------------------------------------------------
     // A tile is 8 parts: K of its 4 pages, then V of its 4 pages; a part is 4 KiB of bf16 (2 KiB of fp8
-    // codes that widen to 4 KiB).  With 4 wavefronts, wavefront w moves K and V of page w; with 8, wavefronts
-    // 0..3 move K of page w and 4..7 move V of page w - 4.  A part's source is a scalar base (pool base +
-    // page offset) plus a per-lane offset fixed for the launch; page offsets travel as 32-bit counts of 256
-    // bytes, a step ahead, in a vector register (lane j < 4 holds page j of the tile) and become scalars by
-    // readlane, so no copy ever waits on a page-table load.
+    // codes that widen to 4 KiB).  Wavefront w moves K and V of page w.  A part's source is a scalar base (pool base +
+    // page offset) plus a per-lane offset fixed for the launch; page ids are loaded a step or more ahead, on the scalar path:
+    // no copy waits for them, and waiting for them is not waiting for copies.
     const int my_page = wave_u & 3;
-    const bool moves_k = NW == 4 || wave_u < 4, moves_v = NW == 4 || wave_u >= 4;
     const char *cache_base = a.pool.pool + (int64_t)a.layer * a.pool.layer_bytes + (int64_t)hk * a.pool.head_part_bytes;
     const uint32_t cache_v_off = (uint32_t)(Hkv * a.pool.head_part_bytes);
-    const uint32_t cache_page_256 = (uint32_t)(a.pool.page_bytes >> 8);
     const char *spool_base = a.spool + (int64_t)hk * PART_BYTES;
     const uint32_t spool_v_off = (uint32_t)Hkv * PART_BYTES;
-    const uint32_t spool_page_256 = (2u * spool_v_off) >> 8;
+    const int64_t spool_page = 2 * (int64_t)spool_v_off;
     // fp8 cache only: codes on their way to LDS.  A 2 KiB part is fetched as four runs of 512 codes, 8 per lane; widened,
     // a lane's 8 codes are 16 bytes at 16 * lane of the run's 1 KiB image, so the stores cover all banks.
     uint2 stage[8];      // [K runs 0..3, V runs 0..3]
@@ -254,30 +289,18 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
 
     // Page indices past the last page are clamped to it: such keys are masked out of the scores, and what
     // they multiply in the second product is finite cache content times a zero weight.
-    auto cache_page_ids = [&](int kt) __attribute__((always_inline)) -> uint32_t {     // raw page ids; scaled to offsets when used
+    auto cache_page = [&](int kt) __attribute__((always_inline)) -> int {       // id of this wavefront's page of tile kt
         if (n_pages == 0) return 0;       // no cached keys: nothing is ever copied from the cache
-        return (uint32_t)pt[min(kt * 4 + (lane & 3), n_pages - 1)];
+        return uniform_record(pt + min(kt * 4 + my_page, n_pages - 1));
     };
+    auto cache_src = [&](int page) __attribute__((always_inline)) -> const char * { return cache_base + (int64_t)page * a.pool.page_bytes; };
     const uint32_t lane16 = lane * 16;
-    // Copies K of one tile (page offsets poff_k, into kdst) and / or V of one tile (poff_v, into vdst); a null
-    // destination skips that half.
-    auto issue_copy_bf16 = [&](uint32_t poff_k, char *kdst, uint32_t poff_v, char *vdst, const char *base, uint32_t v_off) __attribute__((always_inline)) {
-        if (moves_k && kdst) {
-            const uint32_t off256 = __builtin_amdgcn_readlane(poff_k, my_page);
-            copy_4k_to_lds(base + ((uint64_t)off256 << 8) + lane16, kdst + my_page * PART_BYTES);
-        }
-        if (moves_v && vdst) {
-            const uint32_t off256 = __builtin_amdgcn_readlane(poff_v, my_page);
-            copy_4k_to_lds(base + ((uint64_t)off256 << 8) + v_off + lane16, vdst + my_page * PART_BYTES);
-        }
-    };
     char *kdst_codes = nullptr;      // QK8: where the next K tile's codes go
-    auto issue_load_fp8 = [&](uint32_t poff_k, bool want_k, uint32_t poff_v, bool want_v) __attribute__((always_inline)) {
-        staged_k = moves_k && want_k;
-        staged_v = moves_v && want_v;
+    auto issue_load_fp8 = [&](int page_k, bool want_k, int page_v, bool want_v) __attribute__((always_inline)) {
+        staged_k = want_k;
+        staged_v = want_v;
         if (staged_k) {
-            const uint32_t off256 = __builtin_amdgcn_readlane(poff_k, my_page);
-            const char *src = cache_base + ((uint64_t)off256 << 8) + lane16;
+            const char *src = cache_src(page_k) + lane16;
             if (QK8) {      // the codes as they are, straight into LDS (kdst_codes: set by the caller)
                 const auto *g = (const __attribute__((address_space(1))) void *)src;
                 auto *l = (__attribute__((address_space(3))) void *)(kdst_codes + my_page * K8_PART_STRIDE);
@@ -285,14 +308,13 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                 __builtin_amdgcn_global_load_lds(g, l, 16, 1024, 0);
                 staged_k = false;
             } else {
-                const char *src8 = cache_base + ((uint64_t)off256 << 8) + lane * 8;
+                const char *src8 = cache_src(page_k) + lane * 8;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) stage[r] = *reinterpret_cast<const uint2 *>(src8 + r * 512);
             }
         }
         if (staged_v) {
-            const uint32_t off256 = __builtin_amdgcn_readlane(poff_v, my_page);
-            const char *src8 = cache_base + ((uint64_t)off256 << 8) + cache_v_off + lane * 8;
+            const char *src8 = cache_src(page_v) + cache_v_off + lane * 8;
 #pragma unroll
             for (int r = 0; r < 4; ++r) stage[4 + r] = *reinterpret_cast<const uint2 *>(src8 + r * 512);
         }
@@ -318,13 +340,15 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         staged_k = false;
         staged_v = false;
     };
-    // K of one cached tile and / or V of another: kdst / vdst null = none
-    auto fetch_cache = [&](uint32_t ids_k, char *kdst, uint32_t ids_v, char *vdst) __attribute__((always_inline)) {
+    // K of one cached tile (this wavefront's page_k of it) and / or V of another: kdst / vdst null = none
+    auto fetch_cache = [&](int page_k, char *kdst, int page_v, char *vdst) __attribute__((always_inline)) {
         if (KV_FP8) {
             kdst_codes = kdst;
-            issue_load_fp8(ids_k * cache_page_256, kdst != nullptr, ids_v * cache_page_256, vdst != nullptr);
-        } else
-            issue_copy_bf16(ids_k * cache_page_256, kdst, ids_v * cache_page_256, vdst, cache_base, cache_v_off);
+            issue_load_fp8(page_k, kdst != nullptr, page_v, vdst != nullptr);
+        } else {
+            if (kdst) copy_4k_to_lds(cache_src(page_k) + lane16, kdst + my_page * PART_BYTES);
+            if (vdst) copy_4k_to_lds(cache_src(page_v) + cache_v_off + lane16, vdst + my_page * PART_BYTES);
+        }
     };
     auto land_cache = [&](char *kdst, char *vdst) __attribute__((always_inline)) {   // make what was fetched visible in LDS (before the barrier)
         if (KV_FP8) store_fp8(kdst, vdst);
@@ -338,16 +362,16 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     // as the ids are there, so that they travel while Q is loaded and rotated.
     const int n_cache_keys = (MODE == MODE_SUFFIX) ? P : min(P, last_row / g + 1);
     const int n_kt = (n_cache_keys + BN - 1) / BN;
-    // page ids of tiles 0, 1, 2 come with the tile record (lane j < 4 holds page j of a tile); later these
-    // hold the ids of tiles kt + 1 and kt + 2
-    auto spread4 = [&](const int32_t *p4) __attribute__((always_inline)) -> uint32_t {
+    // This wavefront's pages of tiles 0, 1, 2 come with the tile record; the steps take pg_v, of tile kt + 1, and pg_k, of tile
+    // kt + 2.
+    auto of_wave = [&](const int32_t *p4) __attribute__((always_inline)) -> int {
         const int p0 = __builtin_amdgcn_readfirstlane(p4[0]), p1 = __builtin_amdgcn_readfirstlane(p4[1]);
         const int p2 = __builtin_amdgcn_readfirstlane(p4[2]), p3 = __builtin_amdgcn_readfirstlane(p4[3]);
-        const int lo = (lane & 1) ? p1 : p0, hi = (lane & 1) ? p3 : p2;
-        return (uint32_t)((lane & 2) ? hi : lo);
+        const int lo = (my_page & 1) ? p1 : p0, hi = (my_page & 1) ? p3 : p2;
+        return (my_page & 2) ? hi : lo;
     };
-    const uint32_t ids0 = spread4(t.first_pages);
-    uint32_t ids1 = spread4(t.first_pages + 4), ids2 = spread4(t.first_pages + 8);
+    const int pg0 = of_wave(t.first_pages), pg1 = of_wave(t.first_pages + 4), pg2 = of_wave(t.first_pages + 8);
+    int pg_v = pg1, pg_k = pg2;
     float k_scale = 1.f, v_scale = 1.f;
     if (KV_FP8 && P > 0) {      // (nothing has written the scales of a cluster without cached keys)
         const float *sc = a.kv_scale + ((int64_t)cluster * a.n_layers + a.layer) * 2 * Hkv;
@@ -412,8 +436,8 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     const int lim_min = __builtin_amdgcn_readlane(lim[0], 0), lim_max = __builtin_amdgcn_readlane(lim[MI - 1], 31);
 
     if (!KV_FP8 && n_kt > 0) {
-        fetch_cache(ids0, kbuf_of(0), ids0, vbuf_of(0));
-        if (n_kt > 1) fetch_cache(ids1, kbuf_of(1), 0, nullptr);
+        fetch_cache(pg0, kbuf_of(0), pg0, vbuf_of(0));
+        if (n_kt > 1) fetch_cache(pg1, kbuf_of(1), 0, nullptr);
     }
     // ---- Q: load, rotate at position P + qpos (suffix) / qpos (prefix), keep as B operands ----
     // All loads of the phase (Q row halves, then the rotation table entries) are issued before any of them is
@@ -443,7 +467,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                 }
             }
         }
-        if (NW == 4 && !KV_FP8) {       // (with an fp8 cache the registers for it are not there, and prompts are long)
+        if (!KV_FP8) {       // (with an fp8 cache the registers for it are not there, and prompts are long)
             // The operand layout wants 16-byte pieces of 32 different rows per instruction.  Loaded that way the
             // requests are 32 scattered 32-byte runs each; instead instruction j fetches rows 4 j .. 4 j + 3 whole
             // (lane = 16-byte chunk lane % 16 of row 4 j + lane / 16), and the wavefront turns the block by
@@ -724,10 +748,10 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     f32x16 s0[MI], s1[MI];
     if (n_kt > 0) {
         if (KV_FP8) {      // through registers: one tile's worth at a time
-            fetch_cache(ids0, kbuf_of(0), ids0, vbuf_of(0));
+            fetch_cache(pg0, kbuf_of(0), pg0, vbuf_of(0));
             land_cache(kbuf_of(0), vbuf_of(0));
             if (n_kt > 1) {
-                fetch_cache(ids1, kbuf_of(1), 0, nullptr);
+                fetch_cache(pg1, kbuf_of(1), 0, nullptr);
                 land_cache(kbuf_of(1), nullptr);
             }
         } else {
@@ -762,7 +786,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         if (p >= n_own) return;
         char *kd = own_kbuf(i) + wave_u * PART_BYTES, *vd = own_vbuf(i) + wave_u * PART_BYTES;
         if constexpr (OWN_RAW) {
-            const SuffixPage pg = a.spages[own_page0 + p];
+            const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
             const int l = lane_again(), r0 = l >> 4, c = l & 15;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {           // rows 4 j .. 4 j + 3 of the page
@@ -774,7 +798,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                 __builtin_amdgcn_global_load_lds(gv, (__attribute__((address_space(3))) void *)(vd + j * 1024), 16, 0, 0);
             }
         } else {
-            const char *src = spool_base + ((uint64_t)((uint32_t)(own_page0 + p) * spool_page_256) << 8) + lane16;
+            const char *src = spool_base + (own_page0 + p) * spool_page + lane16;
             copy_4k_to_lds(src, kd);
             copy_4k_to_lds(src + spool_v_off, vd);
         }
@@ -787,7 +811,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         if constexpr (OWN_RAW) {
             const int p = i * OWN_PAGES + wave_u;
             if (p >= n_own) return;
-            const SuffixPage pg = a.spages[own_page0 + p];
+            const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
             const int l = lane_again(), pos = pg.pos0 + min(l & 15, pg.n - 1);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
@@ -838,9 +862,8 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         const char *src;
         char *dst;
     };
-    auto cache_part = [&](bool is_v, uint32_t ids, char *dst_half) __attribute__((always_inline)) -> PartCopy {
-        const uint32_t off256 = (uint32_t)__builtin_amdgcn_readlane(ids, my_page) * cache_page_256;
-        return {cache_base + ((uint64_t)off256 << 8) + (is_v ? cache_v_off : 0u) + lane16, dst_half + my_page * PART_BYTES};
+    auto cache_part = [&](bool is_v, int page, char *dst_half) __attribute__((always_inline)) -> PartCopy {
+        return {cache_src(page) + (is_v ? cache_v_off : 0u) + lane16, dst_half + my_page * PART_BYTES};
     };
     auto copy_quarter = [&](const PartCopy &pc, int slot) __attribute__((always_inline)) {     // slot 0, 2, 4, 6 -> quarter 0..3; odd slots: nothing
         const auto *gp = (const __attribute__((address_space(1))) void *)pc.src;
@@ -860,21 +883,20 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     auto cache_step = [&](const int kt, auto kind_tag) __attribute__((always_inline)) {
         constexpr int kind = decltype(kind_tag)::value;
         constexpr bool spread = kind == SPREAD, last = kind == LAST;
-        char *kd = !last && kt + 2 < n_kt ? kbuf_of(kt) : nullptr;
+        char *kd = !last && kt + 2 < n_kt ? kbuf_of(kt + 2) : nullptr;
         char *vd = !last && kt + 1 < n_kt ? vbuf_of(kt + 1) : nullptr;
-        uint32_t ids3 = 0;
-        if (!last) ids3 = cache_page_ids(kt + 3);    // issued before the copies, used a step later
+        const int pg_new = last ? 0 : cache_page(kt + 3);
         PartCopy first = {nullptr, nullptr}, second = {nullptr, nullptr};
         if (spread) {
-            first = cache_part(true, ids1, vd);      // V of tile kt + 1 is needed first
-            second = cache_part(false, ids2, kd);
+            first = cache_part(true, pg_v, vd);      // V is needed first
+            second = cache_part(false, pg_k, kd);
         } else if (last) {
             if (own) own_copy(0);
         } else {
-            if (kd || vd) fetch_cache(ids2, kd, ids1, vd);
+            if (kd || vd) fetch_cache(pg_k, kd, pg_v, vd);
         }
-        ids1 = ids2;
-        ids2 = ids3;
+        pg_v = pg_k;
+        pg_k = pg_new;
         if (spread || MODE == MODE_SUFFIX || kt < n_my) {  // some row of this wave still sees keys of this tile
             const int key0 = kt * BN;
             const bool masked = key0 + BN > lim_min;
@@ -959,8 +981,6 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
         }
         const int wpg_lo = __builtin_amdgcn_readlane(own_first, 0) / kPageTokens;
         const int wpg_hi = __builtin_amdgcn_readlane(own_first + qpos[0], 31) / kPageTokens;
-        // OWN_RAW: V rows are read transposed (ds_read_b64_tr_b16): of the 16 lanes of a group, lane 4 t + u asks for channels 4 u ..
-        // 4 u + 3 of token t and gets channel (lane % 16) of all four tokens.
         const int tr = (lane & 15) >> 2;
         const int lane_trow = (4 * h + tr) * 256 + (n >> 4) * 32 + (lane & 3) * 8;
         for (int ci = 0, c0 = 0; c0 < n_own; ++ci, c0 += OWN_PAGES) {
@@ -978,18 +998,18 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
                 const char *v0 = vc + i0 * PART_BYTES, *v1 = vc + i1 * PART_BYTES;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) frag[i] = *reinterpret_cast<const bf16x8 *>(kp + i * 512);
-                qk_half(s0, [&](int i) __attribute__((always_inline)) {
-                    const char *vp = i < 4 ? v0 : v1;
-                    if constexpr (OWN_RAW) {
-                        const char *at = vp + lane_trow + (((i & 3) ^ tr) * 64);
-                        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-                        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
-                        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at + 8 * 256));
-                        frag[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
-                    } else {
-                        frag[i] = *reinterpret_cast<const bf16x8 *>(vp + lane_voff + (i & 3) * 1024);
-                    }
-                });
+                if constexpr (OWN_RAW) {
+                    qk_half(s0, no_refill);
+                    uint32_t at[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        at[i] = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)((i < 4 ? v0 : v1) + lane_trow + (((i & 3) ^ tr) * 64));
+                    read_v_rows(at, frag);
+                } else {
+                    qk_half(s0, [&](int i) __attribute__((always_inline)) {
+                        frag[i] = *reinterpret_cast<const bf16x8 *>((i < 4 ? v0 : v1) + lane_voff + (i & 3) * 1024);
+                    });
+                }
                 if (KV_FP8) rescale_self(s0, m_ref);
                 // slot 16 p + j is visible iff own_first <= slot <= row_end; the 4 h of the lane's key index is taken off once
                 const int first = own_first - p * kPageTokens - 4 * h;
@@ -1046,12 +1066,12 @@ __global__ void __launch_bounds__(NW * 64, (NW == 4 && MI == 1) ? 2 : 1) attn_mf
     }
 }
 
-template <int NW, int MI, bool FP8, int MODE, bool QK8, bool OWN_RAW>
+template <bool FP8, int MODE, bool QK8, bool OWN_RAW>
 hipError_t launch_one(const AttnArgs &a, int blocks, hipStream_t s)
 {
     static bool configured = false;     // raise the dynamic LDS limit once per instantiation
-    auto kern = attn_mfma_kernel<NW, MI, FP8, MODE, QK8, OWN_RAW>;
-    size_t lds = LDS_TILE_BYTES;
+    auto kern = attn_mfma_kernel<FP8, MODE, QK8, OWN_RAW>;
+    const size_t lds = 4 * HALF_BYTES;      // two K buffers, two V buffers
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -1066,26 +1086,23 @@ hipError_t launch_one(const AttnArgs &a, int blocks, hipStream_t s)
 // One kernel shape is built: 4 wavefronts x 32 rows, two workgroups per CU.  (8 wavefronts x 32 rows run in lock-step
 // through the step barrier and lose the overlap two independent workgroups have; 64 rows per wavefront need more than
 // 256 vector registers.  Both were measured slower and are not compiled.)
-int mfma_tile_rows() { return 128; }
+int mfma_tile_rows() { return NW * MI * 32; }
 
 hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s)
 {
-    constexpr int NW = 4, MI = 1;
     const bool fp8 = a.pool.kv_dtype == SGC_FP8_E4M3;
     if (a.n_tiles <= 0 && a.n_append <= 0) return hipSuccess;
     if (a.mode == MODE_SUFFIX) {
         // a decode step's launch carries, behind its tiles, the blocks that append the step's new tokens
         const int per_block = NW * 64 / 8;
         const int blocks = a.n_tiles + (a.n_append * a.n_kv_heads + per_block - 1) / per_block;
-        if (a.own_raw) {
-            if (fp8 && a.fp8_first_product) return launch_one<NW, MI, true, MODE_SUFFIX, true, true>(a, blocks, s);
-            return fp8 ? launch_one<NW, MI, true, MODE_SUFFIX, false, true>(a, blocks, s) : launch_one<NW, MI, false, MODE_SUFFIX, false, true>(a, blocks, s);
-        }
-        if (fp8 && a.fp8_first_product) return launch_one<NW, MI, true, MODE_SUFFIX, true, false>(a, blocks, s);
-        return fp8 ? launch_one<NW, MI, true, MODE_SUFFIX, false, false>(a, blocks, s) : launch_one<NW, MI, false, MODE_SUFFIX, false, false>(a, blocks, s);
+        if (fp8 && a.fp8_first_product)
+            return a.own_raw ? launch_one<true, MODE_SUFFIX, true, true>(a, blocks, s) : launch_one<true, MODE_SUFFIX, true, false>(a, blocks, s);
+        if (fp8) return a.own_raw ? launch_one<true, MODE_SUFFIX, false, true>(a, blocks, s) : launch_one<true, MODE_SUFFIX, false, false>(a, blocks, s);
+        return a.own_raw ? launch_one<false, MODE_SUFFIX, false, true>(a, blocks, s) : launch_one<false, MODE_SUFFIX, false, false>(a, blocks, s);
     }
     // the prompt's own causal attention always takes the 16-bit first product
-    return fp8 ? launch_one<NW, MI, true, MODE_PREFIX, false, false>(a, a.n_tiles, s) : launch_one<NW, MI, false, MODE_PREFIX, false, false>(a, a.n_tiles, s);
+    return fp8 ? launch_one<true, MODE_PREFIX, false, false>(a, a.n_tiles, s) : launch_one<false, MODE_PREFIX, false, false>(a, a.n_tiles, s);
 }
 
 }  // namespace sgc
