@@ -185,14 +185,14 @@ int stage_begin(sgc_ctx *ctx, size_t bytes, char **host, int *slot)
     return SGC_OK;
 }
 
-// Copies `bytes` of the slot's buffer to `dev` (and, in the same launch, bytes2 from host_offset2 to dev2) and records the
-// event that says the buffer has been read.
+// Copies `bytes` of the slot's buffer to `dev` (and, in the same launch, bytes2 from host_offset2 to dev2; expand: and writes
+// these tile records behind it) and records the event that says the buffer has been read.
 int stage_commit(sgc_ctx *ctx, int slot, void *dev, size_t bytes, hipStream_t s, void *dev2 = nullptr, size_t host_offset2 = 0,
-                 size_t bytes2 = 0)
+                 size_t bytes2 = 0, const ExpandArgs *expand = nullptr)
 {
     if (bytes % 4 != 0 || bytes2 % 4 != 0 || (reinterpret_cast<uintptr_t>(dev) | reinterpret_cast<uintptr_t>(dev2) | host_offset2) % 16 != 0)
         return fail(ctx, SGC_EINVAL, "staged copy of %zu + %zu bytes is not aligned", bytes, bytes2);
-    SGC_HIP(ctx, launch_copy_from_host(dev, ctx->h_stage_dev[slot], bytes, s, dev2, ctx->h_stage_dev[slot] + host_offset2, bytes2));
+    SGC_HIP(ctx, launch_copy_from_host(dev, ctx->h_stage_dev[slot], bytes, s, dev2, ctx->h_stage_dev[slot] + host_offset2, bytes2, expand));
     SGC_HIP(ctx, hipEventRecord(ctx->stage_ev[slot], s));
     ctx->stage_pending[slot] = true;
     return SGC_OK;
@@ -865,23 +865,22 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         for (; k < slots; ++k) hs[k * kXcd + x] = TileSeed{};
     }
     // One copy for jobs, page jobs, seeds and page tables (with the event that says the staging buffer has been read); the tile records
-    // are then written by workgroups appended to the ingest launch, or by a launch of their own when nothing is ingested.
-    rc = stage_commit(ctx, slot, blk.p, copied, s, c->d_tables, copied, table_bytes);
-    if (rc == SGC_OK) c->dirty = false;
-    hipError_t e = hipSuccess;
+    // are then written by workgroups appended to the ingest launch, or behind the copy when nothing is ingested.
     ExpandArgs x{};
     x.seeds = d_seeds;
     x.tiles = const_cast<Tile *>(d_tiles);
     x.n = (int32_t)n_tiles;
     x.jobs = d_jobs;
     x.page_table = c->d_page_table;
-    const bool expand = n_tiles > 0;
+    const ExpandArgs *expand = n_tiles > 0 ? &x : nullptr;
+    rc = stage_commit(ctx, slot, blk.p, copied, s, c->d_tables, copied, table_bytes, attend_only ? expand : nullptr);
+    if (rc == SGC_OK) c->dirty = false;
+    hipError_t e = hipSuccess;
     if (rc == SGC_OK && !attend_only)
         e = launch_prefix_ingest(c->geom, layer, c->d_page_table, d_jobs, (int)jobs.size(), d_page_job, (int)page_job.size(),
                                  reinterpret_cast<const int32_t *>(blk.p + copied - chunks_bytes),
-                                 reinterpret_cast<float *>(blk.p + copied + tiles_bytes), (int)chunk_page0.size(), ctx->p.io_dtype, ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr, expand ? &x : nullptr, s);
-    else if (rc == SGC_OK && expand)
-        e = launch_expand_tiles(x, s);
+                                 reinterpret_cast<float *>(blk.p + copied + tiles_bytes), (int)chunk_page0.size(), ctx->p.io_dtype,
+                                 ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr, expand, s);
     if (rc == SGC_OK && e == hipSuccess && any_q) {
         AttnArgs a;
         fill_common_args(a, ctx, c, layer);
@@ -1038,11 +1037,11 @@ static ExpandArgs plan_expand_args(const sgc_plan *pl, const sgc_cache *c)
     return e;
 }
 
-int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
+// with_tiles: the cache's device tables are current and ordered in front of what comes next on the stream, as a suffix prefill
+// has them; the tile records are then written behind the copy.
+static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
 {
-    if (!pl) return fail(nullptr, SGC_EINVAL, "plan is NULL");
     sgc_ctx *ctx = pl->ctx;
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int want_rows = ctx->use_mfma ? ctx->tile_rows : 0;
     if (pl->uploaded && pl->tile_rows == want_rows) return SGC_OK;
     plan_free_device(pl);
@@ -1117,8 +1116,10 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
         if (p.bytes && p.src) memcpy(host + off, p.src, p.bytes);
         off += (p.bytes + 255) / 256 * 256 + 256;
     }
-    if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s)) != SGC_OK) return rc;
-    pl->expand_pending = !pl->tiles.empty();      // the records are written with the next suffix launch's ingest
+    const ExpandArgs ex = plan_expand_args(pl, pl->cache);
+    const bool expand = with_tiles && !pl->tiles.empty();
+    if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s, nullptr, 0, 0, expand ? &ex : nullptr)) != SGC_OK) return rc;
+    pl->expand_pending = !pl->tiles.empty() && !expand;      // otherwise with the next suffix launch
     if (want_rows > 0 && !pl->spages.empty()) {
         // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps and projected keys
         // (a plain suffix prefill reads its keys and values as they are given; held from here on so that no later call allocates it)
@@ -1132,6 +1133,12 @@ int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
     }
     pl->uploaded = true;
     return SGC_OK;
+}
+
+int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
+{
+    if (!pl) return fail(nullptr, SGC_EINVAL, "plan is NULL");
+    return plan_upload(pl, static_cast<hipStream_t>(hip_stream), false);
 }
 
 int sgc_plan_get_info(const sgc_plan *pl, sgc_plan_info *out)
@@ -1209,7 +1216,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     int rc;
     if ((rc = ensure_rope(ctx, pl->max_position, s)) != SGC_OK) return rc;
     if ((rc = cache_sync(c, s)) != SGC_OK) return rc;
-    if ((rc = sgc_plan_upload(pl, hip_stream)) != SGC_OK) return rc;
+    if ((rc = plan_upload(pl, s, true)) != SGC_OK) return rc;
     if ((rc = refresh_tiles(pl, c, s)) != SGC_OK) return rc;
     pl->last_stream = s;
 

@@ -455,9 +455,9 @@ hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s);
 hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s);
 hipError_t launch_fill_zero_bytes(void *p, size_t bytes, hipStream_t s);
 // bytes (a multiple of 4, both pointers 16-byte aligned) from mapped host memory to device memory, read by a kernel;
-// optionally a second piece in the same launch
+// optionally a second piece in the same launch; expand (may be null): tile records to write behind the copy
 hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2 = nullptr,
-                                 const void *mapped_src2 = nullptr, size_t bytes2 = 0);
+                                 const void *mapped_src2 = nullptr, size_t bytes2 = 0, const ExpandArgs *expand = nullptr);
 // Projections: the bf16 matrix-core kernel (K a multiple of 64, N a multiple of 128; qkv selects the fused
 // epilogue) and a kernel for every other shape and type that deals columns [0, n0), [n0, n0 + n1) and the rest
 // to three row-major matrices (c0 may be null to drop its columns).

@@ -1375,6 +1375,8 @@ hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s)
 // its 25-35 us getting started; a kernel that reads the pinned, mapped staging buffer over the host link is done in
 // the time the link needs.
 // Up to two pieces per launch (a call's own tables and the cache's page tables, when both are due).
+constexpr int kOneGroupTiles = 256;
+constexpr size_t kOneGroupBytes = 32 << 10;
 struct CopyPiece {
     uint4 *dst;
     const uint4 *src;
@@ -1383,7 +1385,16 @@ struct CopyPiece {
 __device__ inline void copy_piece(const CopyPiece &p)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n16; i += stride) p.dst[i] = p.src[i];
+    constexpr int AT_ONCE = 8;          // reads a lane has under way over the link
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n16; i += AT_ONCE * stride) {
+        uint4 v[AT_ONCE];
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k)
+            if (i + k * stride < p.n16) v[k] = p.src[i + k * stride];
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k)
+            if (i + k * stride < p.n16) p.dst[i + k * stride] = v[k];
+    }
     uint32_t *d4 = reinterpret_cast<uint32_t *>(p.dst + p.n16);
     const uint32_t *s4 = reinterpret_cast<const uint32_t *>(p.src + p.n16);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n4; i += stride) d4[i] = s4[i];
@@ -1394,16 +1405,30 @@ __global__ void copy_from_host_kernel(CopyPiece a, CopyPiece b)
     copy_piece(b);
 }
 
-hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2,
-                                 const void *mapped_src2, size_t bytes2)
+// The same by one workgroup, which then writes the tile records that are put together from what it has copied: a launch less
+// (its boundary and its own look-ups) for the tables of ordinary batches.
+__global__ void __launch_bounds__(1024) copy_and_expand_kernel(CopyPiece a, CopyPiece b, ExpandArgs e)
 {
-    if (bytes == 0 && bytes2 == 0) return hipSuccess;
+    copy_piece(a);
+    copy_piece(b);
+    __syncthreads();
+    for (int i = threadIdx.x; i < e.n; i += blockDim.x) expand_one_tile(e, i);
+}
+
+hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2,
+                                 const void *mapped_src2, size_t bytes2, const ExpandArgs *expand)
+{
+    if (bytes == 0 && bytes2 == 0) return expand ? launch_expand_tiles(*expand, s) : hipSuccess;
     const CopyPiece a{static_cast<uint4 *>(dst), static_cast<const uint4 *>(mapped_src), bytes / 16, (bytes % 16) / 4};
     const CopyPiece b{static_cast<uint4 *>(dst2), static_cast<const uint4 *>(mapped_src2), bytes2 / 16, (bytes2 % 16) / 4};
+    if (expand && expand->n > 0 && expand->n <= kOneGroupTiles && bytes + bytes2 <= kOneGroupBytes) {
+        hipLaunchKernelGGL(copy_and_expand_kernel, dim3(1), dim3(1024), 0, s, a, b, *expand);
+        return hipGetLastError();
+    }
     const size_t most = std::max(a.n16, b.n16);
     const unsigned blocks = (unsigned)std::min<size_t>(std::max<size_t>((most + 255) / 256, 1), 1024);
     hipLaunchKernelGGL(copy_from_host_kernel, dim3(blocks), dim3(256), 0, s, a, b);
-    return hipGetLastError();
+    return expand ? launch_expand_tiles(*expand, s) : hipGetLastError();
 }
 
 hipError_t launch_fill_zero_bytes(void *p, size_t bytes, hipStream_t s)
