@@ -322,8 +322,10 @@ struct sgc_ctx {
     char *h_stage[kStageSlots] = {};
     const char *h_stage_dev[kStageSlots] = {};   // the same buffers as kernels address them
     size_t h_stage_cap[kStageSlots] = {};
-    hipEvent_t stage_ev[kStageSlots] = {};
+    hipEvent_t stage_ev[kStageSlots] = {};       // of copies made while the stream was being captured
     bool stage_pending[kStageSlots] = {};
+    uint32_t stage_number[kStageSlots] = {};     // the slot's last copy: its number, and how many words behind the buffer take it
+    int stage_words[kStageSlots] = {};           // (0: the event says when the buffer has been read)
     int stage_next = 0;
     bool timing = false;            // record events around the suffix launch's kernels
     int timing_period = 1;          // ... of every timing_period-th suffix launch
@@ -456,8 +458,15 @@ hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s);
 hipError_t launch_fill_zero_bytes(void *p, size_t bytes, hipStream_t s);
 // bytes (a multiple of 4, both pointers 16-byte aligned) from mapped host memory to device memory, read by a kernel;
 // optionally a second piece in the same launch; expand (may be null): tile records to write behind the copy
-hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2 = nullptr,
-                                 const void *mapped_src2 = nullptr, size_t bytes2 = 0, const ExpandArgs *expand = nullptr);
+// done: each of the launch's *n_words <= kCopyDoneWords workgroups sets its word to number once it has read its part
+// (words null: nothing is set).
+struct CopyDone {
+    uint32_t *words;         // mapped host memory, as kernels address it
+    uint32_t number;
+};
+constexpr int kCopyDoneWords = 64;
+hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2, const void *mapped_src2,
+                                 size_t bytes2, const ExpandArgs *expand, const CopyDone &done, int *n_words);
 // Projections: the bf16 matrix-core kernel (K a multiple of 64, N a multiple of 128; qkv selects the fused
 // epilogue) and a kernel for every other shape and type that deals columns [0, n0), [n0, n0 + n1) and the rest
 // to three row-major matrices (c0 may be null to drop its columns).

@@ -1399,35 +1399,47 @@ __device__ inline void copy_piece(const CopyPiece &p)
     const uint32_t *s4 = reinterpret_cast<const uint32_t *>(p.src + p.n16);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n4; i += stride) d4[i] = s4[i];
 }
-__global__ void copy_from_host_kernel(CopyPiece a, CopyPiece b)
+// Says that this workgroup has read its part of the staging buffer (what it read it has stored, so the reads are done): its
+// word in mapped host memory takes the copy's number.
+__device__ inline void signal_read(const CopyDone &done)
+{
+    __syncthreads();
+    if (threadIdx.x == 0 && done.words)
+        __hip_atomic_store(done.words + blockIdx.x, done.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void copy_from_host_kernel(CopyPiece a, CopyPiece b, CopyDone done)
 {
     copy_piece(a);
     copy_piece(b);
+    signal_read(done);
 }
 
 // The same by one workgroup, which then writes the tile records that are put together from what it has copied: a launch less
 // (its boundary and its own look-ups) for the tables of ordinary batches.
-__global__ void __launch_bounds__(1024) copy_and_expand_kernel(CopyPiece a, CopyPiece b, ExpandArgs e)
+__global__ void __launch_bounds__(1024) copy_and_expand_kernel(CopyPiece a, CopyPiece b, CopyDone done, ExpandArgs e)
 {
     copy_piece(a);
     copy_piece(b);
-    __syncthreads();
+    signal_read(done);          // (its barrier is also what the records below wait for)
     for (int i = threadIdx.x; i < e.n; i += blockDim.x) expand_one_tile(e, i);
 }
 
 hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes, hipStream_t s, void *dst2,
-                                 const void *mapped_src2, size_t bytes2, const ExpandArgs *expand)
+                                 const void *mapped_src2, size_t bytes2, const ExpandArgs *expand, const CopyDone &done, int *n_words)
 {
+    *n_words = 0;
     if (bytes == 0 && bytes2 == 0) return expand ? launch_expand_tiles(*expand, s) : hipSuccess;
     const CopyPiece a{static_cast<uint4 *>(dst), static_cast<const uint4 *>(mapped_src), bytes / 16, (bytes % 16) / 4};
     const CopyPiece b{static_cast<uint4 *>(dst2), static_cast<const uint4 *>(mapped_src2), bytes2 / 16, (bytes2 % 16) / 4};
     if (expand && expand->n > 0 && expand->n <= kOneGroupTiles && bytes + bytes2 <= kOneGroupBytes) {
-        hipLaunchKernelGGL(copy_and_expand_kernel, dim3(1), dim3(1024), 0, s, a, b, *expand);
+        *n_words = 1;
+        hipLaunchKernelGGL(copy_and_expand_kernel, dim3(1), dim3(1024), 0, s, a, b, done, *expand);
         return hipGetLastError();
     }
     const size_t most = std::max(a.n16, b.n16);
-    const unsigned blocks = (unsigned)std::min<size_t>(std::max<size_t>((most + 255) / 256, 1), 1024);
-    hipLaunchKernelGGL(copy_from_host_kernel, dim3(blocks), dim3(256), 0, s, a, b);
+    const unsigned blocks = (unsigned)std::min<size_t>(std::max<size_t>((most + 255) / 256, 1), kCopyDoneWords);
+    *n_words = (int)blocks;
+    hipLaunchKernelGGL(copy_from_host_kernel, dim3(blocks), dim3(256), 0, s, a, b, done);
     return expand ? launch_expand_tiles(*expand, s) : hipGetLastError();
 }
 
