@@ -216,13 +216,11 @@ int stage_begin(sgc_ctx *ctx, size_t bytes, char **host, int *slot)
     return SGC_OK;
 }
 
-// Copies `bytes` of the slot's buffer to `dev` (and, in the same launch, bytes2 from host_offset2 to dev2; expand: and writes
-// these tile records behind it), and notes what will say that the buffer has been read.
-int stage_commit(sgc_ctx *ctx, int slot, void *dev, size_t bytes, hipStream_t s, void *dev2 = nullptr, size_t host_offset2 = 0,
-                 size_t bytes2 = 0, const ExpandArgs *expand = nullptr)
+// Launches what copies the slot's buffer (launch(done, &words): launch_copy_from_host or another launch that does it, which sets
+// `words` words) and notes what will say that the buffer has been read.
+template <typename Launch>
+int stage_launch(sgc_ctx *ctx, int slot, hipStream_t s, Launch launch)
 {
-    if (bytes % 4 != 0 || bytes2 % 4 != 0 || (reinterpret_cast<uintptr_t>(dev) | reinterpret_cast<uintptr_t>(dev2) | host_offset2) % 16 != 0)
-        return fail(ctx, SGC_EINVAL, "staged copy of %zu + %zu bytes is not aligned", bytes, bytes2);
     // A launch that is being captured may run many times or never, at any time after: it sets no words, the event is captured with it.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool known = hipStreamIsCapturing(s, &capture) == hipSuccess;
@@ -231,15 +229,31 @@ int stage_commit(sgc_ctx *ctx, int slot, void *dev, size_t bytes, hipStream_t s,
     CopyDone done{nullptr, 0};
     if (plain) done = {const_cast<uint32_t *>(reinterpret_cast<const uint32_t *>(ctx->h_stage_dev[slot] + ctx->h_stage_cap[slot])), ++ctx->stage_number[slot]};
     int words = 0;
-    SGC_HIP(ctx, launch_copy_from_host(dev, ctx->h_stage_dev[slot], bytes, s, dev2, ctx->h_stage_dev[slot] + host_offset2, bytes2, expand, done, &words));
+    SGC_HIP(ctx, launch(done, &words));
     ctx->stage_words[slot] = plain ? words : 0;
-    if (!plain) {
-        SGC_HIP(ctx, hipEventRecord(ctx->stage_ev[slot], s));
-    } else if (words == 0) {
-        return SGC_OK;          // nothing was copied
-    }
+    if (plain && words == 0) return SGC_OK;          // nothing was copied
+    if (!plain) SGC_HIP(ctx, hipEventRecord(ctx->stage_ev[slot], s));
     ctx->stage_pending[slot] = true;
     return SGC_OK;
+}
+
+int stage_check(sgc_ctx *ctx, const void *dev, size_t bytes, const void *dev2, size_t host_offset2, size_t bytes2)
+{
+    if (bytes % 4 != 0 || bytes2 % 4 != 0 || (reinterpret_cast<uintptr_t>(dev) | reinterpret_cast<uintptr_t>(dev2) | host_offset2) % 16 != 0)
+        return fail(ctx, SGC_EINVAL, "staged copy of %zu + %zu bytes is not aligned", bytes, bytes2);
+    return SGC_OK;
+}
+
+// Copies `bytes` of the slot's buffer to `dev` (and, in the same launch, bytes2 from host_offset2 to dev2; expand: and writes
+// these tile records behind it).
+int stage_commit(sgc_ctx *ctx, int slot, void *dev, size_t bytes, hipStream_t s, void *dev2 = nullptr, size_t host_offset2 = 0,
+                 size_t bytes2 = 0, const ExpandArgs *expand = nullptr)
+{
+    const int rc = stage_check(ctx, dev, bytes, dev2, host_offset2, bytes2);
+    if (rc != SGC_OK) return rc;
+    return stage_launch(ctx, slot, s, [&](const CopyDone &done, int *words) {
+        return launch_copy_from_host(dev, ctx->h_stage_dev[slot], bytes, s, dev2, ctx->h_stage_dev[slot] + host_offset2, bytes2, expand, done, words);
+    });
 }
 
 // The device copy of the page tables is one array
@@ -917,14 +931,30 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     x.jobs = d_jobs;
     x.page_table = c->d_page_table;
     const ExpandArgs *expand = n_tiles > 0 ? &x : nullptr;
-    rc = stage_commit(ctx, slot, blk.p, copied, s, c->d_tables, copied, table_bytes, attend_only ? expand : nullptr);
+    // A small call's ingest copies the tables itself.
+    const bool small = !attend_only && small_ingest_covers(c->geom, (int)jobs.size(), (int)page_job.size(), (int)n_tiles, copied + table_bytes);
+    const float2 *rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
+    if (small) {
+        SmallIngest in{};
+        in.n_jobs = (int32_t)jobs.size();
+        std::copy(jobs.begin(), jobs.end(), in.jobs);
+        for (size_t ji = 0; ji < jobs.size(); ++ji)
+            std::copy(c->cl[jobs[ji].cluster].pages.begin(), c->cl[jobs[ji].cluster].pages.end(), in.pages + jobs[ji].page0);
+        if ((rc = stage_check(ctx, blk.p, copied, c->d_tables, copied, table_bytes)) == SGC_OK)
+            rc = stage_launch(ctx, slot, s, [&](const CopyDone &done, int *words) {
+                *words = 1;
+                return launch_small_ingest(c->geom, layer, in, (int)page_job.size(), ctx->p.io_dtype, rope, blk.p, ctx->h_stage_dev[slot], copied,
+                                           c->d_tables, ctx->h_stage_dev[slot] + copied, table_bytes, done, expand, s);
+            });
+    } else {
+        rc = stage_commit(ctx, slot, blk.p, copied, s, c->d_tables, copied, table_bytes, attend_only ? expand : nullptr);
+    }
     if (rc == SGC_OK) c->dirty = false;
     hipError_t e = hipSuccess;
-    if (rc == SGC_OK && !attend_only)
+    if (rc == SGC_OK && !attend_only && !small)
         e = launch_prefix_ingest(c->geom, layer, c->d_page_table, d_jobs, (int)jobs.size(), d_page_job, (int)page_job.size(),
                                  reinterpret_cast<const int32_t *>(blk.p + copied - chunks_bytes),
-                                 reinterpret_cast<float *>(blk.p + copied + tiles_bytes), (int)chunk_page0.size(), ctx->p.io_dtype,
-                                 ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr, expand, s);
+                                 reinterpret_cast<float *>(blk.p + copied + tiles_bytes), (int)chunk_page0.size(), ctx->p.io_dtype, rope, expand, s);
     if (rc == SGC_OK && e == hipSuccess && any_q) {
         AttnArgs a;
         fill_common_args(a, ctx, c, layer);

@@ -441,6 +441,19 @@ hipError_t launch_expand_tiles(const ExpandArgs &e, hipStream_t s);
 hipError_t launch_prefix_ingest(const PoolGeom &g, int layer, const int32_t *d_page_table, const PrefixJob *d_jobs,
                                 int n_jobs, const int32_t *d_page_job, int n_pages, const int32_t *d_chunk_page0, float *d_amax,
                                 int n_chunks, int io_dtype, const float2 *rope, const ExpandArgs *expand, hipStream_t s);
+// The same for a small call, together with the copy of its tables to the device (see launch_copy_from_host): jobs and page ids
+// go with the launch.
+struct SmallIngest {
+    static constexpr int kJobs = 4, kPages = 256;
+    PrefixJob jobs[kJobs];
+    int32_t n_jobs;
+    int32_t pages[kPages];       // id of every launch-wide page
+};
+struct CopyDone;
+bool small_ingest_covers(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes);
+hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &small, int n_pages, int io_dtype, const float2 *rope, void *dst,
+                               const void *mapped_src, size_t bytes, void *dst2, const void *mapped_src2, size_t bytes2, const CopyDone &done,
+                               const ExpandArgs *expand, hipStream_t s);
 hipError_t launch_cache_export(const PoolGeom &g, int layer, const int32_t *d_pages, int prefix_len,
                                void *k, void *v, hipStream_t s);
 hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pages, int prefix_len,

@@ -168,6 +168,50 @@ __global__ void rope_table_kernel(float2 *table, int n_pos, int half, double bas
     table[idx] = make_float2((float)c, (float)s);
 }
 
+// ---- tables from the host ---------------------------------------------------------------------
+// The tables a batch sends to the device are a few hundred KiB at most.  A copy engine transfer of that size spends most of
+// its 25-35 us getting started; a kernel that reads the pinned, mapped staging buffer over the host link is done in
+// the time the link needs.
+// Up to two pieces per launch (a call's own tables and the cache's page tables, when both are due).
+constexpr int kOneGroupTiles = 256;
+constexpr size_t kOneGroupBytes = 32 << 10;
+typedef __attribute__((ext_vector_type(4))) uint32_t copy_u32x4;
+struct CopyPiece {
+    copy_u32x4 *dst;
+    const copy_u32x4 *src;
+    size_t n16, n4;      // 16-byte chunks, then 4-byte words behind them
+};
+__device__ inline void copy_piece(const CopyPiece &p, size_t first, size_t stride)
+{
+    constexpr int AT_ONCE = 8;          // reads a lane has under way over the link
+    for (size_t i = first; i < p.n16; i += AT_ONCE * stride) {
+        copy_u32x4 v[AT_ONCE];
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k) v[k] = p.src[i + k * stride < p.n16 ? i + k * stride : i];
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k)
+            if (i + k * stride < p.n16) p.dst[i + k * stride] = v[k];
+    }
+    uint32_t *d4 = reinterpret_cast<uint32_t *>(p.dst + p.n16);
+    const uint32_t *s4 = reinterpret_cast<const uint32_t *>(p.src + p.n16);
+    for (size_t i = first; i < p.n4; i += stride) d4[i] = s4[i];
+}
+// Says that this workgroup has read its part of the staging buffer (what it read it has stored, so the reads are done): its
+// word in mapped host memory takes the copy's number.
+__device__ inline void signal_read(const CopyDone &done, int word)
+{
+    __syncthreads();
+    if (threadIdx.x == 0 && done.words)
+        __hip_atomic_store(done.words + word, done.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void copy_from_host_kernel(CopyPiece a, CopyPiece b, CopyDone done)
+{
+    const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    copy_piece(a, first, stride);
+    copy_piece(b, first, stride);
+    signal_read(done, blockIdx.x);
+}
+
 // ---- prefix ingest ---------------------------------------------------------------------------
 // Linear copy of n bytes (a multiple of 16) from LDS to global memory, 16 bytes per thread and turn.
 __device__ inline void copy_out_16(char *dst, const char *lds_src, int n)
@@ -348,19 +392,12 @@ inline unsigned expand_columns(int n_tiles, int n_kv_heads)
 
 // One workgroup per (page, KV head): rotate K, convert, write K and V parts in page order.
 // Tokens past the prefix end are written as zeros so that a whole page can always be read.
-__global__ void ingest_write_kernel(PoolGeom g, int layer, const int32_t *page_table, const PrefixJob *jobs,
-                                    const int32_t *page_job, int n_pages, int io_dtype, const float2 *rope, ExpandArgs ex)
+// pg: page of the job, page: its id in the pool.
+__device__ inline void ingest_write_page(const PoolGeom &g, int layer, const PrefixJob &job, int pg, int page, int hk, int io_dtype, const float2 *rope)
 {
-    if ((int)blockIdx.x >= n_pages) {
-        expand_in_ingest_grid(ex, n_pages);
-        return;
-    }
-    const PrefixJob job = jobs[page_job[blockIdx.x]];
-    const int pg = blockIdx.x - job.page0, hk = blockIdx.y;
     const int P = job.prefix_len;
     const void *k = job.k, *v = job.v;
     const int d = g.head_dim, Hkv = g.n_kv_heads, half = d / 2, pairs = d / 16;
-    const int page = page_table[job.pt_off + pg];
     // The page images are put together in LDS (V is a transpose: element-sized scattered writes) and go out
     // as whole 16-byte rows.
     extern __shared__ __attribute__((aligned(16))) char page_img[];
@@ -411,6 +448,40 @@ __global__ void ingest_write_kernel(PoolGeom g, int layer, const int32_t *page_t
         v_part_from_tile(g.v_part(layer, page, hk), reinterpret_cast<const uint16_t *>(vp));
     else
         copy_out_16(g.v_part(layer, page, hk), vp, part_bytes);
+}
+
+__global__ void ingest_write_kernel(PoolGeom g, int layer, const int32_t *page_table, const PrefixJob *jobs,
+                                    const int32_t *page_job, int n_pages, int io_dtype, const float2 *rope, ExpandArgs ex)
+{
+    if ((int)blockIdx.x >= n_pages) {
+        expand_in_ingest_grid(ex, n_pages);
+        return;
+    }
+    const PrefixJob job = jobs[page_job[blockIdx.x]];
+    const int pg = blockIdx.x - job.page0;
+    ingest_write_page(g, layer, job, pg, page_table[job.pt_off + pg], blockIdx.y, io_dtype, rope);
+}
+
+// A small call's ingest (16- and 32-bit caches): jobs and page ids travel with the launch, so no table has to be on the device
+// before it; what the attention launch behind it reads there is copied, and its tile records written, by one more workgroup of this
+// launch (the last column's first).  A launch less in front of the ingest: its 4 us and its boundary.
+__global__ void ingest_small_kernel(PoolGeom g, int layer, SmallIngest small, int n_pages, int io_dtype, const float2 *rope, CopyPiece a, CopyPiece b,
+                                    CopyDone done, ExpandArgs ex)
+{
+    if ((int)blockIdx.x >= n_pages) {
+        if (blockIdx.y > 0) return;
+        copy_piece(a, threadIdx.x, blockDim.x);
+        copy_piece(b, threadIdx.x, blockDim.x);
+        signal_read(done, 0);
+        for (int i = threadIdx.x; i < ex.n; i += blockDim.x) expand_one_tile(ex, i);
+        return;
+    }
+    int j = 0;
+#pragma unroll
+    for (int i = 1; i < SmallIngest::kJobs; ++i)
+        if (i < small.n_jobs && (int)blockIdx.x >= small.jobs[i].page0) j = i;
+    const PrefixJob &job = small.jobs[j];
+    ingest_write_page(g, layer, job, blockIdx.x - job.page0, small.pages[blockIdx.x], blockIdx.y, io_dtype, rope);
 }
 
 // 4 x 4 bytes: w[t] holds channels 0..3 of token t, out[c] tokens 0..3 of channel c.
@@ -1331,6 +1402,29 @@ hipError_t launch_prefix_ingest(const PoolGeom &g, int layer, const int32_t *d_p
     return hipGetLastError();
 }
 
+static CopyPiece copy_piece_of(void *dst, const void *mapped_src, size_t bytes)
+{
+    return {static_cast<copy_u32x4 *>(dst), static_cast<const copy_u32x4 *>(mapped_src), bytes / 16, (bytes % 16) / 4};
+}
+
+bool small_ingest_covers(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes)
+{
+    return g.kv_dtype != SGC_FP8_E4M3 && n_jobs <= SmallIngest::kJobs && n_pages <= SmallIngest::kPages && n_tiles <= kOneGroupTiles &&
+           staged_bytes <= kOneGroupBytes;
+}
+
+hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &small, int n_pages, int io_dtype, const float2 *rope, void *dst,
+                               const void *mapped_src, size_t bytes, void *dst2, const void *mapped_src2, size_t bytes2, const CopyDone &done,
+                               const ExpandArgs *expand, hipStream_t s)
+{
+    const CopyPiece a = copy_piece_of(dst, mapped_src, bytes), b = copy_piece_of(dst2, mapped_src2, bytes2);
+    ExpandArgs ex{};
+    if (expand) ex = *expand;
+    hipLaunchKernelGGL(ingest_small_kernel, dim3(n_pages + 1, g.n_kv_heads), dim3(128), 2 * (size_t)g.head_part_bytes, s, g, layer, small, n_pages,
+                       io_dtype, rope, a, b, done, ex);
+    return hipGetLastError();
+}
+
 hipError_t launch_expand_tiles(const ExpandArgs &e, hipStream_t s)
 {
     if (e.n <= 0) return hipSuccess;
@@ -1371,56 +1465,13 @@ hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s)
     return hipGetLastError();
 }
 
-// The tables a batch sends to the device are a few hundred KiB at most.  A copy engine transfer of that size spends most of
-// its 25-35 us getting started; a kernel that reads the pinned, mapped staging buffer over the host link is done in
-// the time the link needs.
-// Up to two pieces per launch (a call's own tables and the cache's page tables, when both are due).
-constexpr int kOneGroupTiles = 256;
-constexpr size_t kOneGroupBytes = 32 << 10;
-struct CopyPiece {
-    uint4 *dst;
-    const uint4 *src;
-    size_t n16, n4;      // 16-byte chunks, then 4-byte words behind them
-};
-__device__ inline void copy_piece(const CopyPiece &p)
-{
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    constexpr int AT_ONCE = 8;          // reads a lane has under way over the link
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n16; i += AT_ONCE * stride) {
-        uint4 v[AT_ONCE];
-#pragma unroll
-        for (int k = 0; k < AT_ONCE; ++k)
-            if (i + k * stride < p.n16) v[k] = p.src[i + k * stride];
-#pragma unroll
-        for (int k = 0; k < AT_ONCE; ++k)
-            if (i + k * stride < p.n16) p.dst[i + k * stride] = v[k];
-    }
-    uint32_t *d4 = reinterpret_cast<uint32_t *>(p.dst + p.n16);
-    const uint32_t *s4 = reinterpret_cast<const uint32_t *>(p.src + p.n16);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n4; i += stride) d4[i] = s4[i];
-}
-// Says that this workgroup has read its part of the staging buffer (what it read it has stored, so the reads are done): its
-// word in mapped host memory takes the copy's number.
-__device__ inline void signal_read(const CopyDone &done)
-{
-    __syncthreads();
-    if (threadIdx.x == 0 && done.words)
-        __hip_atomic_store(done.words + blockIdx.x, done.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-__global__ void copy_from_host_kernel(CopyPiece a, CopyPiece b, CopyDone done)
-{
-    copy_piece(a);
-    copy_piece(b);
-    signal_read(done);
-}
-
 // The same by one workgroup, which then writes the tile records that are put together from what it has copied: a launch less
 // (its boundary and its own look-ups) for the tables of ordinary batches.
 __global__ void __launch_bounds__(1024) copy_and_expand_kernel(CopyPiece a, CopyPiece b, CopyDone done, ExpandArgs e)
 {
-    copy_piece(a);
-    copy_piece(b);
-    signal_read(done);          // (its barrier is also what the records below wait for)
+    copy_piece(a, threadIdx.x, blockDim.x);
+    copy_piece(b, threadIdx.x, blockDim.x);
+    signal_read(done, 0);          // (its barrier is also what the records below wait for)
     for (int i = threadIdx.x; i < e.n; i += blockDim.x) expand_one_tile(e, i);
 }
 
@@ -1429,8 +1480,7 @@ hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes
 {
     *n_words = 0;
     if (bytes == 0 && bytes2 == 0) return expand ? launch_expand_tiles(*expand, s) : hipSuccess;
-    const CopyPiece a{static_cast<uint4 *>(dst), static_cast<const uint4 *>(mapped_src), bytes / 16, (bytes % 16) / 4};
-    const CopyPiece b{static_cast<uint4 *>(dst2), static_cast<const uint4 *>(mapped_src2), bytes2 / 16, (bytes2 % 16) / 4};
+    const CopyPiece a = copy_piece_of(dst, mapped_src, bytes), b = copy_piece_of(dst2, mapped_src2, bytes2);
     if (expand && expand->n > 0 && expand->n <= kOneGroupTiles && bytes + bytes2 <= kOneGroupBytes) {
         *n_words = 1;
         hipLaunchKernelGGL(copy_and_expand_kernel, dim3(1), dim3(1024), 0, s, a, b, done, *expand);

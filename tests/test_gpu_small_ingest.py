@@ -1,0 +1,35 @@
+"""Prompts few and short enough that the ingest takes jobs and page ids with its launch, and the sizes just past that (five jobs,
+257 pages, 257 tiles): the cache's contents and the prompts' own attention."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2505_10951_amd import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2505_10951_amd.harness import Session  # noqa: E402
+
+
+@pytest.mark.parametrize("io,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("prefix", [[1], [16, 0, 17], [5, 40, 33, 64], [5, 40, 33, 64, 1], [2048, 2032, 16], [2048, 2032, 17], [512], [513]])
+def test_small_and_general_ingest(io, d, prefix):
+    hq, hkv = (16, 8) if prefix in ([512], [513]) else (2, 1)      # 8 heads x 32 or 33 tokens of four to a tile: 64 and 72 tiles
+    w = workloads.custom("small_ingest", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rope_base=10000.0, io_dtype=io, prefix_len=prefix,
+                         cluster_sizes=[1] * len(prefix), suffix_range=(1, 2), seed=d + len(prefix))
+    with Session(w) as s:
+        for c in range(w.n_clusters):
+            s.alloc_cluster(c)
+        outs = s.prefix_prefill_batched(range(w.n_clusters), with_q=True)
+        for c, (o, _) in enumerate(outs):
+            if prefix[c] == 0:
+                continue
+            rows = np.unique(np.linspace(0, prefix[c] - 1, 9).astype(int))
+            k, v = w.prefix_kv(c)
+            ck, cv, po, _ = orc.prefix_prefill(w.prefix_q(c), k, v, w.rope_base)
+            ek, ev, _, _ = s.export_cluster(c)
+            # K: one rounding to binary16 (2^-11) or none beyond the fp32 rotation; V as given
+            assert np.allclose(ek[:prefix[c]], ck, rtol=1e-5 if io == "f32" else 6e-4, atol=2e-6 if io == "f32" else 1e-4)
+            assert np.array_equal(ev[:prefix[c]], cv)
+            assert float(np.abs(o.float().cpu().numpy()[rows] - po[rows]).max()) <= (2e-5 if io == "f32" else 2e-2)
