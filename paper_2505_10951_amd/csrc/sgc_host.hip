@@ -932,19 +932,26 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     x.page_table = c->d_page_table;
     const ExpandArgs *expand = n_tiles > 0 ? &x : nullptr;
     // A small call's ingest copies the tables itself.
-    const bool small = !attend_only && small_ingest_covers(c->geom, (int)jobs.size(), (int)page_job.size(), (int)n_tiles, copied + table_bytes);
+    const SmallIngestUse use = attend_only ? SMALL_INGEST_NO
+                                           : small_ingest_use(c->geom, (int)jobs.size(), (int)page_job.size(), (int)n_tiles, copied + table_bytes);
+    const bool small = use != SMALL_INGEST_NO;
     const float2 *rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
     if (small) {
-        SmallIngest in{};
+        SmallIngest in;
         in.n_jobs = (int32_t)jobs.size();
         std::copy(jobs.begin(), jobs.end(), in.jobs);
         for (size_t ji = 0; ji < jobs.size(); ++ji)
             std::copy(c->cl[jobs[ji].cluster].pages.begin(), c->cl[jobs[ji].cluster].pages.end(), in.pages + jobs[ji].page0);
         if ((rc = stage_check(ctx, blk.p, copied, c->d_tables, copied, table_bytes)) == SGC_OK)
             rc = stage_launch(ctx, slot, s, [&](const CopyDone &done, int *words) {
-                *words = 1;
-                return launch_small_ingest(c->geom, layer, in, (int)page_job.size(), ctx->p.io_dtype, rope, blk.p, ctx->h_stage_dev[slot], copied,
-                                           c->d_tables, ctx->h_stage_dev[slot] + copied, table_bytes, done, expand, s);
+                const char *staged = ctx->h_stage_dev[slot];
+                if (use == SMALL_INGEST_STAGED_TABLES) {
+                    x.seeds = reinterpret_cast<const TileSeed *>(staged + jobs_bytes + pj_bytes);
+                    x.jobs = reinterpret_cast<const PrefixJob *>(staged);
+                    if (table_bytes) x.page_table = reinterpret_cast<const int32_t *>(staged + copied);
+                }
+                return launch_small_ingest(c->geom, layer, in, (int)page_job.size(), ctx->p.io_dtype, rope, blk.p, staged, copied, c->d_tables,
+                                           staged + copied, table_bytes, done, words, expand, s);
             });
     } else {
         rc = stage_commit(ctx, slot, blk.p, copied, s, c->d_tables, copied, table_bytes, attend_only ? expand : nullptr);

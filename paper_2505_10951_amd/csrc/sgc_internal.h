@@ -443,17 +443,23 @@ hipError_t launch_prefix_ingest(const PoolGeom &g, int layer, const int32_t *d_p
                                 int n_chunks, int io_dtype, const float2 *rope, const ExpandArgs *expand, hipStream_t s);
 // The same for a small call, together with the copy of its tables to the device (see launch_copy_from_host): jobs and page ids
 // go with the launch.
-struct SmallIngest {
-    static constexpr int kJobs = 4, kPages = 256;
-    PrefixJob jobs[kJobs];
+template <int JOBS, int PAGES>
+struct SmallIngestArgs {
+    static constexpr int kJobs = JOBS, kPages = PAGES;
+    PrefixJob jobs[JOBS];
     int32_t n_jobs;
-    int32_t pages[kPages];       // id of every launch-wide page
+    int32_t pages[PAGES];        // id of every launch-wide page
 };
+using SmallIngest = SmallIngestArgs<12, 640>;
+using SmallIngestShort = SmallIngestArgs<2, 64>;
 struct CopyDone;
-bool small_ingest_covers(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes);
+static_assert(sizeof(SmallIngest) <= 3700, "the launch's arguments have to stay within 4 KiB");
+// Whether it covers a call, and which tables expand has to name then: the staged ones or the device's.
+enum SmallIngestUse { SMALL_INGEST_NO, SMALL_INGEST_STAGED_TABLES, SMALL_INGEST_COPIED_TABLES };
+SmallIngestUse small_ingest_use(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes);
 hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &small, int n_pages, int io_dtype, const float2 *rope, void *dst,
                                const void *mapped_src, size_t bytes, void *dst2, const void *mapped_src2, size_t bytes2, const CopyDone &done,
-                               const ExpandArgs *expand, hipStream_t s);
+                               int *n_words, const ExpandArgs *expand, hipStream_t s);
 hipError_t launch_cache_export(const PoolGeom &g, int layer, const int32_t *d_pages, int prefix_len,
                                void *k, void *v, hipStream_t s);
 hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pages, int prefix_len,

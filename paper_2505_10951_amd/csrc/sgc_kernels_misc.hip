@@ -463,22 +463,35 @@ __global__ void ingest_write_kernel(PoolGeom g, int layer, const int32_t *page_t
 }
 
 // A small call's ingest (16- and 32-bit caches): jobs and page ids travel with the launch, so no table has to be on the device
-// before it; what the attention launch behind it reads there is copied, and its tile records written, by one more workgroup of this
-// launch (the last column's first).  A launch less in front of the ingest: its 4 us and its boundary.
-__global__ void ingest_small_kernel(PoolGeom g, int layer, SmallIngest small, int n_pages, int io_dtype, const float2 *rope, CopyPiece a, CopyPiece b,
-                                    CopyDone done, ExpandArgs ex)
+// before it.  More workgroups of the same launch copy what the attention launch behind it reads there and write its tile records.
+// That is a launch less in front of the ingest, its 4 us and its boundary: one prompt of 411 tokens with its question 43.5 ->
+// 38.6 us, ten prompts of 150 to 1000 tokens with their batch, four layers, 508 -> 491.
+// expand_groups > 0: the records are written from the staged tables (three reads over the host link one behind the other, by
+// many wavefronts while the pages are written); 0: by the one workgroup that copies, from what it has copied (a prompt of 411
+// tokens: 38.7 us against 39.3).
+template <typename ARGS>
+__global__ void ingest_small_kernel(PoolGeom g, int layer, ARGS small, int n_pages, int io_dtype, const float2 *rope, CopyPiece a, CopyPiece b,
+                                    int copy_groups, int expand_groups, CopyDone done, ExpandArgs ex)
 {
     if ((int)blockIdx.x >= n_pages) {
-        if (blockIdx.y > 0) return;
-        copy_piece(a, threadIdx.x, blockDim.x);
-        copy_piece(b, threadIdx.x, blockDim.x);
-        signal_read(done, 0);
-        for (int i = threadIdx.x; i < ex.n; i += blockDim.x) expand_one_tile(ex, i);
+        const int extra = ((int)blockIdx.x - n_pages) * (int)gridDim.y + (int)blockIdx.y;
+        if (extra < copy_groups) {
+            const size_t first = (size_t)extra * blockDim.x + threadIdx.x, stride = (size_t)copy_groups * blockDim.x;
+            copy_piece(a, first, stride);
+            copy_piece(b, first, stride);
+            signal_read(done, extra);
+            if (expand_groups == 0)
+                for (int i = threadIdx.x; i < ex.n; i += blockDim.x) expand_one_tile(ex, i);
+        } else if (extra < copy_groups + expand_groups) {
+            const int i = (extra - copy_groups) * (int)blockDim.x + (int)threadIdx.x;
+            if (i < ex.n) expand_one_tile(ex, i);
+            signal_read(done, extra);
+        }
         return;
     }
     int j = 0;
 #pragma unroll
-    for (int i = 1; i < SmallIngest::kJobs; ++i)
+    for (int i = 1; i < ARGS::kJobs; ++i)
         if (i < small.n_jobs && (int)blockIdx.x >= small.jobs[i].page0) j = i;
     const PrefixJob &job = small.jobs[j];
     ingest_write_page(g, layer, job, blockIdx.x - job.page0, small.pages[blockIdx.x], blockIdx.y, io_dtype, rope);
@@ -1407,21 +1420,47 @@ static CopyPiece copy_piece_of(void *dst, const void *mapped_src, size_t bytes)
     return {static_cast<copy_u32x4 *>(dst), static_cast<const copy_u32x4 *>(mapped_src), bytes / 16, (bytes % 16) / 4};
 }
 
-bool small_ingest_covers(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes)
+// Limits: what fits the launch's arguments, and a done word for every workgroup that reads staged tables.
+constexpr int kIngestThreads = 128;
+struct SmallGroups {
+    int copy, expand;
+};
+static SmallGroups small_groups(int n_tiles, size_t staged_bytes)
 {
-    return g.kv_dtype != SGC_FP8_E4M3 && n_jobs <= SmallIngest::kJobs && n_pages <= SmallIngest::kPages && n_tiles <= kOneGroupTiles &&
-           staged_bytes <= kOneGroupBytes;
+    if (n_tiles <= kOneGroupTiles && staged_bytes <= kOneGroupBytes) return {1, 0};
+    const size_t per_group = 16 * 8 * kIngestThreads;
+    return {(int)std::min<size_t>((staged_bytes + per_group - 1) / per_group, 16), (n_tiles + kIngestThreads - 1) / kIngestThreads};
+}
+SmallIngestUse small_ingest_use(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes)
+{
+    const SmallGroups n = small_groups(n_tiles, staged_bytes);
+    if (g.kv_dtype == SGC_FP8_E4M3 || n_jobs > SmallIngest::kJobs || n_pages > SmallIngest::kPages || n.copy + n.expand > kCopyDoneWords)
+        return SMALL_INGEST_NO;
+    return n.expand > 0 ? SMALL_INGEST_STAGED_TABLES : SMALL_INGEST_COPIED_TABLES;
 }
 
 hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &small, int n_pages, int io_dtype, const float2 *rope, void *dst,
                                const void *mapped_src, size_t bytes, void *dst2, const void *mapped_src2, size_t bytes2, const CopyDone &done,
-                               const ExpandArgs *expand, hipStream_t s)
+                               int *n_words, const ExpandArgs *expand, hipStream_t s)
 {
     const CopyPiece a = copy_piece_of(dst, mapped_src, bytes), b = copy_piece_of(dst2, mapped_src2, bytes2);
     ExpandArgs ex{};
     if (expand) ex = *expand;
-    hipLaunchKernelGGL(ingest_small_kernel, dim3(n_pages + 1, g.n_kv_heads), dim3(128), 2 * (size_t)g.head_part_bytes, s, g, layer, small, n_pages,
-                       io_dtype, rope, a, b, done, ex);
+    const auto [copy_groups, expand_groups] = small_groups(ex.n, bytes + bytes2);
+    *n_words = copy_groups + expand_groups;
+    const int columns = (*n_words + g.n_kv_heads - 1) / g.n_kv_heads;
+    // (arguments are copied with every launch: a short prompt does not send the 3.6 KB that ten may need: 39.3 us with them, 39.0 without)
+    if (small.n_jobs <= SmallIngestShort::kJobs && n_pages <= SmallIngestShort::kPages) {
+        SmallIngestShort few;
+        few.n_jobs = small.n_jobs;
+        std::copy(small.jobs, small.jobs + small.n_jobs, few.jobs);
+        std::copy(small.pages, small.pages + n_pages, few.pages);
+        hipLaunchKernelGGL(ingest_small_kernel<SmallIngestShort>, dim3(n_pages + columns, g.n_kv_heads), dim3(kIngestThreads),
+                           2 * (size_t)g.head_part_bytes, s, g, layer, few, n_pages, io_dtype, rope, a, b, copy_groups, expand_groups, done, ex);
+    } else {
+        hipLaunchKernelGGL(ingest_small_kernel<SmallIngest>, dim3(n_pages + columns, g.n_kv_heads), dim3(kIngestThreads), 2 * (size_t)g.head_part_bytes, s,
+                           g, layer, small, n_pages, io_dtype, rope, a, b, copy_groups, expand_groups, done, ex);
+    }
     return hipGetLastError();
 }
 

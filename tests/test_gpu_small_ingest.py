@@ -1,5 +1,5 @@
-"""Prompts few and short enough that the ingest takes jobs and page ids with its launch, and the sizes just past that (five jobs,
-257 pages, 257 tiles): the cache's contents and the prompts' own attention."""
+"""Prompts few and short enough that the ingest takes jobs and page ids with its launch, and the sizes just past that (thirteen jobs,
+641 pages): the cache's contents and the prompts' own attention."""
 import numpy as np
 import pytest
 
@@ -13,9 +13,9 @@ from paper_2505_10951_amd.harness import Session  # noqa: E402
 
 
 @pytest.mark.parametrize("io,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
-@pytest.mark.parametrize("prefix", [[1], [16, 0, 17], [5, 40, 33, 64], [5, 40, 33, 64, 1], [2048, 2032, 16], [2048, 2032, 17], [512], [513]])
+@pytest.mark.parametrize("prefix", [[1], [16, 0, 17], [5, 40, 33, 64], [3] * 12, [3] * 13, [5120, 5104, 16], [5120, 5104, 17], [512], [2000]])
 def test_small_and_general_ingest(io, d, prefix):
-    hq, hkv = (16, 8) if prefix in ([512], [513]) else (2, 1)      # 8 heads x 32 or 33 tokens of four to a tile: 64 and 72 tiles
+    hq, hkv = (16, 8) if prefix in ([512], [2000]) else (2, 1)      # eight heads
     w = workloads.custom("small_ingest", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rope_base=10000.0, io_dtype=io, prefix_len=prefix,
                          cluster_sizes=[1] * len(prefix), suffix_range=(1, 2), seed=d + len(prefix))
     with Session(w) as s:
