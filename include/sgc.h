@@ -181,7 +181,8 @@ int sgc_prefix_prefill(sgc_ctx *ctx, sgc_cache *cache, int32_t cluster_id, int32
  * clusters.  dev_q, dev_k, dev_v, dev_o, dev_lse: HOST arrays of n device pointers, entry i shaped
  * as above for cluster_ids[i] with that cluster's prefix_len; dev_q and dev_o may both be NULL
  * (cache fill only) or hold NULL entries for clusters that need no attention output; dev_lse may be
- * NULL or hold NULL entries.  The pointer arrays are read before the call returns. */
+ * NULL or hold NULL entries.  The pointer arrays are read before the call returns.
+ * What is cached does not depend on the other clusters of the call. */
 int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *cache, int32_t n, const int32_t *cluster_ids,
                                int32_t layer, const void *const *dev_q, const void *const *dev_k,
                                const void *const *dev_v, void *const *dev_o, float *const *dev_lse,

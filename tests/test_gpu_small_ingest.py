@@ -33,3 +33,19 @@ def test_small_and_general_ingest(io, d, prefix):
             assert np.allclose(ek[:prefix[c]], ck, rtol=1e-5 if io == "f32" else 6e-4, atol=2e-6 if io == "f32" else 1e-4)
             assert np.array_equal(ev[:prefix[c]], cv)
             assert float(np.abs(o.float().cpu().numpy()[rows] - po[rows]).max()) <= (2e-5 if io == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("io,kv,d", [("f32", "f32", 64), ("bf16", "bf16", 128)])
+def test_cache_does_not_depend_on_the_other_prompts_of_the_call(io, kv, d):
+    """A prompt's pages by a call of its own (its jobs travel with the launch) and by a call over thirteen: bit for bit."""
+    w = workloads.custom("alone", n_q_heads=2, n_kv_heads=2, head_dim=d, rope_base=500000.0, io_dtype=io, kv_dtype=kv, prefix_len=[100 + c for c in range(13)],
+                         cluster_sizes=[1] * 13, suffix_range=(1, 2), seed=5)
+    with Session(w) as one, Session(w) as all_:
+        for c in range(13):
+            one.alloc_cluster(c)
+            all_.alloc_cluster(c)
+        all_.prefix_prefill_batched(range(13))
+        for c in range(13):
+            one.prefix_prefill(c)
+            for x, y in zip(one.export_cluster(c)[:2], all_.export_cluster(c)[:2]):
+                assert np.array_equal(x, y)
