@@ -330,8 +330,9 @@ int sgc_project_out(sgc_ctx *ctx, const void *dev_o, const void *dev_w_o, int32_
                     void *dev_y, void *hip_stream);
 
 /* ---- kernel timing (measurement aid; no effect on results) -----------------------------------
- * With timing on, sgc_suffix_prefill_batched records HIP events on its launch stream around the
- * suffix K/V ingest kernel and around the attention kernel; the events of the last 128 timed launches
+ * With timing on, sgc_suffix_prefill_batched records HIP events on its launch stream around what it
+ * launches before the attention kernel (tile records that are due; the suffix K/V ingest where there is one)
+ * and around the attention kernel; the events of the last 128 timed launches
  * are kept, so a caller can enqueue many launches without waiting and read all durations afterwards.
  * sgc_timing_get waits for the launch recorded `back` timed launches before the last one (0 = the
  * last) to finish and returns the two durations in milliseconds (either pointer may be NULL);
