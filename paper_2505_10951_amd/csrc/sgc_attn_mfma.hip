@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
     // ---- which tile ----
     Tile t = uniform_record(a.tiles + blockIdx.x);
     // (the whole record is asked for before its first use decides anything: one round trip)
-    asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad), "s"(t.first_pages[0]), "s"(t.first_pages[11]), "s"(t.q[0].tok0), "s"(t.q[3].page0),
+    asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad), "s"(t.first_pages[0]), "s"(t.first_pages[11]), "s"(t.q[0].tok0), "s"(t.q[3].own0),
                  "s"(t.own_page0));
     if (t.n_rows == 0) return;
     // where the rows come from and go to: the batch's packed arrays, or (prefix mode) the job's
@@ -385,14 +385,14 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
 
     // ---- per-lane row bookkeeping ----
     const bool inline_queries = MODE == MODE_SUFFIX && __builtin_amdgcn_readfirstlane(t.n_q) <= kTileQueries;
-    int tq_tok0[kTileQueries], tq_src0[kTileQueries], tq_page0[kTileQueries];
+    int tq_tok0[kTileQueries], tq_src0[kTileQueries], tq_own0[kTileQueries];
 #pragma unroll
     for (int k = 0; k < kTileQueries; ++k) {
         tq_tok0[k] = __builtin_amdgcn_readfirstlane(t.q[k].tok0);
         tq_src0[k] = __builtin_amdgcn_readfirstlane(t.q[k].src0);
-        tq_page0[k] = __builtin_amdgcn_readfirstlane(t.q[k].page0);
+        tq_own0[k] = __builtin_amdgcn_readfirstlane(t.q[k].own0);
     }
-    // Own keys are numbered by slots, 16 to a page, over the suffix pages of all queries the tile touches: page 0 is the
+    // Own keys are numbered by slots, 16 to a page, over the own pages of all queries the tile touches: page 0 is the
     // first page of query sq_lo, and the last one holds the tile's last row's own key.
     const bool own = MODE == MODE_SUFFIX && !a.skip_self;
     const int own_page0 = __builtin_amdgcn_readfirstlane(t.own_page0), n_own = own ? __builtin_amdgcn_readfirstlane(t.n_own_pages) : 0;
@@ -415,12 +415,12 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
                 const int src0 = ge3 ? tq_src0[3] : ge2 ? tq_src0[2] : ge1 ? tq_src0[1] : tq_src0[0];
                 qpos[mi] = tau - first;
                 src_tok[mi] = src0 + qpos[mi];
-                own_first = ((ge3 ? tq_page0[3] : ge2 ? tq_page0[2] : ge1 ? tq_page0[1] : tq_page0[0]) - own_page0) * kPageTokens;
+                own_first = ((ge3 ? tq_own0[3] : ge2 ? tq_own0[2] : ge1 ? tq_own0[1] : tq_own0[0]) - own_page0) * kPageTokens;
             } else {
                 const TokInfo ti = a.tok_info[tau];
                 src_tok[mi] = ti.src;
                 qpos[mi] = ti.qpos;
-                own_first = (ti.page0 - own_page0) * kPageTokens;
+                own_first = (ti.own0 - own_page0) * kPageTokens;
             }
             lim[mi] = P;
         } else {
@@ -785,8 +785,8 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
         const int p = i * OWN_PAGES + wave_u;
         if (p >= n_own) return;
         char *kd = own_kbuf(i) + wave_u * PART_BYTES, *vd = own_vbuf(i) + wave_u * PART_BYTES;
+        const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
         if constexpr (OWN_RAW) {
-            const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
             const int l = lane_again(), r0 = l >> 4, c = l & 15;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {           // rows 4 j .. 4 j + 3 of the page
@@ -798,7 +798,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
                 __builtin_amdgcn_global_load_lds(gv, (__attribute__((address_space(3))) void *)(vd + j * 1024), 16, 0, 0);
             }
         } else {
-            const char *src = spool_base + (own_page0 + p) * spool_page + lane16;
+            const char *src = spool_base + pg.page * spool_page + lane16;
             copy_4k_to_lds(src, kd);
             copy_4k_to_lds(src + spool_v_off, vd);
         }

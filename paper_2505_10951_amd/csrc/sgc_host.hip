@@ -425,12 +425,12 @@ void build_tiles(sgc_plan *pl, int tile_rows)
             for (int q = 0; q < kTileQueries; ++q) {
                 const int32_t sq = t.sq_lo + q;
                 if (sq <= t.sq_hi)
-                    t.q[q] = {pl->sq_tok0[sq], pl->sq_src0[sq], pl->sq_page0[sq]};
+                    t.q[q] = {pl->sq_tok0[sq], pl->sq_src0[sq], pl->sq_own0[sq]};
                 else
                     t.q[q] = {INT32_MAX, 0, 0};
             }
-            t.own_page0 = pl->sq_page0[t.sq_lo];
-            t.n_own_pages = pl->sq_page0[t.sq_hi] - t.own_page0 + t.last_qpos / kPageTokens + 1;
+            t.own_page0 = pl->sq_own0[t.sq_lo];
+            t.n_own_pages = pl->sq_own0[t.sq_hi] - t.own_page0 + t.last_qpos / kPageTokens + 1;
             pl->seeds[k * kXcd + x] = {t.cluster, t.hk, t.row0, t.n_rows, t.sq_lo, t.sq_hi, t.last_qpos, 0};
         }
     }
@@ -473,16 +473,17 @@ void fill_tile_pt_off(sgc_plan *pl, const sgc_cache *c)
 void layout_suffix_pages(sgc_plan *pl)
 {
     pl->spages.clear();
+    pl->sq_own0.resize(pl->sq_len.size());
     int32_t page = 0;
     for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) {
         pl->sq_page0[sq] = page;
-        const int32_t np = (pl->sq_len[sq] + pl->decode_cap + kPageTokens - 1) / kPageTokens;
-        for (int32_t p = 0; p < np; ++p) {
-            const int32_t j = p * kPageTokens;
-            pl->spages.push_back({pl->sq_src0[sq] + j, std::min(pl->sq_len[sq] - j, kPageTokens), pl->cl_prefix_len[pl->sq_cluster[sq]] + j, 0});
-        }
-        page += np;
+        pl->sq_own0[sq] = (int32_t)pl->spages.size();
+        for (int32_t j = 0; j < pl->sq_len[sq]; j += kPageTokens)
+            pl->spages.push_back({pl->sq_src0[sq] + j, std::min(pl->sq_len[sq] - j, kPageTokens), pl->cl_prefix_len[pl->sq_cluster[sq]] + j,
+                                  page + j / kPageTokens});
+        page += (pl->sq_len[sq] + pl->decode_cap + kPageTokens - 1) / kPageTokens;
     }
+    pl->n_pool_pages = page;
 }
 
 // Decode work list: one row group (the g heads of a KV head) per query, all queries of a (cluster, KV head)
@@ -1113,8 +1114,7 @@ static ExpandArgs plan_expand_args(const sgc_plan *pl, const sgc_cache *c)
     e.cl_tok_off = pl->d_cl_tok_off;
     e.sq_tok0 = pl->d_sq_tok0;
     e.sq_src0 = pl->d_sq_src0;
-    e.sq_len = pl->d_sq_len;
-    e.sq_page0 = pl->d_sq_page0;
+    e.sq_own0 = pl->d_sq_own0;
     return e;
 }
 
@@ -1151,7 +1151,7 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     pl->tok_info.clear();
     if (wide_tile) {
         pl->tok_info.resize(pl->tok_src.size());
-        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->tok_sq[i], pl->sq_page0[pl->tok_sq[i]]};
+        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->tok_sq[i], pl->sq_own0[pl->tok_sq[i]]};
     }
     pl->row_dest.clear();      // made when a projection first asks for it
 
@@ -1173,6 +1173,7 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
         {pl->sq_tok0.data(), pl->sq_tok0.size() * 4, (const void **)&pl->d_sq_tok0},
         {pl->sq_cluster.data(), pl->sq_cluster.size() * 4, (const void **)&pl->d_sq_cluster},
         {pl->sq_page0.data(), pl->sq_page0.size() * 4, (const void **)&pl->d_sq_page0},
+        {pl->sq_own0.data(), pl->sq_own0.size() * 4, (const void **)&pl->d_sq_own0},
         {pl->spages.data(), pl->spages.size() * sizeof(SuffixPage), (const void **)&pl->d_spages},
         {pl->seeds.data(), pl->seeds.size() * sizeof(TileSeed), (const void **)&pl->d_seeds},
         {pl->tok_info.data(), pl->tok_info.size() * sizeof(TokInfo), (const void **)&pl->d_tok_info},
@@ -1204,12 +1205,12 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     const bool expand = with_tiles && !pl->tiles.empty();
     if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s, nullptr, 0, 0, expand ? &ex : nullptr)) != SGC_OK) return rc;
     pl->expand_pending = !pl->tiles.empty() && !expand;      // otherwise with the next suffix launch
-    if (want_rows > 0 && !pl->spages.empty()) {
+    if (want_rows > 0 && pl->n_pool_pages > 0) {
         // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps and projected keys
         // (a plain suffix prefill reads its keys and values as they are given; held from here on so that no later call allocates it)
         // (decode: one pool per layer, since the pages have to outlive the layer's suffix launch; zeroed once,
         // so that pages no token has reached yet hold finite values)
-        pl->spool_layer_bytes = pl->spages.size() * (size_t)2 * ctx->p.n_kv_heads * kPageTokens * ctx->p.head_dim * 2;
+        pl->spool_layer_bytes = (size_t)pl->n_pool_pages * 2 * ctx->p.n_kv_heads * kPageTokens * ctx->p.head_dim * 2;
         pl->spool_bytes = pl->spool_layer_bytes * (pl->decode_cap > 0 ? (size_t)ctx->p.n_layers : 1);
         if ((rc = dev_acquire(ctx, pl->spool_bytes, s, &pl->spool_block)) != SGC_OK) return rc;
         pl->d_spool = pl->spool_block.p;

@@ -92,7 +92,7 @@ constexpr int kTileQueries = 4;      // queries a tile record describes inline
 struct TileQuery {
     int32_t tok0;    // first sorted token of the query (INT32_MAX in unused slots)
     int32_t src0;    // first row of the query in the caller's packed arrays
-    int32_t page0;   // first suffix page of the query
+    int32_t own0;    // first own page of the query
 };
 struct Tile {
     int32_t cluster;     // cluster id (index into the cache's per-cluster arrays)
@@ -108,7 +108,7 @@ struct Tile {
     int32_t pad;         // decode tiles: key range index << 24 | position offset (cached keys outside the range)
     int32_t first_pages[12];       // page ids of the cluster's first 12 pages (clamped to its last page)
     TileQuery q[kTileQueries];     // queries sq_lo, sq_lo + 1, ...
-    int32_t own_page0;             // first suffix page of query sq_lo ...
+    int32_t own_page0;             // first own page of query sq_lo ...
     int32_t n_own_pages;           // ... and how many follow up to the last row's own key
     int32_t unused[2];
 };
@@ -134,12 +134,15 @@ struct GenericTile {
     int32_t row0;    // first row inside the unit
 };
 
-// Per suffix page (16 tokens of one query's suffix; the queries' pages follow each other): where its tokens come from.
+// Own pages: 16 question tokens of one query each, numbered through over all queries.  In the suffix page pool a query's pages
+// may be followed by spare ones, kept for generated tokens; those have no number here, so that whoever walks the own pages
+// of neighbouring queries meets none of them (320 questions of ten tokens, 32 heads, room for 900 generated tokens each: walked
+// with the spare pages 1177 us, without 129).
 struct SuffixPage {
     int32_t row0;    // row of its first token in the caller's packed arrays
-    int32_t n;       // tokens it holds (<= 0: none, a page kept free for generated tokens)
+    int32_t n;       // tokens it holds
     int32_t pos0;    // position of its first token (the cluster's prompt counts)
-    int32_t pad;
+    int32_t page;    // its page in the pool
 };
 
 // Per sorted token: where it comes from and where it sits in its query.
@@ -147,7 +150,7 @@ struct TokInfo {
     int32_t src;    // row of the token in the caller's packed arrays
     int32_t qpos;   // index of the token inside its query
     int32_t sq;     // sorted query index
-    int32_t page0;  // first suffix page of the query
+    int32_t own0;   // first own page of the query
 };
 
 // One cluster of a (batched) prefix prefill.
@@ -281,7 +284,7 @@ struct AttnArgs {
     int32_t n_q_heads, n_kv_heads, group, head_dim;
     int32_t io_dtype;
     float scale_log2e;            // softmax_scale * log2(e)
-    const SuffixPage *spages;     // [suffix pages]
+    const SuffixPage *spages;     // [own pages]
     int32_t own_raw;              // MFMA kernel: the rows' own keys are read from k and v as given, not from the suffix pages
     // decode: the one new token of a query sits pos_shift tokens behind the end of its suffix, and the MFMA
     // kernel only does the cached-prefix part (skip_self), leaving the own keys to the decode kernel
@@ -371,7 +374,9 @@ struct sgc_plan {
     std::vector<int32_t> cl_tok_off;
     std::vector<int32_t> tok_src, tok_qpos, tok_sq;
     std::vector<int32_t> sq_src0, sq_len, sq_tok0, sq_cluster, sq_page0;   // non-empty queries only
-    std::vector<sgc::SuffixPage> spages;      // [total suffix pages]
+    std::vector<int32_t> sq_own0;             // [non-empty queries] first own page (sq_page0: first page in the pool)
+    std::vector<sgc::SuffixPage> spages;      // [own pages]
+    int32_t n_pool_pages = 0;                 // pages of the suffix page pool, spare ones included
     std::vector<int32_t> sq_query;            // [non-empty queries] original index of the sorted query
     std::vector<int32_t> cl_sq_off;           // [n_clusters + 1] first sorted query of each cluster
     // decode (off unless sgc_plan_enable_decode was called): pages leave room for decode_cap more tokens per
@@ -402,7 +407,7 @@ struct sgc_plan {
     char *d_blob = nullptr;                   // one device allocation holding every array below
     const int32_t *d_cl_tok_off = nullptr, *d_tok_src = nullptr, *d_tok_qpos = nullptr, *d_tok_sq = nullptr;
     const int32_t *d_sq_src0 = nullptr, *d_sq_len = nullptr, *d_sq_tok0 = nullptr, *d_sq_cluster = nullptr;
-    const int32_t *d_sq_page0 = nullptr;
+    const int32_t *d_sq_page0 = nullptr, *d_sq_own0 = nullptr;
     const sgc::SuffixPage *d_spages = nullptr;
     const sgc::Tile *d_tiles = nullptr;
     std::vector<sgc::TileSeed> seeds;         // one per entry of tiles
@@ -431,7 +436,7 @@ struct ExpandArgs {
     int32_t n;
     const PrefixJob *jobs;
     const int32_t *page_table, *pt_off, *prefix_len;      // the cache's device tables
-    const int32_t *cl_tok_off, *sq_tok0, *sq_src0, *sq_len, *sq_page0;      // the plan's
+    const int32_t *cl_tok_off, *sq_tok0, *sq_src0, *sq_own0;      // the plan's
 };
 hipError_t launch_expand_tiles(const ExpandArgs &e, hipStream_t s);
 
@@ -468,7 +473,7 @@ hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pa
                                const void *k, const void *v, hipStream_t s);
 
 // Suffix ingest: rotate every query's suffix K at prefix_len + j and write K and V as bf16 pages
-// (cache page layout) into the suffix page pool; one workgroup per (suffix page, KV head).  expand: as above.
+// (cache page layout) into the suffix page pool; one workgroup per (own page, KV head).  expand: as above.
 hipError_t launch_suffix_ingest(const AttnArgs &a, int n_spages, const ExpandArgs *expand,
                                 hipStream_t s);
 

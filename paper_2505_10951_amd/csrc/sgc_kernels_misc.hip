@@ -351,10 +351,10 @@ __device__ inline void expand_one_tile(const ExpandArgs &e, int i)
 #pragma unroll
             for (int k = 0; k < kTileQueries; ++k) {
                 const int sq = sd.sq_lo + k;
-                if (sq <= sd.sq_hi) t.q[k] = {e.sq_tok0[sq], e.sq_src0[sq], e.sq_page0[sq]};
+                if (sq <= sd.sq_hi) t.q[k] = {e.sq_tok0[sq], e.sq_src0[sq], e.sq_own0[sq]};
             }
-            t.own_page0 = e.sq_page0[sd.sq_lo];
-            t.n_own_pages = e.sq_page0[sd.sq_hi] - t.own_page0 + sd.last_qpos / kPageTokens + 1;
+            t.own_page0 = e.sq_own0[sd.sq_lo];
+            t.n_own_pages = e.sq_own0[sd.sq_hi] - t.own_page0 + sd.last_qpos / kPageTokens + 1;
         }
         const int n_pages = (t.prefix_len + kPageTokens - 1) / kPageTokens;
         if (n_pages > 0) {
@@ -579,19 +579,18 @@ __global__ void __launch_bounds__(128) ingest_write_fp8_kernel(PoolGeom g, int l
 // Same page layout as the cache, 16-bit only (K binary16, V bf16), for the question tokens of every query of the batch
 // (SubGCache Sec. 3.4: the question tokens are appended to the cached prompt, so suffix token j of a
 // query whose cluster has P prefix tokens is rotated at position P + j).  One workgroup per
-// (suffix page, KV head); tokens past the query's end are written as zeros.
+// (own page, KV head); tokens past the query's end are written as zeros.
 __global__ void suffix_ingest_kernel(AttnArgs a, int n_spages, ExpandArgs ex)
 {
     if ((int)blockIdx.x >= n_spages) {
         expand_in_ingest_grid(ex, n_spages);
         return;
     }
-    const int page = blockIdx.x, hk = blockIdx.y;
+    const int hk = blockIdx.y;
     const int Hkv = a.n_kv_heads, d = a.head_dim, half = d / 2, pairs = d / 16;
-    const SuffixPage pg = a.spages[page];
-    if (pg.n <= 0) return;      // a page kept free for decoded tokens: not this kernel's to write
+    const SuffixPage pg = a.spages[blockIdx.x];
     const int64_t part = (int64_t)kPageTokens * d * 2;
-    char *kg = const_cast<char *>(a.spool) + (int64_t)page * 2 * Hkv * part + (int64_t)hk * part;
+    char *kg = const_cast<char *>(a.spool) + (int64_t)pg.page * 2 * Hkv * part + (int64_t)hk * part;
     char *vg = kg + (int64_t)Hkv * part;
     extern __shared__ __attribute__((aligned(16))) char page_img[];     // both images are built in LDS first
     char *kp = page_img, *vp = page_img + part;
