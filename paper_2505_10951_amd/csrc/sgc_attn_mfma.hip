@@ -1174,7 +1174,7 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
     // ---- the wavefront's units: online softmax as in the kernel above ----
     f32x16 oacc[4], neg_ref;
     float m_ref = 0.f, l_part = 0.f;
-    bool seen = false;
+    bool seen = false, fresh = true;          // fresh: some row of the wavefront has met no key yet
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         neg_ref[r] = 0.f;
@@ -1195,7 +1195,7 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
         f32x16 s = neg_ref;
 #pragma unroll
         for (int kb = 0; kb < 8; ++kb) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, kf[kb]), qf[kb], s, 0, 0, 0);
-        const bool masked = 32 * u + 32 > P;
+        const bool masked = 32 * u + 32 > P, first = u == wave_u;
         if (masked) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
@@ -1208,20 +1208,26 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
 #pragma unroll
             for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
             tmax = half_max(tmax);
-            const float delta = seen ? fmaxf(tmax, 0.f) : tmax;
+            const bool has = tmax > -INFINITY;          // (a unit whose scores are all -inf leaves the row as it was)
+            const float delta = seen ? fmaxf(tmax, 0.f) : (has ? tmax : 0.f);
             if (__any(delta != 0.f)) {
-                const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 1.0f;
                 m_ref += delta;
-                l_part *= alpha;
+                if (!first) {                           // (nothing is accumulated before a wavefront's first unit)
+                    const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 1.0f;
+                    l_part *= alpha;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+#pragma unroll
+                        for (int db = 0; db < 4; ++db) oacc[db][r] *= alpha;
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-#pragma unroll
-                    for (int db = 0; db < 4; ++db) oacc[db][r] *= alpha;
                     s[r] -= delta;
                     neg_ref[r] = -m_ref;
                 }
             }
-            seen = true;
+            seen = seen || has;
+            fresh = __any(!seen);
         };
         auto weights = [&]() __attribute__((always_inline)) {
             bf16x2 ones;
@@ -1237,7 +1243,7 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
                 pf[r >> 3][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
             }
         };
-        const bool careful = masked || !seen;          // (every row sees a key of every unit: seen is the same for all)
+        const bool careful = masked || fresh;
         if (careful) raise_reference();
         weights();
         if (!careful && __any(!(psum <= kKeepBelow))) {

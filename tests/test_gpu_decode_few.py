@@ -22,3 +22,38 @@ def test_rows_and_keys_around_a_wavefront(hq, hkv, per, prefix):
     o, lse = _run_decode(w, 2)[0]
     o_ref, lse_ref = _oracle_decode(w, 0, 2, oracle_caches(w, 0))
     assert np.isfinite(o).all() and np.abs(o - o_ref).max() <= TOL["bf16"] and np.abs(lse - lse_ref).max() <= 5e-2
+
+
+@pytest.mark.parametrize("prefix,masked", [(40, (0, 32)), (300, (32, 64)), (300, (0, 256)), (900, (640, 899))])
+def test_keys_that_score_minus_infinity(prefix, masked):
+    """Whole units of 32 keys with scores of minus infinity count for nothing; the other keys' result stays."""
+    import torch
+    from oracle import oracle as orc
+    from paper_2505_10951_amd.harness import Session, to_device, to_host_f32
+    w = workloads.custom("few_inf", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=0.0, io_dtype="bf16", prefix_len=[prefix],
+                         cluster_sizes=[3], suffix_range=(2, 5), seed=prefix)
+    pk, pv = w.prefix_kv(0)
+    pk = pk.copy()
+    pk[masked[0]:masked[1], :, 5] = -np.inf
+    with Session(w) as s:
+        s.alloc_cluster(0)
+        s.prefix_prefill(0, k=pk, v=pv)
+        s.assign()
+        s.enable_decode(2)
+        q, k, v = w.suffix_qkv()
+        q[:, :, 5] = np.abs(q[:, :, 5])
+        s.suffix_prefill(*(to_device(x, "bf16") for x in (q, k, v)))
+        dq, dk, dv = w.decode_qkv(0)
+        dq[:, :, 5] = np.abs(dq[:, :, 5])
+        lse = torch.zeros((8, 3), device="cuda:0")
+        o = s.decode_step(0, *(to_device(x, "bf16") for x in (dq, dk, dv)), dlse=lse)
+        torch.cuda.synchronize()
+        o, lse = to_host_f32(o), lse.cpu().numpy()
+    keep = np.r_[0:masked[0], masked[1]:prefix]
+    cu = w.cu_seqlens
+    for n in range(3):
+        a, b = int(cu[n]), int(cu[n + 1])
+        S = b - a
+        ref, ref_lse, _ = orc.suffix_prefill(pk[keep], pv[keep], np.concatenate([q[a:b], dq[n:n + 1]]), np.concatenate([k[a:b], dk[n:n + 1]]),
+                                             np.concatenate([v[a:b], dv[n:n + 1]]), 0.0)
+        assert np.abs(o[n] - ref[S]).max() <= TOL["bf16"] and np.abs(lse[:, n] - ref_lse[:, S]).max() <= 5e-2
