@@ -992,8 +992,9 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
             if (c1 < n_own) own_table(ci + 1);
             const char *kc = own_kbuf(ci), *vc = own_vbuf(ci);
             const int row_end = min(own_first + qpos[0], c1 * kPageTokens - 1);
-            for (int p = max(wpg_lo, c0); p <= min(wpg_hi, c1 - 1); p += 2) {
-                const int i0 = p - c0, i1 = min(p + 1, c1 - 1) - c0;       // (a second page past the end: the first again, masked)
+            const int p_last = min(wpg_hi, c1 - 1);
+            for (int p = max(wpg_lo, c0); p <= p_last; p += 2) {
+                const int i0 = p - c0, i1 = min(p + 1, p_last) - c0;       // (past the last page the rows see: the first again, masked)
                 const char *kp = kc + ((n >> 4) ? i1 : i0) * PART_BYTES + (h * kPageTokens + (n & 15)) * 16;
                 const char *v0 = vc + i0 * PART_BYTES, *v1 = vc + i1 * PART_BYTES;
 #pragma unroll

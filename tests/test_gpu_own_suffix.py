@@ -58,3 +58,25 @@ def test_own_keys_by_every_route(hq, hkv, prefix, suffix, kv, rope):
             floor = max(fp8_query_floor(*caches[int(w.labels[n])], *w.suffix_qkv_query(n), w.rope_base) for n in range(w.n_queries) if prefix[labels[n]] > 0)
             o, _ = _run(w, route, sgc.SGC_KERNEL_MFMA_FP8)
             assert float(np.abs(o - ref).max()) <= 4 * floor + 6e-2, route
+
+
+@pytest.mark.parametrize("hq,hkv,suffix", [(2, 1, [16, 16]), (4, 2, [8, 32, 8, 8, 16, 40]), (1, 1, [32, 32, 7]), (8, 1, [4, 4, 4, 20])])
+def test_a_wavefront_sees_no_values_of_queries_it_has_no_rows_of(hq, hkv, suffix):
+    """Values that are not finite may reach rows that share a wavefront's 32 with the query that has them, and no others."""
+    g = hq // hkv
+    w = workloads.custom("nan", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[40],
+                         labels=np.zeros(len(suffix), np.int32), suffix_len=np.array(suffix, np.int32), seed=hq)
+    cu = w.cu_seqlens
+    with Session(w, kernel=sgc.SGC_KERNEL_MFMA) as s:
+        s.alloc_cluster(0)
+        s.prefix_prefill(0)
+        s.assign()
+        dq, dk, dv = (to_device(x, "bf16") for x in w.suffix_qkv())
+        clean = to_host_f32(s.suffix_prefill(dq, dk, dv))
+        for n in range(w.n_queries):
+            bad = dv.clone()
+            bad[cu[n]:cu[n + 1]] = float("nan")
+            o = to_host_f32(s.suffix_prefill(dq, dk, bad))
+            first, last = int(cu[n]) * g // 32, (int(cu[n + 1]) * g - 1) // 32      # wavefronts that hold rows of query n
+            others = np.array([t for t in range(int(cu[-1])) if all(not first <= r // 32 <= last for r in range(t * g, t * g + g))], int)
+            assert np.array_equal(o[others], clean[others]), n
