@@ -190,9 +190,7 @@ __device__ inline void append_new_tokens(const AttnArgs &a, int blk)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const float2 cs = a.rope[(int64_t)pos * (D / 2) + cc * 8 + 2 * i + e];
-                const float p = x1[e], q = x2[e];
-                x1[e] = p * cs.x - q * cs.y;
-                x2[e] = q * cs.x + p * cs.y;
+                rotate_pair(x1[e], x2[e], cs.x, cs.y);
             }
         }
         o1[i] = pack2_f16(x1[0], x1[1]);       // keys are kept as binary16
@@ -510,10 +508,12 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
                     const float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
                     const float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
                     const float4 t4 = cs[mi][kb][i];
-                    x1[2 * i] = a0 * t4.x - b0 * t4.y;
-                    x2[2 * i] = b0 * t4.x + a0 * t4.y;
-                    x1[2 * i + 1] = a1 * t4.z - b1 * t4.w;
-                    x2[2 * i + 1] = b1 * t4.z + a1 * t4.w;
+                    x1[2 * i] = a0;
+                    x2[2 * i] = b0;
+                    x1[2 * i + 1] = a1;
+                    x2[2 * i + 1] = b1;
+                    rotate_pair(x1[2 * i], x2[2 * i], t4.x, t4.y);
+                    rotate_pair(x1[2 * i + 1], x2[2 * i + 1], t4.z, t4.w);
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {      // the score scale (log2 units, cached-K scale included) rides on Q
@@ -843,11 +843,13 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
                 uint32_t o1[4], o2[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float a0 = __uint_as_float(wl[e] << 16), a1 = __uint_as_float(wl[e] & 0xFFFF0000u);
-                    const float b0 = __uint_as_float(wh[e] << 16), b1 = __uint_as_float(wh[e] & 0xFFFF0000u);
+                    float a0 = __uint_as_float(wl[e] << 16), a1 = __uint_as_float(wl[e] & 0xFFFF0000u);
+                    float b0 = __uint_as_float(wh[e] << 16), b1 = __uint_as_float(wh[e] & 0xFFFF0000u);
                     const float4 t4 = own_cs[k][e];
-                    o1[e] = pack2_f16(a0 * t4.x - b0 * t4.y, a1 * t4.z - b1 * t4.w);
-                    o2[e] = pack2_f16(b0 * t4.x + a0 * t4.y, b1 * t4.z + a1 * t4.w);
+                    rotate_pair(a0, b0, t4.x, t4.y);
+                    rotate_pair(a1, b1, t4.z, t4.w);
+                    o1[e] = pack2_f16(a0, a1);
+                    o2[e] = pack2_f16(b0, b1);
                 }
                 *reinterpret_cast<uint4 *>(kp + c * 256 + r * 16) = make_uint4(o1[0], o1[1], o1[2], o1[3]);
                 *reinterpret_cast<uint4 *>(kp + (c + 8) * 256 + r * 16) = make_uint4(o2[0], o2[1], o2[2], o2[3]);
@@ -1161,13 +1163,15 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
             const uint32_t wl[4] = {qlo[kb].x, qlo[kb].y, qlo[kb].z, qlo[kb].w}, wh[4] = {qhi[kb].x, qhi[kb].y, qhi[kb].z, qhi[kb].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
-                const float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
+                float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
+                float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
                 const float4 t4 = cs[kb][i];
-                qf[kb][2 * i] = (_Float16)((a0 * t4.x - b0 * t4.y) * a.scale_log2e);
-                qf[kb][2 * i + 1] = (_Float16)((a1 * t4.z - b1 * t4.w) * a.scale_log2e);
-                qf[kb + 4][2 * i] = (_Float16)((b0 * t4.x + a0 * t4.y) * a.scale_log2e);
-                qf[kb + 4][2 * i + 1] = (_Float16)((b1 * t4.z + a1 * t4.w) * a.scale_log2e);
+                rotate_pair(a0, b0, t4.x, t4.y);
+                rotate_pair(a1, b1, t4.z, t4.w);
+                qf[kb][2 * i] = (_Float16)(a0 * a.scale_log2e);
+                qf[kb][2 * i + 1] = (_Float16)(a1 * a.scale_log2e);
+                qf[kb + 4][2 * i] = (_Float16)(b0 * a.scale_log2e);
+                qf[kb + 4][2 * i + 1] = (_Float16)(b1 * a.scale_log2e);
             }
         }
     }

@@ -297,9 +297,10 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                             const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const float x1 = acc[pi][qj][4 * q4 + e], x2 = acc[pi + 2][qj][4 * q4 + e];
-                                acc[pi][qj][4 * q4 + e] = x1 * co[e] - x2 * si[e];
-                                acc[pi + 2][qj][4 * q4 + e] = x2 * co[e] + x1 * si[e];
+                                float x1 = acc[pi][qj][4 * q4 + e], x2 = acc[pi + 2][qj][4 * q4 + e];
+                                rotate_pair(x1, x2, co[e], si[e]);
+                                acc[pi][qj][4 * q4 + e] = x1;
+                                acc[pi + 2][qj][4 * q4 + e] = x2;
                             }
                         }
                 }
@@ -664,11 +665,8 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float4 t4 = tab[e];
-                    const float a0 = x1[2 * e], b0 = x2[2 * e], a1 = x1[2 * e + 1], b1 = x2[2 * e + 1];
-                    x1[2 * e] = a0 * t4.x - b0 * t4.y;
-                    x2[2 * e] = b0 * t4.x + a0 * t4.y;
-                    x1[2 * e + 1] = a1 * t4.z - b1 * t4.w;
-                    x2[2 * e + 1] = b1 * t4.z + a1 * t4.w;
+                    rotate_pair(x1[2 * e], x2[2 * e], t4.x, t4.y);
+                    rotate_pair(x1[2 * e + 1], x2[2 * e + 1], t4.z, t4.w);
                 }
             }
             char *dst = g.kv_base + (int64_t)page * g.page_bytes + (int64_t)hk * g.part_bytes;

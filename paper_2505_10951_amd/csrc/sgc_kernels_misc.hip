@@ -150,9 +150,7 @@ __device__ inline void rope8(float x1[8], float x2[8], const float2 *tab)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float2 cs = tab[i];
-        const float a = x1[i], b = x2[i];
-        x1[i] = fmaf(a, cs.x, -(b * cs.y));       // (spelled out: every kernel that rotates a key has to round it alike)
-        x2[i] = fmaf(b, cs.x, a * cs.y);
+        rotate_pair(x1[i], x2[i], cs.x, cs.y);
     }
 }
 

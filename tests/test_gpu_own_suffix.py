@@ -80,3 +80,12 @@ def test_a_wavefront_sees_no_values_of_queries_it_has_no_rows_of(hq, hkv, suffix
             first, last = int(cu[n]) * g // 32, (int(cu[n + 1]) * g - 1) // 32      # wavefronts that hold rows of query n
             others = np.array([t for t in range(int(cu[-1])) if all(not first <= r // 32 <= last for r in range(t * g, t * g + g))], int)
             assert np.array_equal(o[others], clean[others]), n
+
+
+@pytest.mark.parametrize("hq,hkv,prefix,suffix", SHAPES)
+def test_rows_as_given_and_pages_agree_bit_for_bit(hq, hkv, prefix, suffix):
+    """Both routes round an own key alike and walk the same pages."""
+    w = workloads.custom("own_bits", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=prefix,
+                         labels=(np.arange(len(suffix)) % len(prefix)).astype(np.int32), suffix_len=np.array(suffix, np.int32), seed=3)
+    (o, lse), (op, lsep) = _run(w, "as given", sgc.SGC_KERNEL_MFMA), _run(w, "decode plan", sgc.SGC_KERNEL_MFMA)
+    assert bool((o == op).all()) and bool((lse == lsep).all())
