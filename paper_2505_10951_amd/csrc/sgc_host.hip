@@ -435,6 +435,28 @@ void build_tiles(sgc_plan *pl, int tile_rows)
         }
     }
     pl->tile_rows = tile_rows;
+    // As a row, an own key is rotated by every tile that reads it; through pages once, by a launch of its own.  Rows against pages,
+    // 8192 question tokens behind a prompt of 128, by the tiles that read a page on average (counted as if every question began a
+    // tile): 2.5 tiles 172 / 185 us (32 heads), 72.6 / 76.0 (8 KV heads, groups of 4), 115.7 / 124.1 (groups of 8); 4 tiles 188 / 201,
+    // 81.5 / 81.3, 124.7 / 128.7; 4.5 tiles 240 / 233, 89.3 / 86.5, 131.4 / 131.6; 6.5 tiles 285 / 267, 106 / 98, 148 / 145.  Longer
+    // prompts change the ratio little (2048: 4.5 tiles 597 / 601, 426 / 433, 795 / 794), except with the first product on fp8 codes,
+    // whose kernel for pages the compiler schedules 3 % worse per cached key, the rotation of a page per 512 of them: groups of 8,
+    // 12 000 tokens, 8.5 tiles 352 / 337 behind 512, 748 / 749 behind 2048, 2317 / 2414 behind 8192; 16.5 tiles 435 / 406, 830 / 812,
+    // 2463 / 2488.
+    // While all tiles run at once the launch itself counts, against 0.4 us of rotation for four pages of a tile: one question whose
+    // last tile reads 8, 12 and 16 pages 18.8 / 21.0, 21.4 / 22.8 and 23.6 / 24.4 us, 24 pages 28.9 / 28.2, 64 pages 59.1 / 57.8.
+    int64_t reads = 0, cached = 0;
+    int32_t most = 0;
+    size_t n_real = 0;
+    for (const Tile &t : pl->tiles) {
+        if (t.n_rows == 0) continue;
+        reads += t.n_own_pages;
+        cached += t.prefix_len;
+        most = std::max(most, t.n_own_pages);
+        ++n_real;
+    }
+    const int64_t pages = (int64_t)pl->spages.size() * ctx->p.n_kv_heads;
+    pl->own_rows_pay = 2 * reads < 9 * pages + (ctx->fp8_first_product ? cached / 256 : 0) || (n_real <= 512 && most <= 16);
 }
 
 // first: first page of the tile's key range inside the cluster's page list; n: pages of the range
@@ -1329,14 +1351,15 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     a.sq_page0 = pl->d_sq_page0;
     a.spages = pl->d_spages;
     // The attention kernel takes the question tokens' keys and values as they are given.  They are made into pages first where
-    // decode steps will read them, and where an output overlaps them (a tile's outputs are stored while others still read).
+    // decode steps will read them, where an output overlaps them (a tile's outputs are stored while others still read), and where
+    // that is the faster (long questions).
     const size_t kv_bytes = (size_t)pl->total_tokens * ctx->p.n_kv_heads * ctx->p.head_dim * dtype_bytes(ctx->p.io_dtype);
     const size_t o_bytes = kv_bytes / ctx->p.n_kv_heads * ctx->p.n_q_heads, lse_bytes = (size_t)pl->total_tokens * ctx->p.n_q_heads * sizeof(float);
     auto overlap = [](const void *p, size_t pn, const void *q, size_t qn) {
         const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(q);
         return p && q && a0 < b0 + qn && b0 < a0 + pn;
     };
-    const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && !overlap(dev_o, o_bytes, dev_k, kv_bytes) &&
+    const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && pl->own_rows_pay && !overlap(dev_o, o_bytes, dev_k, kv_bytes) &&
                          !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
                          !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
     a.own_raw = own_raw ? 1 : 0;

@@ -389,6 +389,7 @@ struct sgc_plan {
     std::vector<int32_t> sq_own0;             // [non-empty queries] first own page (sq_page0: first page in the pool)
     std::vector<sgc::SuffixPage> spages;      // [own pages]
     int32_t n_pool_pages = 0;                 // pages of the suffix page pool, spare ones included
+    bool own_rows_pay = false;                // own keys are cheaper read as rows than through pages (build_tiles)
     std::vector<int32_t> sq_query;            // [non-empty queries] original index of the sorted query
     std::vector<int32_t> cl_sq_off;           // [n_clusters + 1] first sorted query of each cluster
     // decode (off unless sgc_plan_enable_decode was called): pages leave room for decode_cap more tokens per

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2505_10951_amd.harness import Session, to_device, to_host_f32  # noqa: E402
-from ref_util import fp8_query_floor, oracle_caches, tight_bar  # noqa: E402
+from ref_util import fp8_query_floor, oracle_caches, oracle_suffix, tight_bar  # noqa: E402
 
 SHAPES = [
     # head groups of 4: rows of one query, of four, of five in a tile
@@ -89,3 +89,17 @@ def test_rows_as_given_and_pages_agree_bit_for_bit(hq, hkv, prefix, suffix):
                          labels=(np.arange(len(suffix)) % len(prefix)).astype(np.int32), suffix_len=np.array(suffix, np.int32), seed=3)
     (o, lse), (op, lsep) = _run(w, "as given", sgc.SGC_KERNEL_MFMA), _run(w, "decode plan", sgc.SGC_KERNEL_MFMA)
     assert bool((o == op).all()) and bool((lse == lsep).all())
+
+
+@pytest.mark.parametrize("hq,hkv,n,S", [(8, 1, 1, 256), (8, 1, 1, 257), (32, 8, 1, 900), (64, 8, 10, 112), (64, 8, 10, 113), (4, 4, 2, 1000), (8, 8, 18, 500)])
+def test_long_questions_on_both_sides_of_the_rule(hq, hkv, n, S):
+    """Own keys as rows where fewer than 4.5 tiles read a page (small launches: up to 16 pages), through pages above."""
+    w = workloads.custom("long", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[40],
+                         labels=np.zeros(n, np.int32), suffix_len=np.array([S] * n, np.int32), seed=S)
+    o, lse = _run(w, "as given", sgc.SGC_KERNEL_MFMA)
+    op, lsep = _run(w, "decode plan", sgc.SGC_KERNEL_MFMA)
+    assert bool((o == op).all()) and bool((lse == lsep).all())
+    some = [0, n - 1]
+    rows, ref, ref_lse = oracle_suffix(w, queries=sorted(set(some)))
+    bar, lse_bar = tight_bar(w, [0])
+    assert float(np.abs(o[rows] - ref).max()) <= bar and float(np.abs(lse[:, rows] - ref_lse).max()) <= max(lse_bar, 2e-2)
