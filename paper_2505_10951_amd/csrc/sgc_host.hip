@@ -170,13 +170,18 @@ int stage_wait(sgc_ctx *ctx, int i)
             if (__atomic_load_n(stage_done_words(ctx, i) + w, __ATOMIC_ACQUIRE) != ctx->stage_number[i]) return false;
         return true;
     };
-    const auto until = std::chrono::steady_clock::now() + std::chrono::seconds(2);
-    for (int spins = 0; !read(); ++spins) {
-        if (spins < 1000) continue;
-        std::this_thread::yield();
-        if (spins % 1000 == 0 && std::chrono::steady_clock::now() > until) {       // (the device is far behind)
-            SGC_HIP(ctx, hipDeviceSynchronize());
-            if (!read()) return fail(ctx, SGC_EHIP, "a staged copy did not run");
+    // Nothing but the copy is waited for (a synchronisation of the device would wait for other streams' work, which may in turn
+    // wait for this thread).  Past 20 ms the stream is far behind, and the host sleeps between two looks; sooner, a sleep of some
+    // 100 us could let the queue of a loop of small calls run dry.
+    const auto patience = std::chrono::steady_clock::now() + std::chrono::milliseconds(20);
+    bool far_behind = false;
+    for (int looks = 0; !read(); ++looks) {
+        if (looks < 1000) continue;
+        if (!far_behind) {
+            std::this_thread::yield();
+            if (looks % 1000 == 0) far_behind = std::chrono::steady_clock::now() > patience;
+        } else {
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
         }
     }
     return SGC_OK;
