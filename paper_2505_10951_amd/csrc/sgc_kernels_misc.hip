@@ -171,7 +171,11 @@ __global__ void rope_table_kernel(float2 *table, int n_pos, int half, double bas
 // its 25-35 us getting started; a kernel that reads the pinned, mapped staging buffer over the host link is done in
 // the time the link needs.
 // Up to two pieces per launch (a call's own tables and the cache's page tables, when both are due).
-constexpr int kOneGroupTiles = 256;
+// Tables and tile records that one workgroup brings to the device by itself, a launch (or two reads over the link one behind the other)
+// less; past that its own turns cost more.  One workgroup against several, us of a call: questions behind a prompt
+// of 64, 64 tiles 15.2 / 15.8, 128 16.9 / 17.2, 192 17.7 / 17.3, 256 19.6 / 18.2, 640 33.1 / 30.2; prompts' ingest and attention,
+// 104 tiles 18.2 / 19.2, 128 16.6-17.4 / 16.7, 160 18.4 / 17.9, 256 19.0-19.7 / 18.8, 416 28.3 / 25.8.
+constexpr int kOneGroupTiles = 128;
 constexpr size_t kOneGroupBytes = 32 << 10;
 typedef __attribute__((ext_vector_type(4))) uint32_t copy_u32x4;
 struct CopyPiece {

@@ -9,7 +9,7 @@ from paper_2505_10951_amd import workloads
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from paper_2505_10951_amd.harness import Session  # noqa: E402
+from paper_2505_10951_amd.harness import Session, to_device, to_host_f32  # noqa: E402
 
 
 @pytest.mark.parametrize("io,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
@@ -49,3 +49,21 @@ def test_cache_does_not_depend_on_the_other_prompts_of_the_call(io, kv, d):
             one.prefix_prefill(c)
             for x, y in zip(one.export_cluster(c)[:2], all_.export_cluster(c)[:2]):
                 assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("tokens", [1024, 1025])
+def test_tables_by_one_workgroup_and_by_several(tokens):
+    """128 tiles (8 KV heads, 64 tokens to a tile) and 136, of a prompt and of its questions."""
+    w = workloads.custom("tables", n_q_heads=16, n_kv_heads=8, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[tokens],
+                         labels=np.zeros(16, np.int32), suffix_len=np.array([64] * 15 + [tokens - 960], np.int32), seed=tokens)
+    k, v = w.prefix_kv(0)
+    ck, cv, po, _ = orc.prefix_prefill(w.prefix_q(0), k, v, w.rope_base)
+    q, sk, sv = w.suffix_qkv()
+    ref, _ = orc.suffix_prefill_batched(w.labels, w.cu_seqlens, [ck], [cv], q, sk, sv, w.rope_base)
+    with Session(w) as s:
+        s.alloc_cluster(0)
+        o, _ = s.prefix_prefill(0, with_q=True)
+        s.assign()
+        so = s.suffix_prefill(*(to_device(x, "bf16") for x in (q, sk, sv)))
+        torch.cuda.synchronize()
+        assert float(np.abs(to_host_f32(o) - po).max()) <= 2e-2 and float(np.abs(to_host_f32(so) - ref).max()) <= 2e-2
