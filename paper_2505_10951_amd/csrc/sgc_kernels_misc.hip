@@ -1422,6 +1422,8 @@ static CopyPiece copy_piece_of(void *dst, const void *mapped_src, size_t bytes)
 }
 
 // Limits: what fits the launch's arguments, and a done word for every workgroup that reads staged tables.
+static_assert(sizeof(PoolGeom) + 2 * sizeof(CopyPiece) + sizeof(CopyDone) + sizeof(ExpandArgs) + sizeof(float2 *) + 5 * 8 + 256 <= kSmallIngestOtherArgs,
+              "arguments of ingest_small_kernel beside jobs and pages");
 constexpr int kIngestThreads = 128;
 struct SmallGroups {
     int copy, expand;

@@ -1,5 +1,5 @@
-"""Prompts few and short enough that the ingest takes jobs and page ids with its launch, and the sizes just past that (thirteen jobs,
-641 pages): the cache's contents and the prompts' own attention."""
+"""Prompts few and short enough that the ingest takes jobs and page ids with its launch (twelve jobs, 670 pages), and the sizes just past
+that: the cache's contents and the prompts' own attention."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,7 @@ from paper_2505_10951_amd.harness import Session, to_device, to_host_f32  # noqa
 
 
 @pytest.mark.parametrize("io,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
-@pytest.mark.parametrize("prefix", [[1], [16, 0, 17], [5, 40, 33, 64], [3] * 12, [3] * 13, [5120, 5104, 16], [5120, 5104, 17], [512], [2000]])
+@pytest.mark.parametrize("prefix", [[1], [16, 0, 17], [5, 40, 33, 64], [3] * 12, [3] * 13, [5120, 5104, 16], [5120, 5104, 17], [5120, 5584, 16], [5120, 5584, 17], [512], [2000]])
 def test_small_and_general_ingest(io, d, prefix):
     hq, hkv = (16, 8) if prefix in ([512], [2000]) else (2, 1)      # eight heads
     w = workloads.custom("small_ingest", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rope_base=10000.0, io_dtype=io, prefix_len=prefix,
