@@ -266,8 +266,6 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
     const int32_t *pt = a.page_table + __builtin_amdgcn_readfirstlane(t.pt_off);
     const int tok_base = __builtin_amdgcn_readfirstlane(t.tok_base);
     const int last_row = t.row0 + t.n_rows - 1;
-    const int sq_lo = __builtin_amdgcn_readfirstlane(t.sq_lo), sq_hi = __builtin_amdgcn_readfirstlane(t.sq_hi);
-    const int last_qpos = __builtin_amdgcn_readfirstlane(t.last_qpos);
 
     // ---- copy machinery ----------------------------------------------------------------------------
     // A tile is 8 parts: K of its 4 pages, then V of its 4 pages; a part is 4 KiB of bf16 (2 KiB of fp8
@@ -391,7 +389,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
         tq_own0[k] = __builtin_amdgcn_readfirstlane(t.q[k].own0);
     }
     // Own keys are numbered by slots, 16 to a page, over the own pages of all queries the tile touches: page 0 is the
-    // first page of query sq_lo, and the last one holds the tile's last row's own key.
+    // first page of the tile's first query, and the last one holds the tile's last row's own key.
     const bool own = MODE == MODE_SUFFIX && !a.skip_self;
     const int own_page0 = __builtin_amdgcn_readfirstlane(t.own_page0), n_own = own ? __builtin_amdgcn_readfirstlane(t.n_own_pages) : 0;
     bool valid[MI];

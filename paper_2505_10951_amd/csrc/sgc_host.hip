@@ -595,7 +595,7 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
             pl->dtile_key0[k * kXcd + x] = key0;
         }
     pl->dtok.resize(pl->sq_len.size());
-    for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) pl->dtok[sq] = {pl->sq_query[sq], pl->sq_len[sq], (int32_t)sq, 0};
+    for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) pl->dtok[sq] = {pl->sq_query[sq], pl->sq_len[sq], 0, 0};
 }
 
 void plan_free_device(sgc_plan *pl)
@@ -950,7 +950,7 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             }
         for (; k < slots; ++k) hs[k * kXcd + x] = TileSeed{};
     }
-    // One copy for jobs, page jobs, seeds and page tables (with the event that says the staging buffer has been read); the tile records
+    // One copy for jobs, page jobs, seeds and page tables (which also says that the staging buffer has been read); the tile records
     // are then written by workgroups appended to the ingest launch, or behind the copy when nothing is ingested.
     ExpandArgs x{};
     x.seeds = d_seeds;
@@ -1178,7 +1178,7 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     pl->tok_info.clear();
     if (wide_tile) {
         pl->tok_info.resize(pl->tok_src.size());
-        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->tok_sq[i], pl->sq_own0[pl->tok_sq[i]]};
+        for (size_t i = 0; i < pl->tok_src.size(); ++i) pl->tok_info[i] = {pl->tok_src[i], pl->tok_qpos[i], pl->sq_own0[pl->tok_sq[i]], 0};
     }
     pl->row_dest.clear();      // made when a projection first asks for it
 
@@ -1233,8 +1233,9 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s, nullptr, 0, 0, expand ? &ex : nullptr)) != SGC_OK) return rc;
     pl->expand_pending = !pl->tiles.empty() && !expand;      // otherwise with the next suffix launch
     if (want_rows > 0 && pl->n_pool_pages > 0) {
-        // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps and projected keys
-        // (a plain suffix prefill reads its keys and values as they are given; held from here on so that no later call allocates it)
+        // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps, projected keys, long
+        // questions and outputs over the keys (other suffix prefills read keys and values as they are given, but whether one of those comes
+        // is not known here, and no later call should allocate)
         // (decode: one pool per layer, since the pages have to outlive the layer's suffix launch; zeroed once,
         // so that pages no token has reached yet hold finite values)
         pl->spool_layer_bytes = (size_t)pl->n_pool_pages * 2 * ctx->p.n_kv_heads * kPageTokens * ctx->p.head_dim * 2;
@@ -1351,7 +1352,6 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     a.gtiles = pl->d_gtiles;
     a.sq_src0 = pl->d_sq_src0;
     a.sq_len = pl->d_sq_len;
-    a.sq_tok0 = pl->d_sq_tok0;
     a.sq_cluster = pl->d_sq_cluster;
     a.sq_page0 = pl->d_sq_page0;
     a.spages = pl->d_spages;

@@ -161,8 +161,8 @@ struct SuffixPage {
 struct TokInfo {
     int32_t src;    // row of the token in the caller's packed arrays
     int32_t qpos;   // index of the token inside its query
-    int32_t sq;     // sorted query index
     int32_t own0;   // first own page of the query
+    int32_t unused;
 };
 
 // One cluster of a (batched) prefix prefill.
@@ -282,10 +282,9 @@ struct AttnArgs {
     const int32_t *tok_src;       // [T] row of the token in the caller's packed arrays
     const int32_t *tok_qpos;      // [T] index of the token inside its query
     const int32_t *tok_sq;        // [T] sorted query index of the token
-    const TokInfo *tok_info;      // [T] the three above in one record
+    const TokInfo *tok_info;      // [T] what the MFMA kernel needs of a token in one record
     const int32_t *sq_src0;       // [n_queries] first packed row of the query
     const int32_t *sq_len;        // [n_queries] suffix length
-    const int32_t *sq_tok0;       // [n_queries] first sorted token of the query
     const int32_t *sq_cluster;    // [n_queries]
     const int32_t *sq_page0;      // [n_queries] first page of the query in the suffix page pool
     const char *spool;            // suffix page pool (bf16 pages, same layout as cache pages) or null
