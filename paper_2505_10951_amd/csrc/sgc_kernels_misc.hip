@@ -829,7 +829,7 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
         float sum[2] = {wo * acc[gi][0], wo * acc[gi][1]};
 #pragma unroll
         for (int sp = 0; sp < kDecodeDotSplits; ++sp) {
-            if (!(lse_c[sp] > -INFINITY)) continue;
+            if (lse_c[sp] == -INFINITY) continue;          // (a range that came out NaN stays in)
             const float wc = exp2f(lse_c[sp] - M);
             denom += wc;
 #pragma unroll
@@ -1029,7 +1029,7 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (s0 + i >= S_n) break;
-            if (!(lse_c[s0 + i] > -INFINITY)) continue;        // an empty range's output means nothing
+            if (lse_c[s0 + i] == -INFINITY) continue;        // an empty range's output means nothing (one that came out NaN stays in)
             const float wc = exp2f(lse_c[s0 + i] - M);
             denom += wc;
 #pragma unroll

@@ -219,3 +219,34 @@ def test_decode_argument_checks():
         assert e.value.status == sgc.SGC_EINVAL
         s.decode_step(3, t, kv, kv)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("hq,hkv,n", [(8, 2, 3), (8, 2, 40), (32, 1, 2)])
+def test_an_infinite_cached_key_reaches_the_steps_that_see_it(hq, hkv, n):
+    """A key whose score overflows makes the rows that see it NaN, whatever key range of the step it lies in; queries of another
+    cluster and other KV heads keep their results."""
+    w = workloads.custom("inf", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=0.0, io_dtype="bf16", prefix_len=[1500, 1500],
+                         cluster_sizes=[n, n], suffix_range=(2, 5), seed=n)
+    bad_head = hkv - 1
+    dq, dk, dv = w.decode_qkv(0)
+    dq[:, :, 5] = np.abs(dq[:, :, 5])
+    out = []
+    for infinite in (False, True):
+        with Session(w, kernel=sgc.SGC_KERNEL_MFMA) as s:
+            for c in range(2):
+                k, v = w.prefix_kv(c)
+                k = k.copy()
+                if infinite and c == 1:
+                    k[700, bad_head, 5] = np.inf
+                s.alloc_cluster(c)
+                s.prefix_prefill(c, k=k, v=v)
+            s.assign()
+            s.enable_decode(2)
+            s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
+            o = s.decode_step(0, *(to_device(x, "bf16") for x in (dq, dk, dv)))
+            torch.cuda.synchronize()
+            out.append(to_host_f32(o))
+    g = hq // hkv
+    hit = np.zeros(out[0].shape, bool)
+    hit[w.labels == 1, bad_head * g:(bad_head + 1) * g] = True
+    assert np.isnan(out[1][hit]).all() and np.array_equal(out[0][~hit], out[1][~hit])
