@@ -213,7 +213,9 @@ int sgc_plan_destroy(sgc_plan *plan);
  * One launch for every query of every cluster in the plan, one layer.
  * dev_q, dev_o: [T][Hq][d]; dev_k, dev_v: [T][Hkv][d]; packed in original query order by
  * cu_seqlens; before rotation.  dev_lse (may be NULL): [Hq][T] fp32, natural log.
- * o rows are written for every token of every query; nothing else is touched. */
+ * o rows are written for every token of every query; nothing else is touched.
+ * A query's outputs do not depend on queries of other clusters.  With the matrix-core kernel their last bits follow from the
+ * queries of its own cluster in the plan, whose tokens share its softmax steps. */
 int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cache, sgc_plan *plan, int32_t layer,
                                const void *dev_q, const void *dev_k, const void *dev_v,
                                void *dev_o, float *dev_lse, void *hip_stream);

@@ -82,12 +82,13 @@ def test_a_wavefront_sees_no_values_of_queries_it_has_no_rows_of(hq, hkv, suffix
             assert np.array_equal(o[others], clean[others]), n
 
 
+@pytest.mark.parametrize("kv,kernel", [("bf16", sgc.SGC_KERNEL_MFMA), ("fp8_e4m3", sgc.SGC_KERNEL_MFMA), ("fp8_e4m3", sgc.SGC_KERNEL_MFMA_FP8)])
 @pytest.mark.parametrize("hq,hkv,prefix,suffix", SHAPES)
-def test_rows_as_given_and_pages_agree_bit_for_bit(hq, hkv, prefix, suffix):
+def test_rows_as_given_and_pages_agree_bit_for_bit(hq, hkv, prefix, suffix, kv, kernel):
     """Both routes round an own key alike and walk the same pages."""
-    w = workloads.custom("own_bits", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=prefix,
+    w = workloads.custom("own_bits", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", kv_dtype=kv, prefix_len=prefix,
                          labels=(np.arange(len(suffix)) % len(prefix)).astype(np.int32), suffix_len=np.array(suffix, np.int32), seed=3)
-    (o, lse), (op, lsep) = _run(w, "as given", sgc.SGC_KERNEL_MFMA), _run(w, "decode plan", sgc.SGC_KERNEL_MFMA)
+    (o, lse), (op, lsep) = _run(w, "as given", kernel), _run(w, "decode plan", kernel)
     assert bool((o == op).all()) and bool((lse == lsep).all())
 
 
