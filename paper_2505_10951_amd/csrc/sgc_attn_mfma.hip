@@ -1331,10 +1331,14 @@ hipError_t launch_few(const AttnArgs &a, hipStream_t s)
 
 // Where it is the faster: tiles of one row group (with four, whose keys it reads four times, 64 queries over 3001 tokens take 35.1
 // against 23.9 us), and at most 16 of them on an XCD: its workgroups take a compute unit each, and what shares the chip evenly anyway
-// gains nothing (16 prompts of 200 tokens 19.1 -> 17.3 us; of 1000 tokens, in 256 tiles, 29.8 against 27.5).
+// gains nothing (16 prompts of 200 tokens 19.1 -> 17.3 us; of 1000 tokens, in 256 tiles, 29.8 against 27.5); and, with more than
+// 128 rows in all, some tile with more than one 64-key step: a single one costs less than the merge (prompts of 64 tokens, 16 of one
+// query each 15.3 against 14.4 us, 6 queries of 32 heads without groups 16.5 against 15.8, but one query 11.9 against 13.5; of 65 tokens
+// never slower).
 bool few_rows(const AttnArgs &a)
 {
-    return a.mode == MODE_SUFFIX && a.skip_self && a.n_tiles > 0 && a.n_tiles <= 128 && a.tile_groups == 1 && a.pool.kv_dtype != SGC_FP8_E4M3;
+    return a.mode == MODE_SUFFIX && a.skip_self && a.n_tiles > 0 && a.n_tiles <= 128 && a.tile_groups == 1 && (a.tile_keys > BN || a.n_append * a.n_q_heads <= 128) &&
+           a.pool.kv_dtype != SGC_FP8_E4M3;
 }
 
 }  // namespace

@@ -1170,7 +1170,11 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
             for (int64_t r = 0; r < (pl->cl_tok_off[k + 1] - pl->cl_tok_off[k]) * g; r += kGenericRows) pl->gtiles.push_back({k, (int32_t)r});
     }
     int32_t most_rows = 1;
-    for (const Tile &t : pl->dtiles) most_rows = std::max(most_rows, t.n_rows);
+    pl->dtile_keys = 0;
+    for (const Tile &t : pl->dtiles) {
+        most_rows = std::max(most_rows, t.n_rows);
+        pl->dtile_keys = std::max(pl->dtile_keys, t.prefix_len);
+    }
     pl->dtile_groups = (most_rows + 31) / 32;
     // The per-token records are only read by tiles that touch more queries than their own record describes.
     bool wide_tile = false;
@@ -1534,6 +1538,7 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     a.tiles = pl->d_dtiles;
     a.n_tiles = (int32_t)pl->dtiles.size();
     a.tile_groups = pl->dtile_groups;
+    a.tile_keys = pl->dtile_keys;
     a.tok_info = pl->d_dtok;
     a.sq_len = pl->d_sq_len;
     a.sq_page0 = pl->d_sq_page0;

@@ -275,7 +275,8 @@ struct AttnArgs {
     const float2 *rope;           // [rope_len][d/2] (cos, sin) or null when rotation is off
     const Tile *tiles;
     int32_t n_tiles;              // a multiple of 8: the XCDs' shorter lists are filled up with padding tiles
-    int32_t tile_groups;          // decode: 32-row groups of the largest tile
+    int32_t tile_groups;          // decode: 32-row groups of the largest tile ...
+    int32_t tile_keys;            // ... and the most cached keys of a tile
     // suffix mode: sorted-token and sorted-query tables (sorted = grouped by cluster; queries
     // without tokens are left out of the query tables)
     const int32_t *cl_tok_off;    // [n_clusters + 1] first sorted token of each cluster
@@ -396,7 +397,8 @@ struct sgc_plan {
     int32_t decode_cap = 0;
     std::vector<sgc::Tile> dtiles;
     std::vector<int32_t> dtile_key0;          // first cached key of each decode tile's key range
-    int32_t dtile_groups = 4;                 // 32-row groups of the largest decode tile
+    int32_t dtile_groups = 4;                 // 32-row groups of the largest decode tile ...
+    int32_t dtile_keys = 0;                   // ... and the most cached keys of one
     int32_t dec_splits = 1;                   // key ranges per row tile
     std::vector<sgc::TokInfo> dtok;
     size_t spool_layer_bytes = 0;

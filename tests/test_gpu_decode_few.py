@@ -1,6 +1,6 @@
 """Decode steps of few rows: a workgroup has one group of 32 rows and its eight wavefronts share the cached keys.  Sizes around a
 wavefront's 32 keys, a page of 16 and the eight wavefronts' 256; up to 32 rows, and above that the 128-row workgroups; up to 128
-tiles and above."""
+tiles and above; cached keys past 64 or up to 128 rows in all, and otherwise the 128-row workgroups."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,7 @@ from test_gpu_decode import TOL, _oracle_decode, _run_decode
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("prefix", [[1, 15], [31, 33], [255, 256], [257, 300], [2000, 1]])
+@pytest.mark.parametrize("prefix", [[1, 15], [31, 33], [64, 65], [66, 1], [97, 95], [255, 256], [257, 300], [2000, 1]])
 @pytest.mark.parametrize("hq,hkv,per", [(8, 2, 1), (8, 2, 8), (8, 2, 9), (8, 1, 4), (32, 32, 3), (160, 80, 16)])
 def test_rows_and_keys_around_a_wavefront(hq, hkv, per, prefix):
     """(80 heads of two clusters: 160 tiles)"""
