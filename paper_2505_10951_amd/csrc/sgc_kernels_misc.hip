@@ -171,11 +171,12 @@ __global__ void rope_table_kernel(float2 *table, int n_pos, int half, double bas
 // its 25-35 us getting started; a kernel that reads the pinned, mapped staging buffer over the host link is done in
 // the time the link needs.
 // Up to two pieces per launch (a call's own tables and the cache's page tables, when both are due).
-// Tables and tile records that one workgroup brings to the device by itself, a launch (or two reads over the link one behind the other)
-// less; past that its own turns cost more.  One workgroup against several, us of a call: questions behind a prompt
-// of 64, 64 tiles 15.2 / 15.8, 128 16.9 / 17.2, 192 17.7 / 17.3, 256 19.6 / 18.2, 640 33.1 / 30.2; prompts' ingest and attention,
-// 104 tiles 18.2 / 19.2, 128 16.6-17.4 / 16.7, 160 18.4 / 17.9, 256 19.0-19.7 / 18.8, 416 28.3 / 25.8.
-constexpr int kOneGroupTiles = 128;
+// Tables and tile records that one workgroup brings to the device by itself; past that its own turns cost more.  Beside an ingest (two
+// reads over the link one behind the other less), one workgroup against several, us of a prompts' call: 104 tiles 18.2 / 19.2, 128
+// 16.6-17.4 / 16.7, 160 18.4 / 17.9, 256 19.0-19.7 / 18.8, 416 28.3 / 25.8.  As a launch of its own (one less): 64 tiles 15.2 / 15.8,
+// 128 16.9 / 17.2, 192 17.7 / 17.3, 256 19.6 / 18.2, 640 33.1 / 30.2; but the host, which bounds passes this small, has 2 to 3 us less
+// to do (a whole pass with 200 tiles 50.5 / 52.2), so there the line lies past the crossover.
+constexpr int kOneGroupTiles = 128, kOneLaunchTiles = 256;
 constexpr size_t kOneGroupBytes = 32 << 10;
 typedef __attribute__((ext_vector_type(4))) uint32_t copy_u32x4;
 struct CopyPiece {
@@ -1523,7 +1524,7 @@ hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes
     *n_words = 0;
     if (bytes == 0 && bytes2 == 0) return expand ? launch_expand_tiles(*expand, s) : hipSuccess;
     const CopyPiece a = copy_piece_of(dst, mapped_src, bytes), b = copy_piece_of(dst2, mapped_src2, bytes2);
-    if (expand && expand->n > 0 && expand->n <= kOneGroupTiles && bytes + bytes2 <= kOneGroupBytes) {
+    if (expand && expand->n > 0 && expand->n <= kOneLaunchTiles && bytes + bytes2 <= kOneGroupBytes) {
         *n_words = 1;
         hipLaunchKernelGGL(copy_and_expand_kernel, dim3(1), dim3(1024), 0, s, a, b, done, *expand);
         return hipGetLastError();

@@ -51,9 +51,9 @@ def test_cache_does_not_depend_on_the_other_prompts_of_the_call(io, kv, d):
                 assert np.array_equal(x, y)
 
 
-@pytest.mark.parametrize("tokens", [1024, 1025])
+@pytest.mark.parametrize("tokens", [1024, 1025, 2048, 2049])
 def test_tables_by_one_workgroup_and_by_several(tokens):
-    """128 tiles (8 KV heads, 64 tokens to a tile) and 136, of a prompt and of its questions."""
+    """128 and 256 tiles (8 KV heads, 64 tokens to a tile) and 8 more, of a prompt and of its questions."""
     w = workloads.custom("tables", n_q_heads=16, n_kv_heads=8, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[tokens],
                          labels=np.zeros(16, np.int32), suffix_len=np.array([64] * 15 + [tokens - 960], np.int32), seed=tokens)
     k, v = w.prefix_kv(0)
