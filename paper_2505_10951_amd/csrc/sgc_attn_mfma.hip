@@ -510,8 +510,8 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
                     x2[2 * i] = b0;
                     x1[2 * i + 1] = a1;
                     x2[2 * i + 1] = b1;
-                    rotate_pair(x1[2 * i], x2[2 * i], t4.x, t4.y);
-                    rotate_pair(x1[2 * i + 1], x2[2 * i + 1], t4.z, t4.w);
+                    rotate_sums(x1[2 * i], x2[2 * i], t4.x, t4.y);
+                    rotate_sums(x1[2 * i + 1], x2[2 * i + 1], t4.z, t4.w);
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {      // the score scale (log2 units, cached-K scale included) rides on Q
@@ -1167,8 +1167,8 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
                 float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
                 float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
                 const float4 t4 = cs[kb][i];
-                rotate_pair(a0, b0, t4.x, t4.y);
-                rotate_pair(a1, b1, t4.z, t4.w);
+                rotate_sums(a0, b0, t4.x, t4.y);
+                rotate_sums(a1, b1, t4.z, t4.w);
                 qf[kb][2 * i] = (_Float16)(a0 * a.scale_log2e);
                 qf[kb][2 * i + 1] = (_Float16)(a1 * a.scale_log2e);
                 qf[kb + 4][2 * i] = (_Float16)(b0 * a.scale_log2e);
