@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "sgc_internal.h"
+#include "sgc_own_keys.h"
 
 namespace sgc {
 
@@ -1086,27 +1087,49 @@ hipError_t launch_one(const AttnArgs &a, int blocks, hipStream_t s)
 }
 
 // ---- decode steps of few rows ----------------------------------------------------------------------------------
-// The cached part of a decode step has few rows: its tiles are key ranges of row tiles with, often, one row group of 32, for which
-// three of four wavefronts of the kernel above compute nothing, and the one takes about a microsecond a 64-key step: a wavefront
-// alone on its SIMD is bound by issue, and deeper rings of K and V changed nothing.  Here a workgroup has 32 rows, and its wavefronts
-// deal the range's 32-key halves among themselves and merge their softmax states once through LDS.  A wavefront keeps its half's K
-// and V in 16 KiB of LDS of its own: no barrier but the merge's.  The next half is requested as soon as this one's operands are in
-// registers.  A step with its launches (32 query heads, 8 KV heads), one query 17.4 -> 14.4 us over 200 tokens, 29.5 -> 24.8 over
-// 9000; five queries over 3001 tokens 22.9 -> 19.4.
+// A decode step of few rows per cluster is latency: its tiles are key ranges of row tiles with one row group of 32, for which three of
+// four wavefronts of the kernel above compute nothing, and the one takes about a microsecond a 64-key step.  Here a workgroup has
+// the row tile's up to 32 rows, and its wavefronts deal the range's 32-key halves (units) among themselves, each with 16 KiB of LDS of its own
+// for its half's K and V: no barrier but the merge's.  The next unit is requested as soon as this one's operands are in registers.
+// Some of the wavefronts attend over the queries' own keys meanwhile, put the step's new token into its page on the way, and the last of a row
+// tile's ranges to finish adds the ranges up: the whole step is one launch.  As two (cached part; own keys and sums) it took, us
+// with their launches (32 query heads, 8 KV heads): 5 queries over 3001 keys 19.3, now 14.7; one over 9000 24.0 -> 14.0; 16 over a prompt of 1000
+// each 26.0 -> 16.9; 5 without head groups over 500 17.8 -> 11.0.
 // (Suffix prefills over few rows gain as much, but their rows' sums would then follow from the other clusters of the call, and a
 // cluster served by itself would no longer equal the same cluster in a batch bit for bit.  A step's ranges follow from the call
 // as it is.)
 constexpr int NWF = 8;        // wavefronts of a workgroup
 
+// Memory that workgroups of one launch hand to each other: stored through to and loaded from the level that all XCDs share (agent-scope
+// accesses).  A release and an acquire fence instead write back and invalidate a whole XCD's L2, under the other workgroups' reads
+// of the cache: 16 prompts of 1000 tokens in two ranges 27 us a step.
+template <typename T>
+__device__ __forceinline__ void store_shared(T *p, const T &v)
+{
+    static_assert(sizeof(T) % 8 == 0, "eight bytes at a time");
+    uint64_t w[sizeof(T) / 8];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) __hip_atomic_store(reinterpret_cast<uint64_t *>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T load_shared(const T *p)
+{
+    uint64_t w[sizeof(T) / 8];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
 __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
 {
-    if ((int)blockIdx.x >= a.n_tiles) {
-        append_new_tokens(a, (int)blockIdx.x - a.n_tiles);
-        return;
-    }
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     constexpr int SLOT = 4 * PART_BYTES;        // a wavefront's K (two pages), then V; later its 32 x 128 partial outputs
-    float2 *const stats = reinterpret_cast<float2 *>(smem + NWF * SLOT);      // [wavefront][row]: reference maximum, row sum
+    // behind the wavefronts' slots one for the rows' own keys, then [slot][row]: reference maximum, row sum
+    char *const own_slot = smem + NWF * SLOT;
+    float2 *const stats = reinterpret_cast<float2 *>(smem + (NWF + 1) * SLOT);
 
     const int wave_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 31, h = lane >> 5;
@@ -1116,14 +1139,13 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
     const Tile t = uniform_record(a.tiles + blockIdx.x);
     asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad));
     if (t.n_rows == 0) return;
-    void *const o_base = static_cast<char *>(a.o) + (t.pad >> 24) * a.split_o_bytes;
-    float *const lse_base = a.lse ? a.lse + (t.pad >> 24) * a.split_lse_elems : nullptr;
     const int P = t.prefix_len, n_pages = (P + kPageTokens - 1) / kPageTokens;
-    const int row0 = t.row0, last_row = t.row0 + t.n_rows - 1;         // (32 rows at most)
+    const int range = t.pad >> 24, all_cached = P + (t.pad & 0xFFFFFF);
+    const int last_row = t.n_rows - 1;         // (a unit's rows are one tile of 32 at most: row0 is 0)
 
     // ---- the lane's row (rows past the end repeat the last one) ----
-    const bool valid = row0 + n <= last_row;
-    const int rc = min(row0 + n, last_row), tk = rc / g, head = t.hk * g + (rc - tk * g);
+    const bool valid = n <= last_row;
+    const int rc = min(n, last_row), tk = rc / g, head = t.hk * g + (rc - tk * g);
     const TokInfo ti = a.tok_info[t.tok_base + tk];
     const int qpos = ti.qpos, src_tok = ti.src;
     const int64_t io_row = ((int64_t)src_tok * Hq + head) * D;
@@ -1132,165 +1154,235 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
     // ---- K and V of a unit, half a 64-key tile, on their way to the wavefront's slot ----
     const char *cache_base = a.pool.pool + (int64_t)a.layer * a.pool.layer_bytes + (int64_t)t.hk * a.pool.head_part_bytes + lane * 16;
     const int32_t *pt = a.page_table + t.pt_off;
-    auto copy_unit = [&](int u) __attribute__((always_inline)) {
+    // Own keys, below: 16 heads of a query are a task; task k belongs to range k % ranges.  A range's tasks have wavefronts of their own:
+    // a task is a longer chain of round trips than a unit, as many of them as own_cost2 says in halves.
+    const int S = a.n_ranges, halves = (g + 15) / 16, n_tasks = t.n_rows / g * halves;
+    const int tasks_here = n_tasks > range ? (n_tasks - range + S - 1) / S : 0, own_load = a.own_cost2 * tasks_here, own_share = (NWF * own_load + own_load / 2) / max(own_load + 2 * n_units, 1);
+    const int own_waves = tasks_here > 0 ? min(tasks_here, max(1, min(own_share, n_units > 0 ? NWF - 1 : NWF))) : 0, unit_waves = NWF - own_waves;
+    const int my_first = wave_u < unit_waves ? wave_u : n_units;
+    // (the first units' pages come with the tile record)
+    int pg_first0 = 0, pg_first1 = 0;
+#pragma unroll
+    for (int w = 0; w < 6; ++w)
+        if (wave_u == w) {
+            pg_first0 = t.first_pages[2 * w];
+            pg_first1 = t.first_pages[2 * w + 1];
+        }
+    auto copy_unit = [&](int u, bool first) __attribute__((always_inline)) {
         if (u >= n_units) return;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             // (a page past the last is the last one again: its keys are masked)
-            const char *src = cache_base + (int64_t)uniform_record(pt + min(2 * u + i, n_pages - 1)) * a.pool.page_bytes;
+            const int page = first ? (i ? pg_first1 : pg_first0) : uniform_record(pt + min(2 * u + i, n_pages - 1));
+            const char *src = cache_base + (int64_t)page * a.pool.page_bytes;
             copy_4k_to_lds(src, slot + i * PART_BYTES);
             copy_4k_to_lds(src + Hkv * a.pool.head_part_bytes, slot + (2 + i) * PART_BYTES);
         }
     };
-    copy_unit(wave_u);
+    copy_unit(my_first, wave_u < 6);
 
-    // ---- Q: rotated and scaled, as operands ----
-    f16x8 qf[8];
-    {
-        float4 cs[4][4];
-        uint4 qlo[4], qhi[4];
-        const int pos = P + (t.pad & 0xFFFFFF) + a.pos_shift + qpos;
-        const uint16_t *qrow = static_cast<const uint16_t *>(a.q) + io_row + h * 8;
+    if (wave_u >= unit_waves) {
+        // ---- own keys; their rows go into a slot that all tasks of the workgroup share ----
+        for (int k = range + (NWF - 1 - wave_u) * S; k < n_tasks; k += own_waves * S) {
+            const int qi = k / halves, h0 = (k - qi * halves) * 16, j = lane & 15, quad = lane >> 4;
+            const int sq = t.tok_base + qi;
+            const TokInfo own_ti = uniform_record(a.tok_info + sq);
+            const bool live = h0 + j < g;
+            const int64_t part = PART_BYTES, kv_row = ((int64_t)own_ti.src * Hkv + t.hk) * D;
+            OwnKeys w{};
+            w.page_stride = 2 * Hkv * part;
+            w.pages = const_cast<char *>(a.spool) + own_ti.own0 * w.page_stride + t.hk * part;
+            w.v_part = Hkv * part;
+            w.n_keys = own_ti.qpos + a.pos_shift + 1;
+            w.q = static_cast<const uint16_t *>(a.q) + ((int64_t)own_ti.src * Hq + t.hk * g + (live ? h0 + j : 0)) * D;
+            w.scale = live ? a.scale_log2e : 0.f;
+            w.rope = a.rope ? a.rope + (int64_t)(all_cached + w.n_keys - 1) * (D / 2) : nullptr;
+            w.k_new = static_cast<const uint16_t *>(a.k) + kv_row;
+            w.v_new = static_cast<const uint16_t *>(a.v) + kv_row;
+            w.append = h0 == 0;
+            dec_f32x4 O[8];
+            float m, l;
+            own_keys_attend<true, 2, true>(w, O, m, l);
+            const int row = qi * g + h0 + j;
+            if (live) {
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            qlo[kb] = *reinterpret_cast<const uint4 *>(qrow + kb * 16);
-            qhi[kb] = *reinterpret_cast<const uint4 *>(qrow + 64 + kb * 16);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                cs[kb][i] = a.rope ? reinterpret_cast<const float4 *>(a.rope + (int64_t)pos * (D / 2) + kb * 16 + h * 8)[i] : make_float4(1.f, 0.f, 1.f, 0.f);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            const uint32_t wl[4] = {qlo[kb].x, qlo[kb].y, qlo[kb].z, qlo[kb].w}, wh[4] = {qhi[kb].x, qhi[kb].y, qhi[kb].z, qhi[kb].w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
-                float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
-                const float4 t4 = cs[kb][i];
-                rotate_sums(a0, b0, t4.x, t4.y);
-                rotate_sums(a1, b1, t4.z, t4.w);
-                qf[kb][2 * i] = (_Float16)(a0 * a.scale_log2e);
-                qf[kb][2 * i + 1] = (_Float16)(a1 * a.scale_log2e);
-                qf[kb + 4][2 * i] = (_Float16)(b0 * a.scale_log2e);
-                qf[kb + 4][2 * i + 1] = (_Float16)(b1 * a.scale_log2e);
+                for (int cb = 0; cb < 8; ++cb)
+                    *reinterpret_cast<float4 *>(own_slot + row * 512 + (((4 * cb + quad) ^ row) * 16)) = make_float4(O[cb][0], O[cb][1], O[cb][2], O[cb][3]);
+                if (quad == 0) stats[NWF * 32 + row] = make_float2(m, l);
             }
         }
-    }
-
-    // ---- the wavefront's units: online softmax as in the kernel above ----
-    f32x16 oacc[4], neg_ref;
-    float m_ref = 0.f, l_part = 0.f;
-    bool seen = false, fresh = true;          // fresh: some row of the wavefront has met no key yet
+    } else {
+        // ---- Q: rotated and scaled, as operands ----
+        f16x8 qf[8];
+        {
+            float4 cs[4][4];
+            uint4 qlo[4], qhi[4];
+            const int pos = all_cached + a.pos_shift + qpos;
+            const uint16_t *qrow = static_cast<const uint16_t *>(a.q) + io_row + h * 8;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        neg_ref[r] = 0.f;
+            for (int kb = 0; kb < 4; ++kb) {
+                qlo[kb] = *reinterpret_cast<const uint4 *>(qrow + kb * 16);
+                qhi[kb] = *reinterpret_cast<const uint4 *>(qrow + 64 + kb * 16);
 #pragma unroll
-        for (int db = 0; db < 4; ++db) oacc[db][r] = 0.f;
-    }
-    const int lane_koff = (n >> 4) * PART_BYTES + (h * kPageTokens + (n & 15)) * 16;
-    for (int u = wave_u; u < n_units; u += NWF) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the unit has landed (and what waits here is this wavefront's own)
-        bf16x8 kf[8], vf[8];
+                for (int i = 0; i < 4; ++i)
+                    cs[kb][i] = a.rope ? reinterpret_cast<const float4 *>(a.rope + (int64_t)pos * (D / 2) + kb * 16 + h * 8)[i] : make_float4(1.f, 0.f, 1.f, 0.f);
+            }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) kf[i] = *reinterpret_cast<const bf16x8 *>(slot + lane_koff + i * 512);
+            for (int kb = 0; kb < 4; ++kb) {
+                const uint32_t wl[4] = {qlo[kb].x, qlo[kb].y, qlo[kb].z, qlo[kb].w}, wh[4] = {qhi[kb].x, qhi[kb].y, qhi[kb].z, qhi[kb].w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) vf[i] = *reinterpret_cast<const bf16x8 *>(slot + 2 * PART_BYTES + lane * 16 + i * 1024);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // operands are in registers: the slot takes the next unit
-        copy_unit(u + NWF);
-
-        f32x16 s = neg_ref;
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, kf[kb]), qf[kb], s, 0, 0, 0);
-        const bool masked = 32 * u + 32 > P, first = u == wave_u;
-        if (masked) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (32 * u + 8 * (r >> 2) + 4 * h + (r & 3) >= P) s[r] = -INFINITY;
-        }
-        uint32_t pf[2][4];
-        float psum;
-        auto raise_reference = [&]() __attribute__((always_inline)) {
-            float tmax = s[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
-            tmax = half_max(tmax);
-            const bool has = tmax > -INFINITY;          // (a unit whose scores are all -inf leaves the row as it was)
-            const float delta = seen ? fmaxf(tmax, 0.f) : (has ? tmax : 0.f);
-            if (__any(delta != 0.f)) {
-                m_ref += delta;
-                if (!first) {                           // (nothing is accumulated before a wavefront's first unit)
-                    const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 1.0f;
-                    l_part *= alpha;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-#pragma unroll
-                        for (int db = 0; db < 4; ++db) oacc[db][r] *= alpha;
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    s[r] -= delta;
-                    neg_ref[r] = -m_ref;
+                for (int i = 0; i < 4; ++i) {
+                    float a0 = __uint_as_float(wl[i] << 16), a1 = __uint_as_float(wl[i] & 0xFFFF0000u);
+                    float b0 = __uint_as_float(wh[i] << 16), b1 = __uint_as_float(wh[i] & 0xFFFF0000u);
+                    const float4 t4 = cs[kb][i];
+                    rotate_sums(a0, b0, t4.x, t4.y);
+                    rotate_sums(a1, b1, t4.z, t4.w);
+                    qf[kb][2 * i] = (_Float16)(a0 * a.scale_log2e);
+                    qf[kb][2 * i + 1] = (_Float16)(a1 * a.scale_log2e);
+                    qf[kb + 4][2 * i] = (_Float16)(b0 * a.scale_log2e);
+                    qf[kb + 4][2 * i + 1] = (_Float16)(b1 * a.scale_log2e);
                 }
             }
-            seen = seen || has;
-            fresh = __any(!seen);
-        };
-        auto weights = [&]() __attribute__((always_inline)) {
-            bf16x2 ones;
-            ones[0] = (__bf16)1.0f;
-            ones[1] = (__bf16)1.0f;
-            psum = 0.f;
+        }
+
+        // ---- the wavefront's units: online softmax as in the kernel above ----
+        f32x16 oacc[4], neg_ref;
+        float m_ref = 0.f, l_part = 0.f;
+        bool seen = false, fresh = true;          // fresh: some row of the wavefront has met no key yet
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                bf16x2 pk;
-                pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[r]);
-                pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[r + 1]);
-                psum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, psum, false);
-                pf[r >> 3][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
+        for (int r = 0; r < 16; ++r) {
+            neg_ref[r] = 0.f;
+#pragma unroll
+            for (int db = 0; db < 4; ++db) oacc[db][r] = 0.f;
+        }
+        const int lane_koff = (n >> 4) * PART_BYTES + (h * kPageTokens + (n & 15)) * 16;
+        for (int u = my_first; u < n_units; u += unit_waves) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the unit has landed (and what waits here is this wavefront's own)
+            bf16x8 kf[8], vf[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) kf[i] = *reinterpret_cast<const bf16x8 *>(slot + lane_koff + i * 512);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vf[i] = *reinterpret_cast<const bf16x8 *>(slot + 2 * PART_BYTES + lane * 16 + i * 1024);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // operands are in registers: the slot takes the next unit
+            copy_unit(u + unit_waves, false);
+
+            f32x16 s = neg_ref;
+#pragma unroll
+            for (int kb = 0; kb < 8; ++kb) s = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, kf[kb]), qf[kb], s, 0, 0, 0);
+            const bool masked = 32 * u + 32 > P, first = u == my_first;
+            if (masked) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (32 * u + 8 * (r >> 2) + 4 * h + (r & 3) >= P) s[r] = -INFINITY;
             }
-        };
-        const bool careful = masked || fresh;
-        if (careful) raise_reference();
-        weights();
-        if (!careful && __any(!(psum <= kKeepBelow))) {
-            raise_reference();
+            uint32_t pf[2][4];
+            float psum;
+            auto raise_reference = [&]() __attribute__((always_inline)) {
+                float tmax = s[0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
+                tmax = half_max(tmax);
+                const bool has = tmax > -INFINITY;          // (a unit whose scores are all -inf leaves the row as it was)
+                const float delta = seen ? fmaxf(tmax, 0.f) : (has ? tmax : 0.f);
+                if (__any(delta != 0.f)) {
+                    m_ref += delta;
+                    if (!first) {                           // (nothing is accumulated before a wavefront's first unit)
+                        const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 1.0f;
+                        l_part *= alpha;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+#pragma unroll
+                            for (int db = 0; db < 4; ++db) oacc[db][r] *= alpha;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        s[r] -= delta;
+                        neg_ref[r] = -m_ref;
+                    }
+                }
+                seen = seen || has;
+                fresh = __any(!seen);
+            };
+            auto weights = [&]() __attribute__((always_inline)) {
+                bf16x2 ones;
+                ones[0] = (__bf16)1.0f;
+                ones[1] = (__bf16)1.0f;
+                psum = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) {
+                    bf16x2 pk;
+                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[r]);
+                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[r + 1]);
+                    psum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, psum, false);
+                    pf[r >> 3][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
+                }
+            };
+            const bool careful = masked || fresh;
+            if (careful) raise_reference();
             weights();
-        }
-        l_part += psum;
+            if (!careful && __any(!(psum <= kKeepBelow))) {
+                raise_reference();
+                weights();
+            }
+            l_part += psum;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const u32x4 w = {pf[i >> 2][0], pf[i >> 2][1], pf[i >> 2][2], pf[i >> 2][3]};
-            oacc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], __builtin_bit_cast(bf16x8, w), oacc[i & 3], 0, 0, 0);
+            for (int i = 0; i < 8; ++i) {
+                const u32x4 w = {pf[i >> 2][0], pf[i >> 2][1], pf[i >> 2][2], pf[i >> 2][3]};
+                oacc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], __builtin_bit_cast(bf16x8, w), oacc[i & 3], 0, 0, 0);
+            }
+        }
+
+        // ---- partial outputs into the slots: 16-byte chunk c of row n at place c ^ n ----
+        {
+            const float l = half_sum(l_part);
+            if (h == 0) stats[wave_u * 32 + n] = make_float2(seen ? m_ref : -INFINITY, l);
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *reinterpret_cast<float4 *>(slot + n * 512 + (((db * 8 + 2 * q4 + h) ^ n) * 16)) =
+                        make_float4(oacc[db][q4 * 4], oacc[db][q4 * 4 + 1], oacc[db][q4 * 4 + 2], oacc[db][q4 * 4 + 3]);
         }
     }
 
-    // ---- merge: partial outputs into the slots (16-byte chunk c of row n at place c ^ n), then every thread a few chunks ----
-    {
-        const float l = half_sum(l_part);
-        if (h == 0) stats[wave_u * 32 + n] = make_float2(seen ? m_ref : -INFINITY, l);
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                *reinterpret_cast<float4 *>(slot + n * 512 + (((db * 8 + 2 * q4 + h) ^ n) * 16)) =
-                    make_float4(oacc[db][q4 * 4], oacc[db][q4 * 4 + 1], oacc[db][q4 * 4 + 2], oacc[db][q4 * 4 + 3]);
-    }
+    // ---- merge: every thread a few chunks ----
+    // A part that saw no key of a row has reference -inf and sum 0 and is left out; with a sum that is NaN it counts, and so does the NaN.
+    auto part_weight = [](const float2 &st, float M) __attribute__((always_inline)) { return st.x > -INFINITY ? __builtin_amdgcn_exp2f(st.x - M) : st.y; };
+    auto finish = [&](int row, int c, float M, float L, const float4 &sum) __attribute__((always_inline)) {
+        const float inv = 1.0f / L;
+        const int64_t at = __shfl(io_row, row);
+        const int r_head = __shfl(head, row), r_tok = __shfl(src_tok, row);
+        if (row <= last_row) {
+            bf16x4 y;
+            y[0] = (__bf16)(sum.x * inv);
+            y[1] = (__bf16)(sum.y * inv);
+            y[2] = (__bf16)(sum.z * inv);
+            y[3] = (__bf16)(sum.w * inv);
+            *reinterpret_cast<bf16x4 *>(static_cast<uint16_t *>(a.o) + at + c * 4) = y;
+            if (a.lse && c == 0) a.lse[(int64_t)r_head * a.lse_stride + r_tok] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+        }
+    };
+    float4 *const parts = reinterpret_cast<float4 *>(a.parts + (int64_t)t.row_tile * S * kFewPartBytes);      // [range][row][chunk], then ...
+    float2 *const part_stats = reinterpret_cast<float2 *>(parts + (int64_t)S * 32 * 32);                     // ... [range][row]
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16 / NWF; ++k) {
         const int row = ((int)threadIdx.x >> 5) + k * 2 * NWF, c = lane & 31;
-        float2 st[NWF];
+        const int qi = row / g, task = qi * halves + (row - qi * g) / 16;
+        const bool own_here = row <= last_row && task % S == range;      // the shared slot holds the row's own keys
+        float2 st[NWF + 1];
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < NWF; ++w) {
-            st[w] = stats[w * 32 + row];
+        for (int w = 0; w <= NWF; ++w) {
+            st[w] = (w < NWF ? w < unit_waves : own_here) ? stats[w * 32 + row] : make_float2(-INFINITY, 0.f);
             M = fmaxf(M, st[w].x);
         }
         float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < NWF; ++w) {
-            const float f = st[w].x > -INFINITY ? __builtin_amdgcn_exp2f(st[w].x - M) : 0.f;
+        for (int w = 0; w <= NWF; ++w) {
+            if (!(w < NWF ? w < unit_waves : own_here)) continue;
+            const float f = part_weight(st[w], M);
             const float4 o = *reinterpret_cast<const float4 *>(smem + w * SLOT + row * 512 + ((c ^ row) * 16));
             L += f * st[w].y;
             sum.x += f * o.x;
@@ -1298,18 +1390,66 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
             sum.z += f * o.z;
             sum.w += f * o.w;
         }
-        const float inv = 1.0f / L;
-        const int64_t at = __shfl(io_row, row);
-        const int ok = __shfl((int)valid, row), r_head = __shfl(head, row), r_tok = __shfl(src_tok, row);
-        if (ok) {
-            bf16x4 y;
-            y[0] = (__bf16)(sum.x * inv);
-            y[1] = (__bf16)(sum.y * inv);
-            y[2] = (__bf16)(sum.z * inv);
-            y[3] = (__bf16)(sum.w * inv);
-            *reinterpret_cast<bf16x4 *>(static_cast<uint16_t *>(o_base) + at + c * 4) = y;
-            if (lse_base && c == 0) lse_base[(int64_t)r_head * a.lse_stride + r_tok] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+        if (S == 1) {
+            finish(row, c, M, L, sum);
+        } else if (row <= last_row) {
+            store_shared(parts + (range * 32 + row) * 32 + c, sum);
+            if (c == 0) store_shared(part_stats + range * 32 + row, make_float2(M, L));
         }
+    }
+    if (S == 1) return;
+
+    // ---- the last of a row tile's ranges to get here adds all of them up, in their order ----
+    // (Every workgroup stores, counts, and goes; nobody waits for another.  The counter is zero between launches.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): this wavefront's results are where the others will read them
+    __syncthreads();
+    uint32_t *const flag = reinterpret_cast<uint32_t *>(smem);
+    if (threadIdx.x == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(a.arrived + t.row_tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == (uint32_t)(S - 1)) __hip_atomic_store(a.arrived + t.row_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = before;
+    }
+    __syncthreads();
+    if (*flag != (uint32_t)(S - 1)) return;
+#pragma unroll
+    for (int k = 0; k < 16 / NWF; ++k) {
+        const int row = ((int)threadIdx.x >> 5) + k * 2 * NWF, c = lane & 31;
+        if (__builtin_amdgcn_readfirstlane(row) > last_row) continue;       // (of the two rows of a wavefront the first)
+        const int rr = min(row, last_row);
+        float M = -INFINITY, L = 0.f;
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int r0 = 0; r0 < S; r0 += 4) {          // four ranges to a round trip; what is added so far is rescaled to the new maximum
+            float2 st[4];
+            float4 o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = min(r0 + i, S - 1);
+                st[i] = load_shared(part_stats + r * 32 + rr);
+                o[i] = load_shared(parts + (r * 32 + rr) * 32 + c);
+                if (r0 + i >= S) st[i] = make_float2(-INFINITY, 0.f);
+            }
+            float m_new = M;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m_new = fmaxf(m_new, st[i].x);
+            const float keep = M > -INFINITY ? __builtin_amdgcn_exp2f(M - m_new) : 1.f;
+            M = m_new;
+            L *= keep;
+            sum.x *= keep;
+            sum.y *= keep;
+            sum.z *= keep;
+            sum.w *= keep;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (r0 + i >= S) continue;
+                const float f = part_weight(st[i], M);
+                L += f * st[i].y;
+                sum.x += f * o[i].x;
+                sum.y += f * o[i].y;
+                sum.z += f * o[i].z;
+                sum.w += f * o[i].w;
+            }
+        }
+        finish(row, c, M, L, sum);
     }
 }
 
@@ -1317,28 +1457,14 @@ hipError_t launch_few(const AttnArgs &a, hipStream_t s)
 {
     static bool configured = false;     // raise the dynamic LDS limit once
     auto kern = attn_few_kernel;
-    const size_t lds = NWF * (4 * PART_BYTES + 32 * sizeof(float2));
+    const size_t lds = (NWF + 1) * (4 * PART_BYTES + 32 * sizeof(float2));
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    constexpr int per_block = NWF * 64 / 8;      // new tokens (of a decode step) that a block behind the tiles appends
-    const int blocks = a.n_tiles + (a.n_append * a.n_kv_heads + per_block - 1) / per_block;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(NWF * 64), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(a.n_tiles), dim3(NWF * 64), lds, s, a);
     return hipGetLastError();
-}
-
-// Where it is the faster: tiles of one row group (with four, whose keys it reads four times, 64 queries over 3001 tokens take 35.1
-// against 23.9 us), and at most 16 of them on an XCD: its workgroups take a compute unit each, and what shares the chip evenly anyway
-// gains nothing (16 prompts of 200 tokens 19.1 -> 17.3 us; of 1000 tokens, in 256 tiles, 29.8 against 27.5); and, with more than
-// 128 rows in all, some tile with more than one 64-key step: a single one costs less than the merge (prompts of 64 tokens, 16 of one
-// query each 15.3 against 14.4 us, 6 queries of 32 heads without groups 16.5 against 15.8, but one query 11.9 against 13.5; of 65 tokens
-// never slower).
-bool few_rows(const AttnArgs &a)
-{
-    return a.mode == MODE_SUFFIX && a.skip_self && a.n_tiles > 0 && a.n_tiles <= 128 && a.tile_groups == 1 && (a.tile_keys > BN || a.n_append * a.n_q_heads <= 128) &&
-           a.pool.kv_dtype != SGC_FP8_E4M3;
 }
 
 }  // namespace
@@ -1352,7 +1478,7 @@ hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s)
 {
     const bool fp8 = a.pool.kv_dtype == SGC_FP8_E4M3;
     if (a.n_tiles <= 0 && a.n_append <= 0) return hipSuccess;
-    if (few_rows(a)) return launch_few(a, s);
+    if (a.few) return launch_few(a, s);
     if (a.mode == MODE_SUFFIX) {
         // a decode step's launch carries, behind its tiles, the blocks that append the step's new tokens
         const int per_block = NW * 64 / 8;

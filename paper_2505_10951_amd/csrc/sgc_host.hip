@@ -49,6 +49,11 @@ int fail_hip(sgc_ctx *ctx, hipError_t e, const char *what)
         if (e__ != hipSuccess) return fail_hip(ctx, e__, #call); \
     } while (0)
 
+bool overlap(const void *p, size_t pn, const void *q, size_t qn)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(q);
+    return p && q && a0 < b0 + qn && b0 < a0 + pn;
+}
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 bool mfma_covers(const sgc_attn_params &p)
@@ -513,6 +518,17 @@ void layout_suffix_pages(sgc_plan *pl)
     pl->n_pool_pages = page;
 }
 
+// Steps that the one-launch kernel (attn_few_kernel) takes: 16-bit caches and at most 32 rows of a cluster and KV head, where it is the
+// faster.  load, own_load: a row tile's cached and own keys, own keys alone, in 32-key units.  Its workgroups have a compute unit each,
+// so past 256 row tiles short ones lose (24 prompts of 120 tokens, 32 KV heads, a query each: 30.7 against 28.9 us; of 200 tokens 32.1
+// against 33.7), and many long questions are better dealt to all wavefronts of the chip (32 queries of about 105 own keys without head groups:
+// prompts of 60 38.5 against 37.0 us, of 3000 201 against 193; 8 of them with head groups 28.6 against 31.2).
+bool few_row_steps(const sgc_ctx *ctx, int64_t row_tiles, int64_t most_rows, int64_t load, int64_t own_load)
+{
+    return row_tiles > 0 && row_tiles <= kFewRowTiles && most_rows <= 32 && ctx->p.kv_dtype != SGC_FP8_E4M3 && (row_tiles <= 256 || load >= 10) &&
+           own_load <= 150;
+}
+
 // Decode work list: one row group (the g heads of a KV head) per query, all queries of a (cluster, KV head)
 // stacked so that one tile of rows shares the cluster's cached K/V.  Same XCD dealing as build_tiles.
 void build_decode_tiles(sgc_plan *pl, int tile_rows)
@@ -520,19 +536,20 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     const sgc_ctx *ctx = pl->ctx;
     const int g = ctx->p.n_q_heads / ctx->p.n_kv_heads;
     struct Light {
-        int32_t cluster, hk, row0, split;
+        int32_t cluster, hk, row0, split, row_tile;
     };
     struct Unit {
         int32_t cluster, hk;
     };
     std::vector<Unit> units;
     std::vector<double> work;
-    int64_t row_tiles = 0;
+    int64_t row_tiles = 0, most_rows = 0;
     int max_steps = 0;
     for (int c = 0; c < pl->n_clusters; ++c) {
         const int64_t nq = pl->cl_sq_off[c + 1] - pl->cl_sq_off[c];
         if (nq == 0) continue;
         const int64_t nt = (nq * g + tile_rows - 1) / tile_rows;
+        most_rows = std::max(most_rows, nq * g);
         row_tiles += nt * ctx->p.n_kv_heads;
         max_steps = std::max(max_steps, (pl->cl_prefix_len[c] + 63) / 64);
         for (int hk = 0; hk < ctx->p.n_kv_heads; ++hk) {
@@ -549,8 +566,25 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     // third and fourth round trip); 32 x 16 steps, S = 2, 4, 8 -> 22.1, 20.2, 20.9 us.  Past eight ranges only long
     // prompts gain: 8 x 157 steps, S = 8, 16 -> 33.7, 30.3 us.
     auto whole_trips = [](int n, int from) { return n > from ? n / 4 * 4 : n; };
+    // load of a row tile in 32-key units: its cached keys, and its queries' own keys, 16 heads of a query a task of a round trip
+    // for every 32 keys, about 1.75 units each
+    int64_t own_tokens = 0;
+    for (int32_t len : pl->sq_len) own_tokens += len + pl->decode_cap / 2;
+    const int64_t n_sq = std::max<int64_t>((int64_t)pl->sq_len.size(), 1);
+    pl->dec_own_cost2 = (int32_t)std::max<int64_t>(5, (7 * ((own_tokens / n_sq + 31) / 32) + 1) / 2);
+    const int64_t tasks = row_tiles > 0 ? n_sq * ctx->p.n_kv_heads * ((g + 15) / 16) / row_tiles : 0;
+    const int64_t own_load = tasks * pl->dec_own_cost2 / 2, load = 2 * max_steps + own_load;
+    pl->dec_few = few_row_steps(ctx, row_tiles, most_rows, load, own_load);
     int S = 1;
-    if (row_tiles > 0) {
+    if (pl->dec_few) {
+        // The one-launch kernel's workgroups have a compute unit each and eight wavefronts for a range's 32-key units: three units
+        // a wavefront, or fewer while that makes no more than eight ranges, and not more than half the chip.  A step, us: 5 queries over 3001
+        // keys, S = 3, 4, 8, 12 -> 15.1, 14.4, 14.7, 15.2; one over 9000, S = 6, 8, 12 -> 16.4, 14.6, 14.0; 5 without head groups over
+        // 500, S = 1, 2, 3, 8 -> 14.0, 11.5, 11.0, 11.2; 16 over a prompt of 1000 each, S = 1, 2, 3 -> 16.9, 17.3, 22.5.
+        S = (int)std::max((load + 23) / 24, std::min<int64_t>((load + 5) / 6, 8));
+        const int half_chip = (int)std::max<int64_t>(128 / row_tiles, 1);
+        S = std::max(1, std::min({S, load > 24 * half_chip ? (int)(256 / row_tiles) : half_chip, g > 16 ? kDecodeDotSplits : kDecodeMaxSplits}));
+    } else if (row_tiles > 0) {
         const int full = std::min(max_steps / 8, (int)std::min<int64_t>(256 / row_tiles, 256));
         const int half = std::min({max_steps / 3, (int)std::min<int64_t>(128 / row_tiles, 128), 8});
         S = std::max({1, whole_trips(std::min(full, kDecodeMaxSplits), 8), whole_trips(half, 4)});
@@ -564,12 +598,13 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     pl->dec_splits = S;
     std::vector<std::vector<Light>> lists(kXcd);
     const auto of_xcd = deal_to_xcds(work);
+    int32_t n_row_tiles = 0;
     for (int x = 0; x < kXcd; ++x)
         for (int ui : of_xcd[x]) {
             const Unit &u = units[ui];
             const int64_t rows = (int64_t)(pl->cl_sq_off[u.cluster + 1] - pl->cl_sq_off[u.cluster]) * g;
-            for (int64_t r = 0; r < rows; r += tile_rows)
-                for (int sp = 0; sp < S; ++sp) lists[x].push_back({u.cluster, u.hk, (int32_t)r, sp});
+            for (int64_t r = 0; r < rows; r += tile_rows, ++n_row_tiles)
+                for (int sp = 0; sp < S; ++sp) lists[x].push_back({u.cluster, u.hk, (int32_t)r, sp, n_row_tiles});
         }
     size_t slots = 0;
     for (auto &l : lists) slots = std::max(slots, l.size());
@@ -592,10 +627,12 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
             t.tok_base = pl->cl_sq_off[lt.cluster];      // "token" = the query's one new token
             t.sq_hi = -1;
             t.n_q = kTileQueries + 1;                     // row bookkeeping from the table, not from inline records
+            t.row_tile = lt.row_tile;
             pl->dtile_key0[k * kXcd + x] = key0;
         }
+    pl->dec_row_tiles = n_row_tiles;
     pl->dtok.resize(pl->sq_len.size());
-    for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) pl->dtok[sq] = {pl->sq_query[sq], pl->sq_len[sq], 0, 0};
+    for (size_t sq = 0; sq < pl->sq_len.size(); ++sq) pl->dtok[sq] = {pl->sq_query[sq], pl->sq_len[sq], pl->sq_page0[sq], 0};
 }
 
 void plan_free_device(sgc_plan *pl)
@@ -1169,13 +1206,6 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
         for (int k = 0; k < pl->n_clusters; ++k)
             for (int64_t r = 0; r < (pl->cl_tok_off[k + 1] - pl->cl_tok_off[k]) * g; r += kGenericRows) pl->gtiles.push_back({k, (int32_t)r});
     }
-    int32_t most_rows = 1;
-    pl->dtile_keys = 0;
-    for (const Tile &t : pl->dtiles) {
-        most_rows = std::max(most_rows, t.n_rows);
-        pl->dtile_keys = std::max(pl->dtile_keys, t.prefix_len);
-    }
-    pl->dtile_groups = (most_rows + 31) / 32;
     // The per-token records are only read by tiles that touch more queries than their own record describes.
     bool wide_tile = false;
     for (const Tile &t : pl->tiles) wide_tile = wide_tile || (t.n_rows > 0 && t.n_q > kTileQueries);
@@ -1364,10 +1394,6 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     // that is the faster (long questions).
     const size_t kv_bytes = (size_t)pl->total_tokens * ctx->p.n_kv_heads * ctx->p.head_dim * dtype_bytes(ctx->p.io_dtype);
     const size_t o_bytes = kv_bytes / ctx->p.n_kv_heads * ctx->p.n_q_heads, lse_bytes = (size_t)pl->total_tokens * ctx->p.n_q_heads * sizeof(float);
-    auto overlap = [](const void *p, size_t pn, const void *q, size_t qn) {
-        const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(q);
-        return p && q && a0 < b0 + qn && b0 < a0 + pn;
-    };
     const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && pl->own_rows_pay && !overlap(dev_o, o_bytes, dev_k, kv_bytes) &&
                          !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
                          !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
@@ -1419,7 +1445,9 @@ int sgc_plan_enable_decode(sgc_plan *pl, int32_t max_new_tokens)
 // block from the context's pool.  Every GPU the library runs on holds its own copy of the array until the process
 // ends; host code never uses the array's name as an address, only what hipGetSymbolAddress returned for the
 // device that was current.
-static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoAllocScratchBytes];
+// Behind it the counters of a step of few rows: zero when the library is loaded, and left at zero by every step.
+constexpr size_t kNoAllocCounters = kFewRowTiles;
+static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoAllocScratchBytes + kNoAllocCounters * sizeof(uint32_t)];
 constexpr int kMaxDevices = 64;
 static char *g_noalloc_scratch_ptr[kMaxDevices] = {};
 
@@ -1480,22 +1508,68 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
         if ((rc = refresh_tiles(pl, c, s)) != SGC_OK) return rc;
     }
     pl->last_stream = s;
-    // scratch for the cached-prefix part of the step, one set per key range: O [S][n_queries][Hq][d] bf16, then
-    // LSE [S][Hq][n_queries]
-    const int S = std::max(1, pl->dec_splits);
+    char *spool = pl->d_spool + (size_t)layer * pl->spool_layer_bytes;
+
+    AttnArgs a;
+    fill_common_args(a, ctx, c, layer);
+    a.q = dev_q;
+    a.lse_stride = pl->n_queries;
+    a.mode = MODE_SUFFIX;
+    a.tiles = pl->d_dtiles;
+    a.n_tiles = (int32_t)pl->dtiles.size();
+    a.tok_info = pl->d_dtok;
+    a.sq_len = pl->d_sq_len;
+    a.sq_page0 = pl->d_sq_page0;
+    a.spool = spool;
+    a.pos_shift = step;
+    a.skip_self = 1;
+    a.k = dev_k;                 // the step's new tokens: appended by the blocks behind the tiles
+    a.v = dev_v;
+    a.sq_cluster = pl->d_sq_cluster;
+    a.sq_query = pl->d_sq_query;
+    a.n_append = n_sq;
+    a.n_ranges = std::max(1, pl->dec_splits);
+    // Scratch of the step.  One launch (few): the ranges' partial results, and the counters of the row tiles, which every step leaves at
+    // zero.  Two: the cached-prefix part, one set per key range: O [S][n_queries][Hq][d] bf16, then LSE [S][Hq][n_queries].
+    // (One launch stores outputs while others still read the new tokens: not where an output overlaps those.)
+    const int S = a.n_ranges;
     const size_t o_bytes = ((size_t)pl->n_queries * ctx->p.n_q_heads * ctx->p.head_dim * 2 + 255) / 256 * 256;
     const size_t lse_bytes = ((size_t)ctx->p.n_q_heads * pl->n_queries * sizeof(float) + 255) / 256 * 256;
+    const size_t kv_bytes = (size_t)pl->n_queries * ctx->p.n_kv_heads * ctx->p.head_dim * 2;
+    const bool few = pl->dec_few && !overlap(dev_o, o_bytes, dev_k, kv_bytes) && !overlap(dev_o, o_bytes, dev_v, kv_bytes) &&
+                     !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
+    const size_t few_bytes = pl->dec_few && S > 1 ? (size_t)pl->dec_row_tiles * S * kFewPartBytes : 0;
+    const size_t counters = few_bytes > 0 ? 256 * (((size_t)pl->dec_row_tiles * sizeof(uint32_t) + 255) / 256) : 0;
+    const size_t bytes = std::max(few_bytes, S * (o_bytes + lse_bytes));
     char *scratch = nullptr;
+    uint32_t *arrived = nullptr;
     if (no_alloc) {
-        if (S * (o_bytes + lse_bytes) > kNoAllocScratchBytes)
-            return fail(ctx, SGC_ENOMEM, "the step's partial results need %zu bytes, the static scratch array holds %zu",
-                        S * (o_bytes + lse_bytes), kNoAllocScratchBytes);
+        if (bytes > kNoAllocScratchBytes)
+            return fail(ctx, SGC_ENOMEM, "the step's partial results need %zu bytes, the static scratch array holds %zu", bytes, kNoAllocScratchBytes);
         if ((rc = noalloc_scratch(ctx, &scratch)) != SGC_OK) return rc;
+        arrived = reinterpret_cast<uint32_t *>(scratch + kNoAllocScratchBytes);
     } else {
-        if (!pl->dec_scratch.p && (rc = dev_acquire(ctx, S * (o_bytes + lse_bytes), s, &pl->dec_scratch)) != SGC_OK) return rc;
+        if (!pl->dec_scratch.p) {
+            if ((rc = dev_acquire(ctx, bytes + counters, s, &pl->dec_scratch)) != SGC_OK) return rc;
+            SGC_HIP(ctx, launch_fill_zero_bytes(pl->dec_scratch.p + bytes, counters, s));
+        }
         scratch = pl->dec_scratch.p;
+        arrived = reinterpret_cast<uint32_t *>(scratch + bytes);
     }
-    char *spool = pl->d_spool + (size_t)layer * pl->spool_layer_bytes;
+    if (few) {
+        a.o = dev_o;
+        a.lse = dev_lse;
+        a.few = 1;
+        a.own_cost2 = pl->dec_own_cost2;
+        a.parts = scratch;
+        a.arrived = arrived;
+        SGC_HIP(ctx, launch_attn_mfma(a, s));
+        return SGC_OK;
+    }
+    a.o = scratch;
+    a.lse = reinterpret_cast<float *>(scratch + S * o_bytes);
+    a.split_o_bytes = (int64_t)o_bytes;
+    a.split_lse_elems = (int64_t)(lse_bytes / sizeof(float));
 
     DecodeArgs d{};
     d.q = dev_q;
@@ -1526,30 +1600,6 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     d.scale_log2e = ctx->scale * 1.4426950408889634f;
     d.use_mfma = ctx->use_mfma ? 1 : 0;
 
-    AttnArgs a;
-    fill_common_args(a, ctx, c, layer);
-    a.q = dev_q;
-    a.o = scratch;
-    a.lse = reinterpret_cast<float *>(scratch + S * o_bytes);
-    a.split_o_bytes = (int64_t)o_bytes;
-    a.split_lse_elems = (int64_t)(lse_bytes / sizeof(float));
-    a.lse_stride = pl->n_queries;
-    a.mode = MODE_SUFFIX;
-    a.tiles = pl->d_dtiles;
-    a.n_tiles = (int32_t)pl->dtiles.size();
-    a.tile_groups = pl->dtile_groups;
-    a.tile_keys = pl->dtile_keys;
-    a.tok_info = pl->d_dtok;
-    a.sq_len = pl->d_sq_len;
-    a.sq_page0 = pl->d_sq_page0;
-    a.spool = spool;
-    a.pos_shift = step;
-    a.skip_self = 1;
-    a.k = dev_k;                 // the step's new tokens: appended by the blocks behind the tiles
-    a.v = dev_v;
-    a.sq_cluster = pl->d_sq_cluster;
-    a.sq_query = pl->d_sq_query;
-    a.n_append = n_sq;
     SGC_HIP(ctx, launch_attn_mfma(a, s));
     SGC_HIP(ctx, launch_decode_own_keys(d, s));
     return SGC_OK;

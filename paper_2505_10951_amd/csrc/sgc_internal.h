@@ -127,7 +127,8 @@ struct Tile {
     TileQuery q[kTileQueries];     // queries sq_lo, sq_lo + 1, ...
     int32_t own_page0;             // first own page of query sq_lo ...
     int32_t n_own_pages;           // ... and how many follow up to the last row's own key
-    int32_t unused[2];
+    int32_t row_tile;              // decode tiles: number of the row tile that the key range belongs to
+    int32_t unused;
 };
 static_assert(sizeof(Tile) == 160, "tile record layout");
 
@@ -166,7 +167,7 @@ struct SuffixPage {
 struct TokInfo {
     int32_t src;    // row of the token in the caller's packed arrays
     int32_t qpos;   // index of the token inside its query
-    int32_t own0;   // first own page of the query
+    int32_t own0;   // first own page of the query (records of decode steps: its first page in the suffix page pool)
     int32_t unused;
 };
 
@@ -264,6 +265,10 @@ struct GemmArgs {
 
 enum { MODE_SUFFIX = 0, MODE_PREFIX = 1 };
 
+// A key range's partial results for 32 rows: fp32 sums, reference maxima and row sums.
+constexpr int kFewRowTiles = 1024;       // row tiles of a step that it is taken for at most
+constexpr size_t kFewPartBytes = 32 * (128 * sizeof(float) + 2 * sizeof(float));
+
 // Everything an attention kernel needs, by value.
 struct AttnArgs {
     const void *q, *k, *v;   // token-major q [*][Hq][d], k/v [*][Hkv][d] (io dtype), before rotation
@@ -280,8 +285,6 @@ struct AttnArgs {
     const float2 *rope;           // [rope_len][d/2] (cos, sin) or null when rotation is off
     const Tile *tiles;
     int32_t n_tiles;              // a multiple of 8: the XCDs' shorter lists are filled up with padding tiles
-    int32_t tile_groups;          // decode: 32-row groups of the largest tile ...
-    int32_t tile_keys;            // ... and the most cached keys of a tile
     // suffix mode: sorted-token and sorted-query tables (sorted = grouped by cluster; queries
     // without tokens are left out of the query tables)
     const int32_t *cl_tok_off;    // [n_clusters + 1] first sorted token of each cluster
@@ -314,6 +317,13 @@ struct AttnArgs {
     // new tokens [n_queries][Hkv][d]; sq_query: original index of the sorted query) to the suffix pages
     const int32_t *sq_query;
     int32_t n_append;
+    // decode steps of few rows (attn_few_kernel): one launch does the whole step.  n_ranges key ranges per row tile; the partial results
+    // of several go to parts (kFewPartBytes each), arrived counts a row tile's ranges in (zero between launches).
+    int32_t few;
+    int32_t own_cost2;            // a query's own keys against 32 cached keys, in halves
+    char *parts;
+    uint32_t *arrived;
+    int32_t n_ranges;
     // fp8 cache: run the first product on the e4m3 codes, with the query quantised per row (suffix mode)
     int32_t fp8_first_product;
 };
@@ -402,9 +412,10 @@ struct sgc_plan {
     int32_t decode_cap = 0;
     std::vector<sgc::Tile> dtiles;
     std::vector<int32_t> dtile_key0;          // first cached key of each decode tile's key range
-    int32_t dtile_groups = 4;                 // 32-row groups of the largest decode tile ...
-    int32_t dtile_keys = 0;                   // ... and the most cached keys of one
     int32_t dec_splits = 1;                   // key ranges per row tile
+    int32_t dec_row_tiles = 0;
+    int32_t dec_own_cost2 = 0;
+    bool dec_few = false;                     // decode steps are one launch of the kernel for few rows
     std::vector<sgc::TokInfo> dtok;
     size_t spool_layer_bytes = 0;
     sgc_dev_block dec_scratch;                // cached-prefix part of a decode step: O then LSE

@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "sgc_internal.h"
+#include "sgc_own_keys.h"
 
 namespace sgc {
 
@@ -335,7 +336,7 @@ __device__ inline void expand_one_tile(const ExpandArgs &e, int i)
     for (int k = 0; k < kTileQueries; ++k) t.q[k] = {INT32_MAX, 0, 0};
     t.own_page0 = 0;
     t.n_own_pages = 0;
-    t.unused[0] = t.unused[1] = 0;
+    t.row_tile = t.unused = 0;
     if (sd.n_rows > 0) {
         if (e.jobs) {
             const PrefixJob &j = e.jobs[sd.cluster];
@@ -844,26 +845,12 @@ __global__ void __launch_bounds__(64) decode_own_keys_kernel(DecodeArgs a)
 }
 
 // The same step on the matrix cores, head_dim 128, groups of up to 16 query heads per KV head: one wavefront per (sorted
-// query, KV head), no LDS.  v_mfma_f32_16x16x32: a page's 16 tokens are the 16 rows of the first product's left operand
-// (32 channels per instruction are 1 KiB of the page, in lane order), the group's heads are its columns (the unused columns
-// carry zeros), so lane (j, q) = (lane % 16, lane / 16) ends up with the scores of head j against tokens 4 q .. 4 q + 3 of
-// every page.  Those four values of two neighbouring pages are, as they stand, the lane's eight contraction slots of the
-// second product (keys x heads), whose left operand V^T takes, per lane, the 8-byte run of four tokens of channel
-// 16 cb + lane % 16 from each of the two pages.  Keys come in chunks of 2 pages with an online softmax over the chunks.
-// What bounds it is the chain of dependent loads (a few wavefronts per SIMD, 90 MB at 320 queries): the first chunk's keys and
-// the cached part's log-sum-exps are requested before the query rows, a chunk's values before its softmax, the cached
-// part's outputs of four ranges together.  Decode step of 320 queries over prompts of 1024 (8 KV heads, 57 own keys on average):
-// 34.7 -> 34.0 us; without head groups (32 KV heads, prompts of 500) 88.9 -> 82.3; 5 queries over 3001, five ranges:
-// 27.8 -> 25.2.  Chunks of 4 pages: 34.8, 87.3 and 25.5 (168 registers, two of them spilled); 2 pages with the next
-// chunk's keys requested before the softmax 34.9, 83.2 and 25.2.
-typedef __attribute__((ext_vector_type(8))) _Float16 dec_f16x8;
-typedef __attribute__((ext_vector_type(8))) __bf16 dec_bf16x8;
-typedef __attribute__((ext_vector_type(4))) float dec_f32x4;
-typedef __attribute__((ext_vector_type(4))) uint32_t dec_u32x4;
-
+// query, KV head), see own_keys_attend.  The cached part's log-sum-exps are requested first, its outputs of four ranges
+// together.  Decode step of 320 queries over prompts of 1024 (8 KV heads, 57 own keys on average): 34.7 -> 34.0 us; without head
+// groups (32 KV heads, prompts of 500) 88.9 -> 82.3.
 __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs a)
 {
-    constexpr int d = 128, half = 64, CH = 2;        // CH: pages per chunk
+    constexpr int d = 128, half = 64;
     const int lane = threadIdx.x & 63;
     const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = Hq / Hkv;
     const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -873,7 +860,6 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
     const int n = a.sq_query[sq];
     const int n_keys = a.sq_len[sq] + a.step + 1;
     const int P = a.cl_prefix_len[a.sq_cluster[sq]];
-    const int n_pages = (n_keys + kPageTokens - 1) / kPageTokens;
     const bool live = j < g;                           // the lane's column is a head of the group
     const int h = hk * g + (live ? j : 0);
     const int64_t io = ((int64_t)n * Hq + h) * d;
@@ -881,18 +867,6 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
     const int64_t page_stride = 2 * Hkv * part;
     const char *pages = a.spool + (int64_t)a.sq_page0[sq] * page_stride + (int64_t)hk * part;
 
-    const int64_t v_part = (int64_t)Hkv * part;
-    // the scores' left operands of a chunk: pages past the last are read as the last page again and masked
-    dec_u32x4 ka[CH][4];
-    auto load_keys = [&](int pg0) {
-#pragma unroll
-        for (int p = 0; p < CH; ++p) {
-            const char *kp = pages + (int64_t)min(pg0 + p, n_pages - 1) * page_stride + lane * 16;
-#pragma unroll
-            for (int cbk = 0; cbk < 4; ++cbk) ka[p][cbk] = *reinterpret_cast<const dec_u32x4 *>(kp + cbk * 1024);
-        }
-    };
-    load_keys(0);
     // the cached part's log-sum-exps of the lane's head, range q + 4 i in lane group q
     const int S_n = a.n_splits;
     constexpr int LR = kDecodeMaxSplits / 4;
@@ -903,99 +877,17 @@ __global__ void __launch_bounds__(256, 3) decode_own_keys_mfma_kernel(DecodeArgs
         if (q + 4 * i < S_n && a.lse_cached) lse_q[i] = a.lse_cached[(q + 4 * i) * a.split_lse_elems + (int64_t)h * a.n_queries + n];
     }
 
-    // the query rows as right operands: chunk c8 = 4 cbk + q of 8 channels for cbk = 0..3; the rotation pairs chunk c8 with
-    // chunk c8 + 8, both of which this lane holds (cbk and cbk + 2)
-    dec_f16x8 qb[4];
-    {
-        float x1[2][8], x2[2][8];
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int c0 = 8 * (4 * cb + q);
-            load8(a.q, io + c0, SGC_BF16, x1[cb]);
-            load8(a.q, io + half + c0, SGC_BF16, x2[cb]);
-            if (a.rope) rope8(x1[cb], x2[cb], a.rope + (int64_t)(P + n_keys - 1) * half + c0);
-        }
-        const float sc = live ? a.scale_log2e : 0.f;
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                qb[cb][e] = (_Float16)(x1[cb][e] * sc);
-                qb[cb + 2][e] = (_Float16)(x2[cb][e] * sc);
-            }
-    }
-
+    OwnKeys own{};
+    own.pages = const_cast<char *>(pages);
+    own.page_stride = page_stride;
+    own.v_part = (int64_t)Hkv * part;
+    own.n_keys = n_keys;
+    own.q = static_cast<const uint16_t *>(a.q) + io;
+    own.scale = live ? a.scale_log2e : 0.f;
+    own.rope = a.rope ? a.rope + (int64_t)(P + n_keys - 1) * half : nullptr;
     dec_f32x4 O[8];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) O[cb] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
-    for (int pg0 = 0; pg0 < n_pages; pg0 += CH) {
-        // scores of the chunk (log2 units)
-        dec_f32x4 S[CH];
-#pragma unroll
-        for (int p = 0; p < CH; ++p) {
-            dec_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int cbk = 0; cbk < 4; ++cbk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(dec_f16x8, ka[p][cbk]), qb[cbk], acc, 0, 0, 0);
-            S[p] = acc;
-        }
-        // the values, on their way while the scores become weights
-        uint2 v0[CH / 2][8], v1[CH / 2][8];
-#pragma unroll
-        for (int pp = 0; pp < CH / 2; ++pp) {
-            const char *va = pages + (int64_t)min(pg0 + 2 * pp, n_pages - 1) * page_stride + v_part;
-            const char *vb = pages + (int64_t)min(pg0 + 2 * pp + 1, n_pages - 1) * page_stride + v_part;
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                // channel 16 cb + j: 32-channel group cb / 2, token block q & 1, channel (cb % 2) * 16 + j inside it, tokens
-                // 4 q .. 4 q + 3 = the half 8 (q >> 1) of the 16-byte run
-                const int off = ((((cb >> 1) * 2 + (q & 1)) * 32 + (cb & 1) * 16 + j) * 16) + 8 * (q >> 1);
-                v0[pp][cb] = *reinterpret_cast<const uint2 *>(va + off);
-                v1[pp][cb] = *reinterpret_cast<const uint2 *>(vb + off);
-            }
-        }
-        float cmax = -INFINITY;
-#pragma unroll
-        for (int p = 0; p < CH; ++p)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int key = (pg0 + p) * kPageTokens + 4 * q + r;
-                if (key >= n_keys) S[p][r] = -INFINITY;
-                cmax = fmaxf(cmax, S[p][r]);
-            }
-        cmax = fmaxf(cmax, __shfl_xor(cmax, 16));
-        cmax = fmaxf(cmax, __shfl_xor(cmax, 32));
-        const float m_new = fmaxf(m_run, cmax);          // finite: every chunk holds at least one visible key
-        const float alpha = exp2f(m_run - m_new);         // 0 on the first chunk
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) O[cb][r] *= alpha;
-        // weights, rounded to bf16 (the row sum adds the rounded values), two pages = one right operand
-#pragma unroll
-        for (int pp = 0; pp < CH / 2; ++pp) {
-            if (pg0 + 2 * pp >= n_pages) break;            // (wave-uniform)
-            uint16_t w[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                w[e] = f32_to_bf16(exp2f(S[2 * pp + (e >> 2)][e & 3] - m_new));
-                l_run += bf16_to_f32(w[e]);
-            }
-            const dec_u32x4 wb = {(uint32_t)w[0] | ((uint32_t)w[1] << 16), (uint32_t)w[2] | ((uint32_t)w[3] << 16),
-                                  (uint32_t)w[4] | ((uint32_t)w[5] << 16), (uint32_t)w[6] | ((uint32_t)w[7] << 16)};
-#pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                const dec_u32x4 av = {v0[pp][cb].x, v0[pp][cb].y, v1[pp][cb].x, v1[pp][cb].y};
-                O[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, av), __builtin_bit_cast(dec_bf16x8, wb), O[cb], 0, 0, 0);
-            }
-        }
-        if (pg0 + CH < n_pages) load_keys(pg0 + CH);
-    }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    float m_run, l_run;
+    own_keys_attend<false, 2, false>(own, O, m_run, l_run);
     // merge with the cached-prefix part (natural-log LSE there, -inf for an empty range; log2 units here); the lane holds
     // channels 16 cb + 4 q .. + 3 of its head
     const uint16_t *oc = static_cast<const uint16_t *>(a.o_cached);

@@ -57,3 +57,50 @@ def test_keys_that_score_minus_infinity(prefix, masked):
         ref, ref_lse, _ = orc.suffix_prefill(pk[keep], pv[keep], np.concatenate([q[a:b], dq[n:n + 1]]), np.concatenate([k[a:b], dk[n:n + 1]]),
                                              np.concatenate([v[a:b], dv[n:n + 1]]), 0.0)
         assert np.abs(o[n] - ref[S]).max() <= TOL["bf16"] and np.abs(lse[:, n] - ref_lse[:, S]).max() <= 5e-2
+
+
+@pytest.mark.parametrize("hq,hkv,per,prefix,suffix", [(32, 1, 1, [700], (1, 40)),          # 32 heads: two tasks of 16 for a query's own keys
+                                                       (20, 1, 1, [64, 0], (3, 60)),        # 20 heads: a task that is not full
+                                                       (4, 1, 8, [1500], (90, 300)),        # long questions: more tasks than one range has wavefronts
+                                                       (2, 2, 32, [5, 0], (1, 33)),         # 32 queries a row tile, hardly any cached keys
+                                                       (8, 2, 3, [4000, 100], (16, 16))])   # many ranges, one cluster far shorter
+def test_own_keys_of_a_step(hq, hkv, per, prefix, suffix):
+    """18 steps (the new tokens cross a page boundary), the queries' own keys in the launch of the cached ones."""
+    w = workloads.custom("few_own", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=prefix,
+                         cluster_sizes=[per] * len(prefix), suffix_range=suffix, seed=hq + per)
+    o, lse = _run_decode(w, 18)[0]
+    o_ref, lse_ref = _oracle_decode(w, 0, 18, oracle_caches(w, 0))
+    assert np.isfinite(o).all() and np.abs(o - o_ref).max() <= TOL["bf16"] and np.abs(lse - lse_ref).max() <= 5e-2
+
+
+def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
+    """The same step twice gives the same bits (the ranges' counters are back at zero); an output that overlaps the new tokens, whose
+    rows must not be stored before all are read, gives the same result within rounding; a NaN value of one query stays with it."""
+    import torch
+    from paper_2505_10951_amd.harness import Session, to_device, to_host_f32
+    w = workloads.custom("few_again", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=[3000, 40],
+                         cluster_sizes=[4, 2], suffix_range=(2, 30), seed=5)
+    with Session(w) as s:
+        for c in range(2):
+            s.alloc_cluster(c)
+        s.prefix_prefill_batched([0, 1], 0)
+        s.assign()
+        s.enable_decode(2)
+        s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
+        dq, dk, dv = (to_device(x, "bf16") for x in w.decode_qkv(0))
+        first = s.decode_step(0, dq, dk, dv).clone()
+        for _ in range(3):
+            assert torch.equal(s.decode_step(0, dq, dk, dv), first)
+        n, hq, d = dq.shape
+        both = torch.zeros(n * hq * d + dk.numel(), dtype=dq.dtype, device="cuda:0")
+        o, k = both[:n * hq * d].view(n, hq, d), both[n * hq * d - dk.numel():n * hq * d].view(dk.shape)
+        k.copy_(dk)
+        s.decode_step(0, dq, k, dv, do=o)
+        torch.cuda.synchronize()
+        assert np.abs(to_host_f32(o) - to_host_f32(first)).max() <= 1e-2
+        bad = dv.clone()
+        bad[1, 0, 7] = float("nan")
+        o = to_host_f32(s.decode_step(0, dq, dk, bad))
+        assert np.isnan(o[1, :4, 7]).all()
+        o[1, :4, 7] = to_host_f32(first)[1, :4, 7]
+        assert np.array_equal(o, to_host_f32(first))
