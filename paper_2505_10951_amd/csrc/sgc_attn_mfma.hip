@@ -208,6 +208,10 @@ __device__ inline void append_new_tokens(const AttnArgs &a, int blk)
     }
 }
 
+__device__ __forceinline__ const AttnArgs &attn_args(const AttnArgs &a) { return a; }
+template <typename ARGS>
+__device__ __forceinline__ const AttnArgs &attn_args(const ARGS &c) { return c.a; }
+
 // QK8 (fp8 cache only): the first product runs on the cache's e4m3 codes as they are (v_mfma_scale_f32_32x32x64_f8f6f4,
 // twice the bf16 rate): the rotated, scaled query row is quantised to e4m3 with a power-of-two scale of its own, which
 // the instruction applies to the row's products in hardware, so scores come out in the same units as on the other
@@ -215,12 +219,17 @@ __device__ inline void append_new_tokens(const AttnArgs &a, int blk)
 //
 // OWN_RAW: the question tokens' keys and values are taken as the caller gives them (a.k, a.v), rotated and turned on their
 // way into LDS; otherwise they are read from the suffix page pool.
-template <bool KV_FP8, int MODE, bool QK8, bool OWN_RAW>
-__global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
+//
+// ARGS: AttnArgs, or CarriedSuffix / CarriedPrefix, whose tables are read where they arrive, among the launch's arguments.
+template <bool KV_FP8, int MODE, bool QK8, bool OWN_RAW, typename ARGS>
+__global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const ARGS args)
 {
+    constexpr bool CARRIED = !std::is_same_v<ARGS, AttnArgs>;
+    static_assert(!CARRIED || (!KV_FP8 && std::is_same_v<ARGS, std::conditional_t<MODE == MODE_PREFIX, CarriedPrefix, CarriedSuffix>>), "tables of the mode");
+    const AttnArgs &a = attn_args(args);
     static_assert(NW == 4 && MI == 1, "the own-suffix part deals pages to four wavefronts of 32 rows");
     static_assert(!QK8 || KV_FP8, "the fp8 first product needs an fp8 cache");
-    if (MODE == MODE_SUFFIX && (int)blockIdx.x >= a.n_tiles) {
+    if (!CARRIED && MODE == MODE_SUFFIX && (int)blockIdx.x >= a.n_tiles) {
         append_new_tokens(a, (int)blockIdx.x - a.n_tiles);
         return;
     }
@@ -233,23 +242,72 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
     const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = a.group;
 
     // ---- which tile ----
-    Tile t = uniform_record(a.tiles + blockIdx.x);
-    // (the whole record is asked for before its first use decides anything: one round trip)
-    asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad), "s"(t.first_pages[0]), "s"(t.first_pages[11]), "s"(t.q[0].tok0), "s"(t.q[3].own0),
-                 "s"(t.own_page0));
-    if (t.n_rows == 0) return;
+    Tile t;
+    const int32_t *page_table = a.page_table;
+    const SuffixPage *spages = a.spages;
     // where the rows come from and go to: the batch's packed arrays, or (prefix mode) the job's
     const void *q_base = a.q;
     void *o_base = a.o;
     float *lse_base = a.lse;
     int64_t lse_stride = a.lse_stride;
-    if (MODE == MODE_PREFIX) {
-        const PrefixJob job = uniform_record(a.jobs + __builtin_amdgcn_readfirstlane(t.tok_base));
-        q_base = job.q;
-        o_base = job.o;
-        lse_base = job.lse;
-        lse_stride = t.prefix_len;
+    if constexpr (CARRIED) {
+        const auto *c = (const __attribute__((address_space(4))) ARGS *)__builtin_amdgcn_kernarg_segment_ptr();
+        page_table = (const int32_t *)c->pages;
         t.tok_base = 0;
+        t.pad = 0;
+        t.n_q = 0;
+        t.cluster = 0;
+        if constexpr (MODE == MODE_PREFIX) {
+            const uint32_t code = c->tiles[blockIdx.x];
+            const CarriedJob job = uniform_record((const CarriedJob *)&c->jobs[code >> 28]);
+            t.hk = (code >> 18) & 1023;
+            t.row0 = (code & 0x3FFFF) * NW * MI * 32;
+            t.n_rows = min(NW * MI * 32, job.prefix_len * a.group - t.row0);
+            t.prefix_len = job.prefix_len;
+            t.pt_off = job.page0;
+            t.own_page0 = t.n_own_pages = 0;
+            q_base = job.q;
+            o_base = job.o;
+            lse_base = job.lse;
+            lse_stride = job.prefix_len;
+        } else {
+            spages = (const SuffixPage *)c->own_pages;
+            const TileSeed sd = uniform_record((const TileSeed *)&c->tiles[blockIdx.x]);
+            const auto cl = uniform_record((const CarriedSuffix::Cluster *)&c->clusters[sd.cluster]);
+            t.hk = sd.hk;
+            t.row0 = sd.row0;
+            t.n_rows = sd.n_rows;
+            t.prefix_len = cl.prefix_len;
+            t.pt_off = cl.page0;
+            t.tok_base = cl.tok_base;
+            t.n_q = sd.sq_hi - sd.sq_lo + 1;          // (kTileQueries at most)
+#pragma unroll
+            for (int k = 0; k < kTileQueries; ++k) {
+                const TileQuery tq = uniform_record((const TileQuery *)&c->queries[min(sd.sq_lo + k, sd.sq_hi)]);
+                t.q[k] = tq;
+                if (k >= t.n_q) t.q[k].tok0 = INT32_MAX;
+                if (k == 0) t.own_page0 = tq.own0;
+                t.n_own_pages = tq.own0 - t.own_page0 + sd.last_qpos / kPageTokens + 1;      // (the last of them is query sq_hi)
+            }
+        }
+        const int last_page = max((t.prefix_len + kPageTokens - 1) / kPageTokens - 1, 0);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) t.first_pages[k] = t.prefix_len > 0 ? uniform_record(page_table + t.pt_off + min(k, last_page)) : 0;
+        if (t.n_rows <= 0) return;
+    } else {
+        t = uniform_record(a.tiles + blockIdx.x);
+        // (the whole record is asked for before its first use decides anything: one round trip)
+        asm volatile("" ::"s"(t.n_rows), "s"(t.prefix_len), "s"(t.pad), "s"(t.first_pages[0]), "s"(t.first_pages[11]), "s"(t.q[0].tok0), "s"(t.q[3].own0),
+                     "s"(t.own_page0));
+        if (t.n_rows == 0) return;
+        if (MODE == MODE_PREFIX) {
+            const PrefixJob job = uniform_record(a.jobs + __builtin_amdgcn_readfirstlane(t.tok_base));
+            q_base = job.q;
+            o_base = job.o;
+            lse_base = job.lse;
+            lse_stride = t.prefix_len;
+            t.tok_base = 0;
+        }
     }
     // decode tiles cover one key range of the cluster's cache: own output set, positions continue behind ALL cached keys
     const int key_range = __builtin_amdgcn_readfirstlane(t.pad) >> 24;
@@ -264,7 +322,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
     t.n_rows = __builtin_amdgcn_readfirstlane(t.n_rows);
     const int P = __builtin_amdgcn_readfirstlane(t.prefix_len);
     const int n_pages = (P + kPageTokens - 1) / kPageTokens;
-    const int32_t *pt = a.page_table + __builtin_amdgcn_readfirstlane(t.pt_off);
+    const int32_t *pt = page_table + __builtin_amdgcn_readfirstlane(t.pt_off);
     const int tok_base = __builtin_amdgcn_readfirstlane(t.tok_base);
     const int last_row = t.row0 + t.n_rows - 1;
 
@@ -784,7 +842,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
         const int p = i * OWN_PAGES + wave_u;
         if (p >= n_own) return;
         char *kd = own_kbuf(i) + wave_u * PART_BYTES, *vd = own_vbuf(i) + wave_u * PART_BYTES;
-        const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
+        const SuffixPage pg = uniform_record(spages + own_page0 + p);
         if constexpr (OWN_RAW) {
             const int l = lane_again(), r0 = l >> 4, c = l & 15;
 #pragma unroll
@@ -810,7 +868,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
         if constexpr (OWN_RAW) {
             const int p = i * OWN_PAGES + wave_u;
             if (p >= n_own) return;
-            const SuffixPage pg = uniform_record(a.spages + own_page0 + p);
+            const SuffixPage pg = uniform_record(spages + own_page0 + p);
             const int l = lane_again(), pos = pg.pos0 + min(l & 15, pg.n - 1);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
@@ -1071,11 +1129,11 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(const AttnArgs a)
     }
 }
 
-template <bool FP8, int MODE, bool QK8, bool OWN_RAW>
-hipError_t launch_one(const AttnArgs &a, int blocks, hipStream_t s)
+template <bool FP8, int MODE, bool QK8, bool OWN_RAW, typename ARGS>
+hipError_t launch_one(const ARGS &a, int blocks, hipStream_t s)
 {
     static bool configured = false;     // raise the dynamic LDS limit once per instantiation
-    auto kern = attn_mfma_kernel<FP8, MODE, QK8, OWN_RAW>;
+    auto kern = attn_mfma_kernel<FP8, MODE, QK8, OWN_RAW, ARGS>;
     const size_t lds = 4 * HALF_BYTES;      // two K buffers, two V buffers
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1490,6 +1548,16 @@ hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s)
     }
     // the prompt's own causal attention always takes the 16-bit first product
     return fp8 ? launch_one<true, MODE_PREFIX, false, false>(a, a.n_tiles, s) : launch_one<false, MODE_PREFIX, false, false>(a, a.n_tiles, s);
+}
+
+hipError_t launch_attn_carried(const CarriedPrefix &c, hipStream_t s)
+{
+    return c.a.n_tiles > 0 ? launch_one<false, MODE_PREFIX, false, false>(c, c.a.n_tiles, s) : hipSuccess;
+}
+
+hipError_t launch_attn_carried(const CarriedSuffix &c, hipStream_t s)
+{
+    return c.a.n_tiles > 0 ? launch_one<false, MODE_SUFFIX, false, true>(c, c.a.n_tiles, s) : hipSuccess;
 }
 
 }  // namespace sgc

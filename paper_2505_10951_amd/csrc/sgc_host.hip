@@ -825,6 +825,22 @@ int sgc_cache_cluster_pages(const sgc_cache *c, int32_t cluster_id, int32_t *out
     return (int)e.pages.size();
 }
 
+// The tiles of a prefix launch on one XCD: put(k, unit, tile of the unit) for slot k, unit -1 for padding.  A unit's tile t starts at row
+// t * tile rows; descending t, units in dealing order among equals; slot k of XCD x is tile k * 8 + x of the launch.
+}  // extern "C"
+template <typename Put>
+static void for_tiles_of_xcd(const std::vector<int> &units, const std::vector<int> &unit_tiles, size_t slots, Put put)
+{
+    int most = 0;
+    for (int ui : units) most = std::max(most, unit_tiles[ui]);
+    size_t k = 0;
+    for (int t = most - 1; t >= 0; --t)
+        for (int ui : units)
+            if (t < unit_tiles[ui]) put(k++, ui, t);
+    for (; k < slots; ++k) put(k, -1, 0);
+}
+extern "C" {
+
 // ------------------------------------------------------------------------------------------------
 int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int32_t *cluster_ids, int32_t layer,
                                const void *const *dev_q, const void *const *dev_k, const void *const *dev_v,
@@ -940,6 +956,39 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
         for (int ji = 0; ji < (int)jobs.size(); ++ji)
             if (jobs[ji].q)
                 for (int64_t r = 0; r < (int64_t)jobs[ji].prefix_len * g; r += kGenericRows) gtiles.push_back({ji, (int32_t)r});
+    // A small call's tables go with its launches.  (Not where keys are stored alone: the page tables travel beside that, and nothing waits for
+    // them.  Not once a plan has decode steps: those may have to find the device's page tables current.)
+    if (any_q && ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !ctx->decodes && jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages &&
+        slots * kXcd <= CarriedPrefix::kTiles && Hkv <= 1024) {
+        const float2 *rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
+        hipError_t e = hipSuccess;
+        if (!attend_only) {
+            SmallIngest in;
+            in.n_jobs = (int32_t)jobs.size();
+            std::copy(jobs.begin(), jobs.end(), in.jobs);
+            for (const PrefixJob &j : jobs) std::copy(c->cl[j.cluster].pages.begin(), c->cl[j.cluster].pages.end(), in.pages + j.page0);
+            e = launch_small_ingest(c->geom, layer, in, (int)page_job.size(), ctx->p.io_dtype, rope, nullptr, nullptr, 0, nullptr, nullptr, 0, CopyDone{nullptr, 0},
+                                    nullptr, nullptr, s);
+        }
+        if (e == hipSuccess) {
+            CarriedPrefix t;
+            fill_common_args(t.a, ctx, c, layer);
+            t.a.mode = MODE_PREFIX;
+            t.a.n_tiles = (int32_t)(slots * kXcd);
+            for (size_t ji = 0; ji < jobs.size(); ++ji) {
+                const PrefixJob &j = jobs[ji];
+                t.jobs[ji] = {j.q, j.o, j.lse, j.prefix_len, j.page0};
+                std::copy(c->cl[j.cluster].pages.begin(), c->cl[j.cluster].pages.end(), t.pages + j.page0);
+            }
+            for (int x = 0; x < kXcd; ++x)
+                for_tiles_of_xcd(of_xcd[x], unit_tiles, slots, [&](size_t k, int ui, int tile) {
+                    // (a padding tile: one behind the job's last row)
+                    t.tiles[k * kXcd + x] = ui < 0 ? 0x3FFFFu : (uint32_t)units[ui].job << 28 | (uint32_t)units[ui].hk << 18 | (uint32_t)tile;
+                });
+            e = launch_attn_carried(t, s);
+        }
+        return e == hipSuccess ? SGC_OK : fail_hip(ctx, e, "prefix prefill launch");
+    }
     // One block: [jobs][job of each page][tile seeds][generic tiles][chunks] from the host in one copy, then room for the tile records, which
     // are written on the device from the seeds, the jobs and the cache's page table, and for the fp8 ingest's partial maxima.
     const size_t n_tiles = slots * kXcd;
@@ -969,24 +1018,18 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     const int32_t *d_page_job = reinterpret_cast<const int32_t *>(blk.p + jobs_bytes);
     const TileSeed *d_seeds = reinterpret_cast<const TileSeed *>(blk.p + jobs_bytes + pj_bytes);
     const Tile *d_tiles = reinterpret_cast<const Tile *>(blk.p + copied);
-    // a unit's tile t starts at row t * rows_per_tile; descending t, units in dealing order among equals; slot k of XCD x
-    // is tile k * 8 + x of the launch (slots a short list does not fill stay padding tiles: n_rows = 0)
+    // (a padding tile has n_rows = 0)
     TileSeed *hs = reinterpret_cast<TileSeed *>(host + jobs_bytes + pj_bytes);
-    for (int x = 0; x < kXcd && n_tiles > 0; ++x) {
-        int most = 0;
-        for (int ui : of_xcd[x]) most = std::max(most, unit_tiles[ui]);
-        size_t k = 0;
-        for (int t = most - 1; t >= 0; --t)
-            for (int ui : of_xcd[x]) {
-                if (t >= unit_tiles[ui]) continue;
-                const Unit &u = units[ui];
-                const int32_t row0 = t * rows_per_tile;
-                hs[k++ * kXcd + x] = TileSeed{u.job, u.hk, row0,
-                                              (int32_t)std::min<int64_t>(rows_per_tile, (int64_t)jobs[u.job].prefix_len * g - row0),
-                                              0, -1, 0, 0};
+    for (int x = 0; x < kXcd && n_tiles > 0; ++x)
+        for_tiles_of_xcd(of_xcd[x], unit_tiles, slots, [&](size_t k, int ui, int t) {
+            if (ui < 0) {
+                hs[k * kXcd + x] = TileSeed{};
+                return;
             }
-        for (; k < slots; ++k) hs[k * kXcd + x] = TileSeed{};
-    }
+            const Unit &u = units[ui];
+            const int32_t row0 = t * rows_per_tile;
+            hs[k * kXcd + x] = TileSeed{u.job, u.hk, row0, (int32_t)std::min<int64_t>(rows_per_tile, (int64_t)jobs[u.job].prefix_len * g - row0), 0, -1, 0, 0};
+        });
     // One copy for jobs, page jobs, seeds and page tables (which also says that the staging buffer has been read); the tile records
     // are then written by workgroups appended to the ingest launch, or behind the copy when nothing is ingested.
     ExpandArgs x{};
@@ -1184,19 +1227,17 @@ static ExpandArgs plan_expand_args(const sgc_plan *pl, const sgc_cache *c)
 
 // with_tiles: the cache's device tables are current and ordered in front of what comes next on the stream, as a suffix prefill
 // has them; the tile records are then written behind the copy.
-static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
+// cache (may be null): its page tables, if due, go with the same launch.
+static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles, sgc_cache *cache)
 {
     sgc_ctx *ctx = pl->ctx;
     const int want_rows = ctx->use_mfma ? ctx->tile_rows : 0;
-    if (pl->uploaded && pl->tile_rows == want_rows) return SGC_OK;
+    if (pl->uploaded && pl->tile_rows == want_rows) return cache ? cache_sync(cache, s) : SGC_OK;
     plan_free_device(pl);
-    pl->tiles.clear();
-    pl->seeds.clear();
-    pl->tile_rows = 0;
     pl->dtiles.clear();
     pl->dtok.clear();
     if (want_rows > 0) {
-        build_tiles(pl, want_rows);
+        if (pl->tile_rows != want_rows) build_tiles(pl, want_rows);      // (a small call may have built them)
         if (pl->decode_cap > 0) build_decode_tiles(pl, want_rows);
         fill_tile_pt_off(pl, pl->cache);
     }
@@ -1255,7 +1296,9 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     pl->last_stream = s;
     char *host = nullptr;
     int slot = 0;
-    if ((rc = stage_begin(ctx, copied, &host, &slot)) != SGC_OK) return rc;
+    const size_t tables = cache && cache->dirty ? cache_tables_bytes(cache) : 0;
+    if ((rc = stage_begin(ctx, copied + tables, &host, &slot)) != SGC_OK) return rc;
+    if (tables) cache_tables_fill(cache, reinterpret_cast<int32_t *>(host + copied));
     size_t off = 0;
     for (const Piece &p : pieces) {
         *p.dst = pl->d_blob + off;
@@ -1264,7 +1307,8 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
     }
     const ExpandArgs ex = plan_expand_args(pl, pl->cache);
     const bool expand = with_tiles && !pl->tiles.empty();
-    if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s, nullptr, 0, 0, expand ? &ex : nullptr)) != SGC_OK) return rc;
+    if ((rc = stage_commit(ctx, slot, pl->d_blob, copied, s, cache ? cache->d_tables : nullptr, copied, tables, expand ? &ex : nullptr)) != SGC_OK) return rc;
+    if (cache) cache->dirty = false;
     pl->expand_pending = !pl->tiles.empty() && !expand;      // otherwise with the next suffix launch
     if (want_rows > 0 && pl->n_pool_pages > 0) {
         // suffix page pool: 16-bit pages of every query's rotated suffix K and transposed V, for decode steps, projected keys, long
@@ -1285,7 +1329,13 @@ static int plan_upload(sgc_plan *pl, hipStream_t s, bool with_tiles)
 int sgc_plan_upload(sgc_plan *pl, void *hip_stream)
 {
     if (!pl) return fail(nullptr, SGC_EINVAL, "plan is NULL");
-    return plan_upload(pl, static_cast<hipStream_t>(hip_stream), false);
+    // (steps that may not allocate find the page tables on the device as well, also where no prefill of the plan comes first)
+    sgc_cache *c = pl->decode_cap > 0 ? const_cast<sgc_cache *>(pl->cache) : nullptr;
+    if (c) {
+        const int rc = cache_tables_ensure(c);
+        if (rc != SGC_OK) return rc;
+    }
+    return plan_upload(pl, static_cast<hipStream_t>(hip_stream), false, c);
 }
 
 int sgc_plan_get_info(const sgc_plan *pl, sgc_plan_info *out)
@@ -1330,6 +1380,37 @@ static int refresh_tiles(sgc_plan *pl, const sgc_cache *c, hipStream_t s)
     return SGC_OK;
 }
 
+// The tables of a small plan as launch arguments, if they fit and the question tokens' keys are read as given: the tiles are built, on the
+// host alone, the plan is not uploaded, and the cache's device tables are not looked at.
+static bool carry_suffix(sgc_plan *pl, const sgc_cache *c, CarriedSuffix *t)
+{
+    if (pl->sq_len.size() > CarriedSuffix::kQueries || pl->spages.size() > CarriedSuffix::kOwnPages) return false;
+    if (pl->tile_rows != pl->ctx->tile_rows) build_tiles(pl, pl->ctx->tile_rows);
+    if (!pl->own_rows_pay || pl->seeds.size() > CarriedSuffix::kTiles) return false;
+    int n_clusters = 0, n_pages = 0;
+    int32_t index[CarriedSuffix::kClusters];      // cluster ids in use
+    for (size_t i = 0; i < pl->seeds.size(); ++i) {
+        TileSeed &sd = t->tiles[i];
+        sd = pl->seeds[i];
+        if (sd.n_rows == 0) continue;
+        if (sd.sq_hi - sd.sq_lo >= kTileQueries) return false;
+        int k = 0;
+        while (k < n_clusters && index[k] != sd.cluster) ++k;
+        if (k == n_clusters) {
+            const std::vector<int32_t> &pages = c->cl[sd.cluster].pages;
+            if (n_clusters == CarriedSuffix::kClusters || n_pages + pages.size() > CarriedSuffix::kPages) return false;
+            t->clusters[k] = {pl->cl_prefix_len[sd.cluster], n_pages, pl->cl_tok_off[sd.cluster]};
+            std::copy(pages.begin(), pages.end(), t->pages + n_pages);
+            n_pages += (int)pages.size();
+            index[n_clusters++] = sd.cluster;
+        }
+        sd.cluster = k;
+    }
+    for (size_t q = 0; q < pl->sq_len.size(); ++q) t->queries[q] = {pl->sq_tok0[q], pl->sq_src0[q], pl->sq_own0[q]};
+    std::copy(pl->spages.begin(), pl->spages.end(), t->own_pages);
+    return true;
+}
+
 // ------------------------------------------------------------------------------------------------
 int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t layer, const void *dev_q,
                                const void *dev_k, const void *dev_v, void *dev_o, float *dev_lse, void *hip_stream)
@@ -1362,8 +1443,39 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     int rc;
     if ((rc = ensure_rope(ctx, pl->max_position, s)) != SGC_OK) return rc;
-    if ((rc = cache_sync(c, s)) != SGC_OK) return rc;
-    if ((rc = plan_upload(pl, s, true)) != SGC_OK) return rc;
+    const size_t kv_bytes = (size_t)pl->total_tokens * ctx->p.n_kv_heads * ctx->p.head_dim * dtype_bytes(ctx->p.io_dtype);
+    const size_t o_bytes = kv_bytes / ctx->p.n_kv_heads * ctx->p.n_q_heads, lse_bytes = (size_t)pl->total_tokens * ctx->p.n_q_heads * sizeof(float);
+    const bool apart = !overlap(dev_o, o_bytes, dev_k, kv_bytes) && !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
+                       !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
+    hipEvent_t *tev = ctx->ev[ctx->timing_count % sgc_ctx::kTimingRing];
+    if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !pl->uploaded && pl->decode_cap == 0 && !projected && apart) {
+        CarriedSuffix t;
+        if (carry_suffix(pl, c, &t)) {
+            fill_common_args(t.a, ctx, c, layer);
+            t.a.q = dev_q;
+            t.a.k = dev_k;
+            t.a.v = dev_v;
+            t.a.o = dev_o;
+            t.a.lse = dev_lse;
+            t.a.lse_stride = pl->total_tokens;
+            t.a.mode = MODE_SUFFIX;
+            t.a.n_tiles = (int32_t)pl->seeds.size();
+            t.a.own_raw = 1;
+            const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
+            if (timed) {
+                SGC_HIP(ctx, hipEventRecord(tev[0], s));
+                SGC_HIP(ctx, hipEventRecord(tev[1], s));
+            }
+            SGC_HIP(ctx, launch_attn_carried(t, s));
+            if (timed) {
+                SGC_HIP(ctx, hipEventRecord(tev[2], s));
+                ++ctx->timing_count;
+            }
+            return SGC_OK;
+        }
+    }
+    if ((rc = cache_tables_ensure(c)) != SGC_OK) return rc;
+    if ((rc = plan_upload(pl, s, true, c)) != SGC_OK) return rc;
     if ((rc = refresh_tiles(pl, c, s)) != SGC_OK) return rc;
     pl->last_stream = s;
 
@@ -1392,14 +1504,9 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     // The attention kernel takes the question tokens' keys and values as they are given.  They are made into pages first where
     // decode steps will read them, where an output overlaps them (a tile's outputs are stored while others still read), and where
     // that is the faster (long questions).
-    const size_t kv_bytes = (size_t)pl->total_tokens * ctx->p.n_kv_heads * ctx->p.head_dim * dtype_bytes(ctx->p.io_dtype);
-    const size_t o_bytes = kv_bytes / ctx->p.n_kv_heads * ctx->p.n_q_heads, lse_bytes = (size_t)pl->total_tokens * ctx->p.n_q_heads * sizeof(float);
-    const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && pl->own_rows_pay && !overlap(dev_o, o_bytes, dev_k, kv_bytes) &&
-                         !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
-                         !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
+    const bool own_raw = ctx->use_mfma && !skip_ingest && pl->decode_cap == 0 && pl->own_rows_pay && apart;
     a.own_raw = own_raw ? 1 : 0;
     a.spool = pl->d_spool + (pl->decode_cap > 0 ? (size_t)layer * pl->spool_layer_bytes : 0);
-    hipEvent_t *tev = ctx->ev[ctx->timing_count % sgc_ctx::kTimingRing];
     const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
     if (timed) SGC_HIP(ctx, hipEventRecord(tev[0], s));
     // tile records that are due are written by workgroups appended to the ingest launch (they depend on nothing it writes)
@@ -1436,6 +1543,8 @@ int sgc_plan_enable_decode(sgc_plan *pl, int32_t max_new_tokens)
     if (pl->decode_cap == max_new_tokens) return SGC_OK;
     plan_free_device(pl);          // page numbering changes: the device copy is rebuilt at the next upload
     pl->decode_cap = max_new_tokens;
+    pl->tile_rows = 0;
+    ctx->decodes = true;
     layout_suffix_pages(pl);
     return SGC_OK;
 }

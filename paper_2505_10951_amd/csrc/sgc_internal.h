@@ -328,6 +328,40 @@ struct AttnArgs {
     int32_t fp8_first_product;
 };
 
+// ---- small calls: tables with the launch ----------------------------------------------------------------------------------
+// The tables of a small call travel as launch arguments (16-bit caches, matrix-core kernel): nothing is staged, copied or
+// expanded before the attention launch.  One question over a prompt of 411 tokens: four launches become three, 39.5 -> 33.9 us; a prompt of 300
+// tokens attended to behind its projection, with six questions, 148.2 -> 143.0.  The limits are what fits: a launch's arguments are 4 KiB at most, the runtime's own 256 bytes among them.
+constexpr size_t kLaunchArgsBytes = 4096, kRuntimeArgsBytes = 256;
+struct CarriedJob {
+    const void *q;
+    void *o;
+    float *lse;
+    int32_t prefix_len;
+    int32_t page0;               // its first entry of pages
+};
+struct CarriedPrefix {
+    static constexpr int kJobs = 6, kTiles = 256, kPages = 480;
+    AttnArgs a;
+    CarriedJob jobs[kJobs];
+    uint32_t tiles[kTiles];      // job << 28 | KV head << 18 | number of the tile in its (job, KV head)
+    int32_t pages[kPages];
+};
+struct CarriedSuffix {
+    static constexpr int kTiles = 40, kQueries = 48, kOwnPages = 40, kClusters = 6, kPages = 144;
+    AttnArgs a;
+    struct Cluster {
+        int32_t prefix_len, page0, tok_base;
+    };
+    Cluster clusters[kClusters];
+    TileSeed tiles[kTiles];      // (cluster: index into clusters)
+    TileQuery queries[kQueries];
+    SuffixPage own_pages[kOwnPages];
+    int32_t pages[kPages];
+};
+static_assert(sizeof(CarriedPrefix) <= kLaunchArgsBytes - kRuntimeArgsBytes && sizeof(CarriedSuffix) <= kLaunchArgsBytes - kRuntimeArgsBytes,
+              "launch arguments");
+
 }  // namespace sgc
 
 // ---- host objects behind the opaque handles --------------------------------------------------
@@ -361,6 +395,7 @@ struct sgc_ctx {
     bool timing = false;            // record events around the suffix launch's kernels
     int timing_period = 1;          // ... of every timing_period-th suffix launch
     uint64_t timing_launches = 0;   // suffix launches since timing was switched on
+    bool decodes = false;           // some plan has decode steps: a prompt's call keeps the device's page tables current
     // the last kTimingRing timed suffix launches: events before ingest, between, after attention
     static constexpr int kTimingRing = 128;
     hipEvent_t ev[kTimingRing][3] = {};
@@ -491,13 +526,14 @@ struct SmallIngestArgs {
 // runtime's own 256 bytes among them (prompts of 890 tokens each; a job takes the room of 18 pages).  It stays the faster to the end: 640 pages cached 18.4 us, by the
 // general ingest 21.6.  An fp8 ingest is two launches, the first of which (the maxima) needs the tables as well: it waits
 // for their copy.
-constexpr size_t kLaunchArgsBytes = 4096, kSmallIngestOtherArgs = 544;
+constexpr size_t kSmallIngestOtherArgs = 544;
 using SmallIngest = SmallIngestArgs<12, (kLaunchArgsBytes - kSmallIngestOtherArgs - 12 * sizeof(PrefixJob) - 8) / 4>;
 using SmallIngestShort = SmallIngestArgs<2, 64>;
 struct CopyDone;
 // Whether it covers a call, and which tables expand has to name then: the staged ones or the device's.
 enum SmallIngestUse { SMALL_INGEST_NO, SMALL_INGEST_STAGED_TABLES, SMALL_INGEST_COPIED_TABLES };
 SmallIngestUse small_ingest_use(const PoolGeom &g, int n_jobs, int n_pages, int n_tiles, size_t staged_bytes);
+// (bytes 0: there is nothing to copy and nothing to write, the attention launch's tables go with it)
 hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &small, int n_pages, int io_dtype, const float2 *rope, void *dst,
                                const void *mapped_src, size_t bytes, void *dst2, const void *mapped_src2, size_t bytes2, const CopyDone &done,
                                int *n_words, const ExpandArgs *expand, hipStream_t s);
@@ -538,5 +574,8 @@ hipError_t launch_zero_last_pages(char *spool, const int32_t *d_sq_len, const in
 // Rows per workgroup of the MFMA attention kernel.
 int mfma_tile_rows();
 hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s);
+// The same with the tables in the launch's arguments (c.a.n_tiles of them).
+hipError_t launch_attn_carried(const CarriedPrefix &c, hipStream_t s);
+hipError_t launch_attn_carried(const CarriedSuffix &c, hipStream_t s);
 
 }  // namespace sgc

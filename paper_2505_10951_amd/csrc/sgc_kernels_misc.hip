@@ -1342,9 +1342,9 @@ hipError_t launch_small_ingest(const PoolGeom &g, int layer, const SmallIngest &
     const CopyPiece a = copy_piece_of(dst, mapped_src, bytes), b = copy_piece_of(dst2, mapped_src2, bytes2);
     ExpandArgs ex{};
     if (expand) ex = *expand;
-    const auto [copy_groups, expand_groups] = small_groups(ex.n, bytes + bytes2);
-    *n_words = copy_groups + expand_groups;
-    const int columns = (*n_words + g.n_kv_heads - 1) / g.n_kv_heads;
+    const auto [copy_groups, expand_groups] = bytes + bytes2 > 0 ? small_groups(ex.n, bytes + bytes2) : SmallGroups{0, 0};
+    if (n_words) *n_words = copy_groups + expand_groups;
+    const int columns = (copy_groups + expand_groups + g.n_kv_heads - 1) / g.n_kv_heads;
     // (arguments are copied with every launch: a short prompt does not send the 3.6 KB that ten may need: 39.3 us with them, 39.0 without)
     if (small.n_jobs <= SmallIngestShort::kJobs && n_pages <= SmallIngestShort::kPages) {
         SmallIngestShort few;

@@ -1,0 +1,93 @@
+"""Small calls whose tables travel with the launches: the same bits as the calls that copy their tables to the device first, at the
+edges of what a launch's arguments hold (6 clusters; prompts: 480 pages, 256 tiles; questions: 144 pages of prompts, 40 own pages,
+48 queries, 40 tiles, 4 queries a tile) and just past them, where both sides copy."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2505_10951_amd import workloads
+from paper_2505_10951_amd.harness import Session, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _pass(w, copied):
+    """Prompts' outputs and LSE, the batch's outputs and LSE; copied: every table goes through the device's copies."""
+    with Session(w) as s:
+        for c in range(w.n_clusters):
+            s.alloc_cluster(c)
+        if copied:
+            s.assign()
+            s.enable_decode(1)
+        prompts = s.prefix_prefill_batched(list(range(w.n_clusters)), 0, with_q=True, want_lse=True)
+        s.assign()
+        if copied:
+            s.upload_plan()
+        lse = torch.zeros((w.n_q_heads, w.total_suffix_tokens), device="cuda:0")
+        o = s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()), dlse=lse)
+        again = s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
+        torch.cuda.synchronize()
+        assert torch.equal(o, again)
+        return [t.clone() for pair in prompts for t in pair if t is not None and t.numel()] + [o.clone(), lse]
+
+
+def _check(w):
+    for a, b in zip(_pass(w, False), _pass(w, True)):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix", [
+    (32, 8, [411], [1], (23, 23)),
+    (8, 2, [1, 16, 17, 0, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30)),
+    (8, 2, [5, 9, 30, 1, 64, 65, 66], [1] * 7, (1, 9)),                     # seven clusters
+    (4, 2, [2304], [2], (30, 40)), (4, 2, [2305], [2], (30, 40)),           # 144 pages of prompts, 145
+    (2, 2, [7680], [1], (3, 3)), (2, 2, [3840, 3841], [1, 0], (3, 3)),      # 480 pages, 481; 120 tiles
+    (32, 8, [1024], [1], (9, 9)), (32, 8, [1025], [1], (9, 9)),             # 256 tiles, 264
+    (8, 8, [100], [48], (5, 8)), (8, 8, [100], [49], (5, 8)),               # more than four queries a tile
+    (32, 8, [70], [40], (1, 2)), (64, 8, [70], [20], (17, 32)), (64, 8, [70], [21], (17, 32)),      # 40 own pages, 42
+    (32, 8, [300], [10], (16, 16)), (32, 8, [300], [11], (16, 16)),         # five tiles a KV head, six
+])
+def test_same_bits_as_copied_tables(hq, hkv, prefix, sizes, suffix):
+    _check(workloads.custom("carried", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=prefix,
+                            cluster_sizes=sizes, suffix_range=suffix, seed=len(prefix) + sum(sizes)))
+
+
+def test_captured_calls_and_calls_that_copy_behind_them():
+    """Replays take the tables of the calls that were captured; a batch that is too large behind a prompt whose tables were carried
+    brings the page tables to the device itself."""
+    w = workloads.custom("carried_graph", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[300, 90],
+                         cluster_sizes=[2, 3], suffix_range=(4, 20), seed=3)
+    big = workloads.custom("carried_big", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[300, 90],
+                           cluster_sizes=[60, 40], suffix_range=(4, 20), seed=4)
+    with Session(w) as s:
+        for c in range(2):
+            s.alloc_cluster(c)
+        s.prefix_prefill_batched([0, 1], 0, with_q=True)
+        s.assign()
+        q, k, v = (to_device(x, "bf16") for x in w.suffix_qkv())
+        o = torch.empty_like(q)
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            s.suffix_prefill(q, k, v, do=o)
+        side.synchronize()
+        first = o.clone()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            s.suffix_prefill(q, k, v, do=o)
+        for step in range(3):
+            q.copy_(to_device(w.suffix_qkv()[0], "bf16") * (1.0 + step))
+            o.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            eager = s.suffix_prefill(q, k, v)
+            torch.cuda.synchronize()
+            assert torch.equal(o, eager) and (step > 0 or torch.equal(o, first))
+        bq, bk, bv = (to_device(x, "bf16") for x in big.suffix_qkv())
+        s.assign(big.labels, big.suffix_len)
+        got = s.suffix_prefill(bq, bk, bv).clone()
+        s.upload_plan()
+        s.assign(big.labels, big.suffix_len)
+        s.upload_plan()
+        assert torch.equal(got, s.suffix_prefill(bq, bk, bv))
+        torch.cuda.synchronize()
