@@ -958,19 +958,22 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
                 for (int64_t r = 0; r < (int64_t)jobs[ji].prefix_len * g; r += kGenericRows) gtiles.push_back({ji, (int32_t)r});
     // A small call's tables go with its launches.  (Not where keys are stored alone: the page tables travel beside that, and nothing waits for
     // them.  Not once a plan has decode steps: those may have to find the device's page tables current.)
-    if (any_q && ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !ctx->decodes && jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages &&
-        slots * kXcd <= CarriedPrefix::kTiles && Hkv <= 1024) {
+    const bool carried = any_q && !c->d_scale && !ctx->decodes &&
+                         (ctx->use_mfma ? jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles
+                                        : jobs.size() <= CarriedGeneric::kUnits && page_job.size() <= CarriedGeneric::kPages && gtiles.size() <= CarriedGeneric::kTiles);
+    if (carried) {
         const float2 *rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
         hipError_t e = hipSuccess;
+        auto put_pages = [&](const PrefixJob &j, int32_t *pages) { std::copy(c->cl[j.cluster].pages.begin(), c->cl[j.cluster].pages.end(), pages + j.page0); };
         if (!attend_only) {
             SmallIngest in;
             in.n_jobs = (int32_t)jobs.size();
             std::copy(jobs.begin(), jobs.end(), in.jobs);
-            for (const PrefixJob &j : jobs) std::copy(c->cl[j.cluster].pages.begin(), c->cl[j.cluster].pages.end(), in.pages + j.page0);
+            for (const PrefixJob &j : jobs) put_pages(j, in.pages);
             e = launch_small_ingest(c->geom, layer, in, (int)page_job.size(), ctx->p.io_dtype, rope, nullptr, nullptr, 0, nullptr, nullptr, 0, CopyDone{nullptr, 0},
                                     nullptr, nullptr, s);
         }
-        if (e == hipSuccess) {
+        if (e == hipSuccess && ctx->use_mfma) {
             CarriedPrefix t;
             fill_common_args(t.a, ctx, c, layer);
             t.a.mode = MODE_PREFIX;
@@ -978,7 +981,7 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             for (size_t ji = 0; ji < jobs.size(); ++ji) {
                 const PrefixJob &j = jobs[ji];
                 t.jobs[ji] = {j.q, j.o, j.lse, j.prefix_len, j.page0};
-                std::copy(c->cl[j.cluster].pages.begin(), c->cl[j.cluster].pages.end(), t.pages + j.page0);
+                put_pages(j, t.pages);
             }
             for (int x = 0; x < kXcd; ++x)
                 for_tiles_of_xcd(of_xcd[x], unit_tiles, slots, [&](size_t k, int ui, int tile) {
@@ -986,6 +989,17 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
                     t.tiles[k * kXcd + x] = ui < 0 ? 0x3FFFFu : (uint32_t)units[ui].job << 28 | (uint32_t)units[ui].hk << 18 | (uint32_t)tile;
                 });
             e = launch_attn_carried(t, s);
+        } else if (e == hipSuccess) {
+            CarriedGeneric t;
+            fill_common_args(t.a, ctx, c, layer);
+            t.a.mode = MODE_PREFIX;
+            for (size_t ji = 0; ji < jobs.size(); ++ji) {
+                const PrefixJob &j = jobs[ji];
+                t.units[ji] = {j.q, j.o, j.lse, j.prefix_len, j.page0, 0, 0};
+                put_pages(j, t.pages);
+            }
+            for (size_t i = 0; i < gtiles.size(); ++i) t.tiles[i] = {gtiles[i].row0, (uint8_t)gtiles[i].unit, 0, 0, 0};
+            e = launch_attn_generic(t, (int)gtiles.size(), s);
         }
         return e == hipSuccess ? SGC_OK : fail_hip(ctx, e, "prefix prefill launch");
     }
@@ -1411,6 +1425,31 @@ static bool carry_suffix(sgc_plan *pl, const sgc_cache *c, CarriedSuffix *t)
     return true;
 }
 
+// The same for the generic kernel; returns the number of tiles, 0 if they do not fit.
+static int carry_generic(sgc_plan *pl, const sgc_cache *c, CarriedGeneric *t)
+{
+    const int g = pl->ctx->p.n_q_heads / pl->ctx->p.n_kv_heads;
+    if (pl->sq_len.size() > CarriedGeneric::kQueries) return 0;
+    int n_units = 0, n_pages = 0, n_tiles = 0;
+    for (int k = 0; k < pl->n_clusters; ++k) {
+        const int32_t tok0 = pl->cl_tok_off[k], tokens = pl->cl_tok_off[k + 1] - tok0;
+        if (tokens == 0) continue;
+        const std::vector<int32_t> &pages = c->cl[k].pages;
+        const int64_t tiles = ((int64_t)tokens * g + kGenericRows - 1) / kGenericRows;
+        if (n_units == CarriedGeneric::kUnits || n_pages + pages.size() > CarriedGeneric::kPages || n_tiles + tiles > CarriedGeneric::kTiles) return 0;
+        t->units[n_units] = {nullptr, nullptr, nullptr, pl->cl_prefix_len[k], n_pages, tok0, tokens};
+        std::copy(pages.begin(), pages.end(), t->pages + n_pages);
+        n_pages += (int)pages.size();
+        for (int32_t r = 0; r < tokens * g; r += kGenericRows) {
+            const int32_t last = std::min(r + kGenericRows, tokens * g) - 1;
+            t->tiles[n_tiles++] = {r, (uint8_t)n_units, (uint8_t)pl->tok_sq[tok0 + r / g], (uint8_t)pl->tok_sq[tok0 + last / g], 0};
+        }
+        ++n_units;
+    }
+    for (size_t q = 0; q < pl->sq_len.size(); ++q) t->queries[q] = {pl->sq_tok0[q], pl->sq_src0[q], pl->sq_len[q]};
+    return n_tiles;
+}
+
 // ------------------------------------------------------------------------------------------------
 int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t layer, const void *dev_q,
                                const void *dev_k, const void *dev_v, void *dev_o, float *dev_lse, void *hip_stream)
@@ -1448,30 +1487,46 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
     const bool apart = !overlap(dev_o, o_bytes, dev_k, kv_bytes) && !overlap(dev_o, o_bytes, dev_v, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) &&
                        !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
     hipEvent_t *tev = ctx->ev[ctx->timing_count % sgc_ctx::kTimingRing];
+    auto fill_batch = [&](AttnArgs &a) {
+        a.q = dev_q;
+        a.k = dev_k;
+        a.v = dev_v;
+        a.o = dev_o;
+        a.lse = dev_lse;
+        a.lse_stride = pl->total_tokens;
+        a.mode = MODE_SUFFIX;
+    };
+    // a call that is one launch, between the events that time it
+    auto attend = [&](auto launch) -> int {
+        const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
+        if (timed) {
+            SGC_HIP(ctx, hipEventRecord(tev[0], s));
+            SGC_HIP(ctx, hipEventRecord(tev[1], s));
+        }
+        SGC_HIP(ctx, launch());
+        if (timed) {
+            SGC_HIP(ctx, hipEventRecord(tev[2], s));
+            ++ctx->timing_count;
+        }
+        return SGC_OK;
+    };
+    if (!ctx->use_mfma && !c->d_scale && ctx->p.kv_dtype != SGC_FP8_E4M3 && !pl->uploaded && !projected) {
+        CarriedGeneric t;
+        const int n_tiles = carry_generic(pl, c, &t);
+        if (n_tiles > 0) {
+            fill_common_args(t.a, ctx, c, layer);
+            fill_batch(t.a);
+            return attend([&]() { return launch_attn_generic(t, n_tiles, s); });
+        }
+    }
     if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !pl->uploaded && pl->decode_cap == 0 && !projected && apart) {
         CarriedSuffix t;
         if (carry_suffix(pl, c, &t)) {
             fill_common_args(t.a, ctx, c, layer);
-            t.a.q = dev_q;
-            t.a.k = dev_k;
-            t.a.v = dev_v;
-            t.a.o = dev_o;
-            t.a.lse = dev_lse;
-            t.a.lse_stride = pl->total_tokens;
-            t.a.mode = MODE_SUFFIX;
+            fill_batch(t.a);
             t.a.n_tiles = (int32_t)pl->seeds.size();
             t.a.own_raw = 1;
-            const bool timed = ctx->timing && ctx->timing_launches++ % (uint64_t)ctx->timing_period == 0;
-            if (timed) {
-                SGC_HIP(ctx, hipEventRecord(tev[0], s));
-                SGC_HIP(ctx, hipEventRecord(tev[1], s));
-            }
-            SGC_HIP(ctx, launch_attn_carried(t, s));
-            if (timed) {
-                SGC_HIP(ctx, hipEventRecord(tev[2], s));
-                ++ctx->timing_count;
-            }
-            return SGC_OK;
+            return attend([&]() { return launch_attn_carried(t, s); });
         }
     }
     if ((rc = cache_tables_ensure(c)) != SGC_OK) return rc;
@@ -1481,13 +1536,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
 
     AttnArgs a;
     fill_common_args(a, ctx, c, layer);
-    a.q = dev_q;
-    a.k = dev_k;
-    a.v = dev_v;
-    a.o = dev_o;
-    a.lse = dev_lse;
-    a.lse_stride = pl->total_tokens;
-    a.mode = MODE_SUFFIX;
+    fill_batch(a);
     a.tiles = pl->d_tiles;
     a.n_tiles = (int32_t)pl->tiles.size();
     a.cl_tok_off = pl->d_cl_tok_off;

@@ -359,7 +359,30 @@ struct CarriedSuffix {
     SuffixPage own_pages[kOwnPages];
     int32_t pages[kPages];
 };
-static_assert(sizeof(CarriedPrefix) <= kLaunchArgsBytes - kRuntimeArgsBytes && sizeof(CarriedSuffix) <= kLaunchArgsBytes - kRuntimeArgsBytes,
+struct CarriedGeneric {          // either mode, for the generic kernel
+    static constexpr int kUnits = 6, kTiles = 160, kQueries = 64, kPages = 240;
+    AttnArgs a;
+    struct Unit {                // a prompt, or a cluster of the batch
+        const void *q;
+        void *o;
+        float *lse;
+        int32_t prefix_len, page0;
+        int32_t tok_base, n_tokens;      // (of the batch)
+    };
+    Unit units[kUnits];
+    struct Tile {
+        int32_t row0;
+        uint8_t unit, sq_lo, sq_hi, unused;
+    };
+    Tile tiles[kTiles];
+    struct Query {
+        int32_t tok0, src0, len;
+    };
+    Query queries[kQueries];
+    int32_t pages[kPages];
+};
+static_assert(sizeof(CarriedPrefix) <= kLaunchArgsBytes - kRuntimeArgsBytes && sizeof(CarriedSuffix) <= kLaunchArgsBytes - kRuntimeArgsBytes &&
+                  sizeof(CarriedGeneric) <= kLaunchArgsBytes - kRuntimeArgsBytes,
               "launch arguments");
 
 }  // namespace sgc
@@ -548,6 +571,7 @@ hipError_t launch_suffix_ingest(const AttnArgs &a, int n_spages, const ExpandArg
                                 hipStream_t s);
 
 hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s);
+hipError_t launch_attn_generic(const CarriedGeneric &c, int n_gtiles, hipStream_t s);
 // Decode, per (query, head): attention over the query's own keys (the step's new token was appended to the suffix
 // pages by the cached-part launch before) merged with the cached-prefix part.  head_dim 128, bf16.
 hipError_t launch_decode_own_keys(const DecodeArgs &d, hipStream_t s);

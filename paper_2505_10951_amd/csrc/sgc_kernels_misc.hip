@@ -9,6 +9,8 @@
 
 #include <algorithm>
 
+#include <type_traits>
+
 #include "sgc_internal.h"
 #include "sgc_own_keys.h"
 
@@ -1046,16 +1048,21 @@ __device__ inline void load_rotated_quarter(const void *base, int64_t row, int d
     }
 }
 
-template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
+__device__ __forceinline__ const AttnArgs &generic_args(const AttnArgs &a) { return a; }
+__device__ __forceinline__ const AttnArgs &generic_args(const CarriedGeneric &c) { return c.a; }
+
+// ARGS: AttnArgs, or CarriedGeneric, whose tables are read where they arrive, among the launch's arguments.
+template <int D, int NW, typename ARGS>
+__global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
 {
+    constexpr bool CARRIED = std::is_same_v<ARGS, CarriedGeneric>;
+    const AttnArgs &a = generic_args(args);
     constexpr int NQ = D / 4, NB = D / 16, LD = D + 4;
     __shared__ __attribute__((aligned(16))) float o_s[NW][16][LD];
     __shared__ float m_s[NW][16], l_s[NW][16];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int j = lane & 15, q = lane >> 4;
     const int Hq = a.n_q_heads, Hkv = a.n_kv_heads, g = a.group;
-    const GenericTile t = a.gtiles[blockIdx.x];
     const int hk = blockIdx.y;
 
     // ---- the lane's row (rows past the end repeat the last one)
@@ -1063,14 +1070,41 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     void *o_base = a.o;
     float *lse_base = a.lse;
     int64_t lse_stride = a.lse_stride;
-    int cluster = t.unit, P, n_rows, tok_base = 0;
-    if (a.mode == MODE_SUFFIX) {
+    int cluster = 0, P, n_rows, row0, tok_base = 0;
+    int t_sq_lo = 0, t_sq_hi = 0;            // (carried) the tile's queries
+    const int32_t *pt;
+    if constexpr (CARRIED) {
+        const CarriedGeneric::Tile t = args.tiles[blockIdx.x];
+        const CarriedGeneric::Unit &u = args.units[t.unit];
+        row0 = t.row0;
+        t_sq_lo = t.sq_lo;
+        t_sq_hi = t.sq_hi;
+        P = u.prefix_len;
+        pt = args.pages + u.page0;
+        if (a.mode == MODE_SUFFIX) {
+            tok_base = u.tok_base;
+            n_rows = u.n_tokens * g;
+        } else {
+            n_rows = P * g;
+            q_base = u.q;
+            o_base = u.o;
+            lse_base = u.lse;
+            lse_stride = P;
+        }
+    } else if (a.mode == MODE_SUFFIX) {
+        const GenericTile t = a.gtiles[blockIdx.x];
+        cluster = t.unit;
+        row0 = t.row0;
+        pt = a.page_table + a.cl_pt_off[cluster];
         P = a.cl_prefix_len[cluster];
         tok_base = a.cl_tok_off[cluster];
         n_rows = (a.cl_tok_off[cluster + 1] - tok_base) * g;
     } else {
+        const GenericTile t = a.gtiles[blockIdx.x];
         const PrefixJob &job = a.jobs[t.unit];
+        row0 = t.row0;
         cluster = job.cluster;
+        pt = a.page_table + a.cl_pt_off[cluster];
         P = job.prefix_len;
         n_rows = P * g;
         q_base = job.q;
@@ -1079,9 +1113,24 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
         lse_stride = P;
     }
     auto row_of = [&](int i, int &head, int &src, int &qpos, int &sq) {
-        const int r = min(t.row0 + i, n_rows - 1), tk = r / g;
+        const int r = min(row0 + i, n_rows - 1), tk = r / g;
         head = hk * g + (r - tk * g);
-        if (a.mode == MODE_SUFFIX) {
+        if (CARRIED && a.mode == MODE_SUFFIX) {
+            if constexpr (CARRIED) {
+                const int tok = tok_base + tk;
+                CarriedGeneric::Query mine = args.queries[t_sq_lo];
+                sq = t_sq_lo;
+                for (int k = t_sq_lo + 1; k <= t_sq_hi; ++k) {
+                    const CarriedGeneric::Query other = args.queries[k];
+                    if (tok >= other.tok0) {
+                        mine = other;
+                        sq = k;
+                    }
+                }
+                qpos = tok - mine.tok0;
+                src = mine.src0 + qpos;
+            }
+        } else if (a.mode == MODE_SUFFIX) {
             src = a.tok_src[tok_base + tk];
             qpos = a.tok_qpos[tok_base + tk];
             sq = a.tok_sq[tok_base + tk];
@@ -1175,7 +1224,6 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     };
 
     // ---- cached keys: a block is a page
-    const int32_t *pt = a.page_table + a.cl_pt_off[cluster];
     const int kvd = a.pool.kv_dtype;
     auto fetch = [&](int b, float (&kf)[NQ], float (&vf)[NB][4]) {
         const int page = pt[b];
@@ -1210,8 +1258,16 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     if (a.mode == MODE_SUFFIX) {
         int turn = n_blocks;
         for (int si = sq_lo; si <= sq_hi; ++si) {
-            const int n_own = si == sq_hi ? last_qpos + 1 : a.sq_len[si];
-            const int64_t src0 = a.sq_src0[si];
+            int len, first;
+            if constexpr (CARRIED) {
+                len = args.queries[si].len;
+                first = args.queries[si].src0;
+            } else {
+                len = a.sq_len[si];
+                first = a.sq_src0[si];
+            }
+            const int n_own = si == sq_hi ? last_qpos + 1 : len;
+            const int64_t src0 = first;
             for (int b = 0; b * 16 < n_own; ++b, ++turn) {
                 if (turn % NW != wave) continue;
                 float kf[NQ], vf[NB][4];
@@ -1239,7 +1295,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(AttnArgs a)
     __syncthreads();
     const int i = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * NB;         // row i, channels c0 .. c0 + NB - 1
     if (i >= 16) return;
-    if (t.row0 + i >= n_rows) return;
+    if (row0 + i >= n_rows) return;
     row_of(i, head, src, qpos, sq);
     float M = m_s[0][i];
 #pragma unroll
@@ -1472,15 +1528,18 @@ hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pa
     return hipGetLastError();
 }
 
-hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s)
+template <typename ARGS>
+static hipError_t launch_generic(const ARGS &args, const AttnArgs &a, int n_gtiles, hipStream_t s)
 {
     if (n_gtiles <= 0) return hipSuccess;
     const dim3 grid(n_gtiles, a.n_kv_heads);
     if (a.head_dim == 64)
-        hipLaunchKernelGGL((attn_generic_kernel<64, 8>), grid, dim3(512), 0, s, a);
+        hipLaunchKernelGGL((attn_generic_kernel<64, 8, ARGS>), grid, dim3(512), 0, s, args);
     else
-        hipLaunchKernelGGL((attn_generic_kernel<128, 4>), grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((attn_generic_kernel<128, 4, ARGS>), grid, dim3(256), 0, s, args);
     return hipGetLastError();
 }
+hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s) { return launch_generic(a, a, n_gtiles, s); }
+hipError_t launch_attn_generic(const CarriedGeneric &c, int n_gtiles, hipStream_t s) { return launch_generic(c, c.a, n_gtiles, s); }
 
 }  // namespace sgc

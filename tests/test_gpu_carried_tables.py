@@ -1,6 +1,6 @@
 """Small calls whose tables travel with the launches: the same bits as the calls that copy their tables to the device first, at the
 edges of what a launch's arguments hold (6 clusters; prompts: 480 pages, 256 tiles; questions: 144 pages of prompts, 40 own pages,
-48 queries, 40 tiles, 4 queries a tile) and just past them, where both sides copy."""
+48 queries, 40 tiles, 4 queries a tile; generic kernel: 240 pages, 160 tiles, 64 queries) and just past them, where both sides copy."""
 import numpy as np
 import pytest
 
@@ -91,3 +91,33 @@ def test_captured_calls_and_calls_that_copy_behind_them():
         s.upload_plan()
         assert torch.equal(got, s.suffix_prefill(bq, bk, bv))
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("io,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix", [
+    (4, 4, [192, 256], [8, 8], (16, 32)),
+    (8, 2, [1, 16, 0, 17, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30)),
+    (4, 2, [300], [64], (1, 9)), (4, 2, [300], [65], (1, 9)),                    # 64 queries, 65
+    (4, 1, [3840], [1], (640, 640)), (4, 1, [3841], [1], (641, 641)),            # 240 pages and 160 tiles, and past both
+    (16, 16, [40, 7, 1], [5, 20, 0], (0, 4)),                                    # queries without tokens, many in a tile
+])
+def test_generic_kernel_same_bits_as_copied_tables(io, d, hq, hkv, prefix, sizes, suffix):
+    """Prompts: alone against in a call with a prompt of 300 pages, which copies its tables; batch: against an uploaded plan."""
+    w = workloads.custom("carried_generic", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rope_base=10000.0, io_dtype=io, kv_dtype=io,
+                         prefix_len=prefix + [4800], cluster_sizes=sizes + [0], suffix_range=suffix, seed=len(prefix) + sum(sizes))
+    n = len(prefix)
+    out = []
+    for copied in (False, True):
+        with Session(w) as s:
+            for c in range(n + 1):
+                s.alloc_cluster(c)
+            prompts = s.prefix_prefill_batched(list(range(n + 1 if copied else n)), 0, with_q=True, want_lse=True)[:n]
+            s.assign()
+            if copied:
+                s.upload_plan()
+            lse = torch.zeros((hq, w.total_suffix_tokens), device="cuda:0")
+            o = s.suffix_prefill(*(to_device(x, io) for x in w.suffix_qkv()), dlse=lse)
+            torch.cuda.synchronize()
+            out.append([t.clone() for pair in prompts for t in pair if t.numel()] + [o.clone(), lse])
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
