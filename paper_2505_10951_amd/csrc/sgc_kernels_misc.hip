@@ -1052,7 +1052,7 @@ __device__ __forceinline__ const AttnArgs &generic_args(const AttnArgs &a) { ret
 __device__ __forceinline__ const AttnArgs &generic_args(const CarriedGeneric &c) { return c.a; }
 
 // ARGS: AttnArgs, or CarriedGeneric, whose tables are read where they arrive, among the launch's arguments.
-template <int D, int NW, typename ARGS>
+template <int D, int NW, int IO, int KV, typename ARGS>
 __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
 {
     constexpr bool CARRIED = std::is_same_v<ARGS, CarriedGeneric>;
@@ -1145,10 +1145,10 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
     const int n_cache = a.mode == MODE_SUFFIX ? P : qpos + 1;            // cached keys the row sees
     const int n_blocks = ((a.mode == MODE_SUFFIX ? P : last_qpos + 1) + 15) / 16;
     float qf[NQ];
-    load_rotated_quarter<D>(q_base, ((int64_t)src * Hq + head) * D, a.io_dtype, a.rope, (a.mode == MODE_SUFFIX ? P : 0) + qpos, q, qf);
+    load_rotated_quarter<D>(q_base, ((int64_t)src * Hq + head) * D, IO, a.rope, (a.mode == MODE_SUFFIX ? P : 0) + qpos, q, qf);
 
     float k_scale = 1.f, v_scale = 1.f;
-    if (a.kv_scale) {
+    if (KV == SGC_FP8_E4M3) {
         const float *sc = a.kv_scale + ((int64_t)cluster * a.n_layers + a.layer) * 2 * Hkv;
         k_scale = sc[hk];
         v_scale = sc[Hkv + hk];
@@ -1160,7 +1160,8 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
     // A key that a row does not see has weight 0 in the second product, and 0 x Inf and 0 x NaN are NaN.  Where some row does
     // not see some key, values that are not finite are therefore taken out of the product (vf gets zeros) and added here, to the
     // rows that see their key.
-    auto add_nonfinite = [&](const float (&p)[4], float (&vf)[NB][4], int keep, gen_f32x4 (&sum)[NB]) {
+    // (j and q by value: captured by reference q lived in scratch memory)
+    auto add_nonfinite = [j, q](const float (&p)[4], float (&vf)[NB][4], int keep, gen_f32x4 (&sum)[NB]) {
         for (int qq = 0; qq < 4; ++qq) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -1224,14 +1225,13 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
     };
 
     // ---- cached keys: a block is a page
-    const int kvd = a.pool.kv_dtype;
     auto fetch = [&](int b, float (&kf)[NQ], float (&vf)[NB][4]) {
         const int page = pt[b];
         const char *kp = a.pool.k_part(a.layer, page, hk), *vp = a.pool.v_part(a.layer, page, hk);
 #pragma unroll
-        for (int i = 0; i < NQ; i += 8) load8(kp, k_page_index(j, q * NQ + i), k_elem_type(kvd), kf + i);
+        for (int i = 0; i < NQ; i += 8) load8(kp, k_page_index(j, q * NQ + i), k_elem_type(KV), kf + i);
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) load4(vp, v_page_index(4 * q, 16 * cb + j), kvd, vf[cb]);
+        for (int cb = 0; cb < NB; ++cb) load4(vp, v_page_index(4 * q, 16 * cb + j), KV, vf[cb]);
     };
     {
         float kf[NQ], vf[NB][4];
@@ -1239,7 +1239,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
         for (int b = wave; b < n_blocks; b += NW) {
             float kn[NQ], vn[NB][4];
             fetch(min(b + NW, n_blocks - 1), kn, vn);              // the next block's loads travel meanwhile
-            if (a.kv_scale) {
+            if (KV == SGC_FP8_E4M3) {
 #pragma unroll
                 for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
@@ -1272,12 +1272,12 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
                 if (turn % NW != wave) continue;
                 float kf[NQ], vf[NB][4];
                 const int key = min(16 * b + j, n_own - 1);
-                load_rotated_quarter<D>(a.k, ((src0 + key) * Hkv + hk) * D, a.io_dtype, a.rope, P + key, q, kf);
+                load_rotated_quarter<D>(a.k, ((src0 + key) * Hkv + hk) * D, IO, a.rope, P + key, q, kf);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int64_t vrow = ((src0 + min(16 * b + 4 * q + r, n_own - 1)) * Hkv + hk) * D;
 #pragma unroll
-                    for (int cb = 0; cb < NB; ++cb) vf[cb][r] = load1(a.v, vrow + 16 * cb + j, a.io_dtype);
+                    for (int cb = 0; cb < NB; ++cb) vf[cb][r] = load1(a.v, vrow + 16 * cb + j, IO);
                 }
                 block(kf, vf, a.scale_log2e, sq == si ? qpos + 1 - (16 * b + 4 * q) : 0);
             }
@@ -1312,7 +1312,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
     }
     const float inv = 1.0f / L;
     const int64_t orow = ((int64_t)src * Hq + head) * D + c0;
-    if (a.io_dtype == SGC_F32) {
+    if (IO == SGC_F32) {
 #pragma unroll
         for (int c = 0; c < NB; c += 4)
             *reinterpret_cast<float4 *>(static_cast<float *>(o_base) + orow + c) = make_float4(sum[c] * inv, sum[c + 1] * inv, sum[c + 2] * inv, sum[c + 3] * inv);
@@ -1326,7 +1326,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
         }
     }
     if (lse_base && (threadIdx.x & 15) == 0)
-        lse_base[(int64_t)head * lse_stride + (a.mode == MODE_SUFFIX ? src : qpos)] = (M + log2f(L)) * 0.6931471805599453f;
+        lse_base[(int64_t)head * lse_stride + (a.mode == MODE_SUFFIX ? src + 0 : qpos + 0)] = (M + log2f(L)) * 0.6931471805599453f;
 }
 
 }  // namespace
@@ -1528,16 +1528,26 @@ hipError_t launch_cache_import(const PoolGeom &g, int layer, const int32_t *d_pa
     return hipGetLastError();
 }
 
+template <int IO, int KV, typename ARGS>
+static hipError_t launch_generic(const ARGS &args, const AttnArgs &a, int n_gtiles, hipStream_t s)
+{
+    const dim3 grid(n_gtiles, a.n_kv_heads);
+    if (a.head_dim == 64)
+        hipLaunchKernelGGL((attn_generic_kernel<64, 8, IO, KV, ARGS>), grid, dim3(512), 0, s, args);
+    else
+        hipLaunchKernelGGL((attn_generic_kernel<128, 4, IO, KV, ARGS>), grid, dim3(256), 0, s, args);
+    return hipGetLastError();
+}
 template <typename ARGS>
 static hipError_t launch_generic(const ARGS &args, const AttnArgs &a, int n_gtiles, hipStream_t s)
 {
     if (n_gtiles <= 0) return hipSuccess;
-    const dim3 grid(n_gtiles, a.n_kv_heads);
-    if (a.head_dim == 64)
-        hipLaunchKernelGGL((attn_generic_kernel<64, 8, ARGS>), grid, dim3(512), 0, s, args);
+    if (a.io_dtype == SGC_F32) return launch_generic<SGC_F32, SGC_F32>(args, a, n_gtiles, s);
+    if (a.pool.kv_dtype == SGC_BF16) return launch_generic<SGC_BF16, SGC_BF16>(args, a, n_gtiles, s);
+    if constexpr (std::is_same_v<ARGS, AttnArgs>)
+        return launch_generic<SGC_BF16, SGC_FP8_E4M3>(args, a, n_gtiles, s);
     else
-        hipLaunchKernelGGL((attn_generic_kernel<128, 4, ARGS>), grid, dim3(256), 0, s, args);
-    return hipGetLastError();
+        return hipErrorInvalidValue;          // (no call carries the tables of an fp8 cache)
 }
 hipError_t launch_attn_generic(const AttnArgs &a, int n_gtiles, hipStream_t s) { return launch_generic(a, a, n_gtiles, s); }
 hipError_t launch_attn_generic(const CarriedGeneric &c, int n_gtiles, hipStream_t s) { return launch_generic(c, c.a, n_gtiles, s); }
