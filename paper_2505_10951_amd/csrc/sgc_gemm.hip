@@ -51,12 +51,19 @@ __device__ inline uint32_t pack2(float a, float b)
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// 1 KiB (64 lanes x 16 bytes) from per-lane global addresses to the LDS block at lds (wave-uniform).
-__device__ inline void copy_1k_to_lds(const char *src_lane, char *lds)
+// 1 KiB (64 lanes x 16 bytes) to the LDS block at lds (wave-uniform), from `lane_off` + `off` of the operand.  A buffer load: the address
+// costs no vector instruction, and the compiler does not take it for a flat one, behind which it waits for every LDS read in flight.
+typedef __amdgpu_buffer_rsrc_t Operand;
+__device__ __forceinline__ Operand operand(const void *base, uint32_t bytes)
 {
-    const auto *g = (const __attribute__((address_space(1))) void *)src_lane;
-    auto *l = (__attribute__((address_space(3))) void *)lds;
-    __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
+    const uint64_t at = reinterpret_cast<uint64_t>(base);          // (wave-uniform, which the compiler does not see of a row tile's record)
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));      // (the builtin's int would be sign-extended)
+    const uint64_t u = (uint64_t)hi << 32 | lo;
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(u), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ void copy_1k_to_lds(Operand from, uint32_t lane_off, uint32_t off, char *lds)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)lds, 16, lane_off, off, 0, 0);
 }
 
 // Barrier of a step: at most N of this wavefront's copies are still on their way and all its LDS reads have returned.
@@ -115,9 +122,9 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     // Lane (lr, slot) = (lane / 8, lane % 8) lands at LDS chunk `slot` of row 8 i + lr and therefore fetches the
     // global chunk slot ^ perm(row); rows past the operand's end are clamped (their results are never stored).
     const int lr = lane >> 3, slot = lane & 7;
-    const char *a_base = static_cast<const char *>(t.a);
-    const char *b_base = static_cast<const char *>(g.w) + (int64_t)ct * TN * K * 2;
     const int b_rows = min(TN, N - ct * TN);
+    const Operand a_op = operand(t.a, (uint32_t)rows * (uint32_t)(K * 2));
+    const Operand b_op = operand(static_cast<const char *>(g.w) + (int64_t)ct * TN * K * 2, (uint32_t)b_rows * (uint32_t)(K * 2));
     uint32_t a_off[8], b_off[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -128,16 +135,16 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     }
     // copies [lo, hi) of this wavefront's eight of a slab: contraction step kt, ring slot `to`
     auto copy_a = [&](int kt, int to, auto lo, auto hi) __attribute__((always_inline)) {
-        const char *src = a_base + (uint32_t)kt * (TK * 2);
+        const uint32_t off = (uint32_t)kt * (TK * 2);
         char *as = smem + to * SLAB_BYTES + wave * 8192;
 #pragma unroll
-        for (int i = lo; i < hi; ++i) copy_1k_to_lds(src + a_off[i], as + i * 1024);
+        for (int i = lo; i < hi; ++i) copy_1k_to_lds(a_op, a_off[i], off, as + i * 1024);
     };
     auto copy_b = [&](int kt, int to, auto lo, auto hi) __attribute__((always_inline)) {
-        const char *src = b_base + (uint32_t)kt * (TK * 2);
+        const uint32_t off = (uint32_t)kt * (TK * 2);
         char *bs = smem + to * SLAB_BYTES + wave * 8192;
 #pragma unroll
-        for (int i = lo; i < hi; ++i) copy_1k_to_lds(src + b_off[i], bs + i * 1024);
+        for (int i = lo; i < hi; ++i) copy_1k_to_lds(b_op, b_off[i], off, bs + i * 1024);
     };
 
     // ---- which output this wavefront makes
@@ -458,8 +465,8 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
     const int lr = lane >> 3, slot = lane & 7;
     uint32_t off[T::COPIES];
     constexpr int A_COPIES = T::A_BYTES / 4096;
-    const char *a_base = static_cast<const char *>(t.a);
-    const char *b_base = static_cast<const char *>(g.w) + (int64_t)head0 * K * 2;
+    const Operand a_op = operand(t.a, (uint32_t)rows * (uint32_t)(K * 2));
+    const Operand b_op = operand(static_cast<const char *>(g.w) + (int64_t)head0 * K * 2, 128u * (uint32_t)(K * 2));
 #pragma unroll
     for (int i = 0; i < T::COPIES; ++i) {
         const bool is_a = i < A_COPIES;
@@ -473,9 +480,9 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
 #pragma unroll
         for (int i = 0; i < T::COPIES; ++i) {
             if (i < A_COPIES)
-                copy_1k_to_lds(a_base + (off[i] + k_off), st + wave * (T::A_BYTES / 4) + i * 1024);
+                copy_1k_to_lds(a_op, off[i], k_off, st + wave * (T::A_BYTES / 4) + i * 1024);
             else
-                copy_1k_to_lds(b_base + (off[i] + k_off), st + T::A_BYTES + wave * (T::B_BYTES / 4) + (i - A_COPIES) * 1024);
+                copy_1k_to_lds(b_op, off[i], k_off, st + T::A_BYTES + wave * (T::B_BYTES / 4) + (i - A_COPIES) * 1024);
         }
     };
 
