@@ -277,6 +277,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
             bool store = valid;
             char *dst = nullptr;
             int64_t chunk_stride = 16;
+            const float2 *tab = nullptr;                         // (to_pages) the rotation's entries at the token's position
             if (to_pages) {
                 int page, slot16, pos;
                 if (g.kv_dest == 0) {
@@ -293,24 +294,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                 }
                 dst = g.kv_base + (int64_t)page * g.page_bytes + (int64_t)hk * g.part_bytes + slot16 * 16;
                 chunk_stride = 256;
-                if (g.rope) {
-                    const float2 *tab = g.rope + (int64_t)(valid ? pos : 0) * (HD / 2);
-#pragma unroll
-                    for (int pi = 0; pi < 2; ++pi)
-#pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) {
-                            const float4 *cs = reinterpret_cast<const float4 *>(tab + 32 * pi + 8 * q4 + 4 * h);
-                            const float4 c01 = cs[0], c23 = cs[1];
-                            const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                float x1 = acc[pi][qj][4 * q4 + e], x2 = acc[pi + 2][qj][4 * q4 + e];
-                                rotate_pair(x1, x2, co[e], si[e]);
-                                acc[pi][qj][4 * q4 + e] = x1;
-                                acc[pi + 2][qj][4 * q4 + e] = x2;
-                            }
-                        }
-                }
+                if (g.rope) tab = g.rope + (int64_t)(valid ? pos : 0) * (HD / 2);
             } else if (kind == 0) {
                 store = valid && t.c != nullptr;
                 dst = static_cast<char *>(t.c) + ((int64_t)i * g.ldc + col0) * 2;
@@ -318,26 +302,47 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                 char *base = static_cast<char *>(kind == 1 ? t.ck : t.cv);
                 dst = base + ((int64_t)i * (g.n_kv_heads * HD) + hk * HD) * 2;
             }
+            // registers 8 u .. 8 u + 3 are features 16 u + 4 h + 0..3, registers 8 u + 4 .. + 7 features 16 u + 8 + 4 h + 0..3; after the
+            // swap between the two 32-lane halves lane h holds the eight consecutive features 16 u + 8 h .. + 7.  Accumulators pi and
+            // pi + 2 hold the rotation's partners.  Piece by piece, behind a scheduling barrier each: taken together, the accumulators'
+            // copies in ordinary registers did not fit and 80 were spilled.  Llama-3-8B's layer of 16 x 448 rows: 1 957 -> 1 942 us.
+            auto put = [&](const float (&v)[8], int pi, int u) __attribute__((always_inline)) {
+                float x[8];
 #pragma unroll
-            for (int pi = 0; pi < 4; ++pi)
+                for (int e = 0; e < 8; ++e) x[e] = valid ? v[e] : 0.f;
+                // keys that go straight into pages are binary16 there; everything else is bf16
+                const uint32_t a0 = to_pages ? pack2_f16(x[0], x[1]) : pack2(x[0], x[1]);
+                const uint32_t a1 = to_pages ? pack2_f16(x[2], x[3]) : pack2(x[2], x[3]);
+                const uint32_t b0 = to_pages ? pack2_f16(x[4], x[5]) : pack2(x[4], x[5]);
+                const uint32_t b1 = to_pages ? pack2_f16(x[6], x[7]) : pack2(x[6], x[7]);
+                const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+                const uint4 out = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                const int chunk = 4 * pi + 2 * u + h;
+                if (store) *reinterpret_cast<uint4 *>(dst + chunk * chunk_stride) = out;
+            };
+#pragma unroll
+            for (int pi = 0; pi < 2; ++pi)
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    // registers 8 u .. 8 u + 3 are features 16 u + 4 h + 0..3, registers 8 u + 4 .. + 7 features
-                    // 16 u + 8 + 4 h + 0..3; after the swap between the two 32-lane halves lane h holds the eight
-                    // consecutive features 16 u + 8 h .. + 7
-                    float x[8];
+                    float x1[8], x2[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = valid ? acc[pi][qj][8 * u + e] : 0.f;
-                    // keys that go straight into pages are binary16 there; everything else is bf16
-                    const uint32_t a0 = to_pages ? pack2_f16(x[0], x[1]) : pack2(x[0], x[1]);
-                    const uint32_t a1 = to_pages ? pack2_f16(x[2], x[3]) : pack2(x[2], x[3]);
-                    const uint32_t b0 = to_pages ? pack2_f16(x[4], x[5]) : pack2(x[4], x[5]);
-                    const uint32_t b1 = to_pages ? pack2_f16(x[6], x[7]) : pack2(x[6], x[7]);
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-                    const uint4 out = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                    const int chunk = 4 * pi + 2 * u + h;
-                    if (store) *reinterpret_cast<uint4 *>(dst + chunk * chunk_stride) = out;
+                    for (int e = 0; e < 8; ++e) {
+                        x1[e] = acc[pi][qj][8 * u + e];
+                        x2[e] = acc[pi + 2][qj][8 * u + e];
+                    }
+                    if (tab)
+#pragma unroll
+                        for (int q4 = 0; q4 < 2; ++q4) {
+                            const float4 *cs = reinterpret_cast<const float4 *>(tab + 32 * pi + 8 * (2 * u + q4) + 4 * h);
+                            const float4 c01 = cs[0], c23 = cs[1];
+                            const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) rotate_pair(x1[4 * q4 + e], x2[4 * q4 + e], co[e], si[e]);
+                        }
+                    put(x1, pi, u);
+                    put(x2, pi + 2, u);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
         }
     } else {
