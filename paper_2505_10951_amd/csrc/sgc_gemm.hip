@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "sgc_internal.h"
@@ -77,9 +78,146 @@ __device__ __forceinline__ void step_barrier()
     asm volatile("" ::: "memory");
 }
 
-template <bool QKV>
-__global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
+// Row tile rt of the launch; ARGS: GemmArgs, or GemmCarried, whose tiles are read where they arrive, among the launch's arguments.
+__device__ __forceinline__ const GemmArgs &gemm_args(const GemmArgs &a) { return a; }
+__device__ __forceinline__ const GemmArgs &gemm_args(const GemmCarried &c) { return c.a; }
+template <class ARGS>
+__device__ __forceinline__ GemmRowTile row_tile(const GemmArgs &g, int rt, int height)
 {
+    GemmRowTile t;
+    if constexpr (std::is_same_v<ARGS, GemmCarried>) {
+        const auto *c = (const __attribute__((address_space(4))) GemmCarried *)__builtin_amdgcn_kernarg_segment_ptr();
+        t.a = c->tiles[rt].a;
+        t.c = c->tiles[rt].c;
+        t.ck = c->tiles[rt].ck;
+        t.cv = c->tiles[rt].cv;
+        t.rows = c->tiles[rt].rows;
+        t.pos0 = c->tiles[rt].pos0;
+        t.pt_off = c->tiles[rt].pt_off;
+        t.dest0 = c->tiles[rt].dest0;
+    } else if (g.tiles) {
+        t = g.tiles[rt];
+    } else {
+        t.a = static_cast<const char *>(g.a) + (int64_t)rt * height * g.K * 2;
+        t.c = g.c ? static_cast<char *>(g.c) + (int64_t)rt * height * g.ldc * 2 : nullptr;
+        t.ck = t.cv = nullptr;
+        t.rows = (int32_t)min<int64_t>(height, g.M - (int64_t)rt * height);
+        t.pos0 = 0;
+        t.pt_off = 0;
+        t.dest0 = rt * height;
+    }
+    return t;
+}
+
+// The slots behind a question's last row in its last page, which the attention kernel multiplies by zero weights and which
+// therefore have to be finite: the wavefront whose rows (d: its lanes', mine: which of them) hold that last row clears them, for the
+// CH channels that its tile has of the head (channel j of them is half32 + j of the first half of the head, or of the second).
+// A launch of its own before the
+// projection, over all last pages, took 4.0 to 4.8 us: with the row tiles' copy (see sgc_project_qkv_prefix_batched) the layer over a
+// prompt of 300 tokens and 6 questions went 117.4 -> 110.5 us.
+template <int CH>
+__device__ __forceinline__ void clear_behind_last(const GemmArgs &g, const int4 d, bool mine, int kind, int hk, int half32, int lane)
+{
+    const int n_rows = abs(d.z);
+    uint64_t last = __ballot(mine && n_rows < kPageTokens && (d.x & 15) == n_rows - 1);
+    while (last) {
+        const int r = __builtin_ctzll(last);
+        last &= last - 1;
+        const int x = __builtin_amdgcn_readlane(d.x, r), slot = x & 15;
+        char *page = g.kv_base + (int64_t)(x >> 4) * g.page_bytes + (int64_t)(kind == 1 ? hk : g.n_kv_heads + hk) * g.part_bytes;
+        auto channel = [&](int j) __attribute__((always_inline)) { return CH == HD ? j : (j >> 5) * 64 + half32 + (j & 31); };
+        if (kind == 1) {
+#pragma unroll
+            for (int u0 = 0; u0 < 2 * CH; u0 += 64) {
+                const int u = u0 + lane, s = u & 15;
+                if (s > slot) *reinterpret_cast<uint4 *>(page + k_page_index(s, channel(8 * (u >> 4))) * 2) = make_uint4(0, 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int u0 = 0; u0 < 4 * CH; u0 += 64) {
+                const int u = u0 + lane, j = u % CH, s0 = 4 * (u / CH);
+                uint16_t *p = reinterpret_cast<uint16_t *>(page) + v_page_index(s0, channel(j));      // four slots of a channel
+                if (s0 > slot)
+                    *reinterpret_cast<uint2 *>(p) = make_uint2(0, 0);
+                else
+#pragma unroll
+                    for (int e = 1; e < 4; ++e)
+                        if (s0 + e > slot) p[e] = 0;
+            }
+        }
+    }
+}
+
+// A batch's values: a wavefront's n (at most 128) rows of a head's 128 channels into the questions' pages.  They lie in acc as lane =
+// channel 32 qj + l31, register r of accumulator pi = row 32 pi + 8 (r / 4) + 4 h + r % 4, and questions begin at any row: the wavefront
+// lays them out in LDS as [channel][row] and reads a page's 16 tokens of a channel from where they begin, for two 16-byte stores.  Pages
+// that reach over the rows' ends are written row by row.  (All rows one by one from the registers, two bytes
+// a lane: with the slots behind the last row cleared here Llama-3-8B's layer over ten prompts of 1024 tokens and 320 questions of 16 to
+// 64 went 1 944 -> 1 961 us; this way 1 860 -> 1 849, on another card.)
+constexpr int V_TILE_LD = 128 * 2 + 8, V_TILE = 128 * V_TILE_LD;
+static_assert(4 * V_TILE + 64 <= GEMM_LDS, "the slabs' place, and what a page's reads take too much");
+__device__ __forceinline__ void store_own_values(const GemmArgs &g, const f32x16 (&acc)[4][4], int dest0, int n, int hk, char *tile, int lane)
+{
+    const int h = lane >> 5, l31 = lane & 31;
+#pragma unroll
+    for (int pi = 0; pi < 4; ++pi)
+#pragma unroll
+        for (int qj = 0; qj < 4; ++qj) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                *reinterpret_cast<uint2 *>(tile + (32 * qj + l31) * V_TILE_LD + (32 * pi + 8 * q4 + 4 * h) * 2) =
+                    make_uint2(pack2(acc[pi][qj][4 * q4], acc[pi][qj][4 * q4 + 1]), pack2(acc[pi][qj][4 * q4 + 2], acc[pi][qj][4 * q4 + 3]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    char *const pages = g.kv_base + (int64_t)(g.n_kv_heads + hk) * g.part_bytes;
+    for (int r0 = 0; r0 < n; r0 += 64) {
+        const bool valid = r0 + lane < n;
+        const int4 d = g.row_dest[dest0 + (valid ? r0 + lane : r0)];
+        const int slot = d.x & 15, first = r0 + lane - slot;
+        const bool whole = d.z > 0 && first >= 0 && first + d.z <= n;
+        for (uint64_t m = __ballot(valid && whole && slot == 0); m; m &= m - 1) {
+            const int bit = __builtin_ctzll(m), r = r0 + bit;
+            const int x = __builtin_amdgcn_readlane(d.x, bit), held = __builtin_amdgcn_readlane(d.z, bit);
+            char *page = pages + (int64_t)(x >> 4) * g.page_bytes;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const uint2 *src = reinterpret_cast<const uint2 *>(tile + (64 * c + lane) * V_TILE_LD + (r & ~3) * 2);
+                uint32_t w[10], out[8];
+#pragma unroll
+                for (int e = 0; e < 5; ++e) {
+                    const uint2 p = src[e];
+                    w[2 * e] = p.x;
+                    w[2 * e + 1] = p.y;
+                }
+#pragma unroll
+                for (int e = 0; e < 9; ++e) w[e] = (r & 2) ? w[e + 1] : w[e];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    out[e] = __builtin_amdgcn_alignbit(w[e + 1], w[e], (r & 1) * 16) & (held > 2 * e + 1 ? 0xffffffffu : held > 2 * e ? 0xffffu : 0u);
+                uint4 *dst = reinterpret_cast<uint4 *>(page + v_page_index(0, 64 * c + lane) * 2);
+                dst[0] = make_uint4(out[0], out[1], out[4], out[5]);
+                dst[32] = make_uint4(out[2], out[3], out[6], out[7]);
+            }
+        }
+        for (uint64_t m = __ballot(valid && !whole); m; m &= m - 1) {
+            const int bit = __builtin_ctzll(m), r = r0 + bit;
+            const int x = __builtin_amdgcn_readlane(d.x, bit);
+            uint16_t *page = reinterpret_cast<uint16_t *>(pages + (int64_t)(x >> 4) * g.page_bytes);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                uint16_t v;
+                __builtin_memcpy(&v, tile + (64 * c + lane) * V_TILE_LD + r * 2, 2);
+                page[v_page_index(x & 15, 64 * c + lane)] = v;
+            }
+        }
+        clear_behind_last<HD>(g, d, valid && !whole, 2, hk, 0, lane);
+    }
+}
+
+template <bool QKV, class ARGS>
+__global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const ARGS args)
+{
+    const GemmArgs &g = gemm_args(args);
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -102,18 +240,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     const int rt = __builtin_amdgcn_readfirstlane(grp * GM + in % gsz);
     const int ct = __builtin_amdgcn_readfirstlane(in / gsz);
 
-    GemmRowTile t;
-    if (g.tiles) {
-        t = g.tiles[rt];
-    } else {
-        t.a = static_cast<const char *>(g.a) + (int64_t)rt * TM * g.K * 2;
-        t.c = g.c ? static_cast<char *>(g.c) + (int64_t)rt * TM * g.ldc * 2 : nullptr;
-        t.ck = t.cv = nullptr;
-        t.rows = (int32_t)min<int64_t>(TM, g.M - (int64_t)rt * TM);
-        t.pos0 = 0;
-        t.pt_off = 0;
-        t.dest0 = rt * TM;
-    }
+    const GemmRowTile t = row_tile<ARGS>(g, rt, TM);
     const int rows = __builtin_amdgcn_readfirstlane(t.rows);
     const int K = g.K, N = g.N;
     const int n_steps = K / TK;
@@ -264,6 +391,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
     if (kt + 1 < n_steps) step(kt++, std::true_type{}, std::false_type{});
     step(kt, std::false_type{}, std::false_type{});
 
+    if (QKV && g.kv_dest == 1) step_barrier<0>();      // values pass through the slabs' place in LDS: every operand is read
     if (col0 >= N) return;          // the second half of a ragged last column tile
     const int rows16 = (rows + 15) & ~15;
 
@@ -287,7 +415,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                     slot16 = p & 15;
                     pos = p;
                 } else {
-                    const int2 d = g.row_dest[t.dest0 + (valid ? i : 0)];
+                    const int4 d = g.row_dest[t.dest0 + (valid ? i : 0)];
                     page = d.x >> 4;
                     slot16 = d.x & 15;
                     pos = d.y;
@@ -305,7 +433,8 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
             // registers 8 u .. 8 u + 3 are features 16 u + 4 h + 0..3, registers 8 u + 4 .. + 7 features 16 u + 8 + 4 h + 0..3; after the
             // swap between the two 32-lane halves lane h holds the eight consecutive features 16 u + 8 h .. + 7.  Accumulators pi and
             // pi + 2 hold the rotation's partners.  Piece by piece, behind a scheduling barrier each: taken together, the accumulators'
-            // copies in ordinary registers did not fit and 80 were spilled.  Llama-3-8B's layer of 16 x 448 rows: 1 957 -> 1 942 us.
+            // copies in ordinary registers did not fit and 80 were spilled.  Llama-3-8B's layer over ten prompts of
+            // 1024 tokens and 320 questions of 16 to 64: 1 957 -> 1 942 us.
             auto put = [&](const float (&v)[8], int pi, int u) __attribute__((always_inline)) {
                 float x[8];
 #pragma unroll
@@ -345,6 +474,8 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
+    } else if (g.kv_dest == 1) {
+        store_own_values(g, acc, t.dest0 + 128 * wm, min(rows - 128 * wm, 128), hk, smem + wave * V_TILE, lane);
     } else {
         // lane = channel 32 qj + l31 of the head; register r of accumulator pi = token 32 pi + 8 (r / 4) + 4 h + r % 4
 #pragma unroll
@@ -353,7 +484,7 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
             for (int e = 0; e < 2; ++e) {
                 const int r16 = 128 * wm + 32 * pi + 16 * e;      // first of the 16 rows registers 8 e .. 8 e + 7 belong to
                 if (r16 >= rows16) continue;
-                if (g.kv_dest == 0) {
+                {
                     // the 16 rows are one page; register 8 e + i is the page's token 4 h + (i & 3) + 8 (i >> 2)
                     const int page = g.page_table[t.pt_off + ((t.pos0 + r16) >> 4)];
                     char *vp = g.kv_base + (int64_t)page * g.page_bytes + (int64_t)(g.n_kv_heads + hk) * g.part_bytes;
@@ -368,20 +499,14 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const GemmArgs g)
                         const uint4 out = make_uint4(pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7]));
                         *reinterpret_cast<uint4 *>(vp + (((qj * 2 + h) * 32) + l31) * 16) = out;
                     }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const int tok = r16 + 4 * h + (i & 3) + 8 * (i >> 2);
-                        if (tok >= rows) continue;
-                        const int2 d = g.row_dest[t.dest0 + tok];
-                        __bf16 *vp = reinterpret_cast<__bf16 *>(g.kv_base + (int64_t)(d.x >> 4) * g.page_bytes +
-                                                                (int64_t)(g.n_kv_heads + hk) * g.part_bytes);
-#pragma unroll
-                        for (int qj = 0; qj < 4; ++qj) vp[v_page_index(d.x & 15, 32 * qj + l31)] = (__bf16)acc[pi][qj][8 * e + i];
-                    }
                 }
             }
     }
+    if (QKV && kind == 1 && g.kv_dest == 1)
+        for (int r = 128 * wm; r < min(rows, 128 * wm + 128); r += 64) {
+            const bool mine = r + lane < rows;
+            clear_behind_last<HD>(g, g.row_dest[t.dest0 + (mine ? r + lane : r)], mine, kind, hk, 0, lane);
+        }
 }
 
 // ---- the same products in smaller tiles -----------------------------------------------------------------
@@ -409,7 +534,8 @@ struct SmallTile {
     static constexpr int LD = TN + 4;
     static constexpr int PART = KS ? TM * TN * 4 : 0;            // one wavefront's partial tile
     static constexpr int SUM_BYTES = PART + TM * LD * 4;
-    static constexpr int LDS = NST * STAGE > SUM_BYTES ? NST * STAGE : SUM_BYTES;
+    static constexpr int END_BYTES = SUM_BYTES + TM * 16;        // and where the rows go, in a batch's pages
+    static constexpr int LDS = NST * STAGE > END_BYTES ? NST * STAGE : END_BYTES;
     static constexpr int COPIES = STAGE / 4096;                  // 1 KiB copies per wavefront and step
 };
 using Tile64 = SmallTile<64, 64, 5, 2, true>;
@@ -417,9 +543,10 @@ using Tile64x128 = SmallTile<64, 128, 6, 1, true>;
 using Tile128Deep = SmallTile<128, 128, 4, 1, false>;
 using Tile128Pair = SmallTile<128, 128, 2, 2, false>;
 
-template <class T, bool QKV>
-__global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const GemmArgs g)
+template <class T, bool QKV, class ARGS>
+__global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const ARGS args)
 {
+    const GemmArgs &g = gemm_args(args);
     constexpr int TM_ = T::TM, TN_ = T::TN, NST = T::NST, LD = T::LD;
     constexpr int KK = T::KS ? 1 : 4;                            // 16-wide slices of a step this wavefront multiplies
     constexpr int MB = TM_ / (T::KS ? 32 : 64), NB = TN_ / (T::KS ? 32 : 64);    // its 32 x 32 blocks
@@ -445,18 +572,7 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
     const int rt = __builtin_amdgcn_readfirstlane(grp * GM + in % gsz);
     const int ct = __builtin_amdgcn_readfirstlane(in / gsz);
 
-    GemmRowTile t;
-    if (g.tiles) {
-        t = g.tiles[rt];
-    } else {
-        t.a = static_cast<const char *>(g.a) + (int64_t)rt * TM_ * g.K * 2;
-        t.c = g.c ? static_cast<char *>(g.c) + (int64_t)rt * TM_ * g.ldc * 2 : nullptr;
-        t.ck = t.cv = nullptr;
-        t.rows = (int32_t)min<int64_t>(TM_, g.M - (int64_t)rt * TM_);
-        t.pos0 = 0;
-        t.pt_off = 0;
-        t.dest0 = rt * TM_;
-    }
+    const GemmRowTile t = row_tile<ARGS>(g, rt, TM_);
     const int rows = __builtin_amdgcn_readfirstlane(t.rows);
     const int K = g.K;
     const int n_steps = K / TK;
@@ -569,6 +685,17 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
     if (kt < n_steps) step(kt, x0, w0, x1, w1, std::false_type{});
     step_barrier<0>();           // every operand is read; the sums take the slabs' place
 
+    int kind = 0, hk = 0;        // 0 plain, 1 K head, 2 V head
+    if (QKV && head0 >= g.n_plain) {
+        const int kvh = (head0 - g.n_plain) / HD;
+        kind = kvh < g.n_kv_heads ? 1 : 2;
+        hk = kind == 1 ? kvh : kvh - g.n_kv_heads;
+    }
+    const bool slots = QKV && kind != 0 && g.kv_dest == 1;
+    int4 *const dest = reinterpret_cast<int4 *>(smem + T::SUM_BYTES);
+    int4 my_dest = make_int4(0, 0, 0, 0);
+    if (slots && (int)threadIdx.x < rows) my_dest = g.row_dest[t.dest0 + threadIdx.x];
+
     // ---- (KS) the four slices' sums: wavefronts 2 and 3 hand theirs to 0 and 1, which then hand each other half of theirs; the
     // result is written as [TM][LD] behind the hand-over area.
     auto slot_of = [&](char *area, int i, int j, int q4) __attribute__((always_inline)) { return reinterpret_cast<float4 *>(area + (((i * MB + j) * 4 + q4) * 64 + lane) * 16); };
@@ -629,14 +756,9 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
     } else {
         put(first, last);
     }
+    if (slots && (int)threadIdx.x < rows) dest[threadIdx.x] = my_dest;
     __syncthreads();
 
-    int kind = 0, hk = 0;        // 0 plain, 1 K head, 2 V head
-    if (QKV && head0 >= g.n_plain) {
-        const int kvh = (head0 - g.n_plain) / HD;
-        kind = kvh < g.n_kv_heads ? 1 : 2;
-        hk = kind == 1 ? kvh : kvh - g.n_kv_heads;
-    }
     const int rows16 = (rows + 15) & ~15;
     if (kind == 0 || g.kv_dest == 2) {
         char *c = static_cast<char *>(kind == 0 ? t.c : kind == 1 ? t.ck : t.cv);
@@ -660,7 +782,7 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
                 page = g.page_table[t.pt_off + (pos >> 4)];
                 slot16 = pos & 15;
             } else {
-                const int2 d = g.row_dest[t.dest0 + i];
+                const int4 d = dest[i];
                 page = d.x >> 4;
                 slot16 = d.x & 15;
                 pos = d.y;
@@ -700,12 +822,38 @@ __global__ void __launch_bounds__(256, T::WGS) proj_gemm_small_kernel(const Gemm
             *reinterpret_cast<uint4 *>(vp + v_page_index(4 * hh, col_of(j)) * 2) = make_uint4(pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7]));
         }
     } else {
+        // a page whose rows all lie in this tile: its first row's turn writes it, as above; other rows one by one.  (All rows one by
+        // one, two bytes a lane: the projection of the 168 rows of 6 questions 28.5 us, 26.8 so.)
         for (int u = threadIdx.x; u < rows * TN_; u += 256) {
-            const int i = u / TN_, j = u % TN_;
-            const int2 d = g.row_dest[t.dest0 + i];
-            __bf16 *vp = reinterpret_cast<__bf16 *>(g.kv_base + (int64_t)(d.x >> 4) * g.page_bytes + (int64_t)(g.n_kv_heads + hk) * g.part_bytes);
-            vp[v_page_index(d.x & 15, col_of(j))] = (__bf16)cs[i * LD + j];
+            const int i = __builtin_amdgcn_readfirstlane(u / TN_), j = u % TN_;      // (a wavefront has one row's channels)
+            const int4 d = dest[i];
+            const int x0 = __builtin_amdgcn_readfirstlane(d.x), n = __builtin_amdgcn_readfirstlane(d.z), slot = x0 & 15;
+            const bool whole = n > 0 && i >= slot && i - slot + n <= rows;
+            if (whole && slot > 0) continue;
+            char *vp = g.kv_base + (int64_t)(x0 >> 4) * g.page_bytes + (int64_t)(g.n_kv_heads + hk) * g.part_bytes;
+            if (whole) {
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    float x[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int tok = 4 * hh + (e & 3) + 8 * (e >> 2);
+                        x[e] = tok < n ? cs[(i + tok) * LD + j] : 0.f;
+                    }
+                    *reinterpret_cast<uint4 *>(vp + v_page_index(4 * hh, col_of(j)) * 2) = make_uint4(pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7]));
+                }
+            } else {
+                *reinterpret_cast<__bf16 *>(vp + v_page_index(slot, col_of(j)) * 2) = (__bf16)cs[i * LD + j];
+            }
         }
+    }
+    if (slots) {
+        const int r0 = wave * (TM_ / 4), i = r0 + lane;
+        const bool in_tile = lane < TM_ / 4 && i < rows;
+        const int4 d = dest[in_tile ? i : 0];
+        const int slot = d.x & 15;
+        const bool whole = kind == 2 && d.z > 0 && i >= slot && i - slot + d.z <= rows;
+        clear_behind_last<TN_>(g, d, in_tile && !whole, kind, hk, half32, lane);
     }
 }
 
@@ -751,42 +899,36 @@ __global__ void __launch_bounds__(256) proj_generic_kernel(const void *a, const 
     }
 }
 
-// Clears the last page (every head, K and V) of each query whose length is not a multiple of the page size:
-// the projection only writes the slots of real tokens, and the attention kernel multiplies the rest by zero
-// weights, which needs them finite.
-__global__ void __launch_bounds__(256) zero_last_pages_kernel(char *spool, const int32_t *sq_len, const int32_t *sq_page0,
-                                                              int64_t page_bytes)
-{
-    const int S = sq_len[blockIdx.x];
-    if (S <= 0 || (S & 15) == 0) return;
-    uint4 *p = reinterpret_cast<uint4 *>(spool + (int64_t)(sq_page0[blockIdx.x] + ((S - 1) >> 4)) * page_bytes);
-    const int64_t n16 = page_bytes / 16;
-    for (int64_t i = threadIdx.x; i < n16; i += blockDim.x) p[i] = make_uint4(0, 0, 0, 0);
-}
-
 }  // namespace
 
 
 namespace {
 
-template <class T>
-hipError_t launch_small(const GemmArgs &g, bool qkv, hipStream_t s)
+const GemmArgs &gemm_host_args(const GemmArgs &a) { return a; }
+const GemmArgs &gemm_host_args(const GemmCarried &c) { return c.a; }
+
+template <bool QKV, class ARGS>
+hipError_t launch_tiles(const ARGS &args, hipStream_t s)
 {
-    static bool configured = false;
-    constexpr int lds = T::LDS;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(proj_gemm_small_kernel<T, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(proj_gemm_small_kernel<T, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        configured = true;
+    const GemmArgs &g = gemm_host_args(args);
+    const int blocks = (g.n_row_tiles * g.n_col_tiles + 7) / 8 * 8;
+    auto launch = [&](auto kern, int lds, bool &configured) {
+        if (!configured) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            configured = true;
+        }
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, args);
+        return hipGetLastError();
+    };
+    static bool configured[GEMM_64 + 1] = {};
+    switch (g.kind) {
+        case GEMM_128_DEEP: return launch(proj_gemm_small_kernel<Tile128Deep, QKV, ARGS>, Tile128Deep::LDS, configured[g.kind]);
+        case GEMM_128_PAIR: return launch(proj_gemm_small_kernel<Tile128Pair, QKV, ARGS>, Tile128Pair::LDS, configured[g.kind]);
+        case GEMM_64X128: return launch(proj_gemm_small_kernel<Tile64x128, QKV, ARGS>, Tile64x128::LDS, configured[g.kind]);
+        case GEMM_64: return launch(proj_gemm_small_kernel<Tile64, QKV, ARGS>, Tile64::LDS, configured[g.kind]);
+        default: return launch(proj_gemm_kernel<QKV, ARGS>, GEMM_LDS, configured[GEMM_256]);
     }
-    const int per = (g.n_row_tiles * g.n_col_tiles + 7) / 8;
-    if (qkv)
-        hipLaunchKernelGGL((proj_gemm_small_kernel<T, true>), dim3(per * 8), dim3(256), lds, s, g);
-    else
-        hipLaunchKernelGGL((proj_gemm_small_kernel<T, false>), dim3(per * 8), dim3(256), lds, s, g);
-    return hipGetLastError();
 }
 
 // What a launch of n tiles takes, in microseconds, on a chip of 256 CUs: a start, per round of tiles a fixed part (first
@@ -888,30 +1030,16 @@ extern "C" void sgc_debug_projection_plan(const int32_t *slab_rows, int32_t n_sl
     out[1] = p.rest;
 }
 
-hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s)
+hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s, const GemmRowTile *carried)
 {
-    const int total = g.n_row_tiles * g.n_col_tiles;
-    if (total <= 0) return hipSuccess;
-    switch (g.kind) {
-        case GEMM_128_DEEP: return launch_small<Tile128Deep>(g, qkv, s);
-        case GEMM_128_PAIR: return launch_small<Tile128Pair>(g, qkv, s);
-        case GEMM_64X128: return launch_small<Tile64x128>(g, qkv, s);
-        case GEMM_64: return launch_small<Tile64>(g, qkv, s);
-        default: break;
-    }
-    static bool configured[2] = {false, false};
-    const void *kern = qkv ? reinterpret_cast<const void *>(proj_gemm_kernel<true>) : reinterpret_cast<const void *>(proj_gemm_kernel<false>);
-    if (!configured[qkv]) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS);
-        if (e != hipSuccess) return e;
-        configured[qkv] = true;
-    }
-    const int per = (total + 7) / 8;
-    if (qkv)
-        hipLaunchKernelGGL(proj_gemm_kernel<true>, dim3(per * 8), dim3(256), GEMM_LDS, s, g);
-    else
-        hipLaunchKernelGGL(proj_gemm_kernel<false>, dim3(per * 8), dim3(256), GEMM_LDS, s, g);
-    return hipGetLastError();
+    if (g.n_row_tiles * g.n_col_tiles <= 0) return hipSuccess;
+    if (!carried) return qkv ? launch_tiles<true>(g, s) : launch_tiles<false>(g, s);
+    if (!qkv || g.n_row_tiles > GemmCarried::kTiles) return hipErrorInvalidValue;
+    GemmCarried c;
+    c.a = g;
+    memcpy(c.tiles, carried, (size_t)g.n_row_tiles * sizeof(GemmRowTile));
+    memset(c.tiles + g.n_row_tiles, 0, (size_t)(GemmCarried::kTiles - g.n_row_tiles) * sizeof(GemmRowTile));
+    return launch_tiles<true>(c, s);
 }
 
 hipError_t launch_proj_generic(const void *a, const void *w, int64_t M, int N, int K, int io_dtype, void *c0, int n0, void *c1,
@@ -920,14 +1048,6 @@ hipError_t launch_proj_generic(const void *a, const void *w, int64_t M, int N, i
     if (M <= 0 || N <= 0) return hipSuccess;
     hipLaunchKernelGGL(proj_generic_kernel, dim3((N + 15) / 16, (unsigned)((M + 15) / 16)), dim3(256), 0, s, a, w, M, N, K, io_dtype,
                        c0, n0, c1, n1, c2);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_last_pages(char *spool, const int32_t *d_sq_len, const int32_t *d_sq_page0, int n_sq, int64_t page_bytes,
-                                  hipStream_t s)
-{
-    if (n_sq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_last_pages_kernel, dim3(n_sq), dim3(256), 0, s, spool, d_sq_len, d_sq_page0, page_bytes);
     return hipGetLastError();
 }
 

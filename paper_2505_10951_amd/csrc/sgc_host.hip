@@ -1870,16 +1870,17 @@ static bool gemm_covers(const sgc_ctx *ctx, int64_t K, int64_t N)
     return ctx->p.io_dtype == SGC_BF16 && K >= 64 && K % 64 == 0 && K <= (1 << 20) && N >= 128 && N % 128 == 0;
 }
 
-// One launch of a projection: n_row_tiles row tiles of the given kind (tiles null: taken from g.a, g.c, g.M).
-static hipError_t launch_gemm_part(GemmArgs g, int kind, const GemmRowTile *tiles, int32_t n_row_tiles, bool qkv, hipStream_t s)
+// One launch of a projection: n_row_tiles row tiles of the given kind (tiles null: taken from g.a, g.c, g.M; carried: tiles is
+// host memory, and they travel with the launch).
+static hipError_t launch_gemm_part(GemmArgs g, int kind, const GemmRowTile *tiles, int32_t n_row_tiles, bool qkv, hipStream_t s, bool carried = false)
 {
     if (n_row_tiles <= 0) return hipSuccess;
     const int cols = proj_gemm_tile_cols(kind);
     g.kind = kind;
-    g.tiles = tiles;
+    g.tiles = carried ? nullptr : tiles;
     g.n_row_tiles = n_row_tiles;
     g.n_col_tiles = (g.N + cols - 1) / cols;
-    return launch_proj_gemm(g, qkv, s);
+    return launch_proj_gemm(g, qkv, s, carried ? tiles : nullptr);
 }
 
 // A projection whose left operand is one matrix of g.M rows.
@@ -1991,17 +1992,21 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
             }
             row_base += P;
         }
+        // few row tiles travel as the launches' arguments: a copy of theirs took 4.4 us before the first product
+        const bool carried = tiles.size() <= (size_t)GemmCarried::kTiles;
         const size_t bytes = tiles.size() * sizeof(GemmRowTile);
-        sgc_dev_block blk;
-        if ((rc = dev_acquire(ctx, bytes, s, &blk)) != SGC_OK) {
-            dev_release(ctx, stg, s);
-            return rc;
-        }
-        char *host = nullptr;
-        int slot = 0;
-        if ((rc = stage_begin(ctx, bytes, &host, &slot)) == SGC_OK) {
-            memcpy(host, tiles.data(), bytes);
-            rc = stage_commit(ctx, slot, blk.p, bytes, s);
+        sgc_dev_block blk{};
+        if (!carried) {
+            if ((rc = dev_acquire(ctx, bytes, s, &blk)) != SGC_OK) {
+                dev_release(ctx, stg, s);
+                return rc;
+            }
+            char *host = nullptr;
+            int slot = 0;
+            if ((rc = stage_begin(ctx, bytes, &host, &slot)) == SGC_OK) {
+                memcpy(host, tiles.data(), bytes);
+                rc = stage_commit(ctx, slot, blk.p, bytes, s);
+            }
         }
         if (rc == SGC_OK) {
             GemmArgs g{};
@@ -2017,9 +2022,9 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
             g.part_bytes = c->geom.head_part_bytes;
             g.page_table = c->d_page_table;
             g.rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
-            const GemmRowTile *d_tiles = reinterpret_cast<const GemmRowTile *>(blk.p);
-            e = launch_gemm_part(g, GEMM_256, d_tiles, (int32_t)n_big, true, s);
-            if (e == hipSuccess) e = launch_gemm_part(g, plan.rest, d_tiles + n_big, (int32_t)(tiles.size() - n_big), true, s);
+            const GemmRowTile *row_tiles = carried ? tiles.data() : reinterpret_cast<const GemmRowTile *>(blk.p);
+            e = launch_gemm_part(g, GEMM_256, row_tiles, (int32_t)n_big, true, s, carried);
+            if (e == hipSuccess) e = launch_gemm_part(g, plan.rest, row_tiles + n_big, (int32_t)(tiles.size() - n_big), true, s, carried);
         }
         dev_release(ctx, blk, s);
     } else {
@@ -2088,23 +2093,32 @@ int sgc_project_qkv_suffix(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int3
         char *spool = pl->d_spool + (pl->decode_cap > 0 ? (size_t)layer * pl->spool_layer_bytes : 0);
         const int64_t page_bytes = (int64_t)2 * Hkv * kPageTokens * d * 2;
         if (!pl->d_row_dest) {          // first projection on this plan: the per-row destinations go to the device
-            // where the epilogue puts the key and value of each packed row: {16 * page + slot, position}
-            pl->row_dest.resize(2 * pl->tok_src.size());
+            // where the epilogue puts the key and value of each packed row
+            pl->row_dest.resize(pl->tok_src.size());
             for (size_t i = 0; i < pl->tok_src.size(); ++i) {
                 const int32_t sq = pl->tok_sq[i], qpos = pl->tok_qpos[i];
-                pl->row_dest[2 * (size_t)pl->tok_src[i]] = (pl->sq_page0[sq] + qpos / kPageTokens) * kPageTokens + qpos % kPageTokens;
-                pl->row_dest[2 * (size_t)pl->tok_src[i] + 1] = pl->cl_prefix_len[pl->sq_cluster[sq]] + qpos;
+                pl->row_dest[(size_t)pl->tok_src[i]] = make_int4((pl->sq_page0[sq] + qpos / kPageTokens) * kPageTokens + qpos % kPageTokens,
+                                                                 pl->cl_prefix_len[pl->sq_cluster[sq]] + qpos,
+                                                                 -std::min(kPageTokens, pl->sq_len[sq] - qpos / kPageTokens * kPageTokens), 0);
             }
-            const size_t bytes = pl->row_dest.size() * sizeof(int32_t);
+            for (size_t r = 0; r < pl->row_dest.size();) {      // pages whose rows follow each other
+                const int32_t x = pl->row_dest[r].x, n = -pl->row_dest[r].z;
+                int32_t k = 0;
+                if (x % kPageTokens == 0)
+                    while (k < n && r + k < pl->row_dest.size() && pl->row_dest[r + k].x == x + k) ++k;
+                if (k == n)
+                    for (k = 0; k < n; ++k) pl->row_dest[r + k].z = n;
+                r += std::max(k, 1);
+            }
+            const size_t bytes = pl->row_dest.size() * sizeof(int4);
             if ((rc = dev_acquire(ctx, bytes, s, &pl->row_dest_block)) != SGC_OK) return rc;
             char *host = nullptr;
             int slot = 0;
             if ((rc = stage_begin(ctx, bytes, &host, &slot)) != SGC_OK) return rc;
             memcpy(host, pl->row_dest.data(), bytes);
             if ((rc = stage_commit(ctx, slot, pl->row_dest_block.p, bytes, s)) != SGC_OK) return rc;
-            pl->d_row_dest = reinterpret_cast<const int2 *>(pl->row_dest_block.p);
+            pl->d_row_dest = reinterpret_cast<const int4 *>(pl->row_dest_block.p);
         }
-        SGC_HIP(ctx, launch_zero_last_pages(spool, pl->d_sq_len, pl->d_sq_page0, (int)pl->sq_len.size(), page_bytes, s));
         GemmArgs g{};
         g.w = dev_w_qkv;
         g.N = N;

@@ -259,8 +259,14 @@ struct GemmArgs {
     int64_t page_bytes;           // one page, every head, K and V
     int64_t part_bytes;           // K (or V) of one head in one page
     const int32_t *page_table;    // kv_dest 0: flat page ids
-    const int2 *row_dest;         // kv_dest 1: per packed row {16 * page + slot, position}
+    const int4 *row_dest;         // kv_dest 1: per packed row {16 * page + slot, position, n, 0}: the page holds |n| rows, n > 0 if they follow each other in the packed order
     const float2 *rope;           // [position][64] (cos, sin), or null
+};
+// A prompt projection's row tiles among the launch's arguments.
+struct GemmCarried {
+    static constexpr int kTiles = 72;
+    GemmArgs a;
+    GemmRowTile tiles[kTiles];
 };
 
 enum { MODE_SUFFIX = 0, MODE_PREFIX = 1 };
@@ -381,6 +387,7 @@ struct CarriedGeneric {          // either mode, for the generic kernel
     Query queries[kQueries];
     int32_t pages[kPages];
 };
+static_assert(sizeof(GemmCarried) + kRuntimeArgsBytes <= kLaunchArgsBytes, "a launch's arguments");
 static_assert(sizeof(CarriedPrefix) <= kLaunchArgsBytes - kRuntimeArgsBytes && sizeof(CarriedSuffix) <= kLaunchArgsBytes - kRuntimeArgsBytes &&
                   sizeof(CarriedGeneric) <= kLaunchArgsBytes - kRuntimeArgsBytes,
               "launch arguments");
@@ -481,8 +488,8 @@ struct sgc_plan {
     // 2 = un-rotated K then V matrices [T][Hkv d] are kept in proj_kv for the suffix launch to ingest
     int32_t proj_state = 0, proj_layer = -1;
     sgc_dev_block proj_kv;
-    std::vector<int32_t> row_dest;            // [T][2] per packed row: 16 * suffix page + slot, position
-    const int2 *d_row_dest = nullptr;         // uploaded by the first projection on the plan
+    std::vector<int4> row_dest;               // [T] per packed row, see GemmArgs
+    const int4 *d_row_dest = nullptr;         // uploaded by the first projection on the plan
     sgc_dev_block row_dest_block;
     std::vector<sgc::Tile> tiles;
     std::vector<sgc::TokInfo> tok_info;
@@ -590,11 +597,10 @@ hipError_t launch_copy_from_host(void *dst, const void *mapped_src, size_t bytes
 // Projections: the bf16 matrix-core kernel (K a multiple of 64, N a multiple of 128; qkv selects the fused
 // epilogue) and a kernel for every other shape and type that deals columns [0, n0), [n0, n0 + n1) and the rest
 // to three row-major matrices (c0 may be null to drop its columns).
-hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s);
+// carried: g's row tiles in host memory, to travel with the launch (at most GemmCarried::kTiles, qkv)
+hipError_t launch_proj_gemm(const GemmArgs &g, bool qkv, hipStream_t s, const GemmRowTile *carried = nullptr);
 hipError_t launch_proj_generic(const void *a, const void *w, int64_t M, int N, int K, int io_dtype, void *c0, int n0, void *c1,
                                int n1, void *c2, hipStream_t s);
-hipError_t launch_zero_last_pages(char *spool, const int32_t *d_sq_len, const int32_t *d_sq_page0, int n_sq, int64_t page_bytes,
-                                  hipStream_t s);
 // Rows per workgroup of the MFMA attention kernel.
 int mfma_tile_rows();
 hipError_t launch_attn_mfma(const AttnArgs &a, hipStream_t s);
