@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <chrono>
 #include <new>
 #include <numeric>
@@ -1721,6 +1722,8 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
         a.own_cost2 = pl->dec_own_cost2;
         a.parts = scratch;
         a.arrived = arrived;
+        static std::atomic<uint32_t> launches{0};
+        a.launch = launches.fetch_add(1, std::memory_order_relaxed) % 0xffffffu + 1;
         SGC_HIP(ctx, launch_attn_mfma(a, s));
         return SGC_OK;
     }

@@ -324,11 +324,13 @@ struct AttnArgs {
     const int32_t *sq_query;
     int32_t n_append;
     // decode steps of few rows (attn_few_kernel): one launch does the whole step.  n_ranges key ranges per row tile; the partial results
-    // of several go to parts (kFewPartBytes each), arrived counts a row tile's ranges in (zero between launches).
+    // of several go to parts (kFewPartBytes each), arrived counts a row tile's ranges in, above the launch's number (24 bits; zero between
+    // launches).
     int32_t few;
     int32_t own_cost2;            // a query's own keys against 32 cached keys, in halves
     char *parts;
     uint32_t *arrived;
+    uint32_t launch;
     int32_t n_ranges;
     // fp8 cache: run the first product on the e4m3 codes, with the query quantised per row (suffix mode)
     int32_t fp8_first_product;
