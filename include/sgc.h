@@ -246,17 +246,22 @@ int sgc_decode_step_batched(sgc_ctx *ctx, const sgc_cache *cache, sgc_plan *plan
 /* sgc_decode_step_batched for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same
  * results.  The call allocates nothing (no hipMalloc / hipFree / host allocation of the HIP runtime's):
- * the partial results of the step's cached-prompt part, which sgc_decode_step_batched keeps in a block
- * of the context's pool, go to a fixed 32 MiB device array inside the library (one copy per GPU, held
- * until the process ends).  SGC_ENOMEM if they need more: n_queries * Hq * d * 2 bytes plus n_queries *
- * Hq * 4, times the number of key ranges the plan splits long prompts into: up to 16, but more than 8, or
- * ranges shorter than 512 keys, only where they fit the array, so that this can happen at 8 or fewer.  Every
- * table the step reads must already be on the device and current, which is the case once the plan's suffix prefill
- * has run and no cluster was allocated or released since: SGC_ESTATE otherwise (rotary table too short --
- * set max_position to cover prefix + question + generated tokens --, page tables or tile lists stale).
- * All calls on one GPU share the array and it keeps the last call's contents; nothing in it needs
- * clearing (a step overwrites every entry it reads), but two calls whose kernels overlap on one GPU (two
- * streams, two host threads, two contexts) race on it. */
+ * the partial results of the step's key ranges, which sgc_decode_step_batched keeps in a block of the
+ * context's pool, go to a fixed 32 MiB device array inside the library (one copy per GPU, held until
+ * the process ends), and so do, behind them, 1024 counters.  SGC_ENOMEM if the partial results need
+ * more: n_queries * Hq * d * 2 bytes plus n_queries * Hq * 4, times the number of key ranges the plan
+ * splits long prompts into: up to 16, but more than 8, or ranges shorter than 512 keys, only where they
+ * fit the array, so that this can happen at 8 or fewer.  (Steps that are one launch, at most 32 rows of
+ * a cluster and KV head, need 16 640 bytes per range of such rows, in at most 256 ranges of a step.)
+ * Every table the step reads must already be on the device and current, which is the case once the
+ * plan's suffix prefill has run and no cluster was allocated or released since: SGC_ESTATE otherwise
+ * (rotary table too short -- set max_position to cover prefix + question + generated tokens --, page
+ * tables or tile lists stale).
+ * All calls on one GPU share the array: two calls whose kernels overlap on one GPU (two streams, two
+ * host threads, two contexts, replays of captured calls among them) race on it, and the results of
+ * both are then undefined.  Calls that follow are not affected: a step overwrites every partial result
+ * that it reads, and finds the counters at zero or below its own number; under capture, the capture's
+ * first step is preceded by a kernel node that clears them. */
 int sgc_decode_step_batched_noalloc(sgc_ctx *ctx, const sgc_cache *cache, sgc_plan *plan, int32_t layer,
                                     int32_t step, const void *dev_q, const void *dev_k, const void *dev_v,
                                     void *dev_o, float *dev_lse, void *hip_stream);

@@ -1422,8 +1422,8 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
     };
     float4 *const parts = reinterpret_cast<float4 *>(a.parts + (int64_t)t.row_tile * S * kFewPartBytes);      // [range][row][chunk], then ...
     float2 *const part_stats = reinterpret_cast<float2 *>(parts + (int64_t)S * 32 * 32);                     // ... [range][row]
-    // (the row tile's counter starts at the launch's number: what calls that ran into each other on the array of callers that cannot
-    // allocate may have left in it is behind it, and does not reach the calls that follow)
+    // (The row tile's counter starts at the launch's number: what earlier calls that ran into each other may have left in it is below.  A
+    // captured launch keeps its number, so later calls' leftovers are not: a capture clears the counters in front of its first step.)
     if (S > 1 && threadIdx.x == 0) (void)__hip_atomic_fetch_max(a.arrived + t.row_tile, a.launch << 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 #pragma unroll
@@ -1466,9 +1466,9 @@ __global__ void __launch_bounds__(NWF * 64, 2) attn_few_kernel(const AttnArgs a)
     __syncthreads();
     uint32_t *const flag = reinterpret_cast<uint32_t *>(smem);
     if (threadIdx.x == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(a.arrived + t.row_tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((before & 0xff) == (uint32_t)(S - 1)) __hip_atomic_store(a.arrived + t.row_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = before & 0xff;
+        const uint32_t before = __hip_atomic_fetch_add(a.arrived + t.row_tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff;
+        if (before == (uint32_t)(S - 1)) __hip_atomic_store(a.arrived + t.row_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = before;
     }
     __syncthreads();
     if (*flag != (uint32_t)(S - 1)) return;

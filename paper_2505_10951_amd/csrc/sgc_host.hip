@@ -640,6 +640,7 @@ void plan_free_device(sgc_plan *pl)
 {
     dev_release(pl->ctx, pl->dec_scratch, pl->last_stream);
     pl->dec_scratch = sgc_dev_block{};
+    pl->dec_counters_cleared = 0;
     dev_release(pl->ctx, pl->proj_kv, pl->last_stream);
     pl->proj_kv = sgc_dev_block{};
     pl->proj_state = 0;
@@ -1607,11 +1608,12 @@ int sgc_plan_enable_decode(sgc_plan *pl, int32_t max_new_tokens)
 // Behind it the counters of a step of few rows: zero when the library is loaded, and left at zero by every step.
 constexpr size_t kNoAllocCounters = kFewRowTiles;
 static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoAllocScratchBytes + kNoAllocCounters * sizeof(uint32_t)];
+static std::atomic<uint64_t> g_step_launches{0};      // one-launch decode steps so far
 constexpr int kMaxDevices = 64;
 static char *g_noalloc_scratch_ptr[kMaxDevices] = {};
 
 // The array's address on the current device (looked up once per device).
-static int noalloc_scratch(sgc_ctx *ctx, char **out)
+static int noalloc_scratch(sgc_ctx *ctx, char **out, uint64_t **cleared)
 {
     int dev = -1;
     SGC_HIP(ctx, hipGetDevice(&dev));
@@ -1623,6 +1625,51 @@ static int noalloc_scratch(sgc_ctx *ctx, char **out)
         g_noalloc_scratch_ptr[dev] = static_cast<char *>(p);
     }
     *out = g_noalloc_scratch_ptr[dev];
+    static std::array<uint64_t, kMaxDevices> counters_cleared = [] {
+        std::array<uint64_t, kMaxDevices> zero_since_loaded;
+        zero_since_loaded.fill(1);
+        return zero_since_loaded;
+    }();
+    *cleared = &counters_cleared[dev];
+    return SGC_OK;
+}
+
+// Gives a one-launch step its number and clears its counters in front of it where they may not be as the kernel needs them (see AttnArgs): zero,
+// or below the number in the upper 24 bits.  Not captured: the first step on new memory, and the first after the numbers have started
+// anew (cleared: 0, or 1 + the launches' count >> 24 at the last clearing).  What calls that ran into each other may leave is below the
+// next one's number.  A captured step keeps its number, and what has run between capture and replay may be above it: the first step of a
+// capture is preceded by a node that clears them, and the capture's other steps, ordered behind it (steps on the same counters may
+// not overlap), need none.  (16 steps of 5 queries over 3001 tokens, a graph: 236.9 us a replay without that node, 241.5 with it.)
+static int number_step(sgc_ctx *ctx, uint32_t *counters, size_t bytes, uint64_t *cleared, hipStream_t s, uint32_t *number)
+{
+    const uint64_t n = g_step_launches.fetch_add(1, std::memory_order_relaxed) + 1, due = 1 + (n >> 24);
+    *number = (uint32_t)(n & 0xffffffu);
+    if (bytes == 0) return SGC_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    const bool known = hipStreamGetCaptureInfo(s, &capture, &id) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    const bool plain = known && capture == hipStreamCaptureStatusNone;
+    if (plain ? *cleared == due : known && ctx->counters_at == counters && ctx->counters_capture == id && ctx->counters_due == due) return SGC_OK;
+    SGC_HIP(ctx, launch_fill_zero_bytes(counters, bytes, s));
+    if (plain) {
+        *cleared = due;
+    } else {
+        ctx->counters_at = known ? counters : nullptr;
+        ctx->counters_capture = id;
+        ctx->counters_due = due;
+    }
+    return SGC_OK;
+}
+
+int sgc_debug_leave_in_counters(sgc_ctx *ctx, uint32_t arrived)
+{
+    char *scratch = nullptr;
+    uint64_t *cleared = nullptr;
+    const int rc = noalloc_scratch(ctx, &scratch, &cleared);
+    if (rc != SGC_OK) return rc;
+    const std::vector<uint32_t> v(kNoAllocCounters, (uint32_t)g_step_launches.load() << 8 | (arrived & 0xff));
+    SGC_HIP(ctx, hipMemcpy(scratch + kNoAllocScratchBytes, v.data(), v.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     return SGC_OK;
 }
 
@@ -1702,28 +1749,29 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     const size_t bytes = std::max(few_bytes, S * (o_bytes + lse_bytes));
     char *scratch = nullptr;
     uint32_t *arrived = nullptr;
+    uint64_t *cleared = nullptr;
     if (no_alloc) {
         if (bytes > kNoAllocScratchBytes)
             return fail(ctx, SGC_ENOMEM, "the step's partial results need %zu bytes, the static scratch array holds %zu", bytes, kNoAllocScratchBytes);
-        if ((rc = noalloc_scratch(ctx, &scratch)) != SGC_OK) return rc;
+        if ((rc = noalloc_scratch(ctx, &scratch, &cleared)) != SGC_OK) return rc;
         arrived = reinterpret_cast<uint32_t *>(scratch + kNoAllocScratchBytes);
     } else {
         if (!pl->dec_scratch.p) {
             if ((rc = dev_acquire(ctx, bytes + counters, s, &pl->dec_scratch)) != SGC_OK) return rc;
-            SGC_HIP(ctx, launch_fill_zero_bytes(pl->dec_scratch.p + bytes, counters, s));
+            ctx->counters_at = nullptr;          // (the block may be one whose counters this capture has cleared)
         }
         scratch = pl->dec_scratch.p;
         arrived = reinterpret_cast<uint32_t *>(scratch + bytes);
+        cleared = &pl->dec_counters_cleared;
     }
     if (few) {
+        if ((rc = number_step(ctx, arrived, counters, cleared, s, &a.launch)) != SGC_OK) return rc;
         a.o = dev_o;
         a.lse = dev_lse;
         a.few = 1;
         a.own_cost2 = pl->dec_own_cost2;
         a.parts = scratch;
         a.arrived = arrived;
-        static std::atomic<uint32_t> launches{0};
-        a.launch = launches.fetch_add(1, std::memory_order_relaxed) % 0xffffffu + 1;
         SGC_HIP(ctx, launch_attn_mfma(a, s));
         return SGC_OK;
     }

@@ -225,6 +225,9 @@ struct GemmPlan {
 };
 // (n_plain, kv_dest: as in GemmArgs)
 GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int n_plain, int kv_dest);
+// Not part of the interface: writes to the counters of steps that may not allocate what a step launched now would leave there if it ended
+// with `arrived` of a row tile's key ranges counted (see AttnArgs).  Synchronous.
+extern "C" int sgc_debug_leave_in_counters(sgc_ctx *ctx, uint32_t arrived);
 // Not part of the interface: the plan as {big_slabs, rest}, so that tests can say which tiles a shape is computed in.
 extern "C" void sgc_debug_projection_plan(const int32_t *slab_rows, int32_t n_slabs, int32_t N, int32_t K, int32_t n_plain, int32_t kv_dest, int32_t *out);
 
@@ -324,7 +327,7 @@ struct AttnArgs {
     const int32_t *sq_query;
     int32_t n_append;
     // decode steps of few rows (attn_few_kernel): one launch does the whole step.  n_ranges key ranges per row tile; the partial results
-    // of several go to parts (kFewPartBytes each), arrived counts a row tile's ranges in, above the launch's number (24 bits; zero between
+    // of several go to parts (kFewPartBytes each), arrived counts a row tile's ranges in, above the launch's number (24 bits; the count is zero between
     // launches).
     int32_t few;
     int32_t own_cost2;            // a query's own keys against 32 cached keys, in halves
@@ -427,6 +430,10 @@ struct sgc_ctx {
     bool timing = false;            // record events around the suffix launch's kernels
     int timing_period = 1;          // ... of every timing_period-th suffix launch
     uint64_t timing_launches = 0;   // suffix launches since timing was switched on
+    // Counters of one-launch decode steps that a node of a capture has cleared: the capture's id, and where they are (null: none).
+    unsigned long long counters_capture = 0;
+    const void *counters_at = nullptr;
+    uint64_t counters_due = 0;
     bool decodes = false;           // some plan has decode steps: a prompt's call keeps the device's page tables current
     // the last kTimingRing timed suffix launches: events before ingest, between, after attention
     static constexpr int kTimingRing = 128;
@@ -486,6 +493,7 @@ struct sgc_plan {
     std::vector<sgc::TokInfo> dtok;
     size_t spool_layer_bytes = 0;
     sgc_dev_block dec_scratch;                // cached-prefix part of a decode step: O then LSE
+    uint64_t dec_counters_cleared = 0;        // its counters: see clear_step_counters
     // projected keys of the batch (sgc_project_qkv_suffix): 1 = the suffix pages of proj_layer are written,
     // 2 = un-rotated K then V matrices [T][Hkv d] are kept in proj_kv for the suffix launch to ingest
     int32_t proj_state = 0, proj_layer = -1;

@@ -104,3 +104,66 @@ def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
         assert np.isnan(o[1, :4, 7]).all()
         o[1, :4, 7] = to_host_f32(first)[1, :4, 7]
         assert np.array_equal(o, to_host_f32(first))
+
+
+@pytest.mark.parametrize("noalloc", [True, False])
+def test_captured_steps(noalloc):
+    """Replays of captured steps, with other steps between them, give the eager steps' bits, also where the counters of the array of callers
+    that cannot allocate hold what later steps that ran into each other would leave there.  Steps captured on a plan that has run none (its
+    block, counters included, is new) neither need that capture to be replayed nor leave the eager steps behind it without cleared counters."""
+    import torch
+    from paper_2505_10951_amd import sgc
+    from paper_2505_10951_amd.harness import Session, to_device
+    w = workloads.custom("few_graph", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=[2500, 700],
+                         cluster_sizes=[3, 2], suffix_range=(2, 30), seed=9)
+    call = sgc.sgc_decode_step_batched_noalloc if noalloc else sgc.sgc_decode_step_batched
+    with Session(w) as s:
+        for c in range(2):
+            s.alloc_cluster(c)
+        s.prefix_prefill_batched([0, 1], 0)
+        s.assign()
+        s.enable_decode(3)
+        s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
+        steps = [tuple(to_device(x, "bf16") for x in w.decode_qkv(t)) for t in range(3)]
+        outs = [torch.zeros_like(q) for q, _, _ in steps]
+
+        def run(stream):
+            for t, (q, k, v) in enumerate(steps):
+                call(s.ctx, s.cache, s.plan, 0, t, q.data_ptr(), k.data_ptr(), v.data_ptr(), outs[t].data_ptr(), None, stream)
+
+        def capture():
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                run(torch.cuda.current_stream().cuda_stream)
+            return g
+
+        def check(do):
+            for o in outs:
+                o.fill_(7.0)
+            do()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(outs, ref))
+
+        # the reference: another plan of the same batch, eager
+        run(s.stream)
+        torch.cuda.synchronize()
+        ref = [o.clone() for o in outs]
+        assert all(torch.isfinite(o).all() for o in ref)
+        s.assign()
+        s.enable_decode(3)
+        s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
+        torch.cuda.synchronize()
+        dropped = capture()
+        check(lambda: run(s.stream))
+        del dropped
+        first, second = capture(), capture()
+        for k in (0, 1, 2, 5):
+            check(lambda: run(s.stream))
+            if noalloc and k:
+                sgc.lib().sgc_debug_leave_in_counters(s.ctx, k)
+            check(second.replay)
+            check(first.replay)
+            check(first.replay)
+        if noalloc:
+            sgc.lib().sgc_debug_leave_in_counters(s.ctx, 1)
+        check(lambda: run(s.stream))
