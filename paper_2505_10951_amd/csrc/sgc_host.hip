@@ -519,15 +519,41 @@ void layout_suffix_pages(sgc_plan *pl)
     pl->n_pool_pages = page;
 }
 
-// Steps that the one-launch kernel (attn_few_kernel) takes: 16-bit caches and at most 32 rows of a cluster and KV head, where it is the
-// faster.  load, own_load: a row tile's cached and own keys, own keys alone, in 32-key units.  Its workgroups have a compute unit each,
-// so past 256 row tiles short ones lose (24 prompts of 120 tokens, 32 KV heads, a query each: 30.7 against 28.9 us; of 200 tokens 32.1
-// against 33.7), and many long questions are better dealt to all wavefronts of the chip (32 queries of about 105 own keys without head groups:
-// prompts of 60 38.5 against 37.0 us, of 3000 201 against 193; 8 of them with head groups 28.6 against 31.2).
-bool few_row_steps(const sgc_ctx *ctx, int64_t row_tiles, int64_t most_rows, int64_t load, int64_t own_load)
+// What a decode step has to do, in units of 32 keys and a row tile: cached keys, and own keys, of which 16 heads of a query are a task of a
+// round trip for every 32, about 1.75 units each.
+struct StepLoad {
+    int64_t row_tiles = 0, most_rows = 0;      // of a cluster and KV head
+    int64_t max_steps = 0;                     // 64-key steps of the longest prompt
+    int64_t own = 0;                           // own keys, row tiles' mean
+    int64_t own_most = 0, own_total = 0;       // own keys of a row tile at most, of all of them
+    int64_t total = 0;                         // cached and own keys of all
+    int64_t mean() const { return total / std::max<int64_t>(row_tiles, 1); }
+};
+
+// Steps that the one-launch kernel (attn_few_kernel), with S key ranges, takes: 16-bit caches and at most 32 rows of a cluster and KV head, where
+// it is the faster; a workgroup of it has a compute unit and eight wavefronts, and own keys stay with their row tile, while two
+// launches deal own keys to all wavefronts of the chip.  One launch against two, us a step:
+//  - a workgroup may hold 55 units of own keys more than the chip's compute units do on average, and half its cached keys' more, behind which
+//    they hide.  Clusters of uneven sizes, 32 KV heads: 64 row tiles, 375 units in four ranges against 28, 32.1 / 27.2; 96, 70 against 6, 25.1 / 21.1; 192, 387
+//    against 106, 101.0 / 71.0; but 256, 105 against 33 behind 34 cached, 37.7 / 49.5; 128, 243 in two against 58 behind 50, 46.0 / 48.5.
+//  - own keys: 12 queries of 180 to 300 without head groups over 500, 168 units, 21.8 / 28.6, 128 row tiles of them 46.7 / 51.3; 8 with head groups
+//    of 350 to 600 over 2500, 224 units, 35.4 / 42.9.  Past 400 units, or 180 for every compute unit, it is even or slower: 8 x 32 queries of 11
+//    to 600 over 500 311 / 289, 4 x 32 167.6 / 160.7.  Over one 64-key step they are the whole work, and two launches no slower
+//    from 150 units: 8 queries of 350 to 600, 212 units, 31.0 / 29.6.
+//  - past 256 row tiles they come in rounds, of which the fixed part counts, and loses over long prompts: 288 row tiles of 32 rows 201 / 161, of
+//    16 rows 39.0 / 32.8; 320 of 7 rows and 45 units 65.9 / 56.8; 384 of 6 rows over 68 steps 216 / 195; 768 of 2 rows and 21 units 57.2 / 46.6.
+//    Few rows gain: 288 of 2 rows and 12 units 17.7 / 25.6, 52 units 44.2 / 53.0; 512 of 5 rows 23.7 / 29.9; 640 of 14 rows 54.1 / 60.3; 1024 of 4 rows and 50 units 112 / 130; and so do
+//    rounds that are full, own keys above all: 768 of 20 rows and 72 units 99.9 / 108.9; 1024 of 25 rows 157 / 167.
+bool few_row_steps(const sgc_ctx *ctx, const StepLoad &l, int S)
 {
-    return row_tiles > 0 && row_tiles <= kFewRowTiles && most_rows <= 32 && ctx->p.kv_dtype != SGC_FP8_E4M3 && (row_tiles <= 256 || load >= 10) &&
-           own_load <= 150;
+    if (l.row_tiles <= 0 || l.row_tiles > kFewRowTiles || l.most_rows > 32 || ctx->p.kv_dtype == SGC_FP8_E4M3) return false;
+    if (l.own_most > S * (l.own_total / 256 + 55) + l.max_steps) return false;
+    if (l.row_tiles > 256) {
+        if (l.mean() < (l.row_tiles > 512 ? 22 : 10)) return false;
+        if (l.most_rows <= 14) return l.max_steps <= 30 && l.mean() <= (l.row_tiles >= 512 || l.most_rows <= 5 ? 150 : 40);
+        return (l.row_tiles + 255) / 256 * 256 - l.row_tiles <= 16 && 10 * l.own >= 7 * l.mean() && l.mean() <= 165;
+    }
+    return l.own <= (l.max_steps > 1 ? 400 : 150) && l.own * l.row_tiles <= 180 * 256;
 }
 
 // Decode work list: one row group (the g heads of a KV head) per query, all queries of a (cluster, KV head)
@@ -544,15 +570,24 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     };
     std::vector<Unit> units;
     std::vector<double> work;
-    int64_t row_tiles = 0, most_rows = 0;
-    int max_steps = 0;
+    auto own_cost2 = [&](int32_t q0, int32_t q1) -> int32_t {          // a task's units, in halves, from the queries' mean length
+        int64_t tokens = 0;
+        for (int32_t q = q0; q < q1; ++q) tokens += pl->sq_len[q] + pl->decode_cap / 2;
+        return (int32_t)std::max<int64_t>(5, (7 * ((tokens / std::max(q1 - q0, 1) + 31) / 32) + 1) / 2);
+    };
+    StepLoad step;
+    const int halves = (g + 15) / 16;
     for (int c = 0; c < pl->n_clusters; ++c) {
         const int64_t nq = pl->cl_sq_off[c + 1] - pl->cl_sq_off[c];
         if (nq == 0) continue;
-        const int64_t nt = (nq * g + tile_rows - 1) / tile_rows;
-        most_rows = std::max(most_rows, nq * g);
-        row_tiles += nt * ctx->p.n_kv_heads;
-        max_steps = std::max(max_steps, (pl->cl_prefix_len[c] + 63) / 64);
+        const int64_t nt = (nq * g + tile_rows - 1) / tile_rows, steps = (pl->cl_prefix_len[c] + 63) / 64;
+        const int64_t own = nq * halves * own_cost2(pl->cl_sq_off[c], pl->cl_sq_off[c + 1]) / 2;
+        step.most_rows = std::max(step.most_rows, nq * g);
+        step.row_tiles += nt * ctx->p.n_kv_heads;
+        step.max_steps = std::max(step.max_steps, steps);
+        step.own_most = std::max(step.own_most, own);
+        step.own_total += own * ctx->p.n_kv_heads;
+        step.total += (2 * steps + own) * ctx->p.n_kv_heads;
         for (int hk = 0; hk < ctx->p.n_kv_heads; ++hk) {
             units.push_back({c, hk});
             work.push_back((double)nt * (pl->cl_prefix_len[c] + 64.0));
@@ -567,25 +602,23 @@ void build_decode_tiles(sgc_plan *pl, int tile_rows)
     // third and fourth round trip); 32 x 16 steps, S = 2, 4, 8 -> 22.1, 20.2, 20.9 us.  Past eight ranges only long
     // prompts gain: 8 x 157 steps, S = 8, 16 -> 33.7, 30.3 us.
     auto whole_trips = [](int n, int from) { return n > from ? n / 4 * 4 : n; };
-    // load of a row tile in 32-key units: its cached keys, and its queries' own keys, 16 heads of a query a task of a round trip
-    // for every 32 keys, about 1.75 units each
-    int64_t own_tokens = 0;
-    for (int32_t len : pl->sq_len) own_tokens += len + pl->decode_cap / 2;
-    const int64_t n_sq = std::max<int64_t>((int64_t)pl->sq_len.size(), 1);
-    pl->dec_own_cost2 = (int32_t)std::max<int64_t>(5, (7 * ((own_tokens / n_sq + 31) / 32) + 1) / 2);
-    const int64_t tasks = row_tiles > 0 ? n_sq * ctx->p.n_kv_heads * ((g + 15) / 16) / row_tiles : 0;
-    const int64_t own_load = tasks * pl->dec_own_cost2 / 2, load = 2 * max_steps + own_load;
-    pl->dec_few = few_row_steps(ctx, row_tiles, most_rows, load, own_load);
+    const int64_t row_tiles = step.row_tiles;
+    const int max_steps = (int)step.max_steps, n_sq = (int)pl->sq_len.size();
+    pl->dec_own_cost2 = own_cost2(0, n_sq);
+    step.own = row_tiles > 0 ? (int64_t)n_sq * ctx->p.n_kv_heads * halves / row_tiles * pl->dec_own_cost2 / 2 : 0;
     int S = 1;
-    if (pl->dec_few) {
+    if (row_tiles > 0) {
         // The one-launch kernel's workgroups have a compute unit each and eight wavefronts for a range's 32-key units: three units
         // a wavefront, or fewer while that makes no more than eight ranges, and not more than half the chip.  A step, us: 5 queries over 3001
         // keys, S = 3, 4, 8, 12 -> 15.1, 14.4, 14.7, 15.2; one over 9000, S = 6, 8, 12 -> 16.4, 14.6, 14.0; 5 without head groups over
         // 500, S = 1, 2, 3, 8 -> 14.0, 11.5, 11.0, 11.2; 16 over a prompt of 1000 each, S = 1, 2, 3 -> 16.9, 17.3, 22.5.
+        const int64_t load = 2 * max_steps + step.own;
         S = (int)std::max((load + 23) / 24, std::min<int64_t>((load + 5) / 6, 8));
         const int half_chip = (int)std::max<int64_t>(128 / row_tiles, 1);
         S = std::max(1, std::min({S, load > 24 * half_chip ? (int)(256 / row_tiles) : half_chip, g > 16 ? kDecodeDotSplits : kDecodeMaxSplits}));
-    } else if (row_tiles > 0) {
+    }
+    pl->dec_few = few_row_steps(ctx, step, S);
+    if (!pl->dec_few && row_tiles > 0) {
         const int full = std::min(max_steps / 8, (int)std::min<int64_t>(256 / row_tiles, 256));
         const int half = std::min({max_steps / 3, (int)std::min<int64_t>(128 / row_tiles, 128), 8});
         S = std::max({1, whole_trips(std::min(full, kDecodeMaxSplits), 8), whole_trips(half, 4)});
@@ -1812,6 +1845,14 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     SGC_HIP(ctx, launch_attn_mfma(a, s));
     SGC_HIP(ctx, launch_decode_own_keys(d, s));
     return SGC_OK;
+}
+
+void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out)
+{
+    if (!pl->uploaded) build_decode_tiles(pl, pl->ctx->tile_rows);
+    out[0] = pl->dec_few;
+    out[1] = pl->dec_splits;
+    out[2] = pl->dec_row_tiles;
 }
 
 int sgc_decode_step_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t layer, int32_t step,

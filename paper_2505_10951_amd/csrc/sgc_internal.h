@@ -228,6 +228,8 @@ GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int
 // Not part of the interface: writes to the counters of steps that may not allocate what a step launched now would leave there if it ended
 // with `arrived` of a row tile's key ranges counted (see AttnArgs).  Synchronous.
 extern "C" int sgc_debug_leave_in_counters(sgc_ctx *ctx, uint32_t arrived);
+// Not part of the interface: how a plan with decode steps runs them, as {one launch, key ranges, row tiles}.  Host only.
+extern "C" void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out);
 // Not part of the interface: the plan as {big_slabs, rest}, so that tests can say which tiles a shape is computed in.
 extern "C" void sgc_debug_projection_plan(const int32_t *slab_rows, int32_t n_slabs, int32_t N, int32_t K, int32_t n_plain, int32_t kv_dest, int32_t *out);
 

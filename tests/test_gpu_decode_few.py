@@ -1,6 +1,7 @@
-"""Decode steps of few rows: a workgroup has one group of 32 rows and its eight wavefronts share the cached keys.  Sizes around a
-wavefront's 32 keys, a page of 16 and the eight wavefronts' 256; up to 32 rows, and above that the 128-row workgroups; up to 128
-tiles and above; cached keys past 64 or up to 128 rows in all, and otherwise the 128-row workgroups."""
+"""Decode steps of few rows, one launch: a workgroup has one group of 32 rows and one key range, its eight wavefronts share cached and own
+keys, and the last range of a row tile adds up.  Sizes around a wavefront's 32 keys, a page of 16 and the eight wavefronts' 256; up
+to 32 rows of a cluster and KV head and, in two launches, above that; the limits of the rule that says where it is taken, from both sides
+(tests/test_decode_plan.py has the rule itself)."""
 import numpy as np
 import pytest
 
@@ -8,6 +9,7 @@ pytest.importorskip("torch")
 
 from paper_2505_10951_amd import workloads
 from ref_util import oracle_caches
+from test_decode_plan import decode_plan
 from test_gpu_decode import TOL, _oracle_decode, _run_decode
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +18,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("prefix", [[1, 15], [31, 33], [64, 65], [66, 1], [97, 95], [255, 256], [257, 300], [2000, 1]])
 @pytest.mark.parametrize("hq,hkv,per", [(8, 2, 1), (8, 2, 8), (8, 2, 9), (8, 1, 4), (32, 32, 3), (160, 80, 16)])
 def test_rows_and_keys_around_a_wavefront(hq, hkv, per, prefix):
-    """(80 heads of two clusters: 160 tiles)"""
+    """(80 heads of two clusters: 160 row tiles)"""
     w = workloads.custom("few", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=prefix,
                          cluster_sizes=[per, per], suffix_range=(1, 20), seed=per, k_outlier_scale=8.0 if prefix[0] == 2000 else 1.0)
     o, lse = _run_decode(w, 2)[0]
@@ -71,6 +73,25 @@ def test_own_keys_of_a_step(hq, hkv, per, prefix, suffix):
     o, lse = _run_decode(w, 18)[0]
     o_ref, lse_ref = _oracle_decode(w, 0, 18, oracle_caches(w, 0))
     assert np.isfinite(o).all() and np.abs(o - o_ref).max() <= TOL["bf16"] and np.abs(lse - lse_ref).max() <= 5e-2
+
+
+@pytest.mark.parametrize("hq,hkv,sizes,prefix,suffix,one", [
+    (8, 8, [28], [1100], (100, 140), True), (8, 2, [8], [900], (350, 500), True),       # many own keys
+    (8, 8, [28], [60], (100, 140), False),                                              # ... over one 64-key step
+    (16, 16, [16, 2, 1], [150, 150, 150], (90, 110), True), (32, 32, [31, 2, 1], [150, 150, 150], (90, 110), False),      # uneven clusters
+    (32, 32, [2] * 8, [300, 40] * 4, (1, 30), True),                                    # 256 row tiles, one range
+    (8, 8, [14] + [1] * 32, [700] + [300] * 32, (1, 30), True), (8, 8, [15] + [1] * 32, [700] + [300] * 32, (1, 30), False),      # 264, of up to 14 rows and of 15
+    (8, 8, [1] * 128, [900] * 128, (1, 30), True), (8, 8, [1] * 129, [900] * 129, (1, 30), False),     # 1024 row tiles, and past them
+])
+def test_limits_of_the_rule(hq, hkv, sizes, prefix, suffix, one):
+    w = workloads.custom("few_limits", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=prefix,
+                         cluster_sizes=sizes, suffix_range=suffix, seed=hq + sizes[0])
+    assert decode_plan(hq, hkv, [(n, int(w.suffix_len[w.labels == c].mean()), P) for c, (n, P) in enumerate(zip(sizes, prefix))], steps=2)[0] == one
+    o, lse = _run_decode(w, 2)[0]
+    assert np.isfinite(o).all()
+    some = np.unique(np.linspace(0, w.n_queries - 1, 40).astype(int))
+    o_ref, lse_ref = _oracle_decode(w, 0, 2, oracle_caches(w, 0), queries=some)
+    assert np.abs(o[:, some] - o_ref[:, some]).max() <= TOL["bf16"] and np.abs(lse[:, :, some] - lse_ref[:, :, some]).max() <= 5e-2
 
 
 def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
