@@ -994,8 +994,9 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
     // A small call's tables go with its launches.  (Not where keys are stored alone: the page tables travel beside that, and nothing waits for
     // them.  Not once a plan has decode steps: those may have to find the device's page tables current.)
     const bool carried = any_q && !c->d_scale && !ctx->decodes &&
-                         (ctx->use_mfma ? jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles
+                         (ctx->use_mfma ? ctx->p.n_layers <= kCarriedLayers && jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles
                                         : jobs.size() <= CarriedGeneric::kUnits && page_job.size() <= CarriedGeneric::kPages && gtiles.size() <= CarriedGeneric::kTiles);
+    ctx->carried = carried;
     if (carried) {
         const float2 *rope = ctx->p.rope_base > 0.0f ? ctx->d_rope : nullptr;
         hipError_t e = hipSuccess;
@@ -1545,6 +1546,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
         }
         return SGC_OK;
     };
+    ctx->carried = true;
     if (!ctx->use_mfma && !c->d_scale && ctx->p.kv_dtype != SGC_FP8_E4M3 && !pl->uploaded && !projected) {
         CarriedGeneric t;
         const int n_tiles = carry_generic(pl, c, &t);
@@ -1554,7 +1556,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
             return attend([&]() { return launch_attn_generic(t, n_tiles, s); });
         }
     }
-    if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !pl->uploaded && pl->decode_cap == 0 && !projected && apart) {
+    if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && ctx->p.n_layers <= kCarriedLayers && !pl->uploaded && pl->decode_cap == 0 && !projected && apart) {
         CarriedSuffix t;
         if (carry_suffix(pl, c, &t)) {
             fill_common_args(t.a, ctx, c, layer);
@@ -1564,6 +1566,7 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
             return attend([&]() { return launch_attn_carried(t, s); });
         }
     }
+    ctx->carried = false;
     if ((rc = cache_tables_ensure(c)) != SGC_OK) return rc;
     if ((rc = plan_upload(pl, s, true, c)) != SGC_OK) return rc;
     if ((rc = refresh_tiles(pl, c, s)) != SGC_OK) return rc;
@@ -1847,6 +1850,8 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     return SGC_OK;
 }
 
+int sgc_debug_carried(const sgc_ctx *ctx) { return ctx->carried; }
+
 void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out)
 {
     if (!pl->uploaded) build_decode_tiles(pl, pl->ctx->tile_rows);
@@ -2086,6 +2091,7 @@ int sgc_project_qkv_prefix_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const 
         }
         // few row tiles travel as the launches' arguments: a copy of theirs took 4.4 us before the first product
         const bool carried = tiles.size() <= (size_t)GemmCarried::kTiles;
+        ctx->carried = carried;
         const size_t bytes = tiles.size() * sizeof(GemmRowTile);
         sgc_dev_block blk{};
         if (!carried) {

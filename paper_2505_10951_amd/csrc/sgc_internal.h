@@ -228,6 +228,8 @@ GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int
 // Not part of the interface: writes to the counters of steps that may not allocate what a step launched now would leave there if it ended
 // with `arrived` of a row tile's key ranges counted (see AttnArgs).  Synchronous.
 extern "C" int sgc_debug_leave_in_counters(sgc_ctx *ctx, uint32_t arrived);
+// Not part of the interface: whether the tables of the context's last prompt, batch or prompt projection call went with its launches.
+extern "C" int sgc_debug_carried(const sgc_ctx *ctx);
 // Not part of the interface: how a plan with decode steps runs them, as {one launch, key ranges, row tiles}.  Host only.
 extern "C" void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out);
 // Not part of the interface: the plan as {big_slabs, rest}, so that tests can say which tiles a shape is computed in.
@@ -346,6 +348,11 @@ struct AttnArgs {
 // expanded before the attention launch.  One question over a prompt of 411 tokens: four launches become three, 39.5 -> 33.9 us; a prompt of 300
 // tokens attended to behind its projection, with six questions, 148.2 -> 143.0.  The limits are what fits: a launch's arguments are 4 KiB at most, the runtime's own 256 bytes among them.
 constexpr size_t kLaunchArgsBytes = 4096, kRuntimeArgsBytes = 256;
+// Contexts of few layers only (matrix-core kernel): through many the host is far ahead, launches cost it nothing that shows, and the kernels read
+// tables from device memory sooner than from the launch's arguments.  Serving one question over 411 tokens, all layers, us with tables
+// carried / copied: 1 layer 33.0 / 38.5, 4 layers 134.9 / 135.5, 6 203.6 / 201.6, 12 405.5 / 396.4, 32 1 162 / 1 085; over 60 tokens 6 layers 131.6 / 137.1,
+// 8 174.9 / 178.3, 32 731 / 710.
+constexpr int kCarriedLayers = 6;
 struct CarriedJob {
     const void *q;
     void *o;
@@ -432,6 +439,7 @@ struct sgc_ctx {
     bool timing = false;            // record events around the suffix launch's kernels
     int timing_period = 1;          // ... of every timing_period-th suffix launch
     uint64_t timing_launches = 0;   // suffix launches since timing was switched on
+    bool carried = false;           // the last prompt, batch or prompt projection call's tables went with its launches
     // Counters of one-launch decode steps that a node of a capture has cleared: the capture's id, and where they are (null: none).
     unsigned long long counters_capture = 0;
     const void *counters_at = nullptr;

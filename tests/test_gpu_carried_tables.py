@@ -6,7 +6,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2505_10951_amd import workloads
+from paper_2505_10951_amd import sgc, workloads
 from paper_2505_10951_amd.harness import Session, to_device
 
 pytestmark = pytest.mark.gpu
@@ -121,3 +121,18 @@ def test_generic_kernel_same_bits_as_copied_tables(io, d, hq, hkv, prefix, sizes
             out.append([t.clone() for pair in prompts for t in pair if t.numel()] + [o.clone(), lse])
     for a, b in zip(*out):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("layers", [1, 6, 7, 32])
+def test_contexts_of_many_layers_copy(layers):
+    """Where many layers follow each other tables in the launch's arguments are the slower: they are copied, for prompts and batch."""
+    w = workloads.custom("carried_layers", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[100],
+                         cluster_sizes=[2], suffix_range=(5, 9), n_layers=layers, seed=layers)
+    with Session(w) as s:
+        s.alloc_cluster(0)
+        s.prefix_prefill_batched([0], layers - 1, with_q=True)
+        assert sgc.lib().sgc_debug_carried(s.ctx) == (layers <= 6)
+        s.assign()
+        s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv(layers - 1)), layer=layers - 1)
+        torch.cuda.synchronize()
+        assert sgc.lib().sgc_debug_carried(s.ctx) == (layers <= 6)
