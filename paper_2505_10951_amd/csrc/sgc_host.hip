@@ -992,8 +992,8 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             if (jobs[ji].q)
                 for (int64_t r = 0; r < (int64_t)jobs[ji].prefix_len * g; r += kGenericRows) gtiles.push_back({ji, (int32_t)r});
     // A small call's tables go with its launches.  (Not where keys are stored alone: the page tables travel beside that, and nothing waits for
-    // them.  Not once a plan has decode steps: those may have to find the device's page tables current.)
-    const bool carried = any_q && !c->d_scale && !ctx->decodes &&
+    // them.  Not while a plan has decode steps: those may have to find the device's page tables current.)
+    const bool carried = any_q && !c->d_scale && ctx->decode_plans == 0 &&
                          (ctx->use_mfma ? ctx->p.n_layers <= kCarriedLayers && jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles
                                         : jobs.size() <= CarriedGeneric::kUnits && page_job.size() <= CarriedGeneric::kPages && gtiles.size() <= CarriedGeneric::kTiles);
     ctx->carried = carried;
@@ -1404,6 +1404,7 @@ int sgc_plan_destroy(sgc_plan *pl)
 {
     if (!pl) return SGC_OK;
     plan_free_device(pl);
+    if (pl->decode_cap > 0) --pl->ctx->decode_plans;
     delete pl;
     return SGC_OK;
 }
@@ -1629,9 +1630,9 @@ int sgc_plan_enable_decode(sgc_plan *pl, int32_t max_new_tokens)
             return fail(ctx, SGC_EINVAL, "suffix %d + %d new tokens exceeds %d own keys per query", len, max_new_tokens, kDecodeMaxKeys);
     if (pl->decode_cap == max_new_tokens) return SGC_OK;
     plan_free_device(pl);          // page numbering changes: the device copy is rebuilt at the next upload
+    if (pl->decode_cap == 0) ++ctx->decode_plans;
     pl->decode_cap = max_new_tokens;
     pl->tile_rows = 0;
-    ctx->decodes = true;
     layout_suffix_pages(pl);
     return SGC_OK;
 }

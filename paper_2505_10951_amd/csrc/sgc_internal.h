@@ -444,7 +444,7 @@ struct sgc_ctx {
     unsigned long long counters_capture = 0;
     const void *counters_at = nullptr;
     uint64_t counters_due = 0;
-    bool decodes = false;           // some plan has decode steps: a prompt's call keeps the device's page tables current
+    int decode_plans = 0;           // plans with decode steps: while there are any a prompt's call keeps the device's page tables current
     // the last kTimingRing timed suffix launches: events before ingest, between, after attention
     static constexpr int kTimingRing = 128;
     hipEvent_t ev[kTimingRing][3] = {};

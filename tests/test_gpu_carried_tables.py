@@ -136,3 +136,40 @@ def test_contexts_of_many_layers_copy(layers):
         s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv(layers - 1)), layer=layers - 1)
         torch.cuda.synchronize()
         assert sgc.lib().sgc_debug_carried(s.ctx) == (layers <= 6)
+
+
+def test_prompts_around_decode_steps():
+    """A program that serves batch after batch and generates: prompts' tables are carried before a batch has decode steps and again once its plan
+    is gone, not while it is there; and the steps, those that may not allocate among them, find the page tables that they need."""
+    w = workloads.custom("carried_decode", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[300, 90, 40],
+                         cluster_sizes=[2, 3, 0], suffix_range=(4, 20), seed=3)
+    q, k, v = (to_device(x, "bf16") for x in w.suffix_qkv())
+    steps = [tuple(to_device(x, "bf16") for x in w.decode_qkv(t)) for t in range(2)]
+    results = []
+    with Session(w) as s:
+        carried = lambda: sgc.lib().sgc_debug_carried(s.ctx) == 1
+        for batch in range(3):
+            for c in (0, 1) if batch % 2 == 0 else (1, 0):           # other pages the second time
+                s.alloc_cluster(c)
+            s.prefix_prefill_batched([0, 1], 0, with_q=True)
+            assert carried()
+            s.assign()
+            s.enable_decode(2)
+            s.suffix_prefill(q, k, v)
+            got = []
+            for t, (dq, dk, dv) in enumerate(steps):
+                o = torch.empty_like(dq)
+                entry = sgc.sgc_decode_step_batched_noalloc if batch else sgc.sgc_decode_step_batched
+                entry(s.ctx, s.cache, s.plan, 0, t, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), o.data_ptr(), None, s.stream)
+                got.append(o)
+            s.alloc_cluster(2)
+            s.prefix_prefill_batched([2], 0, with_q=True)
+            assert not carried()
+            s.decode_step(1, *steps[1], do=got[1])
+            torch.cuda.synchronize()
+            results.append(torch.stack(got))
+            sgc.sgc_plan_destroy(s.plan)
+            s.plan = None
+            for c in range(3):
+                s.free_cluster(c)
+    assert all(torch.isfinite(r).all() and torch.equal(r, results[0]) for r in results)
