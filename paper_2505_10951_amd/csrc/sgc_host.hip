@@ -1776,11 +1776,12 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
     // zero.  Two: the cached-prefix part, one set per key range: O [S][n_queries][Hq][d] bf16, then LSE [S][Hq][n_queries].
     // (One launch stores outputs while others still read the new tokens: not where an output overlaps those.)
     const int S = a.n_ranges;
-    const size_t o_bytes = ((size_t)pl->n_queries * ctx->p.n_q_heads * ctx->p.head_dim * 2 + 255) / 256 * 256;
-    const size_t lse_bytes = ((size_t)ctx->p.n_q_heads * pl->n_queries * sizeof(float) + 255) / 256 * 256;
+    const size_t o_exact = (size_t)pl->n_queries * ctx->p.n_q_heads * ctx->p.head_dim * 2, lse_exact = (size_t)ctx->p.n_q_heads * pl->n_queries * sizeof(float);
+    const size_t o_bytes = (o_exact + 255) / 256 * 256, lse_bytes = (lse_exact + 255) / 256 * 256;
     const size_t kv_bytes = (size_t)pl->n_queries * ctx->p.n_kv_heads * ctx->p.head_dim * 2;
-    const bool few = pl->dec_few && !overlap(dev_o, o_bytes, dev_k, kv_bytes) && !overlap(dev_o, o_bytes, dev_v, kv_bytes) &&
-                     !overlap(dev_lse, lse_bytes, dev_k, kv_bytes) && !overlap(dev_lse, lse_bytes, dev_v, kv_bytes);
+    const bool few = pl->dec_few && !overlap(dev_o, o_exact, dev_k, kv_bytes) && !overlap(dev_o, o_exact, dev_v, kv_bytes) &&
+                     !overlap(dev_lse, lse_exact, dev_k, kv_bytes) && !overlap(dev_lse, lse_exact, dev_v, kv_bytes);
+    ctx->one_launch = few;
     const size_t few_bytes = pl->dec_few && S > 1 ? (size_t)pl->dec_row_tiles * S * kFewPartBytes : 0;
     const size_t counters = few_bytes > 0 ? 256 * (((size_t)pl->dec_row_tiles * sizeof(uint32_t) + 255) / 256) : 0;
     const size_t bytes = std::max(few_bytes, S * (o_bytes + lse_bytes));
@@ -1852,6 +1853,7 @@ static int decode_step(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, int32_t 
 }
 
 int sgc_debug_carried(const sgc_ctx *ctx) { return ctx->carried; }
+int sgc_debug_one_launch(const sgc_ctx *ctx) { return ctx->one_launch; }
 
 void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out)
 {

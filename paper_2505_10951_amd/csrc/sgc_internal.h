@@ -230,6 +230,8 @@ GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int
 extern "C" int sgc_debug_leave_in_counters(sgc_ctx *ctx, uint32_t arrived);
 // Not part of the interface: whether the tables of the context's last prompt, batch or prompt projection call went with its launches.
 extern "C" int sgc_debug_carried(const sgc_ctx *ctx);
+// Not part of the interface: whether the context's last decode step was one launch.
+extern "C" int sgc_debug_one_launch(const sgc_ctx *ctx);
 // Not part of the interface: how a plan with decode steps runs them, as {one launch, key ranges, row tiles}.  Host only.
 extern "C" void sgc_debug_decode_plan(sgc_plan *pl, int32_t *out);
 // Not part of the interface: the plan as {big_slabs, rest}, so that tests can say which tiles a shape is computed in.
@@ -440,6 +442,7 @@ struct sgc_ctx {
     int timing_period = 1;          // ... of every timing_period-th suffix launch
     uint64_t timing_launches = 0;   // suffix launches since timing was switched on
     bool carried = false;           // the last prompt, batch or prompt projection call's tables went with its launches
+    bool one_launch = false;        // the last decode step was one launch
     // Counters of one-launch decode steps that a node of a capture has cleared: the capture's id, and where they are (null: none).
     unsigned long long counters_capture = 0;
     const void *counters_at = nullptr;

@@ -98,6 +98,7 @@ def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
     """The same step twice gives the same bits (the ranges' counters are back at zero); an output that overlaps the new tokens, whose
     rows must not be stored before all are read, gives the same result within rounding; a NaN value of one query stays with it."""
     import torch
+    from paper_2505_10951_amd import sgc
     from paper_2505_10951_amd.harness import Session, to_device, to_host_f32
     w = workloads.custom("few_again", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=[3000, 40],
                          cluster_sizes=[4, 2], suffix_range=(2, 30), seed=5)
@@ -110,6 +111,7 @@ def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
         s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
         dq, dk, dv = (to_device(x, "bf16") for x in w.decode_qkv(0))
         first = s.decode_step(0, dq, dk, dv).clone()
+        assert sgc.lib().sgc_debug_one_launch(s.ctx)
         for _ in range(3):
             assert torch.equal(s.decode_step(0, dq, dk, dv), first)
         n, hq, d = dq.shape
@@ -118,7 +120,13 @@ def test_step_again_overlapping_and_with_a_value_that_is_not_finite():
         k.copy_(dk)
         s.decode_step(0, dq, k, dv, do=o)
         torch.cuda.synchronize()
+        assert not sgc.lib().sgc_debug_one_launch(s.ctx)
         assert np.abs(to_host_f32(o) - to_host_f32(first)).max() <= 1e-2
+        # outputs that end where the new keys begin do not overlap them: one launch, the same bits
+        one = torch.zeros(n * hq * 2 + dk.numel(), dtype=dq.dtype, device="cuda:0")
+        lse, k = one[:n * hq * 2].view(torch.float32).view(hq, n), one[n * hq * 2:].view(dk.shape)
+        k.copy_(dk)
+        assert torch.equal(s.decode_step(0, dq, k, dv, dlse=lse), first) and sgc.lib().sgc_debug_one_launch(s.ctx)
         bad = dv.clone()
         bad[1, 0, 7] = float("nan")
         o = to_host_f32(s.decode_step(0, dq, dk, bad))
