@@ -1,6 +1,7 @@
 """Small calls whose tables travel with the launches: the same bits as the calls that copy their tables to the device first, at the
 edges of what a launch's arguments hold (6 clusters; prompts: 480 pages, 256 tiles; questions: 144 pages of prompts, 40 own pages,
-48 queries, 40 tiles, 4 queries a tile; generic kernel: 240 pages, 160 tiles, 64 queries) and just past them, where both sides copy."""
+48 queries, 40 tiles, 4 queries a tile; generic kernel: 240 pages, 160 tiles, 64 queries) and just past them, where both sides copy.  Each
+case says which of its two calls carries its tables, and the library has to agree."""
 import numpy as np
 import pytest
 
@@ -13,44 +14,50 @@ pytestmark = pytest.mark.gpu
 
 
 def _pass(w, copied):
-    """Prompts' outputs and LSE, the batch's outputs and LSE; copied: every table goes through the device's copies."""
+    """Whether the prompts' and the batch's tables were carried; prompts' outputs and LSE, the batch's outputs and LSE.  copied: every table
+    goes through the device's copies."""
     with Session(w) as s:
+        carried = lambda: sgc.lib().sgc_debug_carried(s.ctx) == 1
         for c in range(w.n_clusters):
             s.alloc_cluster(c)
         if copied:
             s.assign()
             s.enable_decode(1)
         prompts = s.prefix_prefill_batched(list(range(w.n_clusters)), 0, with_q=True, want_lse=True)
+        routes = [carried()]
         s.assign()
         if copied:
             s.upload_plan()
         lse = torch.zeros((w.n_q_heads, w.total_suffix_tokens), device="cuda:0")
         o = s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()), dlse=lse)
+        routes.append(carried())
         again = s.suffix_prefill(*(to_device(x, "bf16") for x in w.suffix_qkv()))
         torch.cuda.synchronize()
         assert torch.equal(o, again)
-        return [t.clone() for pair in prompts for t in pair if t is not None and t.numel()] + [o.clone(), lse]
+        return routes, [t.clone() for pair in prompts for t in pair if t is not None and t.numel()] + [o.clone(), lse]
 
 
-def _check(w):
-    for a, b in zip(_pass(w, False), _pass(w, True)):
-        assert torch.isfinite(a).all() and torch.equal(a, b)
-
-
-@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix", [
-    (32, 8, [411], [1], (23, 23)),
-    (8, 2, [1, 16, 17, 0, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30)),
-    (8, 2, [5, 9, 30, 1, 64, 65, 66], [1] * 7, (1, 9)),                     # seven clusters
-    (4, 2, [2304], [2], (30, 40)), (4, 2, [2305], [2], (30, 40)),           # 144 pages of prompts, 145
-    (2, 2, [7680], [1], (3, 3)), (2, 2, [3840, 3841], [1, 0], (3, 3)),      # 480 pages, 481; 120 tiles
-    (32, 8, [1024], [1], (9, 9)), (32, 8, [1025], [1], (9, 9)),             # 256 tiles, 264
-    (8, 8, [100], [48], (5, 8)), (8, 8, [100], [49], (5, 8)),               # more than four queries a tile
-    (32, 8, [70], [40], (1, 2)), (64, 8, [70], [20], (17, 32)), (64, 8, [70], [21], (17, 32)),      # 40 own pages, 42
-    (32, 8, [300], [10], (16, 16)), (32, 8, [300], [11], (16, 16)),         # five tiles a KV head, six
+@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix,prompts,batch", [
+    (32, 8, [411], [1], (23, 23), True, True),
+    (8, 2, [1, 16, 17, 0, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30), True, True),
+    (8, 2, [5, 9, 30, 1, 64, 65, 66], [1] * 7, (1, 9), False, False),       # seven clusters
+    (2, 2, [2304], [2], (30, 40), True, True), (2, 2, [2305], [2], (30, 40), True, False),      # 144 pages of prompts, 145
+    (4, 4, [3840, 3840], [1, 0], (3, 3), True, False), (4, 4, [3840, 3841], [1, 0], (3, 3), False, False),      # 480 pages, 481
+    (2, 2, [7680], [1], (3, 3), False, False),                              # 120 tiles, but 60 on one XCD: 480 with padding
+    (32, 8, [1024], [1], (9, 9), True, True), (32, 8, [1025], [1], (9, 9), False, True),        # 256 tiles, 264
+    (8, 8, [100], [48], (5, 8), True, False), (32, 8, [70], [40], (1, 2), True, False),         # more than four queries a tile
+    (2, 2, [70], [10], [49] * 10, True, True), (2, 2, [70], [11], [49] * 10 + [16], True, False),       # 40 own pages, 41
+    (2, 2, [70, 5], [10, 38], [49] * 10 + [0] * 38, True, True), (2, 2, [70, 5], [10, 39], [49] * 10 + [0] * 39, True, False),  # 48 queries, 49, most without tokens
+    (32, 8, [300], [10], (16, 16), True, True), (32, 8, [300], [11], (16, 16), True, False),    # five tiles a KV head, six
 ])
-def test_same_bits_as_copied_tables(hq, hkv, prefix, sizes, suffix):
-    _check(workloads.custom("carried", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=prefix,
-                            cluster_sizes=sizes, suffix_range=suffix, seed=len(prefix) + sum(sizes)))
+def test_same_bits_as_copied_tables(hq, hkv, prefix, sizes, suffix, prompts, batch):
+    lens = {"suffix_range": suffix, "cluster_sizes": sizes} if isinstance(suffix, tuple) else {"suffix_len": suffix, "labels": np.repeat(np.arange(len(sizes)), sizes)}
+    w = workloads.custom("carried", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rope_base=500000.0, io_dtype="bf16", prefix_len=prefix,
+                         seed=len(prefix) + sum(sizes), **lens)
+    (routes, got), (copied, ref) = _pass(w, False), _pass(w, True)
+    assert routes == [prompts, batch] and copied == [False, False]
+    for a, b in zip(got, ref):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
 
 
 def test_captured_calls_and_calls_that_copy_behind_them():
@@ -94,14 +101,16 @@ def test_captured_calls_and_calls_that_copy_behind_them():
 
 
 @pytest.mark.parametrize("io,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
-@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix", [
-    (4, 4, [192, 256], [8, 8], (16, 32)),
-    (8, 2, [1, 16, 0, 17, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30)),
-    (4, 2, [300], [64], (1, 9)), (4, 2, [300], [65], (1, 9)),                    # 64 queries, 65
-    (4, 1, [3840], [1], (640, 640)), (4, 1, [3841], [1], (641, 641)),            # 240 pages and 160 tiles, and past both
-    (16, 16, [40, 7, 1], [5, 20, 0], (0, 4)),                                    # queries without tokens, many in a tile
+@pytest.mark.parametrize("hq,hkv,prefix,sizes,suffix,prompts_carried,batch_carried", [
+    (4, 4, [192, 256], [8, 8], (16, 32), True, True),
+    (8, 2, [1, 16, 0, 17, 200, 64], [1, 2, 1, 3, 1, 1], (1, 30), True, True),
+    (4, 2, [300], [64], (1, 9), True, True), (4, 2, [300], [65], (1, 9), True, False),         # 64 queries, 65
+    (4, 1, [640], [1], (640, 640), True, True), (4, 1, [641], [1], (641, 641), False, False),   # 160 tiles, 161
+    (1, 1, [2560, 1280], [1, 1], (9, 9), False, True), (1, 1, [2560, 1281], [1, 1], (9, 9), False, False),      # 240 pages, 241; 240 tiles
+    (2, 2, [1920, 640], [1, 1], (9, 9), True, True), (2, 2, [1920, 641], [1, 1], (9, 9), False, True),          # 160 tiles of prompts, 161
+    (16, 16, [40, 7, 1], [5, 20, 0], (0, 4), True, True),                                      # queries without tokens, many in a tile
 ])
-def test_generic_kernel_same_bits_as_copied_tables(io, d, hq, hkv, prefix, sizes, suffix):
+def test_generic_kernel_same_bits_as_copied_tables(io, d, hq, hkv, prefix, sizes, suffix, prompts_carried, batch_carried):
     """Prompts: alone against in a call with a prompt of 300 pages, which copies its tables; batch: against an uploaded plan."""
     w = workloads.custom("carried_generic", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rope_base=10000.0, io_dtype=io, kv_dtype=io,
                          prefix_len=prefix + [4800], cluster_sizes=sizes + [0], suffix_range=suffix, seed=len(prefix) + sum(sizes))
@@ -109,15 +118,18 @@ def test_generic_kernel_same_bits_as_copied_tables(io, d, hq, hkv, prefix, sizes
     out = []
     for copied in (False, True):
         with Session(w) as s:
+            carried = lambda: sgc.lib().sgc_debug_carried(s.ctx) == 1
             for c in range(n + 1):
                 s.alloc_cluster(c)
             prompts = s.prefix_prefill_batched(list(range(n + 1 if copied else n)), 0, with_q=True, want_lse=True)[:n]
+            assert carried() == (prompts_carried and not copied)
             s.assign()
             if copied:
                 s.upload_plan()
             lse = torch.zeros((hq, w.total_suffix_tokens), device="cuda:0")
             o = s.suffix_prefill(*(to_device(x, io) for x in w.suffix_qkv()), dlse=lse)
             torch.cuda.synchronize()
+            assert carried() == (batch_carried and not copied)
             out.append([t.clone() for pair in prompts for t in pair if t.numel()] + [o.clone(), lse])
     for a, b in zip(*out):
         assert torch.isfinite(a).all() and torch.equal(a, b)

@@ -6,7 +6,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2505_10951_amd import workloads
+from paper_2505_10951_amd import sgc, workloads
 from paper_2505_10951_amd.harness import Session, to_device, to_host_f32
 from test_gpu_layer import _check, _oracle_layer, _run_layer
 from test_projection_plan import PAGES, SLOTS, plan as tiles_of
@@ -52,4 +52,10 @@ def test_row_tiles_with_the_launch_and_copied(n):
     assert tiles_of(prompts, 512, 64, 256, PAGES)[0] == 2        # one tile a prompt
     w = workloads.custom("row_tiles", n_q_heads=2, n_kv_heads=1, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=prompts,
                          cluster_sizes=[1] * n, suffix_range=(3, 9), seed=n)
+    with Session(w) as s:
+        for c in range(n):
+            s.alloc_cluster(c)
+        dw, dwo = (to_device(x, "bf16") for x in w.layer_weights(64))
+        s.layer_prefix(list(range(n)), 64, dw, dwo, with_output=False)
+        assert sgc.lib().sgc_debug_carried(s.ctx) == (n <= 72)
     _run_layer(w, 64)
