@@ -21,7 +21,8 @@
 //            pages in the cache's K order: 8 consecutive channels of a token are one 16-byte unit;
 //   V heads: the matrix-core operands are swapped for these wavefronts so that a lane owns ONE channel and
 //            16 tokens; when the 16 rows are one page this is the cache's V order (8 tokens of a channel
-//            contiguous) and goes out as 16-byte stores, otherwise element by element.
+//            contiguous) and goes out as 16-byte stores; a batch's, whose questions begin at any row, pass through LDS
+//            and leave in whole pages as well, but for those that reach over the tile's rows (store_own_values).
 // With an fp8 cache (the scale needs the maximum over the whole prompt first) K and V go to a staging
 // matrix and the ingest kernels take it from there.
 #include <hip/hip_runtime.h>
@@ -933,14 +934,16 @@ hipError_t launch_tiles(const ARGS &args, hipStream_t s)
 
 // What a launch of n tiles takes, in microseconds, on a chip of 256 CUs: a start, per round of tiles a fixed part (first
 // copies, sums, stores) and one per 64-wide step, less for a last round that leaves CUs idle or with one workgroup instead of
-// two; tiles that write keys and values into pages cost more, most where the slots are a batch's (two-byte stores of V).
+// two; tiles that write keys and values into pages cost more, most where the slots are a batch's.
 // Fitted to 1053 shapes (16 to 16384 rows, 128 to 12288 columns, contractions of 64 to 8192; plain, prompt and batch
-// products), every tile kind measured on each: within 5 % in the median and 22 % for nine in ten.  Some of them, us,
-// 256 x 256 / 128 x 128 deep / pairs / 64 x 128 / 64 x 64:
-//   1000 x 4096 x 4096 (plain)                   73 / 40 / 46 / 45 / 49
-//   16384 x 4096 x 4096 (plain)                  421 / 620 / 509 / 699 / 760
-//   6400 x 6144 x 1024, batch                    123 / 152 / 118 / 205 / 154
-//   10 x 1024 x 10240 x 1024, prompts            242 / 296 / 236 / 474 / 387
+// products), every tile kind measured on each, when the kernels copied slabs by global loads, stored a batch's values two
+// bytes a lane and cleared its last pages by a launch of its own: within 5 % in the median and 22 % for nine in ten then.  The present ones,
+// on 1 410 other shapes of these ranges: within 7 % and 24 %, most off for a batch's tiles, which have become cheaper.  Some, us,
+// 256 x 256 / 128 x 128 deep / pairs / 64 x 128 / 64 x 64, then and now:
+//   1000 x 4096 x 4096 (plain)                   73 / 40 / 46 / 45 / 49            73 / 39 / 47 / 46 / 50
+//   16384 x 4096 x 4096 (plain)                  421 / 620 / 509 / 699 / 760       395 / 607 / 487 / 700 / 744
+//   6400 x 6144 x 1024, batch                    123 / 152 / 118 / 205 / 154       108 / 143 / 105 / 196 / 145
+//   10 x 1024 x 10240 x 1024, prompts            242 / 296 / 236 / 474 / 387       214 / 310 / 229 / 480 / 373
 struct TileCost {
     double start, round, step;              // per full round
     double last, last_step;                 // of a last round with (nearly) idle CUs
@@ -986,8 +989,10 @@ int proj_gemm_tile_cols(int kind) { return kind == GEMM_256 ? 256 : kind == GEMM
 // with 256 x 256 tiles and the rest in smaller ones (12977 x 4096 columns are 3.2 rounds: the fifth of a round that would
 // take a whole one goes out in 192 tiles of 128 x 128).  A second launch costs its start and the first one's drain: 4 us, 6
 // where slots of a batch are written, nothing beyond the stores counted above where whole pages are.  256 x 256 tiles alone
-// are kept unless something is 3 % cheaper: over the shapes above the choice then takes 1.0 % longer than the best one in the
-// mean, and more than 3 % longer than 256 x 256 tiles alone on three (800 x 12288 x 128 to 512 of a batch, 1 to 4 us).  (One
+// are kept unless something is 3 % cheaper: over the fit's shapes the choice took 1.0 % longer than the best one in the
+// mean, and more than 3 % longer than 256 x 256 tiles alone on three (800 x 12288 x 128 to 512 of a batch, 1 to 4 us).  With the present kernels
+// it takes 2.0 % longer in the mean of those 1 410, and more than 3 % longer than 256 x 256 tiles alone on 42, nearly all of a batch and short
+// contractions (784 x 12288 x 640 46.6 us for 35.3, 3853 x 3072 x 128 38.0 for 26.2; 10 x 1024 x 10240 x 1024 of prompts 229 for 214).  (One
 // time per step whatever the columns hold, and nothing per round, sent 6400 rows x 6144 x 1024 of a batch out in two
 // launches, 140 us for 123.)
 GemmPlan proj_gemm_plan(const int32_t *slab_rows, int n_slabs, int N, int K, int n_plain, int kv_dest)

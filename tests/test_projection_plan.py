@@ -1,6 +1,7 @@
 """The tiles a projection is computed in, against times measured for every choice (MI355X, microseconds): no plan may be
 slower than 256 x 256 tiles alone by more than 5 %, the spread of such measurements, nor than the best choice by more than 10 %.
-Host only: the planner is part of the library, the times are data."""
+Host only: the planner is part of the library, the times are data, those that its estimate was fitted to.  (The kernels have become
+faster since, a batch's most; sgc_gemm.hip says beside the estimate where its choice is no longer the best one.)"""
 import ctypes
 
 import numpy as np
