@@ -435,7 +435,8 @@ __global__ void __launch_bounds__(256, 1) proj_gemm_kernel(const ARGS args)
             // swap between the two 32-lane halves lane h holds the eight consecutive features 16 u + 8 h .. + 7.  Accumulators pi and
             // pi + 2 hold the rotation's partners.  Piece by piece, behind a scheduling barrier each: taken together, the accumulators'
             // copies in ordinary registers did not fit and 80 were spilled.  Llama-3-8B's layer over ten prompts of
-            // 1024 tokens and 320 questions of 16 to 64: 1 957 -> 1 942 us.
+            // 1024 tokens and 320 questions of 16 to 64: 1 957 -> 1 942 us.  (32 were left then; with the values' way through LDS and the
+            // clearing of last pages beside it 48 are, 240 bytes of scratch memory a lane.)
             auto put = [&](const float (&v)[8], int pi, int u) __attribute__((always_inline)) {
                 float x[8];
 #pragma unroll

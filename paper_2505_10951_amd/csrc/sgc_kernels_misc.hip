@@ -1326,7 +1326,7 @@ __global__ void __launch_bounds__(NW * 64) attn_generic_kernel(const ARGS args)
         }
     }
     if (lse_base && (threadIdx.x & 15) == 0)
-        lse_base[(int64_t)head * lse_stride + (a.mode == MODE_SUFFIX ? src + 0 : qpos + 0)] = (M + log2f(L)) * 0.6931471805599453f;
+        lse_base[(int64_t)head * lse_stride + (a.mode == MODE_SUFFIX ? src : qpos)] = (M + log2f(L)) * 0.6931471805599453f;
 }
 
 }  // namespace

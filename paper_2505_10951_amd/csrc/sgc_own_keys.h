@@ -52,7 +52,8 @@ __device__ inline void dec_load8(const uint16_t *p, float out[8])
 // 16 cb + lane % 16 from each of the two pages.  Keys come in chunks of CH pages with an online softmax over the chunks.
 // What bounds it is the chain of dependent loads: the first chunk's keys are requested before the query rows, a chunk's values before
 // its softmax or, TOGETHER, with its keys.  (Many wavefronts a SIMD: chunks of 2, apart; chunks of 4 pages, and 2 pages with the next
-// chunk's keys requested before the softmax, were no faster.  One wavefront by itself: chunks of 4, together.)
+// chunk's keys requested before the softmax, were no faster.  Wavefronts beside attn_few_kernel's others: chunks of 2, together; of 4 spill and
+// cost 10 %.)
 // Results: O (unnormalised, relative to 2^m; channels 16 cb + 4 q .. + 3 of head j), m and the sum l of the rounded weights.
 template <bool FRESH, int CH, bool TOGETHER>
 __device__ __forceinline__ void own_keys_attend(const OwnKeys &w, dec_f32x4 (&O)[8], float &m_run, float &l_run)
