@@ -227,16 +227,23 @@ int stage_begin(sgc_ctx *ctx, size_t bytes, char **host, int *slot)
     return SGC_OK;
 }
 
+// The stream's capture status and the capture's id; what cannot be asked for counts as invalidated.
+hipStreamCaptureStatus capture_of(hipStream_t s, unsigned long long *id = nullptr)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long unused = 0;
+    if (hipStreamGetCaptureInfo(s, &status, id ? id : &unused) == hipSuccess) return status;
+    (void)hipGetLastError();
+    return hipStreamCaptureStatusInvalidated;
+}
+
 // Launches what copies the slot's buffer (launch(done, &words): launch_copy_from_host or another launch that does it, which sets
 // `words` words) and notes what will say that the buffer has been read.
 template <typename Launch>
 int stage_launch(sgc_ctx *ctx, int slot, hipStream_t s, Launch launch)
 {
     // A launch that is being captured may run many times or never, at any time after: it sets no words, the event is captured with it.
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool known = hipStreamIsCapturing(s, &capture) == hipSuccess;
-    if (!known) (void)hipGetLastError();
-    const bool plain = known && capture == hipStreamCaptureStatusNone;
+    const bool plain = capture_of(s) == hipStreamCaptureStatusNone;
     CopyDone done{nullptr, 0};
     if (plain) done = {const_cast<uint32_t *>(reinterpret_cast<const uint32_t *>(ctx->h_stage_dev[slot] + ctx->h_stage_cap[slot])), ++ctx->stage_number[slot]};
     int words = 0;
@@ -992,9 +999,11 @@ int sgc_prefix_prefill_batched(sgc_ctx *ctx, sgc_cache *c, int32_t n, const int3
             if (jobs[ji].q)
                 for (int64_t r = 0; r < (int64_t)jobs[ji].prefix_len * g; r += kGenericRows) gtiles.push_back({ji, (int32_t)r});
     // A small call's tables go with its launches.  (Not where keys are stored alone: the page tables travel beside that, and nothing waits for
-    // them.  Not while a plan has decode steps: those may have to find the device's page tables current.)
+    // them.  Not while a plan has decode steps: those may have to find the device's page tables current.  A captured call's go with it whatever
+    // the number of layers: copies need a staging buffer and memory of their own.)
     const bool carried = any_q && !c->d_scale && ctx->decode_plans == 0 &&
-                         (ctx->use_mfma ? ctx->p.n_layers <= kCarriedLayers && jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles
+                         (ctx->use_mfma ? jobs.size() <= CarriedPrefix::kJobs && page_job.size() <= CarriedPrefix::kPages && slots * kXcd <= CarriedPrefix::kTiles &&
+                                              (ctx->p.n_layers <= kCarriedLayers || capture_of(s) != hipStreamCaptureStatusNone)
                                         : jobs.size() <= CarriedGeneric::kUnits && page_job.size() <= CarriedGeneric::kPages && gtiles.size() <= CarriedGeneric::kTiles);
     ctx->carried = carried;
     if (carried) {
@@ -1557,7 +1566,8 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
             return attend([&]() { return launch_attn_generic(t, n_tiles, s); });
         }
     }
-    if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && ctx->p.n_layers <= kCarriedLayers && !pl->uploaded && pl->decode_cap == 0 && !projected && apart) {
+    if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !pl->uploaded && pl->decode_cap == 0 && !projected && apart &&
+        (ctx->p.n_layers <= kCarriedLayers || capture_of(s) != hipStreamCaptureStatusNone)) {
         CarriedSuffix t;
         if (carry_suffix(pl, c, &t)) {
             fill_common_args(t.a, ctx, c, layer);
@@ -1682,11 +1692,9 @@ static int number_step(sgc_ctx *ctx, uint32_t *counters, size_t bytes, uint64_t 
     const uint64_t n = g_step_launches.fetch_add(1, std::memory_order_relaxed) + 1, due = 1 + (n >> 24);
     *number = (uint32_t)(n & 0xffffffu);
     if (bytes == 0) return SGC_OK;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     unsigned long long id = 0;
-    const bool known = hipStreamGetCaptureInfo(s, &capture, &id) == hipSuccess;
-    if (!known) (void)hipGetLastError();
-    const bool plain = known && capture == hipStreamCaptureStatusNone;
+    const hipStreamCaptureStatus capture = capture_of(s, &id);
+    const bool plain = capture == hipStreamCaptureStatusNone, known = capture == hipStreamCaptureStatusActive;
     if (plain ? *cleared == due : known && ctx->counters_at == counters && ctx->counters_capture == id && ctx->counters_due == due) return SGC_OK;
     SGC_HIP(ctx, launch_fill_zero_bytes(counters, bytes, s));
     if (plain) {

@@ -185,3 +185,33 @@ def test_prompts_around_decode_steps():
             for c in range(3):
                 s.free_cluster(c)
     assert all(torch.isfinite(r).all() and torch.equal(r, results[0]) for r in results)
+
+
+def test_captured_calls_carry(layers=32):
+    """A captured call's tables go with it in contexts of many layers too: copies would need a staging buffer and memory while the stream is being
+    captured."""
+    w = workloads.custom("carried_captured", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[100, 70],
+                         cluster_sizes=[2, 1], suffix_range=(5, 40), n_layers=layers, seed=4)
+    q, k, v = (to_device(x, "bf16") for x in w.suffix_qkv())
+    with Session(w) as s:
+        for c in range(2):
+            s.alloc_cluster(c)
+        prompts = s.prefix_prefill_batched([0, 1], 0, with_q=True)
+        s.assign()
+        g = torch.cuda.CUDAGraph()
+        o = torch.empty_like(q)
+        pq, (pk, pv) = to_device(w.prefix_q(1), "bf16"), (to_device(x, "bf16") for x in w.prefix_kv(1))
+        po = torch.empty_like(pq)
+        with torch.cuda.graph(g):
+            stream = torch.cuda.current_stream().cuda_stream
+            sgc.sgc_prefix_prefill(s.ctx, s.cache, 1, 0, pq.data_ptr(), pk.data_ptr(), pv.data_ptr(), po.data_ptr(), None, 70, stream)
+            assert sgc.lib().sgc_debug_carried(s.ctx) == 1
+            sgc.sgc_suffix_prefill_batched(s.ctx, s.cache, s.plan, 0, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, stream)
+        assert sgc.lib().sgc_debug_carried(s.ctx) == 1
+        for _ in range(3):
+            o.zero_()
+            po.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(o, s.suffix_prefill(q, k, v)) and torch.equal(po, prompts[1][0])
+            assert sgc.lib().sgc_debug_carried(s.ctx) == 0
