@@ -1567,9 +1567,10 @@ int sgc_suffix_prefill_batched(sgc_ctx *ctx, const sgc_cache *cc, sgc_plan *pl, 
         }
     }
     if (ctx->use_mfma && ctx->p.kv_dtype == SGC_BF16 && !pl->uploaded && pl->decode_cap == 0 && !projected && apart &&
-        (ctx->p.n_layers <= kCarriedLayers || capture_of(s) != hipStreamCaptureStatusNone)) {
+        ((ctx->p.n_layers <= kCarriedLayers && pl->carried_calls < kCarriedLayers) || capture_of(s) != hipStreamCaptureStatusNone)) {
         CarriedSuffix t;
         if (carry_suffix(pl, c, &t)) {
+            ++pl->carried_calls;
             fill_common_args(t.a, ctx, c, layer);
             fill_batch(t.a);
             t.a.n_tiles = (int32_t)pl->seeds.size();

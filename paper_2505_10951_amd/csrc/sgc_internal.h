@@ -354,6 +354,8 @@ constexpr size_t kLaunchArgsBytes = 4096, kRuntimeArgsBytes = 256;
 // tables from device memory sooner than from the launch's arguments.  Serving one question over 411 tokens, all layers, us with tables
 // carried / copied: 1 layer 33.0 / 38.5, 4 layers 134.9 / 135.5, 6 203.6 / 201.6, 12 405.5 / 396.4, 32 1 162 / 1 085; over 60 tokens 6 layers 131.6 / 137.1,
 // 8 174.9 / 178.3, 32 731 / 710.
+// The same for a batch's calls on one plan: from its seventh on it is uploaded (64 calls behind each other of one question over 411 tokens 15.2 us each with
+// tables carried, 14.3 from the device; the upload costs 6 us once).
 constexpr int kCarriedLayers = 6;
 struct CarriedJob {
     const void *q;
@@ -499,6 +501,7 @@ struct sgc_plan {
     int32_t decode_cap = 0;
     std::vector<sgc::Tile> dtiles;
     std::vector<int32_t> dtile_key0;          // first cached key of each decode tile's key range
+    int32_t carried_calls = 0;                // batch calls whose tables went with the launch
     int32_t dec_splits = 1;                   // key ranges per row tile
     int32_t dec_row_tiles = 0;
     int32_t dec_own_cost2 = 0;

@@ -187,9 +187,29 @@ def test_prompts_around_decode_steps():
     assert all(torch.isfinite(r).all() and torch.equal(r, results[0]) for r in results)
 
 
-def test_captured_calls_carry(layers=32):
-    """A captured call's tables go with it in contexts of many layers too: copies would need a staging buffer and memory while the stream is being
-    captured."""
+def test_a_plan_used_again_is_uploaded():
+    """Six calls on a plan carry their tables, the seventh uploads it: the same bits, also where clusters came and went in between."""
+    w = workloads.custom("carried_again", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[100, 70, 33],
+                         cluster_sizes=[2, 1, 0], suffix_range=(5, 40), seed=2)
+    q, k, v = (to_device(x, "bf16") for x in w.suffix_qkv())
+    with Session(w) as s:
+        for c in range(2):
+            s.alloc_cluster(c)
+        s.prefix_prefill_batched([0, 1], 0)
+        s.assign()
+        first = s.suffix_prefill(q, k, v).clone()
+        for call in range(2, 11):
+            if call == 8:
+                s.alloc_cluster(2)
+            assert torch.equal(s.suffix_prefill(q, k, v), first)
+            assert sgc.lib().sgc_debug_carried(s.ctx) == (call <= 6)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("layers", [1, 32])
+def test_captured_calls_carry(layers):
+    """A captured call's tables go with it in contexts of many layers too, and on a plan that has carried them six times: copies would need a
+    staging buffer and memory while the stream is being captured."""
     w = workloads.custom("carried_captured", n_q_heads=8, n_kv_heads=2, head_dim=128, rope_base=10000.0, io_dtype="bf16", prefix_len=[100, 70],
                          cluster_sizes=[2, 1], suffix_range=(5, 40), n_layers=layers, seed=4)
     q, k, v = (to_device(x, "bf16") for x in w.suffix_qkv())
@@ -202,6 +222,9 @@ def test_captured_calls_carry(layers=32):
         o = torch.empty_like(q)
         pq, (pk, pv) = to_device(w.prefix_q(1), "bf16"), (to_device(x, "bf16") for x in w.prefix_kv(1))
         po = torch.empty_like(pq)
+        if layers == 1:
+            for _ in range(6):
+                s.suffix_prefill(q, k, v, do=o)
         with torch.cuda.graph(g):
             stream = torch.cuda.current_stream().cuda_stream
             sgc.sgc_prefix_prefill(s.ctx, s.cache, 1, 0, pq.data_ptr(), pk.data_ptr(), pv.data_ptr(), po.data_ptr(), None, 70, stream)
